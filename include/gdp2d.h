@@ -104,7 +104,7 @@ typedef struct {
                                rounds are large, more as they shrink) */
   int32_t tail_engine_max;  /* rounds whose previous round had at most this many
                                candidates run whole inside one workgroup (0 =
-                               default 1024; negative = never) */
+                               default 64; negative = never) */
   /* semantic (quality criteria of Section 4.1) */
   int32_t encroach_mode;    /* 0: a subsegment is encroached by a vertex or splitting
                                point strictly inside its diametric circle (Ruppert);
@@ -121,7 +121,7 @@ typedef struct {
                                run in shared rounds (each phase one launch for all
                                of them, over the whole chip), the others one
                                workgroup each in the single-workgroup engine;
-                               0 = every mesh in the engine */
+                               0 = chosen by the number of meshes */
   /* perf only */
   int32_t cavity_thread_cap;  /* per-thread cavity slots of the grid path (0 = 39;
                                12, 24 or 39): larger cavities go to the cooperative

@@ -123,9 +123,9 @@ struct gdp_mesh {
   int32_t *sadj = nullptr;
   uint32_t *mflag = nullptr;
   CandSet cc{}, mid{};
-  uint32_t *w0_t = nullptr, *w0_s = nullptr, *win_t = nullptr, *win_s = nullptr;
-  int32_t *rank_t = nullptr, *rank_s = nullptr;
-  int32_t *win_ref = nullptr, *fbase = nullptr, *fcount = nullptr, *fan_off = nullptr;
+  uint32_t *w0_t = nullptr, *w0_s = nullptr, *win_t = nullptr, *win_s = nullptr, *win_h = nullptr;
+  int32_t *rank_t = nullptr, *rank_s = nullptr, *rank_h = nullptr;
+  int32_t *w0_list = nullptr, *win_rank = nullptr, *win_fresh = nullptr, *fan_off = nullptr, *fan_len = nullptr;
   int32_t *repl = nullptr;
   int32_t *pool = nullptr;
   int32_t pool_cap = 0;
@@ -148,7 +148,7 @@ struct gdp_mesh {
   uint64_t *keys = nullptr;
   int32_t *rhist = nullptr;
   uint64_t *sel = nullptr;
-  int32_t *tiles_t = nullptr, *tiles_s = nullptr, *tiles_f = nullptr;  // tile prefixes of the three scans
+  int32_t *tiles_t = nullptr, *tiles_s = nullptr, *tiles_h = nullptr;  // tile prefixes of the three scans
   int32_t tiles_cap = 0;
   DevState *d_st = nullptr;
   DevState *h_st = nullptr;       // pinned
@@ -175,10 +175,10 @@ struct gdp_mesh {
 namespace {
 enum ProfId {
   P_SCAN = 0, P_CAP, P_LOCATE, P_CAV_CC, P_CAV_MID, P_CAV_BIG, P_PREFILTER, P_OWN, P_DEP, P_PREFIX,
-  P_WINNERS, P_RECORD, P_WRITE, P_FINISH, P_ENGINE, P_NUM
+  P_RECORD, P_WRITE, P_FINISH, P_ENGINE, P_NUM
 };
 const char *kProfNames[P_NUM] = {"k_scan", "k_cap", "k_locate", "k_cavity_cc", "k_cavity_mid", "k_cavity_big",
-                                  "k_prefilter", "k_own", "k_dep", "k_prefix_sum", "k_winners", "k_record", "k_write",
+                                  "k_prefilter", "k_own", "k_dep", "k_prefix_sum", "k_record", "k_write",
                                   "k_finish", "k_engine"};
 // Records HIP events around the launches issued in its scope (if enabled);
 // items and algorithmic bytes are filled in once the round's counts are read.
@@ -318,6 +318,8 @@ gdp_status grow_seg(gdp_mesh *M, int32_t need) {
   HIPCHECK(dgrow(&M->w0_s, words(oc), words(nc), words(oc), 0, s));
   HIPCHECK(dgrow(&M->win_s, words(oc), words(nc), words(oc), 0, s));
   HIPCHECK(dgrow(&M->rank_s, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(&M->win_h, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(&M->rank_h, words(oc), words(nc), words(oc), 0, s));
   M->m.capS = nc;
   return GDP_OK;
 }
@@ -351,25 +353,32 @@ gdp_status grow_cand(gdp_mesh *M) {
     if (d != GDP_OK) return d;
   }
   int64_t nc = std::max<int64_t>(need, (int64_t)M->wT + M->wT / 2);
-  // called between k_winners and k_record: keep what is already written
+  // may run while a round is abandoned: keep what is already written
   size_t keep = (size_t)M->wT;
-  HIPCHECK(dgrow(&M->win_ref, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->fbase, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->fcount, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(&M->w0_list, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(&M->win_rank, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(&M->win_fresh, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(&M->fan_off, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(&M->fan_len, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(&M->big, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(&M->keys, keep, nc, keep, 0, s));
   int64_t nt = nc / kScanTileSize + 2;
   HIPCHECK(dgrow(&M->tiles_t, 0, nt, 0, 0, s));
   HIPCHECK(dgrow(&M->tiles_s, 0, nt, 0, 0, s));
-  HIPCHECK(dgrow(&M->tiles_f, 0, nt, 0, 0, s));
+  HIPCHECK(dgrow(&M->tiles_h, 0, nt, 0, 0, s));
   M->tiles_cap = (int32_t)nt;
   M->wT = (int32_t)nc;
   return GDP_OK;
 }
 
 constexpr int kHistCap = 64;  // rounds queued between two host synchronisations, at most
-constexpr int64_t kEngineDefaultMax = 1024;  // candidates per round run by the single-workgroup engine
+// Candidates of a round up to which the next rounds run in the
+// single-workgroup engine.  A round of the grid kernels takes 130 us however
+// small (16 dependent launches), one of the engine as long for 100
+// candidates: 1,000-point call 6.5 / 6.1 / 6.4 / 6.8 / 9.5 ms of device time
+// with never / 64 / 128 / 256 / 1024, the 1M-point mesh 16.9 / 16.9 / 16.9 /
+// 17.0 / 17.7.
+constexpr int64_t kEngineDefaultMax = 64;
 // The engine grows its large (cooperative) cavities one after the other, the
 // grid kernels side by side: a mesh whose last round had more of them stays
 // on the grid kernels for the next round (rounded-cocircular inputs give
@@ -404,10 +413,10 @@ Work make_work(gdp_mesh *M, const gdp_params *P, int parity) {
     std::swap(w.cc.p, w.prev_cc_p);
     std::swap(w.mid.elem, w.prev_mid_elem);
   }
-  w.w0_t = M->w0_t; w.w0_s = M->w0_s; w.win_t = M->win_t; w.win_s = M->win_s;
-  w.rank_t = M->rank_t; w.rank_s = M->rank_s;
-  w.tiles_t = M->tiles_t; w.tiles_s = M->tiles_s; w.tiles_f = M->tiles_f;
-  w.win_ref = M->win_ref; w.fbase = M->fbase; w.fcount = M->fcount; w.fan_off = M->fan_off;
+  w.w0_t = M->w0_t; w.w0_s = M->w0_s; w.win_t = M->win_t; w.win_s = M->win_s; w.win_h = M->win_h;
+  w.rank_t = M->rank_t; w.rank_s = M->rank_s; w.rank_h = M->rank_h;
+  w.tiles_t = M->tiles_t; w.tiles_s = M->tiles_s; w.tiles_h = M->tiles_h;
+  w.w0_list = M->w0_list; w.win_rank = M->win_rank; w.win_fresh = M->win_fresh; w.fan_off = M->fan_off; w.fan_len = M->fan_len;
   w.win_cap = M->wT;
   w.repl = M->repl;
   w.pool = M->pool; w.pool_cap = M->pool_cap;
@@ -436,18 +445,31 @@ inline unsigned stride_grid(int64_t n, int bs) {
   return (unsigned)std::min<int64_t>(std::max<int64_t>(1, (n + bs - 1) / bs), 8192);
 }
 
-// Exclusive scans of one or two jobs (b.in == nullptr: one); n_bound bounds
-// the lengths (in device memory) and sizes the grid.
-gdp_status scan(gdp_mesh *M, const ScanJob &a, const ScanJob &b, int64_t n_bound) {
+// Grid of the cavity kernels over about n candidates: every group of lanes
+// takes one, up to the workgroups that fit on the chip at once.
+inline unsigned cavity_grid_for(int64_t n) { return std::min(grid_for(n, kCavGroups), kCavGridMax); }
+
+// Grid of the phases over the owners of their cavities (a group of eight
+// lanes each; about a quarter of n candidates, at most what the chip holds).
+inline unsigned winner_grid(int64_t n, int bs) {
+  return (unsigned)std::min<int64_t>(std::max<int64_t>(1, (2 * n + bs - 1) / bs), 256 * 2048 / bs);
+}
+
+// The scans of a round's winner bitmaps; n_bound bounds their words together
+// and sizes the grid.
+gdp_status scan_winners(gdp_mesh *M, const Work &w, int64_t n_bound) {
   gdp_ctx *ctx = M->ctx;
   hipStream_t s = ctx->stream;
-  int64_t ntiles = std::max<int64_t>(1, (n_bound + kScanTileSize - 1) / kScanTileSize);
+  ScanJobs J;
+  J.j[0] = ScanJob{(const int32_t *)w.win_s, w.rank_s, &w.st->wS, w.tiles_s, &w.cnt->nwin_mid, 1};
+  J.j[1] = ScanJob{(const int32_t *)w.win_t, w.rank_t, &w.st->wT, w.tiles_t, &w.cnt->nwin_cc, 1};
+  J.j[2] = ScanJob{(const int32_t *)w.win_h, w.rank_h, &w.st->wS, w.tiles_h, &w.cnt->nwin_hull, 1};
+  const int64_t ntiles = std::max<int64_t>(1, (n_bound + kScanTileSize - 1) / kScanTileSize);
   if (ntiles > M->tiles_cap) return fail(ctx, GDP_E_NOMEM, "scan tile buffer too small");
   const int32_t *halt = &M->d_st->halt;
   Prof pr(M, P_PREFIX);
-  unsigned g = (unsigned)std::min<int64_t>((b.in ? 2 : 1) * ntiles, 2048);
-  hipLaunchKernelGGL(k_scan_tiles, dim3(g), dim3(256), 0, s, a, b, halt);
-  hipLaunchKernelGGL(k_scan_sums, dim3(b.in ? 2 : 1), dim3(256), 0, s, a, b, halt);
+  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)std::min<int64_t>(3 * ntiles, 2048)), dim3(256), 0, s, J, halt);
+  hipLaunchKernelGGL(k_scan_sums, dim3(3), dim3(256), 0, s, J, halt);
   HIPCHECK(hipGetLastError());
   return GDP_OK;
 }
@@ -483,9 +505,9 @@ void free_mesh_arrays(gdp_mesh *M) {
                   M->d_cnt, M->d_stat, M->mark, M->sadj, M->mflag,
                   M->cc.elem, M->cc.key, M->cc.p, M->cc.loc, M->cc.state, M->cc.off, M->cc.len,
                   M->mid.elem, M->mid.key, M->mid.p, M->mid.loc, M->mid.state, M->mid.off, M->mid.len,
-                  M->w0_t, M->w0_s, M->win_t, M->win_s, M->rank_t, M->rank_s, M->win_ref, M->fbase,
-                  M->fcount, M->fan_off, M->repl, M->pool, M->fan, M->big, M->keys, M->rhist, M->sel,
-                  M->d_st, M->d_hist, M->tiles_t, M->tiles_s, M->tiles_f, M->prev_cc_elem, M->prev_cc_key, M->prev_cc_p, M->prev_mid_elem, M->tstamp,
+                  M->w0_t, M->w0_s, M->win_t, M->win_s, M->win_h, M->rank_t, M->rank_s, M->rank_h, M->w0_list, M->win_rank,
+                  M->win_fresh, M->fan_off, M->fan_len, M->repl, M->pool, M->fan, M->big, M->keys, M->rhist, M->sel,
+                  M->d_st, M->d_hist, M->tiles_t, M->tiles_s, M->tiles_h, M->prev_cc_elem, M->prev_cc_key, M->prev_cc_p, M->prev_mid_elem, M->tstamp,
                   M->cidx_t, M->cidx_s, M->hvis, M->hlist};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -696,13 +718,11 @@ gdp_status enqueue_round(gdp_mesh *M, double B2, const gdp_params *P, bool full,
   est = std::max<int64_t>(est, 1);
   M->cur_round = group_index;
   const int64_t ncand = enqueue_select(M, B2, P, full, est, w);
+  const int cap = P->cavity_thread_cap > 0 ? P->cavity_thread_cap : kCavCapDefault;
   // ---- R5/R6 cavities (marks placed as each valid cavity completes) ----
   {
     Prof pr(M, P_CAV_CC);
-    const unsigned g = stride_grid(ncand, kCavBlockSize);
-    if (P->cavity_thread_cap == 12) hipLaunchKernelGGL((k_cavity<1, 12>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
-    else if (P->cavity_thread_cap == 24) hipLaunchKernelGGL((k_cavity<1, 24>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
-    else hipLaunchKernelGGL((k_cavity<1, kCavCapDefault>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
+    hipLaunchKernelGGL(k_cavity<1>, dim3(cavity_grid_for(ncand)), dim3(kCavBlockSize), 0, s, m, w, cap);
   }
   {
     Prof pr(M, P_CAV_BIG);
@@ -711,10 +731,7 @@ gdp_status enqueue_round(gdp_mesh *M, double B2, const gdp_params *P, bool full,
   }
   {
     Prof pr(M, P_CAV_MID);
-    const unsigned g = stride_grid(ncand / 4, kCavBlockSize);
-    if (P->cavity_thread_cap == 12) hipLaunchKernelGGL((k_cavity<0, 12>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
-    else if (P->cavity_thread_cap == 24) hipLaunchKernelGGL((k_cavity<0, 24>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
-    else hipLaunchKernelGGL((k_cavity<0, kCavCapDefault>), dim3(g), dim3(kCavBlockSize), 0, s, m, w);
+    hipLaunchKernelGGL(k_cavity<0>, dim3(cavity_grid_for(ncand / 4)), dim3(kCavBlockSize), 0, s, m, w, cap);
   }
   {
     Prof pr(M, P_CAV_BIG);
@@ -728,27 +745,18 @@ gdp_status enqueue_round(gdp_mesh *M, double B2, const gdp_params *P, bool full,
   }
   {
     Prof pr(M, P_DEP);
-    hipLaunchKernelGGL(k_dep, dim3(stride_grid(ncand, bs)), dim3(bs), 0, s, m, w);
+    hipLaunchKernelGGL(k_dep, dim3(winner_grid(ncand, bs)), dim3(bs), 0, s, m, w);
   }
   // ---- R10: ranks, fresh slots, capacity check, insertion ----
   gdp_status st;
-  const ScanJob js{(const int32_t *)M->win_s, M->rank_s, &M->d_st->wS, M->tiles_s, &M->d_cnt->nwin_mid, 1};
-  const ScanJob jt{(const int32_t *)M->win_t, M->rank_t, &M->d_st->wT, M->tiles_t, &M->d_cnt->nwin_cc, 1};
-  const ScanJob jf{M->fcount, M->fbase, &M->d_cnt->nwin1, M->tiles_f, &M->d_cnt->fan_total, 0};
-  const ScanJob none{nullptr, nullptr, nullptr, nullptr, nullptr, 0};
-  if ((st = scan(M, js, jt, std::max(words(m.capS), words(m.capT))))) return st;
-  {
-    Prof pr(M, P_WINNERS);
-    hipLaunchKernelGGL(k_winners, dim3(stride_grid(ncand, bs)), dim3(bs), 0, s, w);
-  }
-  if ((st = scan(M, jf, none, std::min<int64_t>(ncand + 1, M->wT)))) return st;
+  if ((st = scan_winners(M, w, std::max(words(m.capS), words(m.capT))))) return st;
   {
     Prof pr(M, P_RECORD);
-    hipLaunchKernelGGL(k_record, dim3(stride_grid(ncand, bs)), dim3(bs), 0, s, m, w);
+    hipLaunchKernelGGL(k_record, dim3(winner_grid(ncand, bs)), dim3(bs), record_lds(bs), s, m, w);
   }
   {
     Prof pr(M, P_WRITE);
-    hipLaunchKernelGGL(k_write, dim3(stride_grid(ncand, bs)), dim3(bs), 0, s, m, w);
+    hipLaunchKernelGGL(k_write, dim3(winner_grid(ncand, bs)), dim3(bs), write_lds(bs), s, m, w);
   }
   {
     Prof pr(M, P_FINISH);
@@ -1012,21 +1020,24 @@ void for_each_array(gdp_mesh *M, const Caps &c, F f) {
   f((void **)&M->w0_s, 4, wS, 0);
   f((void **)&M->win_s, 4, wS, 0);
   f((void **)&M->rank_s, 4, wS, 0);
+  f((void **)&M->win_h, 4, wS, 0);
+  f((void **)&M->rank_h, 4, wS, 0);
   f((void **)&M->repl, 4, 4 * c.T, 0xff);
   f((void **)&M->tstamp, 4, c.T, 0xff);
   f((void **)&M->cidx_t, 4, c.T, 0);
   f((void **)&M->hvis, 4, c.T, 0);
   f((void **)&M->hlist, 4, c.T, 0);
   f((void **)&M->cidx_s, 4, c.S, 0);
-  f((void **)&M->win_ref, 4, c.W, 0);
-  f((void **)&M->fbase, 4, c.W, 0);
-  f((void **)&M->fcount, 4, c.W, 0);
+  f((void **)&M->w0_list, 4, c.W, 0);
+  f((void **)&M->win_rank, 4, c.W, 0);
+  f((void **)&M->win_fresh, 4, c.W, 0);
   f((void **)&M->fan_off, 4, c.W, 0);
+  f((void **)&M->fan_len, 4, c.W, 0);
   f((void **)&M->big, 4, c.W, 0);
   f((void **)&M->keys, 8, c.W, 0);
   f((void **)&M->tiles_t, 4, c.tiles, 0);
   f((void **)&M->tiles_s, 4, c.tiles, 0);
-  f((void **)&M->tiles_f, 4, c.tiles, 0);
+  f((void **)&M->tiles_h, 4, c.tiles, 0);
   f((void **)&M->pool, 4, c.pool, 0);
   f((void **)&M->fan, sizeof(FanRec), c.fan, 0);
   f((void **)&M->d_stat, sizeof(StatLine), kStatStripes, 0);
@@ -1109,6 +1120,7 @@ struct GangItem {
 // Device and pinned buffers of a shared-rounds runner (up to cap meshes).
 struct GangBufs {
   GangDesc *d_desc = nullptr, *h_desc = nullptr;
+  int32_t *d_map = nullptr, *h_map = nullptr;  // mesh of each workgroup, per GangKind
   int32_t *d_status = nullptr, *h_status = nullptr;
   int stride_words = 0;  // words of one mesh's status record
   int cap = 0;
@@ -1116,11 +1128,27 @@ struct GangBufs {
 constexpr int kGangRounds = 2;     // default rounds between two host reads of the meshes' states
 constexpr int kGangRoundsMax = 8;
 
+// Workgroups of a shared launch, per kind, over all meshes (a mesh has at
+// least one): what the chip holds of the phases' kernels, twice over for
+// kGangElem, whose workgroups end at different times.
+constexpr int kGangBlocks[kGangKinds] = {4096, 1536, 1024};
+// Elements per workgroup, and a mesh's most (each workgroup of kGangFinish
+// arrives on one counter of its mesh, about 12 ns apart).
+constexpr int kGangPer[kGangKinds] = {256, 32, 256};
+constexpr int kGangMost[kGangKinds] = {4096, 1536, 256};
+size_t gang_map_words(int cap) {
+  size_t n = 0;
+  for (int k = 0; k < kGangKinds; k++) n += (size_t)kGangBlocks[k] + cap;
+  return n;
+}
+
 bool gang_bufs_alloc(GangBufs &B, int cap) {
   B.cap = cap;
   B.stride_words = (int)((sizeof(DevState) + (1 + kGangRoundsMax) * sizeof(DevCounters)) / 4);
   return dalloc(&B.d_desc, cap) == hipSuccess &&
          hipHostMalloc((void **)&B.h_desc, sizeof(GangDesc) * cap) == hipSuccess &&
+         dalloc(&B.d_map, gang_map_words(cap)) == hipSuccess &&
+         hipHostMalloc((void **)&B.h_map, sizeof(int32_t) * gang_map_words(cap)) == hipSuccess &&
          dalloc(&B.d_status, (size_t)B.stride_words * cap) == hipSuccess &&
          hipHostMalloc((void **)&B.h_status, sizeof(int32_t) * B.stride_words * cap) == hipSuccess;
 }
@@ -1129,6 +1157,8 @@ void gang_bufs_free(GangBufs &B) {
   if (B.d_desc) (void)hipFree(B.d_desc);
   if (B.d_status) (void)hipFree(B.d_status);
   if (B.h_desc) (void)hipHostFree(B.h_desc);
+  if (B.d_map) (void)hipFree(B.d_map);
+  if (B.h_map) (void)hipHostFree(B.h_map);
   if (B.h_status) (void)hipHostFree(B.h_status);
   B = GangBufs();
 }
@@ -1144,59 +1174,87 @@ GangDesc gang_desc(gdp_mesh *M, const gdp_params *P, double B2) {
   d.m = M->m;
   d.w[0] = make_work(M, P, 0);
   d.w[1] = make_work(M, P, 1);
-  // one workgroup runs the device-memory cavity path per mesh and launch
-  d.w[0].huge_ok = d.w[1].huge_ok = 1;
   d.B2 = B2;
   d.pm = P->priority_mode;
   d.K = P->cand_cap_K;
   d.f1 = P->prefilter_f1;
   d.approx_n = P->cavity_approx_n;
   d.max_rounds = P->max_rounds;
-  g.js = ScanJob{(const int32_t *)M->win_s, M->rank_s, &M->d_st->wS, M->tiles_s, &M->d_cnt->nwin_mid, 1};
-  g.jt = ScanJob{(const int32_t *)M->win_t, M->rank_t, &M->d_st->wT, M->tiles_t, &M->d_cnt->nwin_cc, 1};
-  g.jf = ScanJob{M->fcount, M->fbase, &M->d_cnt->nwin1, M->tiles_f, &M->d_cnt->fan_total, 0};
   return g;
 }
 
-// One round of every job in the descriptors (grids sized for the largest).
-void gang_round(hipStream_t s, const GangDesc *D, unsigned n, int64_t max_full, int64_t max_est,
-                int64_t max_ncand, int64_t max_words, bool any_cap, bool any_pre) {
+// Shares out the workgroups of each kind by the meshes' candidates, writes
+// them into the descriptors and the tables, and returns the grids and the
+// tables' offsets.
+struct GangGrids {
+  unsigned n[kGangKinds];
+  size_t off[kGangKinds];
+  size_t words;
+};
+GangGrids gang_share(GangBufs &B, const std::vector<int64_t> &cand) {
+  GangGrids g;
+  size_t at = 0;
+  for (int k = 0; k < kGangKinds; k++) {
+    std::vector<int64_t> need(cand.size());
+    int64_t sum = 0;
+    for (size_t q = 0; q < cand.size(); q++) {
+      need[q] = std::min<int64_t>(std::max<int64_t>(1, (cand[q] + kGangPer[k] - 1) / kGangPer[k]), kGangMost[k]);
+      sum += need[q];
+    }
+    g.off[k] = at;
+    int32_t b0 = 0;
+    for (size_t q = 0; q < cand.size(); q++) {
+      const int64_t nb = sum <= kGangBlocks[k] ? need[q] : std::max<int64_t>(1, need[q] * kGangBlocks[k] / sum);
+      B.h_desc[q].b0[k] = b0;
+      B.h_desc[q].nb[k] = (int32_t)nb;
+      for (int64_t i = 0; i < nb; i++) B.h_map[at++] = (int32_t)q;
+      b0 += (int32_t)nb;
+    }
+    g.n[k] = (unsigned)b0;
+  }
+  g.words = at;
+  return g;
+}
+
+// One round of every job in the descriptors.
+void gang_round(hipStream_t s, const GangBufs &B, unsigned n, const GangGrids &g, int64_t max_words, bool any_cap,
+                bool any_pre, bool any_huge) {
   const int bs = 256;
-  const unsigned gc = std::max(stride_grid(max_full, bs), stride_grid(3 * max_est, bs));
-  hipLaunchKernelGGL(kg_collect, dim3(gc, n), dim3(bs), 0, s, D);
-  hipLaunchKernelGGL(kg_pending, dim3(stride_grid(max_est / 4, bs), n), dim3(bs), 0, s, D);
+  const GangDesc *D = B.d_desc;
+  const int32_t *me = B.d_map + g.off[kGangElem], *mg = B.d_map + g.off[kGangGroup], *mf = B.d_map + g.off[kGangFinish];
+  const dim3 ge(g.n[kGangElem]), gg(g.n[kGangGroup]);
+  // cooperative cavities: one workgroup fills a compute unit's LDS, so they
+  // share the chip's 256 between the meshes
+  const unsigned nbig = std::max(1u, 256u / n);
+  hipLaunchKernelGGL(kg_collect, ge, dim3(bs), 0, s, D, me);
+  hipLaunchKernelGGL(kg_pending, ge, dim3(bs), 0, s, D, me);
   hipLaunchKernelGGL(kg_gate, dim3(1, n), dim3(256), 0, s, D);
   if (any_cap) {
-    hipLaunchKernelGGL(kg_gather_keys, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
-    const unsigned g = std::min<unsigned>(grid_for(max_ncand, 256), 1024);
+    hipLaunchKernelGGL(kg_gather_keys, ge, dim3(bs), 0, s, D, me);
     for (int shift = 56; shift >= 0; shift -= 8) {
-      hipLaunchKernelGGL(kg_radix_hist, dim3(g, n), dim3(256), 0, s, D, shift);
+      hipLaunchKernelGGL(kg_radix_hist, ge, dim3(256), 0, s, D, me, shift);
       hipLaunchKernelGGL(kg_radix_pick, dim3(1, n), dim3(256), 0, s, D, shift);
     }
-    hipLaunchKernelGGL(kg_apply_cap, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
+    hipLaunchKernelGGL(kg_apply_cap, ge, dim3(bs), 0, s, D, me);
   }
-  hipLaunchKernelGGL(kg_locate, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
+  hipLaunchKernelGGL(kg_locate, ge, dim3(bs), 0, s, D, me);
   if (any_pre)
-    for (int mode = 0; mode < 6; mode++)
-      hipLaunchKernelGGL(kg_prefilter, dim3(stride_grid(max_ncand, 128), n), dim3(128), 0, s, D, mode);
-  hipLaunchKernelGGL(kg_cavity<1>, dim3(stride_grid(max_ncand, kCavBlockSize), n), dim3(kCavBlockSize), 0, s, D);
-  hipLaunchKernelGGL(kg_cavity_big, dim3(256, n), dim3(kBigBlockSize), 0, s, D, 0);
-  hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 0);
-  hipLaunchKernelGGL(kg_cavity<0>, dim3(stride_grid(max_ncand / 4, kCavBlockSize), n), dim3(kCavBlockSize), 0, s, D);
-  hipLaunchKernelGGL(kg_cavity_big, dim3(256, n), dim3(kBigBlockSize), 0, s, D, 1);
-  hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 1);
-  hipLaunchKernelGGL(kg_own, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
-  hipLaunchKernelGGL(kg_dep, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
+    for (int mode = 0; mode < 6; mode++) hipLaunchKernelGGL(kg_prefilter, ge, dim3(128), 0, s, D, me, mode);
+  hipLaunchKernelGGL(kg_cavity<1>, gg, dim3(kCavBlockSize), 0, s, D, mg);
+  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig, n), dim3(kBigBlockSize), 0, s, D, 0);
+  if (any_huge) hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 0);
+  hipLaunchKernelGGL(kg_cavity<0>, gg, dim3(kCavBlockSize), 0, s, D, mg);
+  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig, n), dim3(kBigBlockSize), 0, s, D, 1);
+  if (any_huge) hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 1);
+  hipLaunchKernelGGL(kg_own, ge, dim3(bs), 0, s, D, me);
+  hipLaunchKernelGGL(kg_dep, gg, dim3(bs), 0, s, D, mg);
   const int64_t tiles_w = std::max<int64_t>(1, (max_words + kScanTileSize - 1) / kScanTileSize);
-  hipLaunchKernelGGL(kg_scan_tiles, dim3((unsigned)std::min<int64_t>(2 * tiles_w, 2048), n), dim3(256), 0, s, D, 0);
-  hipLaunchKernelGGL(kg_scan_sums, dim3(2, n), dim3(256), 0, s, D, 0);
-  hipLaunchKernelGGL(kg_winners, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
-  const int64_t tiles_f = std::max<int64_t>(1, (max_ncand + 1 + kScanTileSize - 1) / kScanTileSize);
-  hipLaunchKernelGGL(kg_scan_tiles, dim3((unsigned)std::min<int64_t>(tiles_f, 2048), n), dim3(256), 0, s, D, 1);
-  hipLaunchKernelGGL(kg_scan_sums, dim3(1, n), dim3(256), 0, s, D, 1);
-  hipLaunchKernelGGL(kg_record, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
-  hipLaunchKernelGGL(kg_write, dim3(stride_grid(max_ncand, bs), n), dim3(bs), 0, s, D);
-  hipLaunchKernelGGL(kg_finish, dim3(std::min(stride_grid(max_ncand, bs), 256u), n), dim3(bs), 0, s, D);
+  const unsigned gt = (unsigned)std::max<int64_t>(1, std::min<int64_t>(3 * tiles_w, 2048 / n));
+  hipLaunchKernelGGL(kg_scan_tiles, dim3(gt, n), dim3(256), 0, s, D);
+  hipLaunchKernelGGL(kg_scan_sums, dim3(3, n), dim3(256), 0, s, D);
+  hipLaunchKernelGGL(kg_record, gg, dim3(bs), record_lds(bs), s, D, mg);
+  hipLaunchKernelGGL(kg_write, gg, dim3(bs), write_lds(bs), s, D, mg);
+  hipLaunchKernelGGL(kg_finish, dim3(g.n[kGangFinish]), dim3(bs), 0, s, D, mf);
 }
 
 // One group of R shared rounds of every active mesh (at most B.cap), then
@@ -1209,34 +1267,38 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
                 std::vector<std::pair<GangItem, gdp_status>> &finished) {
   hipStream_t s = ctx->stream;
   const int ns = (int)(sizeof(DevState) / 4), nc = (int)(sizeof(DevCounters) / 4);
-  int64_t max_full = 0, max_est = 1, max_ncand = 1, max_words = 1;
-  bool any_cap = false, any_pre = false;
+  int64_t max_words = 1;
+  bool any_cap = false, any_pre = false, any_huge = false;
+  std::vector<int64_t> cand;
   for (size_t q = 0; q < active.size();) {
     GangItem &A = active[q];
     gdp_mesh *M = A.M;
-    gdp_status st = reserve_group(M, A.last_cand, R);
+    // A mesh in a batch or server region is sized for its refinement already;
+    // the loose bound would move it out of the region (an allocation and a
+    // copy per array) for room it does not need.  If a round does come short,
+    // it is abandoned and run again after growth.
+    gdp_status st = M->arena ? GDP_OK : reserve_group(M, A.last_cand, std::min(R, kGangRounds));
     if (st != GDP_OK) {
       finished.push_back({A, st});
       active.erase(active.begin() + q);
       continue;
     }
     const DevMesh &m = M->m;
-    // grids sized for the largest mesh's work this round (a full collection
-    // for a mesh's first round, the candidate lists after it)
-    if (A.full) max_full = std::max<int64_t>(max_full, std::max(m.nT, m.nS));
-    else max_est = std::max<int64_t>(max_est, A.last_cand);
-    max_ncand = std::max<int64_t>(max_ncand, A.full ? (int64_t)m.nT + m.nS : 2 * A.last_cand);
-    max_words = std::max<int64_t>(max_words, std::max(words(m.capS), words(m.capT)));
+    // a full collection for a mesh's first round, the candidate lists after it
+    cand.push_back(A.full ? (int64_t)m.nT + m.nS : A.last_cand);
+    max_words = std::max<int64_t>(max_words, std::max(words(m.nS), words(m.nT)));
     any_cap = any_cap || A.P->cand_cap_K > 0;
     any_pre = any_pre || A.P->prefilter_f1 || A.P->cavity_approx_n > 0;
+    any_huge = any_huge || M->huge_mode;
     B.h_desc[q] = gang_desc(M, A.P, A.B2);
     q++;
   }
   const unsigned n = (unsigned)active.size();
   if (n == 0) return;
-  bool ok = hipMemcpyAsync(B.d_desc, B.h_desc, sizeof(GangDesc) * n, hipMemcpyHostToDevice, s) == hipSuccess;
-  for (int r = 0; ok && r < R; r++)
-    gang_round(s, B.d_desc, n, max_full, max_est, max_ncand, max_words, any_cap, any_pre);
+  const GangGrids grids = gang_share(B, cand);
+  bool ok = hipMemcpyAsync(B.d_desc, B.h_desc, sizeof(GangDesc) * n, hipMemcpyHostToDevice, s) == hipSuccess &&
+            hipMemcpyAsync(B.d_map, B.h_map, sizeof(int32_t) * grids.words, hipMemcpyHostToDevice, s) == hipSuccess;
+  for (int r = 0; ok && r < R; r++) gang_round(s, B, n, grids, max_words, any_cap, any_pre, any_huge);
   if (ok) {
     hipLaunchKernelGGL(kg_status, dim3(1, n), dim3(256), 0, s, B.d_desc, R, B.d_status, B.stride_words);
     ok = hipGetLastError() == hipSuccess &&
@@ -1272,7 +1334,9 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
     gdp_status st = GDP_OK;
     bool over = false;
     if (d.halt == kHaltAbort) {
-      // nothing was written: grow and run the same round again
+      // nothing was written: grow and run the same round again (with the
+      // device-memory cavity path from now on if a cavity outgrew its list)
+      if (c.err & kErrHuge) M->huge_mode = true;
       if (++A.aborts > 16) {
         st = fail(ctx, GDP_E_NOMEM, "round keeps exceeding its buffers");
         over = true;
@@ -1287,7 +1351,8 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
       st = status_of_halt(ctx, d, c);
       over = true;
     }
-    if (!over && hipMemsetAsync(&M->d_st->halt, 0, 2 * sizeof(int32_t), s) != hipSuccess) {  // halt, nhist
+    // (the history was emptied with the read)
+    if (!over && d.halt != 0 && hipMemsetAsync(&M->d_st->halt, 0, sizeof(int32_t), s) != hipSuccess) {
       st = fail(ctx, GDP_E_DEVICE, "round state reset failed");
       over = true;
     }
@@ -1297,6 +1362,17 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
   active.swap(keep);
 }
 
+// Input vertices above which a batched mesh runs in shared rounds when the
+// caller leaves the choice to the library: the engine takes as long as its
+// largest mesh on one compute unit (4,000 points 11 ms, 50,000 points 96 ms),
+// the shared rounds about 0.2 ms a round for all their meshes.  128 meshes of
+// 100 to 50,000 points take 110 ms of device time in the engine alone, 51 in
+// shared rounds alone, 44 / 46 / 42 / 49 split at 1,000 / 2,000 / 4,000 /
+// 8,000.  With more meshes than compute units the engine is busy with several
+// each, and larger ones stay in it: 768 such meshes take 128 ms in the engine
+// alone, 132 split at 4,000, 100 at 8,000.
+constexpr int64_t kBatchSplitFew = 4000, kBatchSplitMany = 8000;
+constexpr int kBatchGangRounds = 4;  // shared rounds between two host reads: no job waits to join a batch
 constexpr size_t kBatchGangMax = 256;  // batched meshes in one group of shared rounds, at most
 constexpr int32_t kBatchLine1DevThreads = 8;  // device Line-1 builders of a batch, each on its own stream
 
@@ -1610,7 +1686,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   // (every phase one launch for all of them, the whole chip per round), the
   // others one workgroup each in the engine launch.  Either way each mesh is
   // the plain loop's.
-  const int64_t split = P->batch_engine_max_v > 0 ? P->batch_engine_max_v : (int64_t)1 << 40;
+  const int64_t split = P->batch_engine_max_v > 0 ? P->batch_engine_max_v : (n <= 256 ? kBatchSplitFew : kBatchSplitMany);
   std::vector<int32_t> order, gang_k;
   for (int32_t k = 0; k < n; k++)
     if (live[k]) (pslgs[ok[k]].n_vertices > split ? gang_k : order).push_back(k);
@@ -1681,7 +1757,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
     std::stable_sort(gang_k.begin(), gang_k.end(), [&](int32_t a, int32_t b) { return nT0[a] > nT0[b]; });
     std::vector<GangItem> active;
     size_t next = 0;
-    const int R = P->rounds_per_sync > 0 ? std::min(P->rounds_per_sync, kGangRoundsMax) : kGangRounds;
+    const int R = P->rounds_per_sync > 0 ? std::min(P->rounds_per_sync, kGangRoundsMax) : kBatchGangRounds;
     while (next < gang_k.size() || !active.empty()) {
       while (next < gang_k.size() && (int)active.size() < gcap) {
         const int32_t k = gang_k[next++];
@@ -2820,11 +2896,12 @@ gdp_status ff_line8(gdp_mesh *M, const gdp_params *P, int32_t np, int32_t nmid, 
   // the in-tile prefix, ntiles the tile prefixes), then the kept midpoints
   {
     const int32_t *no_halt = &F.d_c->err;  // the scan kernels stop on a nonzero word; err is 0 here
-    const ScanJob j{V.alive, V.newid, &F.d_c->np, F.ntiles, &F.d_c->nwin, 0};
-    const ScanJob none{nullptr, nullptr, nullptr, nullptr, nullptr, 0};
+    ScanJobs J;
+    memset(&J, 0, sizeof J);
+    J.j[0] = ScanJob{V.alive, V.newid, &F.d_c->np, F.ntiles, &F.d_c->nwin, 0};
     const unsigned g = (unsigned)std::min<int64_t>(std::max<int64_t>(1, (np + kFfScanTile - 1) / kFfScanTile), 2048);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(g), dim3(256), 0, s, j, none, no_halt);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, j, none, no_halt);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(g), dim3(256), 0, s, J, no_halt);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, J, no_halt);
     hipLaunchKernelGGL(kf_nwin_mid, dim3(1), dim3(64), 0, s, V);
   }
   hipLaunchKernelGGL(kf_final_point, dim3(ff_grid(np)), dim3(256), 0, s, V);

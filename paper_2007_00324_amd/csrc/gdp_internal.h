@@ -90,10 +90,10 @@ struct DevCounters {
   int32_t nwin;        // winners of the round
   // line 1
   int32_t nmk;          // midpoint candidates (flagged subsegments)
-  int32_t nwin1;        // nwin + 1 (scan length)
+  int32_t nw0;          // points that hold every mark of their cavity (list length)
   int32_t abort;        // the round was abandoned before any mesh write (capacity)
   int32_t nmk0;         // midpoint candidates after the collection (R4/R5 add more)
-  int32_t fan_total;    // total of the fresh-count scan (fbase[nwin] is what is used)
+  int32_t nwin_hull;    // midpoint winners on the hull (one fresh slot instead of two)
   int32_t nhuge;        // cavities continued in device memory (beyond the LDS list)
   int64_t cav_len[2];   // per-thread cavities [midpoints, circumcenters]: triangles grown
   int64_t cav_bnd[2];   // ... and their boundary edges

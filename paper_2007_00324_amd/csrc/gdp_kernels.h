@@ -23,13 +23,15 @@ struct Work {
   uint32_t *mflag;     // [capS] subsegment flagged as a midpoint candidate
   CandSet cc, mid;
   uint32_t *w0_t, *w0_s, *win_t, *win_s;  // element bitmaps
-  int32_t *rank_t, *rank_s;               // exclusive prefix of bitmap popcounts (per tile)
-  int32_t *tiles_t, *tiles_s, *tiles_f;   // tile prefixes of the three scans
-  int32_t *win_ref;    // [nwin] winner -> (class bit 31 set for midpoints) | candidate
-  int32_t *fbase;      // [nwin+1] exclusive prefix of fresh-slot counts
-  int32_t *fcount;     // [nwin] fresh slots per winner (1 or 2)
-  int32_t *fan_off;    // [nwin]
-  int32_t win_cap;     // length of win_ref / fbase / fcount / fan_off
+  uint32_t *win_h;                        // winning midpoints on the hull
+  int32_t *rank_t, *rank_s, *rank_h;      // exclusive prefix of bitmap popcounts (per tile)
+  int32_t *tiles_t, *tiles_s, *tiles_h;   // tile prefixes of the three scans
+  int32_t *w0_list;    // [nw0] points that hold their marks: (bit 31 set for midpoints) | candidate
+  int32_t *win_rank;   // [nw0] winner rank (-1: dropped by the dependency test)
+  int32_t *win_fresh;  // [nw0] fresh slots of the winners before it
+  int32_t *fan_off;    // [nw0] its fan records
+  int32_t *fan_len;    // [nw0]
+  int32_t win_cap;     // length of these lists
   int32_t *repl;       // [4*capT] new slot that replaces (old slot, edge)
   int32_t *pool;
   int32_t pool_cap;
@@ -70,6 +72,10 @@ struct ScanJob {
   int mode;              // 0: counts, 1: popcounts of 32-bit words
 };
 
+struct ScanJobs {
+  ScanJob j[3];  // in == nullptr: unused
+};
+
 // Every round kernel returns at once when st->halt is set; lengths come from
 // device memory, and the grids only bound the parallelism (grid-stride loops).
 __global__ void k_scan(DevMesh m, Work w, double B2, int pm);
@@ -83,16 +89,15 @@ __global__ void k_apply_cap(Work w);
 __global__ void k_locate(DevMesh m, Work w);
 __global__ void k_prefilter(DevMesh m, Work w, int mode, int n);
 constexpr int kApproxMaxN = 16;
-constexpr int kCavCapDefault = 39;  // per-thread cavity slots of the grid kernel (LDS per 128-thread block)
-template <int IS_CC, int CAP>
-__global__ void k_cavity(DevMesh m, Work w);
+constexpr int kCavCapDefault = 39;  // largest cavity of the grid kernel's lane groups
+template <int IS_CC>
+__global__ void k_cavity(DevMesh m, Work w, int cap);
 __global__ void k_cavity_big(DevMesh m, Work w, int phase);
 __global__ void k_cavity_huge(DevMesh m, Work w, int phase);
 __global__ void k_own(Work w);
 __global__ void k_dep(DevMesh m, Work w);
-__global__ void k_scan_tiles(ScanJob a, ScanJob b, const int32_t *halt);
-__global__ void k_scan_sums(ScanJob a, ScanJob b, const int32_t *halt);
-__global__ void k_winners(Work w);
+__global__ void k_scan_tiles(ScanJobs J, const int32_t *halt);
+__global__ void k_scan_sums(ScanJobs J, const int32_t *halt);
 __global__ void k_record(DevMesh m, Work w);
 __global__ void k_write(DevMesh m, Work w);
 __global__ void k_finish(DevMesh m, Work w);
@@ -128,39 +133,47 @@ struct EngDesc {
 constexpr int kEngBlock = 1024;
 __global__ void k_engine(const EngDesc *descs, int n_mesh, int32_t *head, int round_limit);
 
-// Round-boundary batching (the serving form's shared rounds): one launch per
-// phase for a set of meshes.  Workgroup (x, y) works on mesh y, with the
-// grid-stride loops of the single-mesh kernels over x; each mesh takes its
-// round's workspace from its own serial, its halt code stops its part of
-// every launch, and the first round of a mesh (DevState.full) is a full
-// collection.  Semantic parameters come from each mesh's descriptor.
+// Round-boundary batching (the shared rounds of the serving and the batched
+// form): one launch per phase for a set of meshes, with the grid-stride loops
+// of the single-mesh kernels.  The workgroups of a phase over elements are
+// shared out by the meshes' work: mesh y has workgroups b0[k] .. b0[k] +
+// nb[k] - 1 of kind k, and map (of that kind) gives the mesh of each.  Each
+// mesh takes its round's workspace from its own serial, its halt code stops
+// its part of every launch, and the first round of a mesh (DevState.full) is
+// a full collection.  Semantic parameters come from each mesh's descriptor.
+enum GangKind {
+  kGangElem = 0,    // a thread per element
+  kGangGroup = 1,   // a group of lanes per element
+  kGangFinish = 2,  // as kGangElem, few workgroups (each arrives on one counter of its mesh)
+  kGangKinds = 3
+};
 struct GangDesc {
   EngDesc e;
-  ScanJob js, jt, jf;  // the round's scans (subsegment and triangle winner bitmaps, fresh-slot counts)
+  int32_t b0[kGangKinds], nb[kGangKinds];
 };
-__global__ void kg_collect(const GangDesc *G);
-__global__ void kg_pending(const GangDesc *G);
+__global__ void kg_collect(const GangDesc *G, const int32_t *map);
+__global__ void kg_pending(const GangDesc *G, const int32_t *map);
 __global__ void kg_gate(const GangDesc *G);
-__global__ void kg_gather_keys(const GangDesc *G);
-__global__ void kg_radix_hist(const GangDesc *G, int shift);
+__global__ void kg_gather_keys(const GangDesc *G, const int32_t *map);
+__global__ void kg_radix_hist(const GangDesc *G, const int32_t *map, int shift);
 __global__ void kg_radix_pick(const GangDesc *G, int shift);
-__global__ void kg_apply_cap(const GangDesc *G);
-__global__ void kg_locate(const GangDesc *G);
-__global__ void kg_prefilter(const GangDesc *G, int mode);
+__global__ void kg_apply_cap(const GangDesc *G, const int32_t *map);
+__global__ void kg_locate(const GangDesc *G, const int32_t *map);
+__global__ void kg_prefilter(const GangDesc *G, const int32_t *map, int mode);
 template <int IS_CC>
-__global__ void kg_cavity(const GangDesc *G);
+__global__ void kg_cavity(const GangDesc *G, const int32_t *map);
 __global__ void kg_cavity_big(const GangDesc *G, int phase);
 __global__ void kg_cavity_huge(const GangDesc *G, int phase);
-__global__ void kg_own(const GangDesc *G);
-__global__ void kg_dep(const GangDesc *G);
-__global__ void kg_scan_tiles(const GangDesc *G, int which);
-__global__ void kg_scan_sums(const GangDesc *G, int which);
-__global__ void kg_winners(const GangDesc *G);
-__global__ void kg_record(const GangDesc *G);
-__global__ void kg_write(const GangDesc *G);
-__global__ void kg_finish(const GangDesc *G);
+__global__ void kg_own(const GangDesc *G, const int32_t *map);
+__global__ void kg_dep(const GangDesc *G, const int32_t *map);
+__global__ void kg_scan_tiles(const GangDesc *G);
+__global__ void kg_scan_sums(const GangDesc *G);
+__global__ void kg_record(const GangDesc *G, const int32_t *map);
+__global__ void kg_write(const GangDesc *G, const int32_t *map);
+__global__ void kg_finish(const GangDesc *G, const int32_t *map);
 // Copies each mesh's DevState, running counters and first `rounds` history
-// records to out + y * stride_words (32-bit words), for one host read.
+// records to out + y * stride_words (32-bit words), for one host read, and
+// empties its history.
 __global__ void kg_status(const GangDesc *G, int rounds, int32_t *out, int stride_words);
 
 // Flip-Flop insertion (Section 4.3, Line 8; gdp_ff_core.h).  Line 6 of such
@@ -199,9 +212,14 @@ __global__ void kf_compact_fix(FfView V, int n_live);
 __global__ void kf_rotate(FfView V, int n);
 __global__ void kf_all_slots(FfView V, int n, int wst);  // every slot onto the worklist
 
-constexpr int kCavBlockSize = 128;
+constexpr int kCavBlockSize = 256;
+constexpr int kCavGroups = 32;        // cavities side by side in a workgroup of k_cavity
+constexpr unsigned kCavGridMax = 256 * 5;  // workgroups of k_cavity that fill the chip (LDS bound: 5 per compute unit)
 constexpr int kBigBlockSize = 256;
 constexpr int kHugeBlock = 1024;
 constexpr int kScanTileSize = 256 * 8;
+// Dynamic LDS of k_record and k_write with bs threads.
+constexpr unsigned record_lds(int bs) { return (unsigned)bs / 8 * 64 * 4; }
+constexpr unsigned write_lds(int bs) { return (unsigned)bs / 8 * 216 * 4; }
 
 }  // namespace gdp

@@ -194,21 +194,6 @@ __device__ __forceinline__ void stat_add(const Work &w, int f, uint64_t v) {
   for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
   if (__lane_id() == 0 && v) atomicAdd((unsigned long long *)&stat_line(w)->v[f], (unsigned long long)v);
 }
-// Four small statistics summed at once: each lane's values must stay below
-// 2^10 (the per-thread cavity slices bound them), so a wave's sums fit the
-// 16-bit fields of one 64-bit word.
-__device__ __forceinline__ void stat_add4(const Work &w, const int f[4], uint32_t a, uint32_t b, uint32_t c,
-                                         uint32_t d) {
-  uint64_t v = (uint64_t)a | ((uint64_t)b << 16) | ((uint64_t)c << 32) | ((uint64_t)d << 48);
-  for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k);
-  if (__lane_id() == 0 && v) {
-    StatLine *l = stat_line(w);
-    for (int i = 0; i < 4; i++) {
-      const uint64_t x = (v >> (16 * i)) & 0xffffu;
-      if (x) atomicAdd((unsigned long long *)&l->v[f[i]], (unsigned long long)x);
-    }
-  }
-}
 // Two statistics summed at once whose wave sums fit 32 bits.
 __device__ __forceinline__ void stat_add2(const Work &w, int f0, int f1, uint32_t a, uint32_t b) {
   uint64_t v = (uint64_t)a | ((uint64_t)b << 32);
@@ -234,9 +219,6 @@ __device__ __forceinline__ int bit_rank(const uint32_t *bm, const int32_t *words
   uint32_t below = (i & 31) ? (w & ((1u << (i & 31)) - 1u)) : 0u;
   return words_prefix[i >> 5] + tiles[(i >> 5) / kScanTileSize] + __popc(below);
 }
-
-// Exclusive prefix of the fresh-slot counts at winner r.
-__device__ __forceinline__ int fbase_at(const Work &w, int r) { return w.fbase[r] + w.tiles_f[r / kScanTileSize]; }
 
 __device__ __forceinline__ int orient_pts(const Work &w, double2 a, double2 b, double2 c) {
   return orient2d(a.x, a.y, b.x, b.y, c.x, c.y, w.tally);
@@ -763,9 +745,51 @@ __global__ __launch_bounds__(kPreBlock) void k_prefilter(DevMesh m, Work w, int 
 }
 
 // ---------------------------------------------------------------------------
-// R5 / R6: Bowyer-Watson cavities.  Per-thread growth in an LDS slice; a
-// cavity larger than the slice goes to the cooperative kernel below.
+// R5 / R6: Bowyer-Watson cavities, each grown by a group of kGrp lanes; a
+// cavity larger than the group's list goes to the cooperative kernel below.
+//
+// The unit of work is a boundary edge, not a triangle: the queue holds the
+// edges of the cavity found so far that have not been tested, and the lanes
+// of the group take the next kGrp of them.  A lane tests the triangle across
+// its edge; one whose circle holds the point joins the cavity and queues its
+// two other edges; any other edge is a boundary edge of the finished cavity.
+// The cavity of a point has no vertex inside, so its triangles form a tree
+// and every edge is tested once: 2 |C| + 1 edges, in about as many steps as
+// the tree is deep.
+//
+// What bounds it: each step is two dependent levels of gathers (the records
+// of the triangle across and the edge's end points, then the far vertex)
+// and one FP64 circle test, so a round lasts as long as its longest chain of
+// steps until the candidates fill the chip, and then as long as the lines it
+// gathers.  One lane per cavity (three circle tests per step, a step per
+// triangle, the wave waiting for its largest of 64 cavities) took 150 us a
+// round on the mesh of 50,000 points and 183 on that of 1,000,000; this takes
+// 49 and 116 (640,000 candidates: 318 -> 249).  Eight lanes: most steps of a
+// cavity of 8 triangles (the average) keep under eight edges waiting; four
+// lanes and twice the cavities took 59 and 124.
 // ---------------------------------------------------------------------------
+constexpr int kGrp = 8;         // lanes per cavity
+constexpr int kRing = 64;       // queue entries (at most len + 4 wait at once)
+constexpr int kListMax = 56;    // cavity triangles a group can list
+constexpr int kGrpWords = 3 * kRing + kListMax;  // LDS of a group; = 56 mod 64 banks, so that the eight
+                                                 // groups of a wave start in different banks
+constexpr int kCap = kCavCapDefault;
+static_assert(kCap <= kListMax && kListMax + 4 <= kRing, "cavity list and queue of a group");
+constexpr int kCavBlock = kCavBlockSize;
+
+__device__ __forceinline__ int grp_lane() { return __lane_id() & (kGrp - 1); }
+__device__ __forceinline__ int grp_first() { return __lane_id() & ~(kGrp - 1); }
+// The lanes of the caller's group for which p holds.
+__device__ __forceinline__ unsigned grp_ballot(bool p) {
+  return (unsigned)(__ballot(p) >> grp_first()) & ((1u << kGrp) - 1u);
+}
+// Orders the LDS accesses of a wave's lanes (one wave: the hardware keeps
+// them in program order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 struct CavCheck {
   int nbnd;
   bool fan_bad;
@@ -773,152 +797,158 @@ struct CavCheck {
   int ntest;  // incircle evaluations
 };
 
-// per-thread cavity capacity of the grid kernel: 39 slots x 128 threads (plus
-// a few bytes) is the most LDS that still lets 8 workgroups (16 waves) share a
-// compute unit's 160 KB; larger cavities go to the cooperative kernel
-constexpr int kCap = kCavCapDefault;
-// per-lane statistics of a per-thread cavity (size, boundary edges, circle
-// tests: at most three per slot) stay below 2^10 (see stat_add4)
-constexpr int kStat4Cap = 1023 / 3 - 2;
-static_assert(kCap <= kStat4Cap, "per-thread cavity statistics fit stat_add4");
-constexpr int kCavBlock = kCavBlockSize;
-
-// Grows the cavity of p from the seeds into lds[j * ls + tid] (a slice of
-// cap entries).  Returns the size, or -1 if it exceeds cap (the cavity then
-// goes to the cooperative path; the set of triangles is the same).
-// FILTER: the geometric tests use the FP64 filters alone, and a test they
-// cannot decide returns -2 (the cavity then goes to the cooperative path,
-// which evaluates exactly); this keeps the exact evaluations, and the
-// registers and scratch they need, out of the per-thread kernels.
+// Grows the cavity of p from the seeds (s1 < 0: one seed) into the group's
+// list, S[3 * kRing ..].  Returns the size, or -1 if it exceeds cap or (with
+// FILTER) the FP64 filter cannot decide a test: the cavity then goes to the
+// cooperative path, which evaluates exactly; this keeps the exact
+// evaluations, and the registers and scratch they need, out of the grid
+// kernels.  Every value but the list is uniform over the group.
 //
-// The boundary checks are made on the way: an edge of a cavity triangle is
-// internal iff its neighbour is in the cavity, and that is decided when the
-// triangle is taken from the list (a neighbour already listed is internal;
-// one that fails the circle test never enters).  For each boundary edge:
-// the count, the fan orientation (p strictly left of it), and for
-// circumcenters an encroached boundary subsegment (all are flagged; a
-// cavity that overflows flags a subset of what the cooperative path flags
-// for the same cavity).  The split subsegment of a midpoint (skip_k) is
-// not a boundary edge.  A cavity left undecided by a filter (FILTER) has
-// flagged a subset too.
+// Queue entry: (o, u, v): the edge u -> v of a cavity triangle and the
+// triangle o across it, -1 on the hull, or -2 - (4 t + e) for edge e of t
+// when it is a subsegment (never crossed).  For each boundary edge: the
+// count, the fan orientation (p strictly left of it), and for circumcenters
+// an encroached boundary subsegment (all are flagged; a cavity handed over
+// has flagged a subset of what the cooperative path flags for it).  The
+// split subsegment of a midpoint (skip_k) is not a boundary edge.
 template <bool FILTER>
-__device__ __forceinline__ int grow_local(const DevMesh &m, const Work &w, int32_t *lds, int ls, int cap, int tid,
-                                          const int *seeds, int nseeds, double2 p, int skip_k, bool is_cc,
-                                          CavCheck &ck) {
+__device__ __forceinline__ int grow_group(const DevMesh &m, const Work &w, int32_t *S, int cap, int s0, int s1,
+                                          double2 p, int skip_k, bool is_cc, CavCheck &ck) {
+  int32_t *qo = S, *qu = S + kRing, *qv = S + 2 * kRing, *list = S + 3 * kRing;
+  const int gl = grp_lane(), g0 = grp_first();
+  const unsigned below = (1u << gl) - 1u;
+  int len = s1 >= 0 && s1 != s0 ? 2 : 1;
+  int head = 0, tail = 3 * len;
   ck = CavCheck{0, false, false, 0};
-  int len = 0;
-  for (int s = 0; s < nseeds; s++) {
-    bool dup = false;
-    for (int q = 0; q < len; q++) dup |= lds[q * ls + tid] == seeds[s];
-    if (!dup) lds[(len++) * ls + tid] = seeds[s];
-  }
-  for (int h = 0; h < len; h++) {
-    const int t = lds[h * ls + tid];
+  if (gl < tail) {
+    const int t = gl < 3 ? s0 : s1, e = gl < 3 ? gl : gl - 3;
     const int4 tri = m.tv[t];
-    const int4 nb = m.tn[t];
-    // the three neighbours are distinct triangles, so they can be screened
-    // against the list together and then tested in edge order
-    int o[3];
-    bool c[3], in[3];
-    for (int e = 0; e < 3; e++) {
-      o[e] = comp(nb, e);
-      in[e] = false;
+    const int o = comp(m.tn[t], e);
+    qo[gl] = ((tri.w >> e) & 1) ? -2 - (4 * t + e) : (o < 0 ? -1 : o);
+    qu[gl] = comp(tri, e);
+    qv[gl] = comp(tri, e == 2 ? 0 : e + 1);
+  }
+  for (int j = 4 * gl; j < kListMax; j += 4 * kGrp)
+    *reinterpret_cast<int4 *>(list + j) = make_int4(j == 0 ? s0 : -1, j == 0 && len == 2 ? s1 : -1, -1, -1);
+  wave_lds_sync();
+  bool stop = false, fan_bad = false, enc = false;  // fan_bad, enc: this lane's
+  while (head < tail) {
+    // Straight-line code: lanes without an edge repeat the group's last one
+    // and an edge without a triangle across reads slot 0 (their results are
+    // masked), so a step has no branches but the rare ones.
+    const int nrun = min(kGrp, tail - head);
+    const bool act = gl < nrun;
+    const int qi = (head + min(gl, nrun - 1)) & (kRing - 1);
+    const int o = qo[qi], u = qu[qi], v = qv[qi];
+    const int oc = max(o, 0);
+    const double2 U = m.vxy[u], V = m.vxy[v];
+    const int4 to = m.tv[oc], no = m.tn[oc];
+    // listed: an internal edge (reached the other way)
+    bool in = false;
+    for (int q = 0; q < len; q += 4) {
+      const int4 x = *reinterpret_cast<const int4 *>(list + q);
+      in |= (x.x == o) | (x.y == o) | (x.z == o) | (x.w == o);
     }
-    for (int q = 0; q < len; q++) {
-      const int x = lds[q * ls + tid];
-      in[0] = in[0] || x == o[0];
-      in[1] = in[1] || x == o[1];
-      in[2] = in[2] || x == o[2];
+    // far vertex, and its index in the record (the edge is v -> u there)
+    const bool f0 = (to.x != u) & (to.x != v), f1 = (to.y != u) & (to.y != v);
+    const int fi = f0 ? 0 : (f1 ? 1 : 2);
+    const int f = f0 ? to.x : (f1 ? to.y : to.z);
+    const double2 F = m.vxy[f];
+    // the filters of gdp_exact.h without their branches; the orientation of
+    // the edge is one of the circle test's 2x2 minors
+    const double fx = F.x - p.x, fy = F.y - p.y, vx = V.x - p.x, vy = V.y - p.y, ux = U.x - p.x, uy = U.y - p.y;
+    const double vu1 = vx * uy, vu2 = ux * vy;
+    const double uf1 = ux * fy, uf2 = fx * uy;
+    const double fv1 = fx * vy, fv2 = vx * fy;
+    const double od = vu2 - vu1, op = fabs(vu1) + fabs(vu2), ob = 6.0 * kU * op;
+    const double fl = fx * fx + fy * fy, vl = vx * vx + vy * vy, ul = ux * ux + uy * uy;
+    const double det = fl * (vu1 - vu2) + vl * (uf1 - uf2) + ul * (fv1 - fv2);
+    const double perm = op * fl + (fabs(uf1) + fabs(uf2)) * vl + (fabs(fv1) + fabs(fv2)) * ul;
+    const double ib = 12.0 * kU * perm;
+    const bool left = (op > kTiny) & (od > ob), right = (op > kTiny) & (-od > ob);
+    const bool inside = (perm > kTiny) & (det > ib), outside = (perm > kTiny) & (-det > ib);
+    const bool test = act & (o >= 0) & !in;
+    bool und = test & !(inside | outside);
+    bool acc = test & inside;
+    if (!FILTER && und) {
+      // (the neighbour's vertices in its own order)
+      const double2 A = m.vxy[to.x], B = m.vxy[to.y], C = m.vxy[to.z];
+      acc = incircle(A.x, A.y, B.x, B.y, C.x, C.y, p.x, p.y, w.tally) > 0;
+      und = false;
     }
-    // in: internal (a listed neighbour across a non-subsegment edge);
-    // c: to be tested by the circle test; the rest (subsegment and hull
-    // edges) are boundary
-    for (int e = 0; e < 3; e++) {
-      const bool sub = (tri.w >> e) & 1;
-      in[e] = in[e] && !sub;
-      c[e] = !sub && o[e] >= 0 && !in[e];
-    }
-    if (in[0] && in[1] && in[2]) continue;
-    // independent loads: the neighbours' records, this triangle's vertices
-    // and subsegments; then only the far vertex of each neighbour
-    int4 to[3];
-    for (int e = 0; e < 3; e++) to[e] = c[e] ? m.tv[o[e]] : make_int4(0, 0, 0, 0);
-    const int4 ts = tri.w ? m.ts[t] : make_int4(-1, -1, -1, 0);
-    const double2 P[3] = {m.vxy[tri.x], m.vxy[tri.y], m.vxy[tri.z]};
-    double2 F[3];
-    int fv[3];
-    for (int e = 0; e < 3; e++) {
-      fv[e] = -1;
-      if (!c[e]) continue;
-      const int u = comp(tri, e), v = comp(tri, (e + 1) % 3);
-      fv[e] = (to[e].x != u && to[e].x != v) ? to[e].x : ((to[e].y != u && to[e].y != v) ? to[e].y : to[e].z);
-      F[e] = m.vxy[fv[e]];
-    }
-    for (int e = 0; e < 3; e++) {
-      if (in[e]) continue;
-      const double2 Pu = P[e], Pv = P[(e + 1) % 3];
-      if (c[e]) {
-        const int u = comp(tri, e);
-        // the neighbour's vertices in its own order (the same arguments as
-        // a direct evaluation on its record)
-        const double2 A = to[e].x == fv[e] ? F[e] : (to[e].x == u ? Pu : Pv);
-        const double2 B = to[e].y == fv[e] ? F[e] : (to[e].y == u ? Pu : Pv);
-        const double2 C = to[e].z == fv[e] ? F[e] : (to[e].z == u ? Pu : Pv);
-        ck.ntest++;
-        int in;
+    bool bnd = act & !in & !acc;
+    if (o <= -2) {
+      // a subsegment: the split one is no boundary edge; any other may be
+      // encroached by a circumcenter
+      const int sid = reinterpret_cast<const int32_t *>(m.ts)[-2 - o];
+      if (skip_k >= 0 && sid == skip_k) {
+        bnd = false;
+      } else if (bnd && is_cc && sid >= 0) {
+        int en;
         if (FILTER) {
-          in = incircle_filter(A.x, A.y, B.x, B.y, C.x, C.y, p.x, p.y);
-          if (in == kUndecided) return -2;
+          en = encroaches_filter(w.enc_mode, U.x, U.y, V.x, V.y, p.x, p.y);
+          und |= en == kUndecided;
         } else {
-          in = incircle(A.x, A.y, B.x, B.y, C.x, C.y, p.x, p.y, w.tally);
+          en = encroached(w, U, V, p) ? 1 : 0;
         }
-        if (in > 0) {
-          if (len == cap) return -1;
-          lds[(len++) * ls + tid] = o[e];
-          continue;
-        }
-      }
-      // a boundary edge
-      const int sid = ((tri.w >> e) & 1) ? comp(ts, e) : -1;
-      if (skip_k >= 0 && sid == skip_k) continue;
-      ck.nbnd++;
-      if (is_cc && sid >= 0) {
-        int enc;
-        if (FILTER) {
-          enc = encroaches_filter(w.enc_mode, Pu.x, Pu.y, Pv.x, Pv.y, p.x, p.y);
-          if (enc == kUndecided) return -2;
-        } else {
-          enc = encroached(w, Pu, Pv, p) ? 1 : 0;
-        }
-        if (enc) {
+        if (en == 1) {
           flag_mid(w, sid);
-          ck.enc = true;
+          enc = true;
         }
       }
-      int o;
-      if (FILTER) {
-        o = orient2d_filter(Pu.x, Pu.y, Pv.x, Pv.y, p.x, p.y);
-        if (o == kUndecided) return -2;
-      } else {
-        o = orient_pts(w, Pu, Pv, p);
-      }
-      if (o <= 0) ck.fan_bad = true;
     }
-  }
-  // insertion sort (ascending slots)
-  for (int a = 1; a < len; a++) {
-    int x = lds[a * ls + tid];
-    int b = a - 1;
-    while (b >= 0 && lds[b * ls + tid] > x) {
-      lds[(b + 1) * ls + tid] = lds[b * ls + tid];
-      b--;
+    const bool o_und = bnd & !(left | right);
+    if (FILTER) {
+      und |= o_und;
+      fan_bad |= bnd & right;
+    } else {
+      fan_bad |= o_und ? orient_pts(w, U, V, p) <= 0 : (bnd & right);
     }
-    lds[(b + 1) * ls + tid] = x;
+    ck.ntest += __popc(grp_ballot(test));
+    ck.nbnd += __popc(grp_ballot(bnd));
+    const unsigned am = grp_ballot(acc);
+    int na = __popc(am), r = __popc(am & below);
+    stop = (FILTER && grp_ballot(und) != 0) || len + na > cap;
+    if (stop) break;
+    if (acc) list[len + r] = o;
+    wave_lds_sync();
+    // two lanes can reach one triangle in the same step: the first one counts
+    bool dup = false;
+    if (acc)
+      for (int k = 0; k < r; k++) dup |= list[len + k] == o;
+    if (grp_ballot(dup) != 0) {
+      acc = acc && !dup;
+      const unsigned am2 = grp_ballot(acc);
+      const int na1 = na;
+      na = __popc(am2);
+      r = __popc(am2 & below);
+      wave_lds_sync();
+      if (gl < na1) list[len + gl] = -1;
+      wave_lds_sync();
+      if (acc) list[len + r] = o;
+    }
+    if (acc) {
+      const int e1 = fi, e2 = fi == 0 ? 2 : fi - 1;  // far -> v, u -> far
+      const int i1 = (tail + 2 * r) & (kRing - 1), i2 = (i1 + 1) & (kRing - 1);
+      const int o1 = max(comp(no, e1), -1), o2 = max(comp(no, e2), -1);
+      qo[i1] = ((to.w >> e1) & 1) ? -2 - (4 * o + e1) : o1;
+      qu[i1] = f;
+      qv[i1] = v;
+      qo[i2] = ((to.w >> e2) & 1) ? -2 - (4 * o + e2) : o2;
+      qu[i2] = u;
+      qv[i2] = f;
+    }
+    head += nrun;
+    tail += 2 * na;
+    len += na;
+    wave_lds_sync();
   }
-  return len;
+  ck.fan_bad = grp_ballot(fan_bad) != 0;
+  ck.enc = grp_ballot(enc) != 0;
+  return stop ? -1 : len;
 }
 
-// Outcome of one per-thread cavity: alive (cavity left in the LDS slice),
+// Outcome of one group's cavity: alive (cavity left in the group's list),
 // dropped (with the counter it feeds) or handed to the cooperative kernel.
 struct CavRes {
   int len;        // cavity size when grown (0 otherwise)
@@ -926,130 +956,230 @@ struct CavRes {
   int alive;
   int enc_reject, fan_invalid, unsplittable, mid_cand;
   int ntest;      // incircle evaluations made while growing
+  uint64_t key;   // the candidate's (alive)
 };
 
 template <bool FILTER>
-__device__ __forceinline__ CavRes cavity_one(const DevMesh &m, const Work &w, int32_t *lds, int ls, int cap, int tid,
-                                             int ci, int is_cc) {
-  CavRes res{0, 0, 0, 0, 0, 0, 0, 0};
-  CandSet S = is_cc ? w.cc : w.mid;
-  int st = S.state[ci];
-  if (st & (kStDone | kStSkip | kStBig)) return res;
-  int seeds[2], nseeds = 0, skip_k = -1, expect = 2;
+__device__ __forceinline__ CavRes cavity_one(const DevMesh &m, const Work &w, int32_t *S_lds, int cap, int ci,
+                                             int is_cc) {
+  CavRes res{0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const CandSet &S = is_cc ? w.cc : w.mid;
+  const bool lead = grp_lane() == 0;
+  int s0 = -1, s1 = -1, skip_k = -1, expect = 2;
   double2 p;
+  int st = S.state[ci];
   if (is_cc) {
-    if (!(st & kStFound)) return res;
-    seeds[nseeds++] = S.loc[ci];
+    // (loaded together; the located triangle is not set unless found)
+    s0 = S.loc[ci];
     p = S.p[ci];
+    res.key = S.key[ci];
+    if ((st & (kStDone | kStSkip | kStBig)) || !(st & kStFound)) return res;
   } else {
-    int k = S.elem[ci];
+    const int k = S.elem[ci];
+    if (st & (kStDone | kStSkip | kStBig)) return res;
     res.mid_cand = 1;
     const int a0 = w.sadj[2 * k], a1 = w.sadj[2 * k + 1];  // with the subsegment's record
-    SplitPt r = seg_split(m, k, w.pm, w.split_mode);
-    S.key[ci] = r.key;
+    const SplitPt r = seg_split(m, k, w.pm, w.split_mode);
     p = make_double2(r.px, r.py);
-    S.p[ci] = p;
-    int2 sk = m.sv[k];
-    double2 A = m.vxy[sk.x], B = m.vxy[sk.y];
-    if ((p.x == A.x && p.y == A.y) || (p.x == B.x && p.y == B.y)) {
+    res.key = r.key;
+    const int2 sk = m.sv[k];
+    const double2 A = m.vxy[sk.x], B = m.vxy[sk.y];
+    const bool uns = (p.x == A.x && p.y == A.y) || (p.x == B.x && p.y == B.y);
+    if (lead) {
+      S.key[ci] = r.key;
+      S.p[ci] = p;
+      if (uns) S.state[ci] = st | kStDone;
+    }
+    if (uns) {
       res.unsplittable = 1;
-      S.state[ci] = st | kStDone;
       return res;
     }
-    if (a0 >= 0) seeds[nseeds++] = a0 >> 2;
-    if (a1 >= 0) seeds[nseeds++] = a1 >> 2;
+    s0 = a0 >= 0 ? a0 >> 2 : a1 >> 2;
+    s1 = a0 >= 0 && a1 >= 0 ? a1 >> 2 : -1;
     skip_k = k;
-    expect = nseeds == 2 ? 2 : 1;
-    S.state[ci] = st | kStFound;
+    expect = s1 >= 0 ? 2 : 1;
+    st |= kStFound;
   }
   CavCheck ck;
-  int len = grow_local<FILTER>(m, w, lds, ls, cap, tid, seeds, nseeds, p, skip_k, is_cc != 0, ck);
+  ck = CavCheck{0, false, false, 0};
+  // (a subsegment without a triangle on either side has an empty cavity)
+  const int len = s0 < 0 ? 0 : grow_group<FILTER>(m, w, S_lds, cap, s0, s1, p, skip_k, is_cc != 0, ck);
   res.ntest = ck.ntest;
   if (len < 0) {
-    S.state[ci] = st | kStBig | kStFound;
-    int q = atomicAdd(&w.cnt->nbig, 1);
-    if (q < w.big_cap) w.big[q] = (is_cc ? 0 : (int)0x80000000) | ci;
-    else atomicOr(&w.cnt->err, kErrCavity);
+    if (lead) {
+      S.state[ci] = st | kStBig | kStFound;
+      int q = atomicAdd(&w.cnt->nbig, 1);
+      if (q < w.big_cap) w.big[q] = (is_cc ? 0 : (int)0x80000000) | ci;
+      else atomicOr(&w.cnt->err, kErrCavity);
+    }
     return res;
   }
   res.len = len;
   res.bnd = ck.nbnd;
-  if (is_cc && ck.enc) {
-    res.enc_reject = 1;
-    S.state[ci] |= kStDone;
-  } else if (ck.fan_bad || ck.nbnd - len != expect) {
-    res.fan_invalid = 1;
-    S.state[ci] |= kStDone;
-  } else {
-    res.alive = 1;
-  }
+  const bool rej = is_cc && ck.enc;
+  if (rej) res.enc_reject = 1;
+  else if (ck.fan_bad || ck.nbnd - len != expect) res.fan_invalid = 1;
+  else res.alive = 1;
+  if (lead) S.state[ci] = res.alive ? st : (st | kStDone);
   return res;
 }
 
-// Per-thread cavities of one class (lds: cap slices of ls entries; the
-// threads tid < ls take part).
-// The midpoint list is final when this runs for midpoints (they are flagged
-// only by the scan, the walk and the circumcenter cavities), so its length
-// is read from device memory.  The loop is uniform over the workgroup so
-// that pool space and statistics are handled once per wave.
-// Candidates [lo, hi) of the class (hi < 0: to the end of the list); tid is
-// the thread's index in the group that runs the loop (its LDS slice).
+// Pool room for the cavities of a wave (need: the group leaders' sizes, 0 on
+// other lanes; all lanes of the wave take part).  Atomics on one address are
+// served about 12 ns apart, so a workgroup takes one piece of the pool up
+// front (s_pool, chunk_end: LDS, taken by LDS atomics) and a wave that finds
+// it empty takes a piece of its own (fb_cur, fb_end), at least `more` long.
+__device__ __forceinline__ int pool_take(const Work &w, int need, int *s_pool, int chunk_end, int more, int &fb_cur,
+                                         int &fb_end) {
+  const int lane = __lane_id();
+  int x = need;
+  for (int d = kGrp; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d);
+    if (lane >= d) x += y;
+  }
+  const int total = __shfl(x, 64 - kGrp);
+  int base = 0;
+  if (total > 0) {
+    if (chunk_end > 0) {
+      if (lane == 0) base = atomicAdd(s_pool, total);
+      base = __shfl(base, 0);
+    }
+    if (base + total > chunk_end) {
+      if (total > fb_end - fb_cur) {
+        const int take = max(total, more);
+        int g = 0;
+        if (lane == 0) g = atomicAdd(&w.cnt->pool_used, take);
+        fb_cur = __shfl(g, 0);
+        fb_end = fb_cur + take;
+      }
+      base = fb_cur;
+      fb_cur += total;
+    }
+  }
+  return base + x - need;
+}
+
+// Statistics of a workgroup's cavities, summed in LDS (indexed by StatField)
+// and added to its wave's stat line once, after a barrier.
+__device__ __forceinline__ void stat_lds_clear(uint32_t *s) {
+  for (int f = threadIdx.x; f < kStFields; f += blockDim.x) s[f] = 0;
+}
+__device__ __forceinline__ void stat_lds_flush(const Work &w, const uint32_t *s) {
+  for (int f = threadIdx.x; f < kStFields; f += blockDim.x) {
+    const unsigned long long x = s[f];
+    if (!x) continue;
+    unsigned long long *d = (unsigned long long *)&stat_line(w)->v[f];
+    if (f == kStCavMax) atomicMax(d, x);
+    else atomicAdd(d, x);
+  }
+}
+
+// Group cavities of candidates [lo, hi) of one class (hi < 0: to the end of
+// the list).  lds: kGrpWords per group; grp: the group's index among those
+// that run the loop, ngrp of which take candidates side by side; stat: the
+// workgroup's statistics.  The midpoint list is final when this runs for
+// midpoints (they are flagged only by the scan, the walk and the
+// circumcenter cavities), so its length is read from device memory.  With
+// L.blk (grid kernels: every thread of the workgroup runs the loop, which is
+// uniform over it) pool space is taken per workgroup.
 template <bool FILTER = false>
-__device__ __forceinline__ void cavity_part(const DevMesh &m, const Work &w, int is_cc, int32_t *lds, int ls, int cap,
-                                            const Lanes &L, int lo = 0, int hi = -1, int tid = -1) {
-  if (tid < 0) tid = threadIdx.x;
+__device__ __forceinline__ void cavity_part(const DevMesh &m, const Work &w, int is_cc, int32_t *lds, int cap,
+                                            uint32_t *stat, int first, int ngrp, int grp, bool blk, int lo = 0,
+                                            int hi = -1) {
+  __shared__ int s_pool[2];
   const int n = hi >= 0 ? hi : (is_cc ? w.cnt->ncc : w.cnt->nmk);
-  CandSet S = is_cc ? w.cc : w.mid;
-  for (int base = lo + L.base0; base < n; base += L.stride) {
-    int ci = base + tid;
-    CavRes r{0, 0, 0, 0, 0, 0, 0, 0};
-    if (ci < n) r = cavity_one<FILTER>(m, w, lds, ls, cap, tid, ci, is_cc);
-    int off = group_alloc(&w.cnt->pool_used, r.alive ? r.len : 0, L);
+  const CandSet &S = is_cc ? w.cc : w.mid;
+  int32_t *G = lds + grp * kGrpWords;
+  const int gl = grp_lane(), g0 = grp_first();
+  const int per_blk = blockDim.x / kGrp;
+  int chunk_end = 0, fb_cur = 0, fb_end = 0;
+  bool have = !blk;
+  if (blk && lo + first < n && threadIdx.x == 0) {
+    // room for eight triangles per candidate, the usual average, while that
+    // leaves a quarter of the pool to the waves' own pieces
+    const int iters = (n - lo - first + ngrp - 1) / ngrp;
+    const int per = (int)min((int64_t)8, (int64_t)w.pool_cap * 3 / 4 / max(n, 1));
+    const int take = iters * per_blk * per;
+    const int b = take > 0 ? atomicAdd(&w.cnt->pool_used, take) : 0;
+    s_pool[0] = b;
+    s_pool[1] = b + take;
+  }
+  for (int base = lo + first; base < n; base += ngrp) {
+    const int ci = base + grp;
+    CavRes r{0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (ci < n) r = cavity_one<FILTER>(m, w, G, cap, ci, is_cc);
+    if (!have) {
+      __syncthreads();
+      chunk_end = s_pool[1];
+      have = true;
+    } else if (!blk) {
+      chunk_end = 0;
+    }
+    const int left = (n - base - 1) / ngrp;  // iterations after this one
+    int off = pool_take(w, gl == 0 && r.alive ? r.len : 0, s_pool, chunk_end, min(left, 8) * 64, fb_cur, fb_end);
+    off = __shfl(off, g0);
     bool counted = r.len > 0 && !r.alive;  // dropped cavities count in the statistics now
     if (r.alive) {
       if (off + r.len > w.pool_cap) {
-        atomicOr(&w.cnt->err, kErrPool);  // the round is abandoned and run again
+        if (gl == 0) atomicOr(&w.cnt->err, kErrPool);  // the round is abandoned and run again
       } else {
         // R8 marks are placed as soon as the cavity is known to be valid:
         // validity depends on this cavity alone, and atomicMax is order free.
-        uint64_t key = S.key[ci];
-        for (int j = 0; j < r.len; j++) {
-          int t = lds[j * ls + tid];
+        // (The pool keeps the order of growth; the insertion sorts the slots
+        // of a winner.)
+        for (int j = gl; j < r.len; j += kGrp) {
+          const int t = G[3 * kRing + j];
           w.pool[off + j] = t;
-          atomicMax((unsigned long long *)&w.mark[t], (unsigned long long)key);
+          atomicMax((unsigned long long *)&w.mark[t], (unsigned long long)r.key);
         }
-        S.off[ci] = off;
-        S.len[ci] = r.len;
-        S.state[ci] |= kStDone | kStAlive;
         counted = true;
+        if (gl == 0) {
+          S.off[ci] = off;
+          S.len[ci] = r.len;
+          S.state[ci] |= kStDone | kStAlive;
+        }
       }
     }
-    // (summed per iteration: nothing stays live across the cavity work)
-    stat_max(w, kStCavMax, counted ? r.len : 0);
-    const int f4a[4] = {kStCavTri, is_cc ? kStCavLen1 : kStCavLen0, is_cc ? kStCavBnd1 : kStCavBnd0, kStInTests};
-    const int f4b[4] = {is_cc ? kStMarks1 : kStMarks0, kStEncReject, kStFanInvalid, kStUnsplittable};
-    stat_add4(w, f4a, counted ? r.len : 0, r.len, r.bnd, r.ntest);
-    stat_add4(w, f4b, (r.alive && counted) ? r.len : 0, r.enc_reject, r.fan_invalid, r.unsplittable);
-    stat_add(w, kStMidCand, r.mid_cand);
+    if (gl == 0) {
+      if (counted) {
+        atomicMax(&stat[kStCavMax], (uint32_t)r.len);
+        atomicAdd(&stat[kStCavTri], (uint32_t)r.len);
+        if (r.alive) atomicAdd(&stat[is_cc ? kStMarks1 : kStMarks0], (uint32_t)r.len);
+      }
+      if (r.len) {
+        atomicAdd(&stat[is_cc ? kStCavLen1 : kStCavLen0], (uint32_t)r.len);
+        atomicAdd(&stat[is_cc ? kStCavBnd1 : kStCavBnd0], (uint32_t)r.bnd);
+      }
+      if (r.ntest) atomicAdd(&stat[kStInTests], (uint32_t)r.ntest);
+      if (r.enc_reject) atomicAdd(&stat[kStEncReject], 1u);
+      if (r.fan_invalid) atomicAdd(&stat[kStFanInvalid], 1u);
+      if (r.unsplittable) atomicAdd(&stat[kStUnsplittable], 1u);
+      if (r.mid_cand) atomicAdd(&stat[kStMidCand], 1u);
+    }
   }
 }
 
 // One kernel symbol per class (circumcenters: IS_CC = 1), so that profiles
-// tell them apart, and per slice length CAP (the per-thread capacity; a
-// cavity beyond it goes to the cooperative path: perf only).
-template <int IS_CC, int CAP>
-__global__ __launch_bounds__(kCavBlock, 4) void k_cavity(DevMesh m, Work w) {
-  static_assert(CAP <= kStat4Cap, "per-thread cavity statistics fit stat_add4");
-  __shared__ int32_t lds[CAP * kCavBlock];
-  if (w.st->halt) return;
-  cavity_part<true>(m, w, IS_CC, lds, kCavBlock, CAP, grid_lanes());
+// tell them apart.  cap: a cavity beyond it goes to the cooperative path
+// (perf only).
+template <int IS_CC>
+__device__ __forceinline__ void cavity_grid(const DevMesh &m, const Work &w, int cap, int bx, int nb) {
+  __shared__ __attribute__((aligned(16))) int32_t lds[kGrpWords * (kCavBlock / kGrp)];
+  __shared__ uint32_t stat[kStFields];
+  constexpr int per = kCavBlock / kGrp;
+  stat_lds_clear(stat);
+  __syncthreads();
+  cavity_part<true>(m, w, IS_CC, lds, cap, stat, bx * per, nb * per, (int)threadIdx.x / kGrp, true);
+  __syncthreads();
+  stat_lds_flush(w, stat);
 }
-template __global__ void k_cavity<0, kCap>(DevMesh m, Work w);
-template __global__ void k_cavity<1, kCap>(DevMesh m, Work w);
-template __global__ void k_cavity<0, 24>(DevMesh m, Work w);
-template __global__ void k_cavity<1, 24>(DevMesh m, Work w);
-template __global__ void k_cavity<0, 12>(DevMesh m, Work w);
-template __global__ void k_cavity<1, 12>(DevMesh m, Work w);
+template <int IS_CC>
+__global__ __launch_bounds__(kCavBlock, 5) void k_cavity(DevMesh m, Work w, int cap) {
+  if (w.st->halt) return;
+  cavity_grid<IS_CC>(m, w, cap, (int)blockIdx.x, (int)gridDim.x);
+}
+template __global__ void k_cavity<0>(DevMesh m, Work w, int cap);
+template __global__ void k_cavity<1>(DevMesh m, Work w, int cap);
 
 // Cooperative growth of one large cavity per workgroup (the tuple-parallel
 // ExpandList idea of Section 5.3: the frontier of <point, triangle> tuples
@@ -1361,12 +1491,20 @@ __device__ __forceinline__ bool cand_at(const Work &w, int c, int ncc, CandSet &
   S = w.mid; ci = c - ncc; is_cc = 0; return true;
 }
 
-__device__ __forceinline__ void own_one(const Work &w, int c, int ncc, int &lost) {
+// Fresh slots of a winner: two, or one for a midpoint on a hull subsegment.
+__device__ __forceinline__ int fresh_of(const Work &w, int is_cc, int e) {
+  if (is_cc) return 2;
+  return (w.sadj[2 * e] >= 0 && w.sadj[2 * e + 1] >= 0) ? 2 : 1;
+}
+
+// Whether candidate c holds every mark of its cavity (lost: it was judged and
+// does not).
+__device__ __forceinline__ bool own_one(const Work &w, int c, int ncc, int &lost) {
   CandSet S;
   int ci, is_cc;
   cand_at(w, c, ncc, S, ci, is_cc);
   int st = S.state[ci];
-  if (!(st & kStAlive)) return;
+  if (!(st & kStAlive)) return false;
   uint64_t key = S.key[ci];
   int off = S.off[ci], len = S.len[ci];
   // independent loads, kIlp slots at a time (the marks are tested after)
@@ -1385,17 +1523,32 @@ __device__ __forceinline__ void own_one(const Work &w, int c, int ncc, int &lost
     S.state[ci] = st | kStW0;
     bit_set(is_cc ? w.w0_t : w.w0_s, S.elem[ci]);
   } else {
-    lost = 1;
+    lost++;
   }
+  return own;
 }
 
+// The owners go to a list, so that the later phases run over them alone (a
+// quarter of the candidates of a large round).  A thread of a large round
+// judges several candidates before list space is taken, which keeps the
+// atomics on the one counter few.
+constexpr int kOwnPer = 4;
 __device__ __forceinline__ void own_part(const Work &w, const Lanes &L) {
   const int ncc = w.cnt->ncc, n = ncc + w.cnt->nmk;
+  const int per = L.blk && n > 65536 ? kOwnPer : 1;
   int n_lost = 0;
-  for (int base = L.base0; base < n; base += L.stride) {
-    int c = base + threadIdx.x, lost = 0;
-    if (c < n) own_one(w, c, ncc, lost);
-    n_lost += lost;
+  for (int base = L.base0 * per; base < n; base += L.stride * per) {
+    unsigned own = 0;
+    for (int k = 0; k < per; k++) {
+      const int c = base + k * (int)blockDim.x + (int)threadIdx.x;
+      if (c < n && own_one(w, c, ncc, n_lost)) own |= 1u << k;
+    }
+    int off = group_alloc(&w.cnt->nw0, __popc(own), L);
+    for (int k = 0; k < per; k++) {
+      if (!((own >> k) & 1u)) continue;
+      const int c = base + k * (int)blockDim.x + (int)threadIdx.x;
+      w.w0_list[off++] = c < ncc ? c : ((int)0x80000000 | (c - ncc));
+    }
   }
   stat_add(w, kStLostMark, n_lost);
 }
@@ -1405,77 +1558,80 @@ __global__ void k_own(Work w) {
   own_part(w, grid_lanes());
 }
 
-// R9: Delaunay dependency across a shared non-subsegment cavity edge.
-// Returns true if the candidate is dropped.
-__device__ __forceinline__ bool dep_one(const DevMesh &m, const Work &w, int c, int ncc, int &ntest) {
-  CandSet S;
+// The insertion phases give each owner (then each winner) a group of kGrp
+// lanes, one cavity triangle or fan record per lane: their loads are a few
+// dependent levels whatever the cavity's size (one thread per owner walked
+// its cavity two triangles at a time: k_dep 33, k_record 45, k_write 87 us
+// per round at 50,000 points, for a few thousand winners as for 100,000).
+struct GrpLanes {
+  int first, stride, grp;  // list entries first + grp, + stride, ...
+};
+__device__ __forceinline__ GrpLanes grp_lanes(const Lanes &L) {
+  return {L.base0 / kGrp, L.stride / kGrp, (int)threadIdx.x / kGrp};
+}
+__device__ __forceinline__ const CandSet &cand_ref(const Work &w, int ref, int &ci, int &is_cc) {
+  is_cc = (ref & 0x80000000) ? 0 : 1;
+  ci = ref & 0x7fffffff;
+  return is_cc ? w.cc : w.mid;
+}
+
+// R9: Delaunay dependency across a shared non-subsegment cavity edge, the
+// lanes of a group over the cavity's triangles.  Returns true if the
+// candidate is dropped (uniform over the group).
+__device__ __forceinline__ bool dep_one(const DevMesh &m, const Work &w, int ref, int &ntest) {
   int ci, is_cc;
-  cand_at(w, c, ncc, S, ci, is_cc);
-  int st = S.state[ci];
-  if (!(st & kStW0)) return false;
-  uint64_t key = S.key[ci];
-  double2 p = S.p[ci];
-  int off = S.off[ci], len = S.len[ci];
-  int skip_k = is_cc ? -1 : S.elem[ci];
+  const CandSet &S = cand_ref(w, ref, ci, is_cc);
+  const int gl = grp_lane();
+  const uint64_t key = S.key[ci];
+  const double2 p = S.p[ci];
+  const int off = S.off[ci], len = S.len[ci], st = S.state[ci], elem = S.elem[ci];
   bool drop = false;
-  constexpr int B = 2;  // cavity triangles per batch
-  for (int j0 = 0; j0 < len && !drop; j0 += B) {
-    int tt[B];
-    int4 tri_[B], nb_[B], ts_[B];
-    uint64_t mo_[B][3];
-#pragma unroll
-    for (int i = 0; i < B; i++) tt[i] = j0 + i < len ? w.pool[off + j0 + i] : -1;
-#pragma unroll
-    for (int i = 0; i < B; i++) {
-      const bool v = tt[i] >= 0;
-      tri_[i] = v ? m.tv[tt[i]] : make_int4(0, 0, 0, 0);
-      nb_[i] = v ? m.tn[tt[i]] : make_int4(-1, -1, -1, 0);
-      ts_[i] = v ? m.ts[tt[i]] : make_int4(-1, -1, -1, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < B; i++)
+  for (int j = gl; j < ((len + kGrp - 1) & ~(kGrp - 1)); j += kGrp) {
+    bool hit = false;
+    if (j < len) {
+      const int t = w.pool[off + j];
+      const int4 tri = m.tv[t], nb = m.tn[t];
+      const int4 ts = tri.w ? m.ts[t] : make_int4(-1, -1, -1, 0);
+      uint64_t mo[3];
 #pragma unroll
       for (int e = 0; e < 3; e++) {
-        const int o = comp(nb_[i], e);
-        const bool sub = ((tri_[i].w >> e) & 1) && comp(ts_[i], e) >= 0;
-        mo_[i][e] = (!sub && o >= 0) ? w.mark[o] : 0ull;
+        // subsegment edges (incl. the split one) and hull edges have no owner across
+        const int o = comp(nb, e);
+        const bool sub = ((tri.w >> e) & 1) && comp(ts, e) >= 0;
+        mo[e] = (!sub && o >= 0) ? w.mark[o] : 0ull;
       }
 #pragma unroll
-    for (int i = 0; i < B; i++)
-#pragma unroll
-    for (int e = 0; e < 3; e++) {
-      if (drop || tt[i] < 0) continue;
-      const int4 tri = tri_[i];
-      // subsegment edges (incl. the split one) and hull edges were given mark 0
-      uint64_t mo = mo_[i][e];
-      if (mo == key || mo == 0) continue;  // inside this cavity, or unclaimed
-      int q_cc = (mo >> 63) ? 0 : 1;
-      int qid = (int)perm32_inv((uint32_t)(mo & 0xffffffffu));
-      if (!bit_get(q_cc ? w.w0_t : w.w0_s, qid)) continue;
-      if (!(key < mo)) continue;  // only the lower key of a dependent pair drops
-      double2 q = q_cc ? w.cc.p[w.cidx_t[qid]] : w.mid.p[w.cidx_s[qid]];
-      double2 U = m.vxy[comp(tri, e)], V = m.vxy[comp(tri, (e + 1) % 3)];
-      ntest++;
-      if (incircle(U.x, U.y, V.x, V.y, p.x, p.y, q.x, q.y, w.tally) > 0) drop = true;
+      for (int e = 0; e < 3; e++) {
+        // inside this cavity, unclaimed, or the other is the lower key (only
+        // the lower key of a dependent pair drops)
+        if (mo[e] == key || mo[e] == 0 || !(key < mo[e])) continue;
+        const int q_cc = (mo[e] >> 63) ? 0 : 1;
+        const int qid = (int)perm32_inv((uint32_t)(mo[e] & 0xffffffffu));
+        if (!bit_get(q_cc ? w.w0_t : w.w0_s, qid)) continue;
+        const double2 q = q_cc ? w.cc.p[w.cidx_t[qid]] : w.mid.p[w.cidx_s[qid]];
+        const double2 U = m.vxy[comp(tri, e)], V = m.vxy[comp(tri, e == 2 ? 0 : e + 1)];
+        ntest++;
+        hit |= incircle(U.x, U.y, V.x, V.y, p.x, p.y, q.x, q.y, w.tally) > 0;
+      }
     }
+    drop = grp_ballot(hit) != 0;
+    if (drop) break;
   }
-  (void)skip_k;
-  if (!drop) {
+  if (!drop && gl == 0) {
     S.state[ci] = st | kStWin;
-    bit_set(is_cc ? w.win_t : w.win_s, S.elem[ci]);
+    bit_set(is_cc ? w.win_t : w.win_s, elem);
+    if (!is_cc && fresh_of(w, 0, elem) == 1) bit_set(w.win_h, elem);
   }
   return drop;
 }
 
 __device__ __forceinline__ void dep_part(const DevMesh &m, const Work &w, const Lanes &L) {
-  const int ncc = w.cnt->ncc, n = ncc + w.cnt->nmk;
+  const int n = w.cnt->nw0;
+  const GrpLanes g = grp_lanes(L);
   int n_drop = 0, ntest = 0;
-  for (int base = L.base0; base < n; base += L.stride) {
-    int c = base + threadIdx.x;
-    if (c < n) n_drop += dep_one(m, w, c, ncc, ntest);
-  }
-  stat_add(w, kStDepDrop, n_drop);
-  stat_add(w, kStInTests, ntest);
+  for (int i = g.first + g.grp; i < n; i += g.stride)
+    if (dep_one(m, w, w.w0_list[i], ntest) && grp_lane() == 0) n_drop++;
+  stat_add2(w, kStDepDrop, kStInTests, n_drop, ntest);
 }
 
 __global__ void k_dep(DevMesh m, Work w) {
@@ -1519,7 +1675,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int *total) {
 }
 
 // Exclusive scans in two launches: per-tile scans (the workgroups stride
-// over the tiles of one or two jobs), then one workgroup per job scans the
+// over the tiles of one to three jobs), then one workgroup per job scans the
 // tile totals in place.  A reader adds the tile prefix itself:
 // value(i) = out[i] + tiles[i / kScanTile].
 __device__ void scan_tile(const ScanJob &j, int n, int tile) {
@@ -1544,20 +1700,27 @@ __device__ void scan_tile(const ScanJob &j, int n, int tile) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_tiles(ScanJob a, ScanJob b, const int32_t *halt) {
-  if (*halt) return;
-  const int na = *a.n_dev, nb = b.in ? *b.n_dev : 0;
-  const int ta = (na + kScanTile - 1) / kScanTile, tb = (nb + kScanTile - 1) / kScanTile;
-  for (int tile = blockIdx.x; tile < ta + tb; tile += gridDim.x) {
-    if (tile < ta) scan_tile(a, na, tile);
-    else scan_tile(b, nb, tile - ta);
+__device__ __forceinline__ void scan_tiles(const ScanJobs &J) {
+  int t[3], n[3];
+  for (int k = 0; k < 3; k++) {
+    n[k] = J.j[k].in ? *J.j[k].n_dev : 0;
+    t[k] = (n[k] + kScanTile - 1) / kScanTile;
+  }
+  for (int tile = blockIdx.x; tile < t[0] + t[1] + t[2]; tile += gridDim.x) {
+    if (tile < t[0]) scan_tile(J.j[0], n[0], tile);
+    else if (tile < t[0] + t[1]) scan_tile(J.j[1], n[1], tile - t[0]);
+    else scan_tile(J.j[2], n[2], tile - t[0] - t[1]);
   }
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_sums(ScanJob a, ScanJob b, const int32_t *halt) {
-  __shared__ int s_total;
+__global__ __launch_bounds__(kScanBlock) void k_scan_tiles(ScanJobs J, const int32_t *halt) {
   if (*halt) return;
-  const ScanJob &j = blockIdx.x == 0 ? a : b;
+  scan_tiles(J);
+}
+
+// One workgroup per job.
+__device__ __forceinline__ void scan_sums(const ScanJob &j) {
+  __shared__ int s_total;
   if (!j.in) return;
   const int ntiles = (*j.n_dev + kScanTile - 1) / kScanTile;
   int carry = 0;
@@ -1572,56 +1735,14 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_sums(ScanJob a, ScanJob b, 
   if (threadIdx.x == 0) *j.total = carry;
 }
 
+__global__ __launch_bounds__(kScanBlock) void k_scan_sums(ScanJobs J, const int32_t *halt) {
+  if (*halt) return;
+  scan_sums(blockIdx.x == 0 ? J.j[0] : (blockIdx.x == 1 ? J.j[1] : J.j[2]));
+}
+
 // ---------------------------------------------------------------------------
 // R10: insertion
 // ---------------------------------------------------------------------------
-// Fresh slots of a winner: two, or one for a midpoint on a hull subsegment.
-__device__ __forceinline__ int fresh_of(const Work &w, int is_cc, int e) {
-  if (is_cc) return 2;
-  return (w.sadj[2 * e] >= 0 && w.sadj[2 * e + 1] >= 0) ? 2 : 1;
-}
-
-__device__ __forceinline__ void winner_one(const Work &w, int c, int ncc, int nwin_mid) {
-  CandSet S;
-  int ci, is_cc;
-  cand_at(w, c, ncc, S, ci, is_cc);
-  if (!(S.state[ci] & kStWin)) return;
-  int e = S.elem[ci];
-  int r, fresh;
-  if (is_cc) {
-    r = nwin_mid + bit_rank(w.win_t, w.rank_t, w.tiles_t, e);
-    fresh = 2;
-  } else {
-    r = bit_rank(w.win_s, w.rank_s, w.tiles_s, e);
-    fresh = (w.sadj[2 * e] >= 0 && w.sadj[2 * e + 1] >= 0) ? 2 : 1;
-  }
-  w.win_ref[r] = (is_cc ? 0 : (int)0x80000000) | ci;
-  w.fcount[r] = fresh;
-}
-
-// Winner ranks: midpoints by subsegment id, then circumcenters by slot.
-// Also sets nwin, and a zero fresh count after the last winner, so that the
-// exclusive scan over nwin + 1 entries ends with the total.
-__device__ __forceinline__ void winners_part(const Work &w, const Lanes &L) {
-  const int ncc = w.cnt->ncc, n = ncc + w.cnt->nmk;
-  const int nwin_mid = w.cnt->nwin_mid;
-  if (first_lane(L)) {
-    int nwin = nwin_mid + w.cnt->nwin_cc;
-    w.cnt->nwin = nwin;
-    w.cnt->nwin1 = nwin + 1;
-    w.fcount[nwin] = 0;
-  }
-  for (int base = L.base0; base < n; base += L.stride) {
-    int c = base + threadIdx.x;
-    if (c < n) winner_one(w, c, ncc, nwin_mid);
-  }
-}
-
-__global__ void k_winners(Work w) {
-  if (w.st->halt) return;
-  winners_part(w, grid_lanes());
-}
-
 __device__ __forceinline__ bool owner_wins(const Work &w, uint64_t mo) {
   if (mo == 0) return false;
   int q_cc = (mo >> 63) ? 0 : 1;
@@ -1629,228 +1750,302 @@ __device__ __forceinline__ bool owner_wins(const Work &w, uint64_t mo) {
   return bit_get(q_cc ? w.win_t : w.win_s, qid);
 }
 
-// Fan records of each winner: boundary edges in canonical order (cavity
-// slots ascending, edge index 0..2; the split subsegment is skipped).  The
-// j-th fan triangle takes the j-th cavity slot, then fresh slots.
-__device__ __forceinline__ void record_one(const DevMesh &m, const Work &w, int r, int foff) {
-  int ref = w.win_ref[r];
-  int is_cc = (ref & 0x80000000) ? 0 : 1;
-  int ci = ref & 0x7fffffff;
-  CandSet S = is_cc ? w.cc : w.mid;
-  uint64_t key = S.key[ci];
-  int off = S.off[ci], len = S.len[ci];
-  int skip_k = is_cc ? -1 : S.elem[ci];
-  int fresh_base = w.st->nT + fbase_at(w, r);
-  int b = len + (fbase_at(w, r + 1) - fbase_at(w, r));
-  w.fan_off[r] = foff;
-  int j = 0;
-  constexpr int B = 2;  // cavity triangles per batch
-  for (int q0 = 0; q0 < len; q0 += B) {
-    int tt[B];
-    int4 tri_[B], nb_[B], ts_[B], to_[B][3];
-    uint64_t mk_[B][3];
+// Fan records of a winner: boundary edges in canonical order (cavity slots
+// ascending, edge index 0..2; the split subsegment is skipped).  The j-th fan
+// triangle takes the j-th cavity slot, then fresh slots.  The lanes of the
+// group take one cavity triangle each; a lane's place among the records is
+// the boundary edges of the lanes below.  sl: kSortMax LDS words of the
+// group; a cavity of at most kSortMax slots is sorted there (rank by
+// counting), a larger one is in the pool in ascending order (the cooperative
+// paths sort).
+constexpr int kSortMax = 64;
+static_assert(kListMax <= kSortMax, "cavities of the lane groups are sorted by the insertion");
+__device__ __forceinline__ void record_one(const DevMesh &m, const Work &w, int32_t *sl, int ref, int foff, int fresh,
+                                           int fresh_base) {
+  int ci, is_cc;
+  const CandSet &S = cand_ref(w, ref, ci, is_cc);
+  const int gl = grp_lane();
+  const unsigned below = (1u << gl) - 1u;
+  const uint64_t key = S.key[ci];
+  const int off = S.off[ci], len = S.len[ci];
+  const int skip_k = is_cc ? -1 : S.elem[ci];
+  const int b = len + fresh;
+  const bool lds = len <= kSortMax;
+  if (lds) {
+    int x[kSortMax / kGrp];
 #pragma unroll
-    for (int i = 0; i < B; i++) tt[i] = q0 + i < len ? w.pool[off + q0 + i] : -1;
-#pragma unroll
-    for (int i = 0; i < B; i++) {
-      const bool v = tt[i] >= 0;
-      tri_[i] = v ? m.tv[tt[i]] : make_int4(0, 0, 0, 0);
-      nb_[i] = v ? m.tn[tt[i]] : make_int4(-1, -1, -1, 0);
-      ts_[i] = v ? m.ts[tt[i]] : make_int4(-1, -1, -1, 0);
+    for (int i = 0; i < kSortMax / kGrp; i++) {
+      const int j = i * kGrp + gl;
+      x[i] = j < len ? w.pool[off + j] : 0x7fffffff;
+      if (i * kGrp < ((len + 3) & ~3)) sl[j] = x[i];
     }
+    wave_lds_sync();
+    int r[kSortMax / kGrp];
 #pragma unroll
-    for (int i = 0; i < B; i++)
-#pragma unroll
-      for (int e = 0; e < 3; e++) {
-        const int o = comp(nb_[i], e);
-        mk_[i][e] = o >= 0 ? w.mark[o] : 0ull;
-        to_[i][e] = o >= 0 ? m.tv[o] : make_int4(0, 0, 0, 0);
+    for (int i = 0; i < kSortMax / kGrp; i++) {
+      r[i] = 0;
+      if (i * kGrp >= len) continue;
+      for (int q = 0; q < len; q += 4) {
+        const int4 y = *reinterpret_cast<const int4 *>(sl + q);
+        r[i] += (y.x < x[i]) + (y.y < x[i]) + (y.z < x[i]) + (y.w < x[i]);
       }
+    }
+    wave_lds_sync();
 #pragma unroll
-    for (int i = 0; i < B; i++)
+    for (int i = 0; i < kSortMax / kGrp; i++)
+      if (i * kGrp + gl < len) sl[r[i]] = x[i];
+    wave_lds_sync();
+  }
+  int jbase = 0;
+  for (int q0 = 0; q0 < len; q0 += kGrp) {
+    const int q = q0 + gl;
+    const bool v = q < len;
+    const int t = v ? (lds ? sl[q] : w.pool[off + q]) : 0;
+    const int4 tri = m.tv[t], nb = m.tn[t];
+    const int4 ts = tri.w ? m.ts[t] : make_int4(-1, -1, -1, 0);
+    uint64_t mk[3];
+    int4 to[3];
 #pragma unroll
     for (int e = 0; e < 3; e++) {
-      if (tt[i] < 0) continue;
-      const int t = tt[i];
-      const int4 tri = tri_[i], ts = ts_[i];
-      int sid = ((tri.w >> e) & 1) ? comp(ts, e) : -1;
-      if (skip_k >= 0 && sid == skip_k) continue;
-      int o = comp(nb_[i], e);
-      if (sid < 0 && o >= 0 && mk_[i][e] == key) continue;
-      int slot = j < len ? w.pool[off + j] : fresh_base + (j - len);
-      int u = comp(tri, e), v = comp(tri, (e + 1) % 3);
-      int jn = -1;
-      if (o >= 0) {
-        int4 to = to_[i][e];
-        if (to.x == v && to.y == u) jn = 0;
-        else if (to.y == v && to.z == u) jn = 1;
-        else jn = 2;
+      const int o = max(comp(nb, e), 0);
+      mk[e] = w.mark[o];
+      to[e] = m.tv[o];
+    }
+    bool bnd[3];
+    int before = 0, total = 0;
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int sid = ((tri.w >> e) & 1) ? comp(ts, e) : -1;
+      const bool inner = sid < 0 && comp(nb, e) >= 0 && mk[e] == key;
+      bnd[e] = v && !inner && !(skip_k >= 0 && sid == skip_k);
+      const unsigned bm = grp_ballot(bnd[e]);
+      before += __popc(bm & below);
+      total += __popc(bm);
+    }
+    int j = jbase + before;
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      if (!bnd[e]) continue;
+      const int sid = ((tri.w >> e) & 1) ? comp(ts, e) : -1;
+      const int o = comp(nb, e), u = comp(tri, e), vv = comp(tri, e == 2 ? 0 : e + 1);
+      const int jn = o < 0 ? -1 : ((to[e].x == vv && to[e].y == u) ? 0 : ((to[e].y == vv && to[e].z == u) ? 1 : 2));
+      if (j < b) {  // always, for a cavity that passed the boundary count check
+        const int slot = j < len ? (lds ? sl[j] : w.pool[off + j]) : fresh_base + (j - len);
+        w.fan[foff + j] = FanRec{slot, u, vv, o, jn, sid};
+        w.repl[t * 4 + e] = slot;
       }
-      if (j >= b) {  // cannot happen for a cavity that passed the boundary count check
-        j++;
-        continue;
-      }
-      FanRec f;
-      f.slot = slot; f.u = u; f.v = v; f.o = o; f.jn = jn; f.ts = sid;
-      w.fan[foff + j] = f;
-      w.repl[t * 4 + e] = slot;
       j++;
     }
+    jbase += total;
   }
-  if (j != b) {
+  if (jbase != b && gl == 0) {
     atomicOr(&w.cnt->err, kErrCavity);
     if (atomicCAS(&w.cnt->dbg_set, 0, 1) == 0) {
       w.cnt->dbg[0] = is_cc;
       w.cnt->dbg[1] = S.elem[ci];
       w.cnt->dbg[2] = len;
       w.cnt->dbg[3] = b;
-      w.cnt->dbg[4] = j;
+      w.cnt->dbg[4] = jbase;
       w.cnt->dbg[5] = S.state[ci];
     }
   }
 }
 
+// Ranks, fan offsets and fan records of the winners.  Winner ranks: midpoints
+// by subsegment id, then circumcenters by slot (from the scanned winner
+// bitmaps; RANKED: engine_rank has set them).  Fresh slots are given out in
+// rank order, two per winner and one per midpoint on the hull, so their
+// prefix at rank r is 2 r less the hull midpoints before it.
 // The capacity check of the round comes first: every thread evaluates it on
 // the same counts; if anything would overflow, the round is abandoned before
 // the mesh is written and the host grows the buffers and runs it again.
-__device__ __forceinline__ void record_part(const DevMesh &m, const Work &w, const Lanes &L) {
+// A workgroup takes a tile of the list: one thread per entry for the ranks
+// and the fan space (one atomic per tile), then one group per entry.  Tiles
+// are small while the list is, so that every group of a small round has at
+// most a few entries.  lds: kSortMax words per group.
+template <bool RANKED>
+__device__ __forceinline__ void record_part(const DevMesh &m, const Work &w, int32_t *lds, const Lanes &L) {
   const DevState *st = w.st;
   DevCounters *c = w.cnt;
-  const int nwin = c->nwin;
-  const int fresh = fbase_at(w, nwin);
-  const int64_t need_fan = (int64_t)c->pool_used + 2 * (int64_t)nwin;
+  const int nwin_mid = c->nwin_mid, nwin = nwin_mid + c->nwin_cc, n_hull = c->nwin_hull, nw0 = c->nw0;
+  const int nT = st->nT, fresh_all = 2 * nwin - n_hull;
+  // (the winners' cavities are disjoint)
+  const int64_t need_fan = (int64_t)min(c->pool_used, nT) + 2 * (int64_t)nwin;
   const bool over = (c->err & (kErrPool | kErrHuge)) || (int64_t)st->nV + nwin > m.capV ||
-                    (int64_t)st->nT + fresh > m.capT || (int64_t)st->nS + c->nwin_mid > m.capS ||
+                    (int64_t)nT + fresh_all > m.capT || (int64_t)st->nS + nwin_mid > m.capS ||
                     need_fan > w.fan_cap || nwin + 1 > w.win_cap;
   if (first_lane(L)) {
-    c->fresh_total = fresh;
+    c->nwin = nwin;
+    c->fresh_total = fresh_all;
     c->abort = over ? 1 : 0;
   }
   if (over) return;
-  for (int base = L.base0; base < nwin; base += L.stride) {
-    int r = base + threadIdx.x;
+  const int per = (int)blockDim.x / kGrp, nblk = L.stride / (int)blockDim.x;
+  const int tile = min((int)blockDim.x, max(1, (nw0 / nblk + per - 1) / per) * per);
+  for (int base = L.base0 / (int)blockDim.x * tile; base < nw0; base += nblk * tile) {
+    const int n = min(tile, nw0 - base);
     int b = 0, len = 0, steps = 0, cc = 0;
-    if (r < nwin) {
-      const int ref = w.win_ref[r];
-      cc = (ref & 0x80000000) ? 0 : 1;
-      const CandSet S = cc ? w.cc : w.mid;
-      len = S.len[ref & 0x7fffffff];
-      b = len + (fbase_at(w, r + 1) - fbase_at(w, r));
-      if (cc) steps = (S.state[ref & 0x7fffffff] >> kStepShift) & 0x7fff;
+    const int i = base + (int)threadIdx.x;
+    int r = -1, fb = 0;
+    if ((int)threadIdx.x < n) {
+      int ci;
+      const CandSet &S = cand_ref(w, w.w0_list[i], ci, cc);
+      const int state = S.state[ci];
+      if (state & kStWin) {
+        const int e = S.elem[ci];
+        len = S.len[ci];
+        if (RANKED) {
+          r = w.win_rank[i];
+          fb = w.win_fresh[i];
+        } else if (cc) {
+          r = nwin_mid + bit_rank(w.win_t, w.rank_t, w.tiles_t, e);
+          fb = 2 * r - n_hull;
+        } else {
+          r = bit_rank(w.win_s, w.rank_s, w.tiles_s, e);
+          fb = 2 * r - bit_rank(w.win_h, w.rank_h, w.tiles_h, e);
+        }
+        b = len + fresh_of(w, cc, e);
+        if (cc) steps = (state >> kStepShift) & 0x7fff;
+      }
     }
-    int foff = group_alloc(&w.cnt->fan_used, b, L);
-    if (r < nwin) record_one(m, w, r, foff);
+    const int foff = group_alloc(&c->fan_used, b, L);
+    if ((int)threadIdx.x < n) {
+      w.win_rank[i] = r;
+      w.win_fresh[i] = fb;
+      w.fan_off[i] = foff;
+      w.fan_len[i] = b;
+    }
     // the winners' share of the round's memory work (winners' cavities are
     // disjoint, so a wave's sums of sizes and fan edges stay below 2^32)
     stat_add2(w, kStWinCav, kStWinBnd, len, b);
     stat_add2(w, kStWinCcCav, kStWinCcBnd, cc ? len : 0, cc ? b : 0);
     stat_add(w, kStWinSteps, steps);
+    __syncthreads();
+    for (int q = (int)threadIdx.x / kGrp; q < n; q += per) {
+      const int k = base + q;
+      if (w.win_rank[k] < 0) continue;
+      int ci, is_cc;
+      const int ref = w.w0_list[k];
+      const CandSet &S = cand_ref(w, ref, ci, is_cc);
+      record_one(m, w, lds + (int)threadIdx.x / kGrp * kSortMax, ref, w.fan_off[k], w.fan_len[k] - S.len[ci],
+                 nT + w.win_fresh[k]);
+    }
+    __syncthreads();
   }
 }
 
 __global__ void k_record(DevMesh m, Work w) {
+  extern __shared__ __attribute__((aligned(16))) int32_t dyn_lds[];
   if (w.st->halt) return;
-  record_part(m, w, grid_lanes());
+  record_part<false>(m, w, dyn_lds, grid_lanes());
 }
 
-__device__ __forceinline__ void write_one(const DevMesh &m, const Work &w, int r, int nV, int nS, int serial) {
-  int ref = w.win_ref[r];
-  int is_cc = (ref & 0x80000000) ? 0 : 1;
-  int ci = ref & 0x7fffffff;
-  CandSet S = is_cc ? w.cc : w.mid;
-  int len = S.len[ci];
-  int b = len + (fbase_at(w, r + 1) - fbase_at(w, r));
-  int foff = w.fan_off[r];
-  int pid = nV + r;
-  double2 p = S.p[ci];
-  int k = -1, knew = -1, a = -1, bb = -1;
+// Inserts the winner of list entry k, a fan record per lane.  The neighbours
+// inside the fan are the records that start where this one ends and end
+// where it starts: found among the fan's (u, v) in LDS (lu, lv, ls: kFanMax
+// words each), or in memory for a larger fan.
+constexpr int kFanMax = 72;
+__device__ __forceinline__ void write_one(const DevMesh &m, const Work &w, int32_t *lds, int k, int nV, int nS,
+                                          int serial) {
+  int32_t *lu = lds, *lv = lds + kFanMax, *ls = lds + 2 * kFanMax;
+  const int gl = grp_lane();
+  const int r = w.win_rank[k], foff = w.fan_off[k], b = w.fan_len[k];
+  int ci, is_cc;
+  const CandSet &S = cand_ref(w, w.w0_list[k], ci, is_cc);
+  if (r < 0) return;
+  const FanRec f0 = w.fan[foff + min(gl, b - 1)];
+  const double2 p = S.p[ci];
+  const int pid = nV + r;
+  int seg = -1, knew = -1, sa = -1, sb = -1;
   if (!is_cc) {
-    k = S.elem[ci];
+    seg = S.elem[ci];
     knew = nS + r;  // midpoint winners take ranks 0..nwin_mid-1
-    int2 sk = m.sv[k];
-    a = sk.x;
-    bb = sk.y;
+    const int2 sk = m.sv[seg];
+    sa = sk.x;
+    sb = sk.y;
   }
-  // kIlp fan records at a time: the records, then the outside marks, their
-  // owners' win bits and replacement slots, each a batch of loads; a fan of
-  // at most kIlp records finds its neighbours in registers
-  for (int j0 = 0; j0 < b; j0 += kIlp) {
-    FanRec F[kIlp];
-    uint64_t mo[kIlp];
-    bool ow[kIlp];
-    int rp[kIlp];
-#pragma unroll
-    for (int i = 0; i < kIlp; i++) F[i] = j0 + i < b ? w.fan[foff + j0 + i] : FanRec{-1, -2, -2, -1, 0, -1};
-#pragma unroll
-    for (int i = 0; i < kIlp; i++) mo[i] = F[i].o >= 0 ? w.mark[F[i].o] : 0ull;
-#pragma unroll
-    for (int i = 0; i < kIlp; i++) ow[i] = F[i].o >= 0 && owner_wins(w, mo[i]);
-#pragma unroll
-    for (int i = 0; i < kIlp; i++) rp[i] = ow[i] ? w.repl[F[i].o * 4 + F[i].jn] : -1;
-#pragma unroll
-    for (int i = 0; i < kIlp; i++) {
-      if (j0 + i >= b) continue;
-      const FanRec f = F[i];
-      const int s = f.slot;
-      int n0;
-      if (f.o < 0) n0 = -1;
-      else if (ow[i]) n0 = rp[i];
-      else {
+  const bool in_lds = b <= kFanMax;
+  if (in_lds) {
+    const int bp = (b + 3) & ~3;
+    for (int j = gl; j < bp; j += kGrp) {
+      const FanRec f = j < kGrp ? f0 : w.fan[foff + min(j, b - 1)];
+      lu[j] = j < b ? f.u : -2;
+      lv[j] = j < b ? f.v : -2;
+      ls[j] = f.slot;
+    }
+    wave_lds_sync();
+  }
+  for (int j = gl; j < b; j += kGrp) {
+    const FanRec f = j < kGrp ? f0 : w.fan[foff + j];
+    const int s = f.slot;
+    int n0 = -1;
+    if (f.o >= 0) {
+      const uint64_t mo = w.mark[f.o];
+      if (owner_wins(w, mo)) {
+        n0 = w.repl[f.o * 4 + f.jn];
+      } else {
         n0 = f.o;
         ((int32_t *)m.tn)[f.o * 4 + f.jn] = s;
       }
-      int n1 = -1, n2 = -1;
-      if (b <= kIlp) {
-#pragma unroll
-        for (int g = 0; g < kIlp; g++) {
-          if (g >= b) continue;
-          if (F[g].u == f.v) n1 = F[g].slot;
-          if (F[g].v == f.u) n2 = F[g].slot;
-        }
-      } else {
-        for (int g = 0; g < b; g++) {
-          FanRec h = w.fan[foff + g];
-          if (h.u == f.v) n1 = h.slot;
-          if (h.v == f.u) n2 = h.slot;
-        }
-      }
-      int s1 = -1, s2 = -1;
-      if (!is_cc) {
-        s1 = f.v == a ? k : (f.v == bb ? knew : -1);
-        s2 = f.u == a ? k : (f.u == bb ? knew : -1);
-      }
-      int mask = (f.ts >= 0 ? 1 : 0) | (s1 >= 0 ? 2 : 0) | (s2 >= 0 ? 4 : 0);
-      m.tv[s] = make_int4(f.u, f.v, pid, mask);
-      m.tn[s] = make_int4(n0, n1, n2, 0);
-      m.ts[s] = make_int4(f.ts, s1, s2, 0);
-      w.tstamp[s] = serial;
     }
+    int n1 = -1, n2 = -1;
+    if (in_lds) {
+      int i1 = -1, i2 = -1;
+      for (int g = 0; g < b; g += 4) {
+        const int4 x = *reinterpret_cast<const int4 *>(lu + g), y = *reinterpret_cast<const int4 *>(lv + g);
+        i1 = x.x == f.v ? g : (x.y == f.v ? g + 1 : (x.z == f.v ? g + 2 : (x.w == f.v ? g + 3 : i1)));
+        i2 = y.x == f.u ? g : (y.y == f.u ? g + 1 : (y.z == f.u ? g + 2 : (y.w == f.u ? g + 3 : i2)));
+      }
+      if (i1 >= 0) n1 = ls[i1];
+      if (i2 >= 0) n2 = ls[i2];
+    } else {
+      for (int g = 0; g < b; g++) {
+        const FanRec h = w.fan[foff + g];
+        if (h.u == f.v) n1 = h.slot;
+        if (h.v == f.u) n2 = h.slot;
+      }
+    }
+    int s1 = -1, s2 = -1;
+    if (!is_cc) {
+      s1 = f.v == sa ? seg : (f.v == sb ? knew : -1);
+      s2 = f.u == sa ? seg : (f.u == sb ? knew : -1);
+    }
+    const int mask = (f.ts >= 0 ? 1 : 0) | (s1 >= 0 ? 2 : 0) | (s2 >= 0 ? 4 : 0);
+    m.tv[s] = make_int4(f.u, f.v, pid, mask);
+    m.tn[s] = make_int4(n0, n1, n2, 0);
+    m.ts[s] = make_int4(f.ts, s1, s2, 0);
+    w.tstamp[s] = serial;
   }
-  m.vxy[pid] = p;
-  m.vkind[pid] = is_cc ? 2 : 1;
-  if (!is_cc) {
-    m.sv[k] = make_int2(a, pid);
-    m.sv[knew] = make_int2(pid, bb);
-    m.spar[knew] = m.spar[k];
-    m.spend[knew] = 0;
-    w.sadj[2 * knew] = -1;
-    w.sadj[2 * knew + 1] = -1;
-    w.mflag[knew] = 0u;
+  if (gl == 0) {
+    m.vxy[pid] = p;
+    m.vkind[pid] = is_cc ? 2 : 1;
+    if (!is_cc) {
+      m.sv[seg] = make_int2(sa, pid);
+      m.sv[knew] = make_int2(pid, sb);
+      m.spar[knew] = m.spar[seg];
+      m.spend[knew] = 0;
+      w.sadj[2 * knew] = -1;
+      w.sadj[2 * knew + 1] = -1;
+      w.mflag[knew] = 0u;
+    }
   }
 }
 
-__device__ __forceinline__ void write_part(const DevMesh &m, const Work &w, const Lanes &L) {
+constexpr int kWriteWords = 3 * kFanMax;  // LDS of a group in write_part
+__device__ __forceinline__ void write_part(const DevMesh &m, const Work &w, int32_t *lds, const Lanes &L) {
   if (w.cnt->abort) return;
-  const int nwin = w.cnt->nwin, nV = w.st->nV, nS = w.st->nS, serial = w.st->serial;
-  for (int base = L.base0; base < nwin; base += L.stride) {
-    int r = base + threadIdx.x;
-    if (r < nwin) write_one(m, w, r, nV, nS, serial);
+  const int n = w.cnt->nw0, nV = w.st->nV, nS = w.st->nS, serial = w.st->serial;
+  const GrpLanes g = grp_lanes(L);
+  for (int i = g.first + g.grp; i < n; i += g.stride) {
+    write_one(m, w, lds + g.grp * kWriteWords, i, nV, nS, serial);
+    wave_lds_sync();
   }
 }
 
 __global__ void k_write(DevMesh m, Work w) {
+  extern __shared__ __attribute__((aligned(16))) int32_t dyn_lds[];
   if (w.st->halt) return;
-  write_part(m, w, grid_lanes());
+  write_part(m, w, dyn_lds, grid_lanes());
 }
 
 // R11: clear marks and bitmap bits of every candidate; pending flags.  A
@@ -1875,7 +2070,10 @@ __device__ __forceinline__ void finish_one(const DevMesh &m, const Work &w, int 
   int e = S.elem[ci];
   uint32_t bit = 1u << (e & 31);
   if (st & kStW0) atomicAnd(&(is_cc ? w.w0_t : w.w0_s)[e >> 5], ~bit);
-  if (st & kStWin) atomicAnd(&(is_cc ? w.win_t : w.win_s)[e >> 5], ~bit);
+  if (st & kStWin) {
+    atomicAnd(&(is_cc ? w.win_t : w.win_s)[e >> 5], ~bit);
+    if (!is_cc) atomicAnd(&w.win_h[e >> 5], ~bit);
+  }
   if (!is_cc) {
     // pending := (pending or flagged this round) and not split; an entry the
     // cap skipped is not "flagged" unless R4/R5 flagged it again (own entry)
@@ -2362,27 +2560,30 @@ __device__ void engine_select(const Work &w, int K, int32_t *h) {
 
 // Winner ranks by counting (at most kEngRankMax winners): rank = number of
 // winners with a smaller (class, element) key, midpoints first, which is the
-// order the bitmap ranks give.  Returns false if there are more winners.
+// order the bitmap ranks give; the key's lowest bit marks a hull midpoint.
+// Returns false if there are more winners.
 constexpr int kEngRankMax = 2048;
 __device__ bool engine_rank(const Work &w, int32_t *lds) {
-  __shared__ int s_nw, s_nmid;
+  __shared__ int s_nw, s_nmid, s_nhull;
   int32_t *key = lds, *ref = lds + kEngRankMax;
   if (threadIdx.x == 0) {
     s_nw = 0;
     s_nmid = 0;
+    s_nhull = 0;
   }
   __syncthreads();
-  const int ncc = w.cnt->ncc, n = ncc + w.cnt->nmk;
-  for (int c = threadIdx.x; c < n; c += blockDim.x) {
-    CandSet S;
+  const int n = w.cnt->nw0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
     int ci, is_cc;
-    cand_at(w, c, ncc, S, ci, is_cc);
+    const CandSet &S = cand_ref(w, w.w0_list[i], ci, is_cc);
     if (!(S.state[ci] & kStWin)) continue;
-    int pos = atomicAdd(&s_nw, 1);
+    const int e = S.elem[ci], hull = 2 - fresh_of(w, is_cc, e);
+    const int pos = atomicAdd(&s_nw, 1);
     if (!is_cc) atomicAdd(&s_nmid, 1);
+    if (hull) atomicAdd(&s_nhull, 1);
     if (pos < kEngRankMax) {
-      key[pos] = (int32_t)(((uint32_t)is_cc << 31) | (uint32_t)S.elem[ci]);
-      ref[pos] = (is_cc ? 0 : (int)0x80000000) | ci;
+      key[pos] = (int32_t)(((uint32_t)is_cc << 31) | ((uint32_t)e << 1) | (uint32_t)hull);
+      ref[pos] = i;
     }
   }
   __syncthreads();
@@ -2390,17 +2591,20 @@ __device__ bool engine_rank(const Work &w, int32_t *lds) {
   if (nw > kEngRankMax) return false;
   for (int i = threadIdx.x; i < nw; i += blockDim.x) {
     const uint32_t k = (uint32_t)key[i];
-    int r = 0;
-    for (int j = 0; j < nw; j++) r += (uint32_t)key[j] < k;
-    w.win_ref[r] = ref[i];
-    w.fcount[r] = fresh_of(w, (k >> 31) != 0, (int)(k & 0x7fffffffu));
+    int r = 0, h = 0;
+    for (int j = 0; j < nw; j++) {
+      const uint32_t x = (uint32_t)key[j];
+      const int lt = x < k;
+      r += lt;
+      h += lt & (int)(x & 1u) & (int)(~x >> 31);
+    }
+    w.win_rank[ref[i]] = r;
+    w.win_fresh[ref[i]] = 2 * r - h;
   }
   if (threadIdx.x == 0) {
     w.cnt->nwin_mid = s_nmid;
     w.cnt->nwin_cc = nw - s_nmid;
-    w.cnt->nwin = nw;
-    w.cnt->nwin1 = nw + 1;
-    w.fcount[nw] = 0;
+    w.cnt->nwin_hull = s_nhull;
   }
   return true;
 }
@@ -2552,24 +2756,34 @@ __device__ void engine_big(const DevMesh &m, const Work &w, BigShared &sh, int p
   }
 }
 
-// The engine's per-thread cavities: half the workgroup, with slices twice as
-// long as the grid kernel's (large cavities are common in small meshes with
-// clustered points, and the cooperative path runs them one at a time here).
+// The engine's group cavities: half the workgroup takes the circumcenters
+// while the other half takes the midpoints listed before them, with longer
+// lists than the grid kernels' (large cavities are common in small meshes
+// with clustered points, and the cooperative path runs them one at a time
+// here).
 constexpr int kEngCavThreads = kEngBlock / 2;
 constexpr int kEngCap = 48;
-// midpoint cavities listed before the circumcenter cavities run on the other
-// half of the workgroup at the same time, in slices of their own
-constexpr int kEngMidCap = 24;
-static_assert(kEngCap <= kStat4Cap && kEngMidCap <= kStat4Cap, "engine cavity statistics fit stat_add4");
-constexpr int kEngMidLdsWords = kEngMidCap * kEngCavThreads;
-constexpr int kEngLdsWords = (kEngCap * kEngCavThreads > (int)(sizeof(BigShared) / 4)) ? kEngCap * kEngCavThreads
-                                                                                     : (int)(sizeof(BigShared) / 4);
+static_assert(kEngCap <= kListMax, "engine cavity lists");
+constexpr int kEngCavWords = kGrpWords * (kEngBlock / kGrp);
+constexpr int kEngLdsWords = kEngCavWords > (int)(sizeof(BigShared) / 4) ? kEngCavWords : (int)(sizeof(BigShared) / 4);
 static_assert(kApproxMax * kEngBlock <= kEngLdsWords, "prefilter slices fit in the engine's LDS");
-static_assert(2 * kEngRankMax <= kEngLdsWords, "winner keys fit in the engine's LDS");
+static_assert(2 * kEngRankMax <= kEngLdsWords && kWriteWords * (kEngBlock / kGrp) <= kEngLdsWords &&
+                  kSortMax * (kEngBlock / kGrp) <= kEngLdsWords,
+              "winner keys, cavity sorts and fans fit in the engine's LDS");
+
+// The scans of the winner bitmaps.
+__device__ __forceinline__ ScanJobs winner_scans(const Work &w) {
+  ScanJobs J;
+  J.j[0] = ScanJob{(const int32_t *)w.win_s, w.rank_s, &w.st->wS, w.tiles_s, &w.cnt->nwin_mid, 1};
+  J.j[1] = ScanJob{(const int32_t *)w.win_t, w.rank_t, &w.st->wT, w.tiles_t, &w.cnt->nwin_cc, 1};
+  J.j[2] = ScanJob{(const int32_t *)w.win_h, w.rank_h, &w.st->wS, w.tiles_h, &w.cnt->nwin_hull, 1};
+  return J;
+}
 
 // Rounds of one mesh until it halts or round_limit rounds have completed.
 __device__ void engine_mesh(const EngDesc &d, int32_t *lds, int round_limit) {
   __shared__ int s_ser, s_full, s_halt, s_mid0;
+  __shared__ uint32_t s_stat[kStFields];
   const DevMesh &m = d.m;
   DevState *st = d.w[0].st;
   const Lanes L = block_lanes();
@@ -2622,19 +2836,22 @@ __device__ void engine_mesh(const EngDesc &d, int32_t *lds, int round_limit) {
     // on the other; then the midpoints the circumcenter cavities flagged.
     // (Marks are order free and a midpoint cavity depends on no other.)
     BigShared &sh = *reinterpret_cast<BigShared *>(lds);
-    const Lanes LC{0, kEngCavThreads, 0};
+    constexpr int kHalf = kEngCavThreads / kGrp;
+    const int grp = (int)threadIdx.x / kGrp;
     if (threadIdx.x == 0) s_mid0 = w.cnt->nmk;
+    stat_lds_clear(s_stat);
     __syncthreads();
     const int mid0 = s_mid0;
     if (threadIdx.x < kEngCavThreads)
-      cavity_part(m, w, 1, lds, kEngCavThreads, kEngCap, LC);
+      cavity_part(m, w, 1, lds, kEngCap, s_stat, 0, kHalf, grp, false);
     else
-      cavity_part(m, w, 0, lds + kEngLdsWords, kEngCavThreads, kEngMidCap, LC, 0, mid0,
-                  (int)threadIdx.x - kEngCavThreads);
+      cavity_part(m, w, 0, lds + kHalf * kGrpWords, kEngCap, s_stat, 0, kHalf, grp - kHalf, false, 0, mid0);
     phase_sync();
     engine_big(m, w, sh, 0);
     phase_sync();
-    if (threadIdx.x < kEngCavThreads) cavity_part(m, w, 0, lds, kEngCavThreads, kEngCap, LC, mid0);
+    cavity_part(m, w, 0, lds, kEngCap, s_stat, 0, 2 * kHalf, grp, false, mid0);
+    phase_sync();
+    stat_lds_flush(w, s_stat);
     phase_sync();
     engine_big(m, w, sh, 1);
     phase_sync();
@@ -2644,22 +2861,20 @@ __device__ void engine_mesh(const EngDesc &d, int32_t *lds, int round_limit) {
     dep_part(m, w, L);
     phase_sync();
     // R10 ranks, fresh slots, capacity check, insertion
-    const ScanJob js{(const int32_t *)w.win_s, w.rank_s, &w.st->wS, w.tiles_s, &w.cnt->nwin_mid, 1};
-    const ScanJob jt{(const int32_t *)w.win_t, w.rank_t, &w.st->wT, w.tiles_t, &w.cnt->nwin_cc, 1};
-    const ScanJob jf{w.fcount, w.fbase, &w.cnt->nwin1, w.tiles_f, &w.cnt->fan_total, 0};
-    if (!engine_rank(w, lds)) {  // many winners: bitmap ranks as in the grid kernels
+    if (engine_rank(w, lds)) {
       phase_sync();
-      engine_scan(js);
-      engine_scan(jt);
+      record_part<true>(m, w, lds, L);
+    } else {  // many winners: bitmap ranks as in the grid kernels
+      const ScanJobs J = winner_scans(w);
       phase_sync();
-      winners_part(w, L);
+      engine_scan(J.j[0]);
+      engine_scan(J.j[1]);
+      engine_scan(J.j[2]);
+      phase_sync();
+      record_part<false>(m, w, lds, L);
     }
     phase_sync();
-    engine_scan(jf);
-    phase_sync();
-    record_part(m, w, L);
-    phase_sync();
-    write_part(m, w, L);
+    write_part(m, w, lds, L);
     phase_sync();
     finish_part(m, w, L);
     phase_sync();
@@ -2671,7 +2886,7 @@ __device__ void engine_mesh(const EngDesc &d, int32_t *lds, int round_limit) {
 // runs each for at most round_limit rounds.
 __global__ __launch_bounds__(kEngBlock) void k_engine(const EngDesc *descs, int n_mesh, int32_t *head,
                                                       int round_limit) {
-  __shared__ int32_t lds[kEngLdsWords + kEngMidLdsWords];
+  __shared__ __attribute__((aligned(16))) int32_t lds[kEngLdsWords];
   __shared__ int s_i;
   for (;;) {
     __syncthreads();
@@ -2685,31 +2900,40 @@ __global__ __launch_bounds__(kEngBlock) void k_engine(const EngDesc *descs, int 
 
 // ---------------------------------------------------------------------------
 // Round-boundary batching: the round's phases for a set of meshes, one
-// launch each (gridDim.y = meshes).  The bodies are the single-mesh phases;
-// each workgroup copies its mesh's descriptor (mesh arrays and the round's
-// workspace, chosen by the mesh's own serial) into registers first.
+// launch each.  The bodies are the single-mesh phases.  A workgroup of a
+// phase over elements finds its mesh in a table (map) and its place among
+// that mesh's workgroups in the mesh's descriptor, so that meshes of
+// different sizes share the chip by their work; the others are launched with
+// gridDim.y = meshes.  Each workgroup copies its mesh's descriptor (mesh
+// arrays and the round's workspace, chosen by the mesh's own serial) into
+// registers first.
 // ---------------------------------------------------------------------------
-#define GANG_MESH                                           \
-  const GangDesc &g_ = G[blockIdx.y];                       \
-  const int par_ = g_.e.w[0].st->serial & 1;                \
+#define GANG_MESH_OF(y_)                                    \
+  const GangDesc &g_ = G[y_];                               \
+  const int par_ = __builtin_amdgcn_readfirstlane(g_.e.w[0].st->serial & 1); \
   const DevMesh m = g_.e.m;                                 \
   const Work w = g_.e.w[par_];
+#define GANG_MESH GANG_MESH_OF(blockIdx.y)
+#define GANG_SHARE(kind)                                    \
+  GANG_MESH_OF(__builtin_amdgcn_readfirstlane(map[blockIdx.x]))                            \
+  const int bx_ = (int)blockIdx.x - g_.b0[kind], nb_ = g_.nb[kind];
+#define GANG_LANES (Lanes{bx_ * (int)blockDim.x, nb_ * (int)blockDim.x, 1})
 
-__global__ void kg_collect(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_collect(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   if (w.st->halt) return;
   if (w.st->full) {
-    scan_part(m, w, g_.e.B2, g_.e.pm, grid_lanes());
+    scan_part(m, w, g_.e.B2, g_.e.pm, GANG_LANES);
   } else {
-    carry_part(w, grid_lanes());
-    dirty_part(m, w, g_.e.B2, g_.e.pm, grid_lanes());
+    carry_part(w, GANG_LANES);
+    dirty_part(m, w, g_.e.B2, g_.e.pm, GANG_LANES);
   }
 }
 
-__global__ void kg_pending(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_pending(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   if (w.st->halt || w.st->full) return;
-  pending_part(m, w, grid_lanes());
+  pending_part(m, w, GANG_LANES);
 }
 
 __global__ void kg_gate(const GangDesc *G) {
@@ -2718,22 +2942,22 @@ __global__ void kg_gate(const GangDesc *G) {
   (void)gate_part(w, g_.e.max_rounds);
 }
 
-__global__ void kg_gather_keys(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_gather_keys(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   if (w.st->halt || g_.e.K <= 0) return;
-  gather_part(m, w, g_.e.pm, grid_lanes());
+  gather_part(m, w, g_.e.pm, GANG_LANES);
 }
 
-__global__ void kg_radix_hist(const GangDesc *G, int shift) {
+__global__ void kg_radix_hist(const GangDesc *G, const int32_t *map, int shift) {
   __shared__ int h[256];
-  GANG_MESH
+  GANG_SHARE(kGangElem)
   (void)m;
   if (w.st->halt || g_.e.K <= 0) return;
   const int n = w.cnt->ncc + w.cnt->nmk;
   const uint64_t prefix = w.sel[0], pmask = w.sel[1];
   for (int i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
   __syncthreads();
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
+  for (int c = bx_ * blockDim.x + threadIdx.x; c < n; c += nb_ * blockDim.x) {
     uint64_t k = w.keys[c];
     if ((k & pmask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1);
   }
@@ -2749,36 +2973,35 @@ __global__ void kg_radix_pick(const GangDesc *G, int shift) {
   radix_pick_part(w, shift, g_.e.K);
 }
 
-__global__ void kg_apply_cap(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_apply_cap(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   (void)m;
   if (w.st->halt || g_.e.K <= 0) return;
-  apply_part(w, grid_lanes());
+  apply_part(w, GANG_LANES);
 }
 
-__global__ void kg_locate(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_locate(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   if (w.st->halt) return;
-  locate_part(m, w, grid_lanes());
+  locate_part(m, w, GANG_LANES);
 }
 
-__global__ __launch_bounds__(kPreBlock) void kg_prefilter(const GangDesc *G, int mode) {
+__global__ __launch_bounds__(kPreBlock) void kg_prefilter(const GangDesc *G, const int32_t *map, int mode) {
   __shared__ int32_t lds[kApproxMax * kPreBlock];
-  GANG_MESH
+  GANG_SHARE(kGangElem)
   if (w.st->halt) return;
   if (mode < 3 ? !g_.e.f1 : g_.e.approx_n <= 0) return;
-  prefilter_part(m, w, mode, mode < 3 ? 0 : g_.e.approx_n, lds, grid_lanes());
+  prefilter_part(m, w, mode, mode < 3 ? 0 : g_.e.approx_n, lds, GANG_LANES);
 }
 
 template <int IS_CC>
-__global__ __launch_bounds__(kCavBlock, 4) void kg_cavity(const GangDesc *G) {
-  __shared__ int32_t lds[kCap * kCavBlock];
-  GANG_MESH
+__global__ __launch_bounds__(kCavBlock, 5) void kg_cavity(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangGroup)
   if (w.st->halt) return;
-  cavity_part<true>(m, w, IS_CC, lds, kCavBlock, kCap, grid_lanes());
+  cavity_grid<IS_CC>(m, w, kCap, bx_, nb_);
 }
-template __global__ void kg_cavity<0>(const GangDesc *G);
-template __global__ void kg_cavity<1>(const GangDesc *G);
+template __global__ void kg_cavity<0>(const GangDesc *G, const int32_t *map);
+template __global__ void kg_cavity<1>(const GangDesc *G, const int32_t *map);
 
 __global__ __launch_bounds__(kBigBlock) void kg_cavity_big(const GangDesc *G, int phase) {
   __shared__ BigShared sh;
@@ -2807,81 +3030,56 @@ __global__ __launch_bounds__(kHugeBlock) void kg_cavity_huge(const GangDesc *G, 
   }
 }
 
-__global__ void kg_own(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_own(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangElem)
   (void)m;
   if (w.st->halt) return;
-  own_part(w, grid_lanes());
+  own_part(w, GANG_LANES);
 }
 
-__global__ void kg_dep(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_dep(const GangDesc *G, const int32_t *map) {
+  GANG_SHARE(kGangGroup)
   if (w.st->halt) return;
-  dep_part(m, w, grid_lanes());
+  dep_part(m, w, GANG_LANES);
 }
 
-// which = 0: the two winner bitmaps; 1: the fresh-slot counts.
-__global__ __launch_bounds__(kScanBlock) void kg_scan_tiles(const GangDesc *G, int which) {
+__global__ __launch_bounds__(kScanBlock) void kg_scan_tiles(const GangDesc *G) {
   const GangDesc &g = G[blockIdx.y];
   if (g.e.w[0].st->halt) return;
-  const ScanJob a = which == 0 ? g.js : g.jf;
-  const ScanJob b = which == 0 ? g.jt : ScanJob{nullptr, nullptr, nullptr, nullptr, nullptr, 0};
-  const int na = *a.n_dev, nb = b.in ? *b.n_dev : 0;
-  const int ta = (na + kScanTile - 1) / kScanTile, tb = (nb + kScanTile - 1) / kScanTile;
-  for (int tile = blockIdx.x; tile < ta + tb; tile += gridDim.x) {
-    if (tile < ta) scan_tile(a, na, tile);
-    else scan_tile(b, nb, tile - ta);
-  }
+  scan_tiles(winner_scans(g.e.w[0]));
 }
 
-// Launched with gridDim.x = 2 (both jobs of which = 0; one of which = 1).
-__global__ __launch_bounds__(kScanBlock) void kg_scan_sums(const GangDesc *G, int which) {
-  __shared__ int s_total;
+// Launched with gridDim.x = 3.
+__global__ __launch_bounds__(kScanBlock) void kg_scan_sums(const GangDesc *G) {
   const GangDesc &g = G[blockIdx.y];
   if (g.e.w[0].st->halt) return;
-  if (which == 1 && blockIdx.x != 0) return;
-  const ScanJob j = which == 1 ? g.jf : (blockIdx.x == 0 ? g.js : g.jt);
-  const int ntiles = (*j.n_dev + kScanTile - 1) / kScanTile;
-  int carry = 0;
-  for (int start = 0; start < ntiles; start += kScanBlock) {
-    int idx = start + threadIdx.x;
-    int x = idx < ntiles ? j.tiles[idx] : 0;
-    int e = block_excl_scan(x, &s_total);
-    if (idx < ntiles) j.tiles[idx] = e + carry;
-    carry += s_total;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *j.total = carry;
+  const ScanJobs J = winner_scans(g.e.w[0]);
+  scan_sums(blockIdx.x == 0 ? J.j[0] : (blockIdx.x == 1 ? J.j[1] : J.j[2]));
 }
 
-__global__ void kg_winners(const GangDesc *G) {
-  GANG_MESH
-  (void)m;
+__global__ void kg_record(const GangDesc *G, const int32_t *map) {
+  extern __shared__ __attribute__((aligned(16))) int32_t dyn_lds[];
+  GANG_SHARE(kGangGroup)
   if (w.st->halt) return;
-  winners_part(w, grid_lanes());
+  record_part<false>(m, w, dyn_lds, GANG_LANES);
 }
 
-__global__ void kg_record(const GangDesc *G) {
-  GANG_MESH
+__global__ void kg_write(const GangDesc *G, const int32_t *map) {
+  extern __shared__ __attribute__((aligned(16))) int32_t dyn_lds[];
+  GANG_SHARE(kGangGroup)
   if (w.st->halt) return;
-  record_part(m, w, grid_lanes());
+  write_part(m, w, dyn_lds, GANG_LANES);
 }
 
-__global__ void kg_write(const GangDesc *G) {
-  GANG_MESH
-  if (w.st->halt) return;
-  write_part(m, w, grid_lanes());
-}
-
-__global__ void kg_finish(const GangDesc *G) {
+__global__ void kg_finish(const GangDesc *G, const int32_t *map) {
   __shared__ int s_last;
-  GANG_MESH
+  GANG_SHARE(kGangFinish)
   if (w.st->halt) return;
-  finish_part(m, w, grid_lanes());
+  finish_part(m, w, GANG_LANES);
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
-    s_last = atomicAdd(&w.st->done_blocks, 1) == (int)gridDim.x - 1;
+    s_last = atomicAdd(&w.st->done_blocks, 1) == nb_ - 1;
   }
   __syncthreads();
   if (!s_last) return;
@@ -2890,6 +3088,8 @@ __global__ void kg_finish(const GangDesc *G) {
   round_end(w);
 }
 
+// One workgroup per mesh; the history is handed over, so the mesh's next
+// group starts an empty one.
 __global__ void kg_status(const GangDesc *G, int rounds, int32_t *out, int stride_words) {
   const GangDesc &g = G[blockIdx.y];
   const Work &w = g.e.w[0];
@@ -2899,8 +3099,13 @@ __global__ void kg_status(const GangDesc *G, int rounds, int32_t *out, int strid
   for (int i = threadIdx.x; i < ns; i += blockDim.x) o[i] = st[i];
   for (int i = threadIdx.x; i < nc; i += blockDim.x) o[ns + i] = cn[i];
   for (int i = threadIdx.x; i < rounds * nc; i += blockDim.x) o[ns + nc + i] = hi[i];
+  __syncthreads();
+  if (threadIdx.x == 0) w.st->nhist = 0;
 }
+#undef GANG_LANES
+#undef GANG_SHARE
 #undef GANG_MESH
+#undef GANG_MESH_OF
 
 // ---------------------------------------------------------------------------
 // Measurement: 64-bit atomicMax at random slots of a table in device memory,
