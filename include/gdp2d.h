@@ -227,14 +227,12 @@ gdp_status gdp_mesh_create(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh **out);
    the first step; Section 7.1 builds it on the CPU): the same canonical CDT
    as gdp_mesh_create, element for element, built by kernels on the context
    stream from the host arrays of *pslg (copied to the device; the caller
-   keeps ownership).  Points are inserted by rounds of parallel
-   Bowyer-Watson insertion, missing segments recovered by rounds of
-   pseudo-polygon retriangulation.  Blocks until done.  Errors:
+   keeps ownership).  Points are inserted by rounds of parallel splits, each
+   followed by passes of parallel edge flips, missing segments recovered by
+   rounds of pseudo-polygon retriangulation.  Blocks until done.  Errors:
    GDP_E_ARG (NULL, fewer than 3 vertices), GDP_E_INPUT (invalid PSLG: the
    host builder's checks; its message may differ), GDP_E_NOMEM,
-   GDP_E_DEVICE.  Cavities of any size are handled (one larger than a
-   round's per-point lists waits for a round of its own).  On error
-   *out = NULL. */
+   GDP_E_DEVICE.  On error *out = NULL. */
 gdp_status gdp_mesh_create_device(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh **out);
 
 /* Same CDT, host only (no device needed).  Writes the counts to *n_tri and,

@@ -10,16 +10,16 @@
 //
 // Stages, all on one stream:
 //   1. Delaunay triangulation of the points and a large enclosing triangle by
-//      rounds of parallel Bowyer-Watson insertion.  Each pending point walks
-//      to the triangle holding it; each triangle elects one point (largest
-//      key); an elected point grows its cavity (triangles whose circle holds
-//      it) and stamps its key with atomicMax on the cavity and on the ring of
-//      triangles across the cavity boundary; a point whose cavity and ring
-//      all still carry its key replaces the cavity by its fan.  Disjoint
-//      cavity+ring regions make the insertions of one round independent: a
-//      point outside another's region is outside every circle of that
-//      other's new fan (the fan triangle on a boundary edge has, on the far
-//      side of the edge, a circle inside the circle of the ring triangle).
+//      rounds of insertion and flips.  The points are renumbered along a
+//      Morton curve (the ids decide ties and the final order only), so that
+//      neighbouring lanes work on neighbouring triangles.  Each pending point
+//      walks to the triangle holding it; each triangle takes one point
+//      (largest key), splits 1-3 (2-4 for a point on an edge, which needs
+//      both triangles), and edges that are not locally Delaunay are flipped
+//      in passes until none is left.  Every triangle that holds points is
+//      split in every round, so the points of each triangle fall to a third
+//      per round.  An evenly spread sample of the points goes first, in one
+//      workgroup.
 //   2. Segment recovery by rounds: a segment whose edge is missing walks the
 //      triangles it crosses and stamps them and their outer neighbours; a
 //      segment that keeps every stamp replaces the crossed triangles by the
@@ -34,6 +34,7 @@
 //      layout.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -43,14 +44,13 @@ namespace gdp {
 namespace {
 
 constexpr int kBlk = 256;        // block of the plain kernels
-constexpr int kCavBlk = 128;     // block of the cavity kernels
-constexpr int kLdsCap = 32;      // cavity triangles per thread kept in LDS
-constexpr int kBigSlots = 64;    // cavities above kLdsCap handled per round
-constexpr int kBigCap = 16384;   // triangles of one such cavity (a larger one waits, see mark_cavity)
 constexpr int kWalkCap = 1 << 20;   // steps of one walk or rotation
+constexpr int kSeedMax = 4096;      // points of the sample
+constexpr uint64_t kPassMax = 1ull << 23;  // flip passes of a build (24 bits of a claim)
+constexpr int kPassBatch = 6;       // flip passes between two host reads (even: the worklist ends where it began)
 
 enum CdtErr : int {
-  kEOk = 0, kEDup, kEWalk, kECavity, kERepeat, kEOnSeg, kECross, kELeave, kEDir, kEHull, kEUnused,
+  kEOk = 0, kEDup, kEWalk, kERepeat, kEOnSeg, kECross, kELeave, kEDir, kEHull, kEUnused,
   kEDisk, kEInternal = 100  // + the site that found an inconsistency
 };
 
@@ -58,7 +58,6 @@ const char *cdt_err_text(int e) {
   switch (e) {
     case kEDup: return "duplicate point";
     case kEWalk: return "point location failed";
-    case kECavity: return "a Delaunay cavity exceeded the device builder's capacity";
     case kERepeat: return "repeated segment";
     case kEOnSeg: return "a vertex lies in the interior of a segment";
     case kECross: return "segments cross";
@@ -80,27 +79,34 @@ std::string cdt_err_string(int e) {
 struct Ctr {
   int npend;   // entries appended to the next pending list
   int nwin;    // insertions this round
-  int nbig;    // big cavity slots taken
   int pool;    // ints of the per-round pool taken
   int err;     // first error code
   int nkeep;   // kept triangles (final stage)
   int nhull;   // boundary edges of the kept region
-  int first;   // smallest list index of a pending point (rounds with one forced insertion)
+  int ntri;    // triangles so far
+  int nlist[2];  // flip worklists (one read, one built per pass)
+  int ncand[2];  // flip candidates (by the parity of the pass)
+  int first_stamp, first_pass;  // after the sample: the last stamp and pass used
 };
 
 struct Bld {
-  const double2 *P;  // nv + 3 points: the input, then the enclosing triangle
+  const double2 *P;    // nv + 3 points along the Morton curve, then the enclosing triangle
+  const int *id;       // their ids (nv .. nv + 2: the enclosing triangle)
   int nv;
   int4 *tv, *tn, *ts;  // triangle slots: vertices, neighbours, segment id per edge (-1 none)
   int capT;
-  int *ntri;
-  uint64_t *pick, *mark;  // per slot: elected key, largest cavity stamp (round << 32 | key)
-  uint64_t *ring;         // per slot: largest ring stamp of a point cavity
-  int *hint, *state;      // per point: last triangle, -2 / -1 (LDS cavity) / big slot
-  int *vt;                // per vertex: an incident triangle
-  int *big;               // kBigSlots * kBigCap, or the whole area for the one cavity of a solo round
-  int big_all;            // ints of the area (>= capT: room for any cavity)
-  int *pool;              // per-round scratch
+  uint64_t *pick;      // per slot: key of the point that splits it, then of the segment that crosses it (round << 32 | key)
+  uint64_t *mark;      // per slot: claim of a flip (pass << 40 | edge), then stamp of a segment (round << 32 | key)
+  int *loc, *state;    // per point: 4 * (last triangle) + edge it lies on (3: inside); per segment: start triangle
+  int *vt;             // per vertex: an incident triangle
+  // flips
+  int4 *grp;           // slots that replaced a split triangle (shares fc0's memory: no flips then)
+  int *sstamp;         // round in which the slot was split
+  int *wstamp;         // pass stamp: on the worklist
+  int *list[2];
+  int4 *fc0, *fc1;     // candidates: (t, e, o, j) and the four outer slots
+  uint64_t *fprio;
+  int *pool;           // per-round scratch of the segment recovery
   int pool_cap;
   Ctr *c;
 };
@@ -122,23 +128,19 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
   return h;
 }
 
-// Pending points take part in a round's election only while a second mix of
-// their id is at most the round's threshold: a random sample of about four
-// points per triangle while the mesh is coarse, so the early rounds do not
-// walk every point.
-__device__ __forceinline__ bool sampled(int p, uint32_t thresh) { return mix32((uint32_t)p ^ 0x5bd1e995u) <= thresh; }
-
 __device__ __forceinline__ int orient_ids(const double2 *P, int a, int b, int c) {
   const double2 A = P[a], B = P[b], C = P[c];
   return orient2d(A.x, A.y, B.x, B.y, C.x, C.y);
 }
 
 // incircle with the symbolic perturbation of the lifting map (gdp_exact.h)
-// on points given by their ids; equal ids (a chain vertex repeated around a
+// by the ids of the points; equal ids (a chain vertex repeated around a
 // slit) keep their argument order.
-__device__ int incircle_sos(const double2 *P, int a, int b, int c, int d) {
-  const double2 A = P[a], B = P[b], C = P[c], D = P[d];
-  return gdp::incircle_sos(A.x, A.y, B.x, B.y, C.x, C.y, D.x, D.y, a, b, c, d);
+__device__ __forceinline__ int incircle_sos(const Bld &bl, int a, int b, int c, int d) {
+  const double2 A = bl.P[a], B = bl.P[b], C = bl.P[c], D = bl.P[d];
+  const int f = incircle_filter(A.x, A.y, B.x, B.y, C.x, C.y, D.x, D.y);
+  if (f != kUndecided) return f;
+  return gdp::incircle_sos(A.x, A.y, B.x, B.y, C.x, C.y, D.x, D.y, bl.id[a], bl.id[b], bl.id[c], bl.id[d]);
 }
 
 __device__ __forceinline__ int eidx(const int4 &v, int u, int w) {
@@ -165,284 +167,586 @@ __device__ __forceinline__ int wave_take(int *counter, int n) {
   return base + x - n;
 }
 
-struct List {
-  int *p;
-  int stride;
-  __device__ __forceinline__ int &operator[](int i) const { return p[(size_t)i * stride]; }
-};
+// The same by a whole workgroup of kBlk threads: one atomic per workgroup.
+// Atomics on one address are served about 12 ns apart, so with one per wave a
+// pass over a million elements would wait 190 us for each counter.
+__device__ __forceinline__ int block_take(int *counter, int n) {
+  __shared__ int s_part[kBlk / 64], s_base;
+  const int lane = __lane_id(), wid = threadIdx.x >> 6;
+  int x = n;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) s_part[wid] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int acc = 0;
+    for (int i = 0; i < kBlk / 64; i++) {
+      const int t = s_part[i];
+      s_part[i] = acc;
+      acc += t;
+    }
+    s_base = acc ? atomicAdd(counter, acc) : 0;
+  }
+  __syncthreads();
+  x += s_base + s_part[wid] - n;
+  __syncthreads();
+  return x;
+}
+// Space from a counter in memory (BLOCK: by every thread of the workgroup) or
+// in LDS (by every lane of the wave).
+template <bool BLOCK>
+__device__ __forceinline__ int take(int *counter, int n) {
+  return BLOCK ? block_take(counter, n) : wave_take(counter, n);
+}
 
 // ---------------------------------------------------------------------------
-// Stage 1: Delaunay triangulation by parallel Bowyer-Watson rounds
+// Stage 1: Delaunay triangulation by insertion rounds and flip passes
 // ---------------------------------------------------------------------------
-__global__ void k_init(Bld b, int *pend) {
+// Bounding box of the points, each block's extremes by atomics on the
+// monotone integer image of a double.
+__device__ __forceinline__ unsigned long long ord_of(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  return (b >> 63) ? ~b : (b | (1ull << 63));
+}
+double ord_to(unsigned long long o) {
+  const unsigned long long b = (o >> 63) ? (o & ~(1ull << 63)) : ~o;
+  double x;
+  memcpy(&x, &b, sizeof x);
+  return x;
+}
+// box: max of x, y and of -x, -y (all zero bits at first: below every double)
+__global__ __launch_bounds__(kBlk) void k_box(const double2 *xy, int nv, unsigned long long *box) {
+  unsigned long long m[4] = {0, 0, 0, 0};
+  const int stride = gridDim.x * blockDim.x;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
+    const double2 p = xy[i];
+    m[0] = max(m[0], ord_of(p.x));
+    m[1] = max(m[1], ord_of(p.y));
+    m[2] = max(m[2], ord_of(-p.x));
+    m[3] = max(m[3], ord_of(-p.y));
+  }
+  for (int k = 0; k < 4; k++) {
+    for (int d = 32; d >= 1; d >>= 1) {
+      const unsigned long long o = (unsigned long long)__shfl_xor((long long)m[k], d);
+      m[k] = max(m[k], o);
+    }
+    if (__lane_id() == 0) atomicMax(&box[k], m[k]);
+  }
+}
+
+// 16-bit cells of the box per axis, interleaved.
+__global__ __launch_bounds__(kBlk) void k_morton(const double2 *xy, int nv, double x0, double y0, double sx, double sy,
+                                                 uint64_t *keys, int *vals) {
+  const int stride = gridDim.x * blockDim.x;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
+    const double2 p = xy[i];
+    uint32_t c[2] = {(uint32_t)min(max((p.x - x0) * sx, 0.0), 65535.0), (uint32_t)min(max((p.y - y0) * sy, 0.0), 65535.0)};
+    for (int k = 0; k < 2; k++) {
+      uint32_t x = c[k];
+      x = (x | (x << 8)) & 0x00ff00ffu;
+      x = (x | (x << 4)) & 0x0f0f0f0fu;
+      x = (x | (x << 2)) & 0x33333333u;
+      x = (x | (x << 1)) & 0x55555555u;
+      c[k] = x;
+    }
+    keys[i] = c[0] | (c[1] << 1);
+    vals[i] = i;
+  }
+}
+
+// The points along the curve, their ids, the inverse permutation and the
+// first triangle.
+__global__ __launch_bounds__(kBlk) void k_reorder(Bld b, const double2 *xy, double2 *P, const int *vals, int *id,
+                                                  int *rank, double L) {
   const int stride = gridDim.x * blockDim.x;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < b.nv; i += stride) {
-    pend[i] = i;
-    b.hint[i] = 0;
+    const int v = vals[i];
+    P[i] = xy[v];
+    id[i] = v;
+    rank[v] = i;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    P[b.nv] = make_double2(-4 * L, -4 * L);
+    P[b.nv + 1] = make_double2(8 * L, -4 * L);
+    P[b.nv + 2] = make_double2(-4 * L, 8 * L);
+    for (int k = 0; k < 3; k++) id[b.nv + k] = b.nv + k;
     b.tv[0] = make_int4(b.nv, b.nv + 1, b.nv + 2, 0);
     b.tn[0] = make_int4(-1, -1, -1, 0);
-    b.ts[0] = make_int4(-1, -1, -1, 0);
-    *b.ntri = 1;
+    b.c->ntri = 1;
   }
 }
 
-// Walks each pending point to its triangle and elects, per triangle, the
-// point with the largest key (waves whose lanes share a triangle combine
-// their keys before the atomic).
-// relocate = 1: the points outside the sample walk too (their start
-// triangles are refreshed each time the mesh has doubled) but do not elect.
-__global__ void k_locate(Bld b, const int *pend, int np, uint32_t round, int solo, uint32_t thresh, int relocate) {
+__device__ __forceinline__ uint64_t point_key(int p, uint32_t round) { return ((uint64_t)round << 32) | mix32((uint32_t)p); }
+
+// Walks point p (act) from its last triangle to the one holding it and
+// claims that (and the one across the edge it lies on) for the round's
+// split.  All lanes of the wave take part: lanes that share a triangle
+// combine their keys before the atomic while such groups are large.
+__device__ __forceinline__ void dt_locate(const Bld &b, int p, bool act, uint32_t round) {
   const int lane = __lane_id();
-  const int stride = gridDim.x * blockDim.x;
-  for (int base = blockIdx.x * blockDim.x; base < np; base += stride) {
-    const int i = base + threadIdx.x;
-    const int p = i < np ? pend[i] : -1;  // -1: an inserted point left in the list
-    bool act = p >= 0;
-    int t = 0;
-    uint64_t key = 0;
-    if (solo && act) atomicMin(&b.c->first, i);
-    const bool elect = act && sampled(p, thresh);
-    if (!elect && !relocate) act = false;
-    if (act) {
-      t = b.hint[p];
-      int from = -1;
-      const double2 q = b.P[p];
-      int steps = 0;
-      for (;;) {
-        const int4 v = b.tv[t];
-        const int4 n = b.tn[t];
-        int moved = -1;
-        for (int e = 0; e < 3; e++) {
-          const int o = comp(n, e);
-          if (o == from && o >= 0) continue;
-          const double2 U = b.P[comp(v, e)], W = b.P[comp(v, (e + 1) % 3)];
-          if (orient2d(U.x, U.y, W.x, W.y, q.x, q.y) < 0) { moved = e; break; }
+  int t = 0, e = 3, o = -1;
+  uint64_t key = 0;
+  if (act) {
+    t = b.loc[p] >> 2;
+    key = point_key(p, round);
+    int from = -1;
+    const double2 q = b.P[p];
+    for (int steps = 0;; steps++) {
+      const int4 v = b.tv[t], n = b.tn[t];
+      const double2 A = b.P[v.x], B = b.P[v.y], C = b.P[v.z];
+      const int s0 = orient2d(A.x, A.y, B.x, B.y, q.x, q.y), s1 = orient2d(B.x, B.y, C.x, C.y, q.x, q.y),
+                s2 = orient2d(C.x, C.y, A.x, A.y, q.x, q.y);
+      const int m = (s0 < 0 && n.x != from) ? 0 : ((s1 < 0 && n.y != from) ? 1 : ((s2 < 0 && n.z != from) ? 2 : -1));
+      if (m < 0) {
+        if ((s0 == 0) + (s1 == 0) + (s2 == 0) >= 2) {
+          set_err(b.c, kEDup);  // on a vertex
+          act = false;
         }
-        if (moved < 0) {
-          const double2 A = b.P[v.x], B = b.P[v.y], C = b.P[v.z];
-          if ((A.x == q.x && A.y == q.y) || (B.x == q.x && B.y == q.y) || (C.x == q.x && C.y == q.y)) {
-            set_err(b.c, kEDup);
-            act = false;
-          }
-          break;
-        }
-        const int o = comp(n, moved);
-        if (o < 0 || ++steps > kWalkCap) { set_err(b.c, kEWalk); act = false; break; }
-        from = t;
-        t = o;
+        e = s0 == 0 ? 0 : (s1 == 0 ? 1 : (s2 == 0 ? 2 : 3));
+        o = e < 3 ? comp(n, e) : -1;
+        break;
       }
-      b.hint[p] = t;
-      key = ((uint64_t)round << 32) | mix32((uint32_t)p);
-      if (!elect) act = false;
-    }
-    // combine the keys of lanes that share a triangle while such groups are
-    // large (early rounds: few triangles, many points each)
-    uint64_t left = __ballot(act);
-    for (int it = 0; it < 64 && left; it++) {
-      const int leader = __ffsll((unsigned long long)left) - 1;
-      const int tl = __shfl(t, leader);
-      const bool same = act && t == tl;
-      const uint64_t m = __ballot(same);
-      if (it > 0 && __popcll(m) < 3) break;
-      long long best = same ? (long long)key : 0;
-      for (int d = 32; d >= 1; d >>= 1) {
-        long long o = __shfl_xor(best, d);
-        best = (unsigned long long)o > (unsigned long long)best ? o : best;
+      const int nx = comp(n, m);
+      if (nx < 0 || steps > kWalkCap) {
+        set_err(b.c, kEWalk);
+        act = false;
+        break;
       }
-      if (lane == leader) atomicMax((unsigned long long *)&b.pick[tl], (unsigned long long)best);
-      if (same) act = false;
-      left &= ~m;
+      from = t;
+      t = nx;
     }
-    if (act) atomicMax((unsigned long long *)&b.pick[t], (unsigned long long)key);
+    b.loc[p] = 4 * t + e;
+  }
+  if (act && o >= 0) atomicMax((unsigned long long *)&b.pick[o], (unsigned long long)key);
+  uint64_t left = __ballot(act);
+  for (int it = 0; it < 64 && left; it++) {
+    const int leader = __ffsll((unsigned long long)left) - 1;
+    const int tl = __shfl(t, leader);
+    const bool same = act && t == tl;
+    const uint64_t m = __ballot(same);
+    if (it > 0 && __popcll(m) < 3) break;
+    long long best = same ? (long long)key : 0;
+    for (int d = 32; d >= 1; d >>= 1) {
+      long long x = __shfl_xor(best, d);
+      best = (unsigned long long)x > (unsigned long long)best ? x : best;
+    }
+    if (lane == leader) atomicMax((unsigned long long *)&b.pick[tl], (unsigned long long)best);
+    if (same) act = false;
+    left &= ~m;
+  }
+  if (act) atomicMax((unsigned long long *)&b.pick[t], (unsigned long long)key);
+}
+
+// Splits the triangle(s) of point p if it holds them; returns whether it did.
+// A new triangle is (x, y, p): edge 0 is the outer one, which still names the
+// old neighbour (dt_fix follows).  The new triangles go to the worklist.
+template <bool BLOCK>
+__device__ __forceinline__ bool dt_split(const Bld &b, int p, bool act, uint32_t round, int wst, int *ntri, int *nlist) {
+  int t0 = 0, e0 = 3, t1 = -1;
+  bool own = false;
+  if (act) {
+    const uint64_t key = point_key(p, round);
+    t0 = b.loc[p] >> 2;
+    e0 = b.loc[p] & 3;
+    own = b.pick[t0] == key;
+    if (own && e0 < 3) {
+      t1 = comp(b.tn[t0], e0);
+      own = t1 >= 0 && b.pick[t1] == key;
+    }
+  }
+  const int base = take<BLOCK>(ntri, own ? 2 : 0);
+  const int lb = take<BLOCK>(nlist, own ? (e0 < 3 ? 4 : 3) : 0);
+  if (!own) return false;
+  if (base + 2 > b.capT) {  // not reached: 2 nv + 1 triangles in the end
+    set_err(b.c, kEInternal + 1);
+    for (int i = 0; i < (e0 < 3 ? 4 : 3); i++) b.list[0][lb + i] = t0;
+    return false;
+  }
+  const int4 v = b.tv[t0], n = b.tn[t0];
+  int slot[4], x[4], out[4], k = 3;
+  if (e0 == 3) {
+    slot[0] = t0; slot[1] = base; slot[2] = base + 1; slot[3] = -1;
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = -1;
+    out[0] = n.x; out[1] = n.y; out[2] = n.z; out[3] = -1;
+    b.grp[t0] = make_int4(t0, base, base + 1, -1);
+  } else {
+    // edge (u, v) of t0 = (u, v, w) and t1 = (v, u, x): around p the quad u, x, v, w
+    const int4 v1 = b.tv[t1], n1 = b.tn[t1];
+    const int u = comp(v, e0), vv = comp(v, (e0 + 1) % 3), w = comp(v, (e0 + 2) % 3);
+    const int e1 = v1.x == vv ? 0 : (v1.y == vv ? 1 : 2);
+    k = 4;
+    slot[0] = t1; slot[1] = base; slot[2] = t0; slot[3] = base + 1;
+    x[0] = u; x[1] = comp(v1, (e1 + 2) % 3); x[2] = vv; x[3] = w;
+    out[0] = comp(n1, (e1 + 1) % 3); out[1] = comp(n1, (e1 + 2) % 3);
+    out[2] = comp(n, (e0 + 1) % 3); out[3] = comp(n, (e0 + 2) % 3);
+    const int4 g = make_int4(slot[0], slot[1], slot[2], slot[3]);
+    b.grp[t0] = g;
+    b.grp[t1] = g;
+    b.sstamp[t1] = (int)round;
+  }
+  b.sstamp[t0] = (int)round;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    if (i >= k) continue;
+    const bool last = i == k - 1;
+    const int s = slot[i];
+    b.tv[s] = make_int4(x[i], last ? x[0] : x[(i + 1) & 3], p, 0);
+    b.tn[s] = make_int4(out[i], last ? slot[0] : slot[(i + 1) & 3], i == 0 ? slot[k - 1] : slot[(i + 3) & 3], 0);
+    b.wstamp[s] = wst;
+    b.list[0][lb + i] = s;
+  }
+  return true;
+}
+
+// The outer edge of a new triangle: the neighbour it names was split too (the
+// edge is the outer edge of one of its replacements) or has its pointer set.
+__device__ __forceinline__ void dt_fix(const Bld &b, int s, uint32_t round) {
+  const int o = b.tn[s].x;
+  if (o < 0) return;
+  const int4 v = b.tv[s];
+  if (b.sstamp[o] == (int)round) {
+    const int4 g = b.grp[o];
+    const int c[4] = {g.x, g.y, g.z, g.w};
+    int found = -1;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      if (c[k] < 0) continue;
+      const int4 w = b.tv[c[k]];
+      if (w.x == v.y && w.y == v.x) found = c[k];
+    }
+    if (found < 0) set_err(b.c, kEInternal + 2);
+    else *comp_ptr(b.tn, s, 0) = found;
+  } else {
+    const int j = eidx(b.tv[o], v.y, v.x);
+    if (j < 0) set_err(b.c, kEInternal + 3);
+    else *comp_ptr(b.tn, o, j) = s;
   }
 }
 
-// Cavity of point p, breadth first from the triangles already in L[0..n)
-// (the caller puts the start triangle there and stamps / checks it).
-// mode 0: stamp key on the cavity (mark) and on the ring around it (ring);
-// a triangle already stamped with key is already listed.  mode 1: rebuild
-// the list from the stamps (pick marks the listed triangles), requiring that
-// no larger key holds a cavity triangle in its cavity or ring, nor a ring
-// triangle in its cavity.  Rings may overlap: a ring triangle only has one
-// neighbour pointer per cavity rewritten.  Returns n when done, -1 when the
-// list is full (h and n then allow a resume with a larger list), -2 when a
-// larger key holds the region.
-__device__ int grow(const Bld &b, int p, List L, int cap, uint64_t key, int mode, int &h, int &n) {
-  for (; h < n; h++) {
-    const int4 nb = b.tn[L[h]];
+// Flip check of one worklist triangle (act): every edge that is not locally
+// Delaunay claims its two triangles and the four around them with one 64-bit
+// atomicMax of (pass, edge).
+template <bool BLOCK>
+__device__ __forceinline__ void dt_check(const Bld &b, int t, bool act, int in_stamp, uint64_t pass, int *ncand) {
+  int4 a = make_int4(0, 0, 0, 0), na = make_int4(-1, -1, -1, 0);
+  int j[3] = {0, 0, 0};
+  int flip = 0;  // bits: the edges to flip
+  if (act) {
+    a = b.tv[t];
+    na = b.tn[t];
+    // the three neighbours and their far vertices, loaded together
+    int d[3];
+    int4 v[3];
+    int st[3];
+#pragma unroll
     for (int e = 0; e < 3; e++) {
-      const int o = comp(nb, e);
-      if (o < 0) continue;
-      if (mode == 1) {
-        const uint64_t m = b.mark[o];
-        if (m > key) return -2;
-        if (m != key) continue;  // ring
-        if (b.ring[o] > key) return -2;
-        if (b.pick[o] == key) continue;  // listed
-        if (n == cap) return -1;
-        b.pick[o] = key;
-      } else {
-        if (b.mark[o] == key) continue;  // listed
-        const int4 v = b.tv[o];
-        if (incircle_sos(b.P, v.x, v.y, v.z, p) <= 0) {
-          atomicMax((unsigned long long *)&b.ring[o], (unsigned long long)key);
-          continue;
-        }
-        if (n == cap) return -1;
-        const uint64_t old = atomicMax((unsigned long long *)&b.mark[o], (unsigned long long)key);
-        if (old > key) return -2;
-        if (old == key) continue;
+      const int o = max(comp(na, e), 0);
+      v[e] = b.tv[o];
+      st[e] = b.wstamp[o];
+    }
+    const double2 P[3] = {b.P[a.x], b.P[a.y], b.P[a.z]};
+    double2 D[3];
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int u = comp(a, e);
+      // the edge runs the other way in the neighbour: its end u comes second
+      j[e] = v[e].y == u ? 0 : (v[e].z == u ? 1 : 2);
+      d[e] = j[e] == 0 ? v[e].z : (j[e] == 1 ? v[e].x : v[e].y);
+      D[e] = b.P[d[e]];
+    }
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int o = comp(na, e);
+      if (o < 0 || (o < t && st[e] == in_stamp)) continue;  // the lower slot on the list checks the edge
+      const double2 U = P[e], W = P[e == 2 ? 0 : e + 1], C = P[e == 0 ? 2 : e - 1], Q = D[e];
+      int in = incircle_filter(U.x, U.y, W.x, W.y, C.x, C.y, Q.x, Q.y);
+      if (in == kUndecided) {
+        const int u = comp(a, e), w = comp(a, e == 2 ? 0 : e + 1), c = comp(a, e == 0 ? 2 : e - 1);
+        in = gdp::incircle_sos(U.x, U.y, W.x, W.y, C.x, C.y, Q.x, Q.y, b.id[u], b.id[w], b.id[c], b.id[d[e]]);
       }
-      L[n++] = o;
+      if (in > 0) flip |= 1 << e;
     }
   }
-  return n;
-}
-
-// Stamps the start triangle and grows the cavity of p (mode 0) in L; on a
-// full list continues in a large list of the global pool when one is free.
-// Returns the state: -1 (cavity in LDS), a big-list slot, or -2 (none).  A
-// cavity beyond a big list waits: the point stays pending, its cavity
-// shrinks as its neighbourhood fills in, and a round that inserts nothing
-// is followed by a solo round whose one point may use the whole area, which
-// holds any cavity (the triangles of a cavity are distinct live slots).
-__device__ int mark_cavity(const Bld &b, int p, int t0, uint64_t key, List L, int cap, bool big_only) {
-  const uint64_t old = atomicMax((unsigned long long *)&b.mark[t0], (unsigned long long)key);
-  if (old > key) return -2;
-  int h = 0, n = 1;
-  if (big_only) {
-    const List G{b.big, 1};
-    G[0] = t0;
-    const int r = grow(b, p, G, b.big_all, key, 0, h, n);
-    if (r == -1) set_err(b.c, kEInternal + 3);
-    return r > 0 ? 0 : -2;
+  // (a triangle has at most three edges to flip and an edge enters once, so
+  // there are at most 3/2 candidates per slot; the lists hold two)
+  int idx = take<BLOCK>(ncand, __popc(flip));
+#pragma unroll
+  for (int e = 0; e < 3; e++) {
+    if (!(flip & (1 << e))) continue;
+    const int o = comp(na, e), je = j[e];
+    const int4 nb = b.tn[o];
+    const int4 f1 = make_int4(comp(na, e == 2 ? 0 : e + 1), comp(na, e == 0 ? 2 : e - 1), comp(nb, je == 2 ? 0 : je + 1),
+                              comp(nb, je == 0 ? 2 : je - 1));
+    const uint64_t prio = (pass << 40) | (uint64_t)(t < o ? 4 * (int64_t)t + e : 4 * (int64_t)o + je);
+    b.fc0[idx] = make_int4(t, e, o, je);
+    b.fc1[idx] = f1;
+    b.fprio[idx] = prio;
+    idx++;
+    atomicMax((unsigned long long *)&b.mark[t], (unsigned long long)prio);
+    atomicMax((unsigned long long *)&b.mark[o], (unsigned long long)prio);
+    if (f1.x >= 0) atomicMax((unsigned long long *)&b.mark[f1.x], (unsigned long long)prio);
+    if (f1.y >= 0) atomicMax((unsigned long long *)&b.mark[f1.y], (unsigned long long)prio);
+    if (f1.z >= 0) atomicMax((unsigned long long *)&b.mark[f1.z], (unsigned long long)prio);
+    if (f1.w >= 0) atomicMax((unsigned long long *)&b.mark[f1.w], (unsigned long long)prio);
   }
-  L[0] = t0;
-  int r = grow(b, p, L, cap, key, 0, h, n);
-  if (r > 0) return -1;
-  if (r == -2) return -2;
-  const int slot = atomicAdd(&b.c->nbig, 1);
-  if (slot >= kBigSlots) return -2;
-  const List G{b.big + (size_t)slot * kBigCap, 1};
-  for (int k = 0; k < n; k++) G[k] = L[k];
-  r = grow(b, p, G, kBigCap, key, 0, h, n);
-  return r > 0 ? slot : -2;
 }
 
-__global__ __launch_bounds__(kCavBlk) void k_mark(Bld b, const int *pend, int np, uint32_t round, int solo,
-                                                  uint32_t thresh) {
-  __shared__ int s_list[kLdsCap * kCavBlk];
-  const List lds{&s_list[threadIdx.x], kCavBlk};
-  const int stride = gridDim.x * blockDim.x;
-  const int first = solo ? b.c->first : -1;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < np; i += stride) {
-    const int p = pend[i];
-    if (p < 0) continue;
-    const uint64_t key = ((uint64_t)round << 32) | mix32((uint32_t)p);
-    const int t0 = b.hint[p];
-    int st = -2;
-    if (solo) {
-      if (i == first) st = mark_cavity(b, p, t0, key, lds, kLdsCap, true);
-    } else if (sampled(p, thresh) && b.pick[t0] == key) {
-      st = mark_cavity(b, p, t0, key, lds, kLdsCap, false);
+// A candidate (act) whose six claims hold is flipped: it is the only writer of
+// the six triangles in the pass.  The triangles of the others are checked
+// again.  Each triangle enters the next worklist once.
+template <bool BLOCK>
+__device__ __forceinline__ void dt_apply(const Bld &b, int i, bool act, int wst, int *out, int *nout) {
+  int t = 0, o = 0;
+  bool win = false;
+  if (act) {
+    const int4 f = b.fc0[i], g = b.fc1[i];
+    const uint64_t prio = b.fprio[i];
+    const int e = f.y, j = f.w;
+    t = f.x;
+    o = f.z;
+    const uint64_t m0 = b.mark[t], m1 = b.mark[o], m2 = b.mark[max(g.x, 0)], m3 = b.mark[max(g.y, 0)],
+                   m4 = b.mark[max(g.z, 0)], m5 = b.mark[max(g.w, 0)];
+    win = m0 == prio && m1 == prio && (g.x < 0 || m2 == prio) && (g.y < 0 || m3 == prio) &&
+          (g.z < 0 || m4 == prio) && (g.w < 0 || m5 == prio);
+    if (win) {
+      // t = (u, v, w) with edge e = (u, v), o = (v, u, d) with edge j: (u, v)
+      // gives way to (d, w): (u, d, w) in t, (d, v, w) in o
+      const int4 a = b.tv[t], bv = b.tv[o];
+      const int u = comp(a, e), v = comp(a, (e + 1) % 3), w = comp(a, (e + 2) % 3), d = comp(bv, (j + 2) % 3);
+      b.tv[t] = make_int4(u, d, w, 0);
+      b.tn[t] = make_int4(g.z, o, g.y, 0);
+      b.tv[o] = make_int4(d, v, w, 0);
+      b.tn[o] = make_int4(g.w, g.x, t, 0);
+      if (g.z >= 0) {
+        const int q = eidx(b.tv[g.z], d, u);
+        if (q < 0) set_err(b.c, kEInternal + 4);
+        else *comp_ptr(b.tn, g.z, q) = t;
+      }
+      if (g.x >= 0) {
+        const int q = eidx(b.tv[g.x], w, v);
+        if (q < 0) set_err(b.c, kEInternal + 5);
+        else *comp_ptr(b.tn, g.x, q) = o;
+      }
     }
-    b.state[p] = st;
   }
+  const bool pt = act && atomicExch(&b.wstamp[t], wst) != wst;
+  const bool po = win && atomicExch(&b.wstamp[o], wst) != wst;
+  int at = take<BLOCK>(nout, (pt ? 1 : 0) + (po ? 1 : 0));
+  if (pt) out[at++] = t;
+  if (po) out[at] = o;
 }
 
-// compact = 1: the points not inserted go to pend_out; compact = 0: the
-// list stays and each inserted point leaves -1 in its entry.
-__global__ __launch_bounds__(kCavBlk) void k_insert(Bld b, int *pend, int np, uint32_t round, int *pend_out,
-                                                    int compact, int solo) {
-  __shared__ int s_list[kLdsCap * kCavBlk];
-  const List lds{&s_list[threadIdx.x], kCavBlk};
+__global__ __launch_bounds__(kBlk) void k_dt_locate(Bld b, const int *pend, int np, uint32_t round) {
   const int stride = gridDim.x * blockDim.x;
   for (int base = blockIdx.x * blockDim.x; base < np; base += stride) {
     const int i = base + threadIdx.x;
-    int p = i < np ? pend[i] : -1;
-    const bool act = p >= 0;
-    int n = -2;
-    List L = lds;
-    if (act) {
-      const int st = b.state[p];
-      if (st != -2) {
-        const uint64_t key = ((uint64_t)round << 32) | mix32((uint32_t)p);
-        int cap = kLdsCap;
-        if (st >= 0) { L = List{b.big + (size_t)st * kBigCap, 1}; cap = solo ? b.big_all : kBigCap; }
-        const int t0 = b.hint[p];
-        if (b.mark[t0] == key && b.ring[t0] <= key) {
-          b.pick[t0] = key;
-          L[0] = t0;
-          int h = 0, m = 1;
-          n = grow(b, p, L, cap, key, 1, h, m);
-        }
-      }
+    dt_locate(b, i < np ? pend[i] : 0, i < np, round);
+  }
+}
+
+__global__ __launch_bounds__(kBlk) void k_dt_split(Bld b, const int *pend, int np, uint32_t round, int wst, int *pend_out) {
+  const int stride = gridDim.x * blockDim.x;
+  for (int base = blockIdx.x * blockDim.x; base < np; base += stride) {
+    const int i = base + threadIdx.x;
+    const int p = i < np ? pend[i] : 0;
+    const bool done = dt_split<true>(b, p, i < np, round, wst, &b.c->ntri, &b.c->nlist[0]);
+    const int po = block_take(&b.c->npend, i < np && !done ? 1 : 0);
+    if (i < np && !done) pend_out[po] = p;
+  }
+}
+
+__global__ __launch_bounds__(kBlk) void k_dt_fix(Bld b, uint32_t round) {
+  const int n = b.c->nlist[0], stride = gridDim.x * blockDim.x;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dt_fix(b, b.list[0][i], round);
+}
+
+// A flip pass is these two launches; worklists and candidate counts
+// alternate, each emptied by a launch that does not use it.  Bound by latency:
+// a check is three dependent gathers (list, triangle, neighbours and points),
+// an apply the same, and most passes hold few entries.  A million points take
+// 212 passes of 20 + 11 us; with one atomic per wave and list instead of one per
+// workgroup the two kernels took 40 + 31 us.
+__global__ __launch_bounds__(kBlk) void k_dt_check(Bld b, int cur, int in_stamp, uint64_t pass) {
+  const int n = b.c->nlist[cur], stride = gridDim.x * blockDim.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) b.c->nlist[cur ^ 1] = 0;
+  for (int base = blockIdx.x * blockDim.x; base < n; base += stride) {
+    const int i = base + threadIdx.x;
+    dt_check<true>(b, i < n ? b.list[cur][i] : 0, i < n, in_stamp, pass, &b.c->ncand[pass & 1]);
+  }
+}
+__global__ __launch_bounds__(kBlk) void k_dt_apply(Bld b, int cur, int wst, uint64_t pass) {
+  const int n = b.c->ncand[pass & 1], stride = gridDim.x * blockDim.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) b.c->ncand[(pass + 1) & 1] = 0;
+  for (int base = blockIdx.x * blockDim.x; base < n; base += stride) {
+    const int i = base + threadIdx.x;
+    dt_apply<true>(b, i, i < n, wst, b.list[cur ^ 1], &b.c->nlist[cur ^ 1]);
+  }
+}
+
+// Passes over a short worklist inside one workgroup (two barriers instead of
+// two launches each), until it is empty: list s_n[cur] entries in b.list[cur].
+struct SeedShared {
+  int n[2], ncand;
+};
+__device__ __forceinline__ void dt_flips(const Bld &b, SeedShared &sh, int &cur, int &stamp, uint64_t &pass) {
+  for (;;) {
+    __syncthreads();
+    const int n = sh.n[cur];
+    if (n == 0 || pass > kPassMax) break;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      sh.n[cur ^ 1] = 0;
+      sh.ncand = 0;
     }
-    const bool win = n > 0;
-    const int fresh = wave_take(b.ntri, win ? 2 : 0);
-    const int bo = wave_take(&b.c->pool, win ? 4 * (n + 2) : 0);
-    if (compact) {
-      const int po = wave_take(&b.c->npend, act && !win ? 1 : 0);
-      if (act && !win) pend_out[po] = p;
+    __syncthreads();
+    pass++;
+    for (int base = 0; base < n; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      dt_check<false>(b, i < n ? b.list[cur][i] : 0, i < n, stamp, pass, &sh.ncand);
     }
-    if (!win) continue;
-    if (!compact) pend[i] = -1;
-    if (fresh + 2 > b.capT || bo + 4 * (n + 2) > b.pool_cap) { set_err(b.c, kEInternal + 1); continue; }
-    int *B = b.pool + bo;
-    const uint64_t key = ((uint64_t)round << 32) | mix32((uint32_t)p);
-    // the cavity boundary as a cycle: from a boundary edge (u, w), rotate
-    // around w inside the cavity to the next boundary edge
-    int ft = -1, fe = -1;
-    for (int h = 0; h < n && ft < 0; h++) {
-      const int4 nbv = b.tn[L[h]];
-      for (int e = 0; e < 3; e++) {
-        const int o = comp(nbv, e);
-        if (o < 0 || b.mark[o] != key) { ft = L[h]; fe = e; break; }
-      }
+    __syncthreads();
+    const int nc = sh.ncand;
+    stamp++;
+    for (int base = 0; base < nc; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      dt_apply<false>(b, i, i < nc, stamp, b.list[cur ^ 1], &sh.n[cur ^ 1]);
     }
-    bool linked = ft >= 0;
-    int nb = 0, ct = ft, ce = fe;
-    while (linked) {
-      if (nb >= n + 2) { linked = false; break; }
-      const int4 v = b.tv[ct];
-      const int o = comp(b.tn[ct], ce);
-      const int u = comp(v, ce), w = comp(v, (ce + 1) % 3);
-      const int oe = o >= 0 ? eidx(b.tv[o], w, u) : -1;
-      if (o >= 0 && oe < 0) { linked = false; break; }
-      B[4 * nb] = u;
-      B[4 * nb + 1] = w;
-      B[4 * nb + 2] = o;
-      B[4 * nb + 3] = oe;
-      nb++;
-      int t2 = ct, e2 = (ce + 1) % 3;
-      for (int guard = 0;; guard++) {
-        const int n2 = comp(b.tn[t2], e2);
-        if (n2 < 0 || b.mark[n2] != key) break;
-        const int k = vidx(b.tv[n2], w);
-        if (k < 0 || guard > n) { linked = false; break; }
-        t2 = n2;
-        e2 = k;
-      }
-      ct = t2;
-      ce = e2;
-      if (ct == ft && ce == fe) break;
+    cur ^= 1;
+  }
+}
+
+// A grid pass costs two launches, about 10 us; a pass of this over n
+// entries about 3 us per 1,024.
+constexpr int kTailMax = 2048;
+constexpr int kSeedBlk = 1024;
+// stamp / pass: the last ones used; the kernel may use as many as it needs
+// (the host leaves a gap of kTailGap).
+constexpr int kTailGap = 1 << 12;
+__global__ __launch_bounds__(kSeedBlk) void k_dt_tail(Bld b, int cur, int stamp, uint64_t pass) {
+  __shared__ SeedShared sh;
+  const int n0 = b.c->nlist[cur];
+  if (n0 == 0 || n0 > kTailMax) return;
+  if (threadIdx.x == 0) sh.n[cur] = n0;
+  const int cur0 = cur;
+  // (bounded by the gap: what is left goes on with the next launch)
+  int passes = 0;
+  for (; passes < kTailGap; passes++) {
+    __syncthreads();
+    const int n = sh.n[cur];
+    if (n == 0 || (n > kTailMax && cur == cur0)) break;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      sh.n[cur ^ 1] = 0;
+      sh.ncand = 0;
     }
-    linked = linked && nb == n + 2;
-    if (!linked) { set_err(b.c, kEInternal + 2); continue; }
-    atomicAdd(&b.c->nwin, 1);
-    for (int j = 0; j < nb; j++) {
-      const int u = B[4 * j], w = B[4 * j + 1], o = B[4 * j + 2], oe = B[4 * j + 3];
-      const int jn = j + 1 == nb ? 0 : j + 1, jp = j == 0 ? nb - 1 : j - 1;
-      const int s = j < n ? L[j] : fresh + (j - n);
-      const int sn = jn < n ? L[jn] : fresh + (jn - n);
-      const int sp = jp < n ? L[jp] : fresh + (jp - n);
-      b.tv[s] = make_int4(u, w, p, 0);
-      b.tn[s] = make_int4(o, sn, sp, 0);
-      b.ts[s] = make_int4(-1, -1, -1, 0);
-      if (o >= 0) *comp_ptr(b.tn, o, oe) = s;
+    __syncthreads();
+    pass++;
+    for (int base = 0; base < n; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      dt_check<false>(b, i < n ? b.list[cur][i] : 0, i < n, stamp, pass, &sh.ncand);
     }
+    __syncthreads();
+    const int nc = sh.ncand;
+    stamp++;
+    for (int base = 0; base < nc; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      dt_apply<false>(b, i, i < nc, stamp, b.list[cur ^ 1], &sh.n[cur ^ 1]);
+    }
+    cur ^= 1;
+  }
+  __syncthreads();
+  // an even number of passes leaves the list where the host expects it; else
+  // it is copied there
+  const int n = sh.n[cur];
+  if (cur != cur0)
+    for (int i = threadIdx.x; i < n; i += blockDim.x) b.list[cur0][i] = b.list[cur][i];
+  // the next pass takes these entries as written with this stamp
+  for (int i = threadIdx.x; i < n; i += blockDim.x) b.wstamp[b.list[cur][i]] = stamp;
+  if (threadIdx.x == 0) {
+    b.c->nlist[cur0] = n;
+    b.c->ncand[0] = 0;
+    b.c->ncand[1] = 0;
+    b.c->nwin = stamp;
+  }
+}
+
+// The sample: every step-th point along the curve, inserted round by round
+// in one workgroup, where a round costs barriers instead of launches (4,096
+// points 3.0 ms; with samples of 512, 1,024 or 2,048 and more rounds on the grid
+// a build of 60,013 points took 15.3, 14.7, 14.6 ms against 15.1 and one of a
+// million 38.6, 39.4, 38.7 against 37.6).  pend: two lists of ns entries.  Leaves the rounds in
+// nwin and the remaining points (0) in npend.
+__global__ __launch_bounds__(kSeedBlk) void k_dt_seed(Bld b, int ns, int step, int *pend0, int *pend1) {
+  __shared__ SeedShared sh;
+  __shared__ int s_ntri, s_left, s_err;
+  int *pend[2] = {pend0, pend1};
+  for (int i = threadIdx.x; i < ns; i += blockDim.x) {
+    pend0[i] = i * step;
+    b.loc[i * step] = 3;
+  }
+  if (threadIdx.x == 0) s_ntri = 1;
+  int np = ns, pc = 0, cur = 0, stamp = 0;
+  uint32_t round = 0;
+  uint64_t pass = 0;
+  while (np > 0) {
+    round++;
+    if (threadIdx.x == 0) {
+      s_left = 0;
+      sh.n[0] = 0;
+      // (set by atomics of other waves: read past the first-level cache)
+      s_err = __hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (s_err) break;
+    for (int base = 0; base < np; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      dt_locate(b, i < np ? pend[pc][i] : 0, i < np, round);
+    }
+    __syncthreads();
+    stamp++;
+    for (int base = 0; base < np; base += blockDim.x) {
+      const int i = base + threadIdx.x;
+      const int p = i < np ? pend[pc][i] : 0;
+      const bool done = dt_split<false>(b, p, i < np, round, stamp, &s_ntri, &sh.n[0]);
+      const int po = wave_take(&s_left, i < np && !done ? 1 : 0);
+      if (i < np && !done) pend[pc ^ 1][po] = p;
+    }
+    __syncthreads();
+    const int nl = sh.n[0];
+    for (int i = threadIdx.x; i < nl; i += blockDim.x) dt_fix(b, b.list[0][i], round);
+    __syncthreads();
+    cur = 0;
+    dt_flips(b, sh, cur, stamp, pass);
+    __syncthreads();
+    // every round inserts at least the point of the largest key
+    if (s_left >= np || pass > kPassMax) {
+      if (threadIdx.x == 0) set_err(b.c, kEInternal + 6);
+      np = s_left;
+      break;
+    }
+    np = s_left;
+    pc ^= 1;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    b.c->ntri = s_ntri;
+    b.c->npend = np;
+    b.c->nwin = (int)round;
+    b.c->first_stamp = stamp;
+    b.c->first_pass = (int)pass;
+  }
+}
+
+// Every other point starts at a triangle of the sample point before it.
+__global__ __launch_bounds__(kBlk) void k_dt_start(Bld b, int ns, int step, int *pend) {
+  const int stride = gridDim.x * blockDim.x;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < b.nv; i += stride) {
+    const int s = min(i / step, ns - 1), k = i - s * step;
+    if (k == 0) continue;
+    b.loc[i] = 4 * b.vt[s * step] + 3;
+    pend[i - s - 1] = i;
   }
 }
 
@@ -578,6 +882,11 @@ __device__ int seg_walk(const Bld &b, int a, int bb, int t0, uint64_t key, int m
   return kc;
 }
 
+__global__ void k_seg_rank(const int2 *seg, int ns, const int *rank, int2 *out) {
+  const int stride = gridDim.x * blockDim.x;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ns; i += stride) out[i] = make_int2(rank[seg[i].x], rank[seg[i].y]);
+}
+
 __global__ void k_seg_mark(Bld b, const int2 *seg, const int *list, int nl, uint32_t round, int *sstart) {
   const int stride = gridDim.x * blockDim.x;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += stride) {
@@ -609,11 +918,16 @@ __global__ void k_seg_mark(Bld b, const int2 *seg, const int *list, int nl, uint
   }
 }
 
+constexpr int kSegGrp = 8;
+
 // Constrained Delaunay triangulation of the pseudo-polygon with base p->q
 // and chain c[0..m) (from the p side to the q side, left of p->q); out[i] is
 // the outer triangle / segment id across the polygon edge E[i+1]->E[i] of
 // E = (p, c_0, .., c_{m-1}, q).  New triangles take the slots slot[*next..].
-// Returns the slot of the triangle on the base.
+// Returns the slot of the triangle on the base.  Run by kSegGrp lanes: all of
+// them keep the same state and store the same values; the scan for the apex is
+// shared out, each step taking the first of kSegGrp vertices that is inside
+// the circle of the best one so far, as a scan of one by one would.
 __device__ int tri_poly(const Bld &b, int p, int q, const int *c, int m, const int *out, const int *outcn,
                         const int *slot, int &next, int *stk) {
   auto E = [&](int i) { return i == 0 ? p : (i == m + 1 ? q : c[i - 1]); };
@@ -628,6 +942,7 @@ __device__ int tri_poly(const Bld &b, int p, int q, const int *c, int m, const i
       else set_err(b.c, kEInternal + 10);
     }
   };
+  const int gl = __lane_id() & (kSegGrp - 1), g0 = __lane_id() - gl;
   int sp = 0, root = -1;
   stk[0] = 0; stk[1] = m; stk[2] = -1; stk[3] = 0;
   sp = 1;
@@ -635,10 +950,20 @@ __device__ int tri_poly(const Bld &b, int p, int q, const int *c, int m, const i
     sp--;
     const int lo = stk[4 * sp], hi = stk[4 * sp + 1], ps = stk[4 * sp + 2], pe = stk[4 * sp + 3];
     const int u = E(lo), w = E(hi + 1);
-    int best = lo;
-    for (int k = lo + 1; k < hi; k++)
-      if (incircle_sos(b.P, u, w, c[best], c[k]) > 0) best = k;
-    const int cb = c[best];
+    int best = lo, cb = c[lo];
+    for (int k = lo + 1; k < hi;) {
+      const int x = k + gl, cx = x < hi ? c[x] : -1;
+      const int in = x < hi && incircle_sos(b, u, w, cb, cx) > 0;
+      const unsigned hit = (unsigned)(__ballot(in) >> g0) & ((1u << kSegGrp) - 1);
+      if (!hit) {
+        k += kSegGrp;
+        continue;
+      }
+      const int f = __ffs(hit) - 1;
+      best = k + f;
+      cb = __shfl(cx, g0 + f);
+      k = best + 1;
+    }
     const int s = slot[next++];
     b.tv[s] = make_int4(u, w, cb, 0);
     b.tn[s] = make_int4(ps, -1, -1, 0);
@@ -656,11 +981,18 @@ __device__ int tri_poly(const Bld &b, int p, int q, const int *c, int m, const i
   return root;
 }
 
-__global__ void k_seg_insert(Bld b, const int2 *seg, const int *list, int nl, uint32_t round, const int *sstart,
-                             int *list_out) {
-  const int stride = gridDim.x * blockDim.x;
-  for (int base = blockIdx.x * blockDim.x; base < nl; base += stride) {
-    const int i = base + threadIdx.x;
+// The segments that keep every stamp of their walk are inserted, kSegGrp lanes
+// to a segment.  Bound by the dependent loads of the longest segment (about
+// one microsecond for each triangle it crosses and walk).  One thread per
+// segment, which compared every chain edge with every crossed triangle for the
+// slits and scanned for each apex alone, took 1.83 ms a round of a million
+// points against 0.51 here.
+__global__ __launch_bounds__(kBlk) void k_seg_insert(Bld b, const int2 *seg, const int *list, int nl, uint32_t round,
+                                                     const int *sstart, int *list_out) {
+  const int per = kBlk / kSegGrp, stride = gridDim.x * per;
+  const int gl = __lane_id() & (kSegGrp - 1), g0 = __lane_id() - gl;
+  for (int base = blockIdx.x * per; base < nl; base += stride) {
+    const int i = base + (int)threadIdx.x / kSegGrp;
     bool act = i < nl;
     int s = -1, kc = -2, m = 0, n = 0, t0 = -1;
     int2 ab = make_int2(0, 0);
@@ -678,9 +1010,9 @@ __global__ void k_seg_insert(Bld b, const int2 *seg, const int *list, int nl, ui
     }
     const bool win = act && kc > 0;
     const int need = win ? kc + 3 * (m + 1) + 3 * (n + 1) + 4 * (kc + 2) + (m + n + 2) : 0;
-    const int po = wave_take(&b.c->pool, need);
-    const int lo = wave_take(&b.c->npend, act && !win ? 1 : 0);
-    if (act && !win) list_out[lo] = s;
+    const int po = __shfl(wave_take(&b.c->pool, gl == 0 ? need : 0), g0);
+    const int lo = wave_take(&b.c->npend, gl == 0 && act && !win ? 1 : 0);
+    if (gl == 0 && act && !win) list_out[lo] = s;
     if (!win) continue;
     if (po + need > b.pool_cap) { set_err(b.c, kEInternal + 11); continue; }
     int *q = b.pool + po;
@@ -693,36 +1025,41 @@ __global__ void k_seg_insert(Bld b, const int2 *seg, const int *list, int nl, ui
     w.ro = q; q += n + 1;
     w.rcn = q; q += n + 1;
     int *stk = q; q += 4 * (kc + 2);
-    int *rev = q;  // right chain reversed, then its outs reversed
+    int *rev = q;  // right chain reversed
     int m2, n2;
     if (seg_walk(b, ab.x, ab.y, t0, key, 2, w, m2, n2) != kc || m2 != m || n2 != n) { set_err(b.c, kEInternal + 12); continue; }
     // Where the crossed region wraps around a vertex, an edge of a chain has
     // crossed triangles on both sides (a slit): it stays an edge of the new
     // triangulation, linked between the two new triangles that carry it.
-    int nslit = 0;
-    for (int k = 0; k <= m + n + 1; k++) {
+    for (int x = gl; x < kc; x += kSegGrp) b.pick[w.crossed[x]] = key;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    bool slit = false;
+    for (int k = gl; k <= m + n + 1; k += kSegGrp) {
       int *op = k <= m ? &w.lo[k] : &w.ro[k - m - 1];
-      if (*op < 0) continue;
-      for (int x = 0; x < kc; x++)
-        if (w.crossed[x] == *op) { *op = -2; nslit++; break; }
+      if (*op >= 0 && b.pick[*op] == key) {
+        *op = -2;
+        slit = true;
+      }
     }
-    atomicAdd(&b.c->nwin, 1);
-    int next = 0;
-    const int rl = tri_poly(b, ab.x, ab.y, w.lc, m, w.lo, w.lcn, w.crossed, next, stk);
+    slit = ((__ballot(slit) >> g0) & ((1u << kSegGrp) - 1)) != 0;
     // right side: base b->a, chain R_n..R_1, out[i] = edge R_{n-i} -> R_{n+1-i}
-    for (int k = 0; k < n; k++) rev[k] = w.rc[n - 1 - k];
-    for (int k = 0; k <= n / 2; k++) {
+    for (int k = gl; k < n; k += kSegGrp) rev[k] = w.rc[n - 1 - k];
+    for (int k = gl; k <= n / 2; k += kSegGrp) {
       const int x = n - k;
       int t1 = w.ro[k]; w.ro[k] = w.ro[x]; w.ro[x] = t1;
       int t2 = w.rcn[k]; w.rcn[k] = w.rcn[x]; w.rcn[x] = t2;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (gl == 0) atomicAdd(&b.c->nwin, 1);
+    int next = 0;
+    const int rl = tri_poly(b, ab.x, ab.y, w.lc, m, w.lo, w.lcn, w.crossed, next, stk);
     const int rr = tri_poly(b, ab.y, ab.x, rev, n, w.ro, w.rcn, w.crossed, next, stk);
     if (next != kc) { set_err(b.c, kEInternal + 13); continue; }
     *comp_ptr(b.tn, rl, 0) = rr;
     *comp_ptr(b.tn, rr, 0) = rl;
     *comp_ptr(b.ts, rl, 0) = s;
     *comp_ptr(b.ts, rr, 0) = s;
-    for (int x = 0; x < kc && nslit > 0; x++) {
+    for (int x = 0; x < kc && slit; x++) {
       const int t = w.crossed[x];
       const int4 tv = b.tv[t];
       for (int e = 0; e < 3; e++) {
@@ -749,7 +1086,7 @@ __device__ __forceinline__ bool is_out(const Bld &b, int t) {
   return v.x >= b.nv || v.y >= b.nv || v.z >= b.nv;
 }
 
-__global__ void k_keep(Bld b, int nt, int *used, uint64_t *keys, int *vals) {
+__global__ __launch_bounds__(kBlk) void k_keep(Bld b, int nt, int *used, uint64_t *keys, int *vals) {
   const int stride = gridDim.x * blockDim.x;
   for (int base = blockIdx.x * blockDim.x; base < nt; base += stride) {
     const int t = base + threadIdx.x;
@@ -777,12 +1114,12 @@ __global__ void k_keep(Bld b, int nt, int *used, uint64_t *keys, int *vals) {
         const int y = comp(b.tv[cur], (ce + 1) % 3);
         if (orient_ids(b.P, u, x, y) < 0) set_err(b.c, kEDisk);
       }
-      const int r = (v.y < v.x && v.y < v.z) ? 1 : ((v.z < v.x && v.z < v.y) ? 2 : 0);
-      key = ((uint64_t)(uint32_t)comp(v, r) << 32) | (uint32_t)comp(v, (r + 1) % 3);
+      const int4 w = make_int4(b.id[v.x], b.id[v.y], b.id[v.z], 0);
+      const int r = (w.y < w.x && w.y < w.z) ? 1 : ((w.z < w.x && w.z < w.y) ? 2 : 0);
+      key = ((uint64_t)(uint32_t)comp(w, r) << 32) | (uint32_t)comp(w, (r + 1) % 3);
     }
-    const int slot = wave_take(&b.c->nkeep, keep ? 1 : 0);
-    const int hsum = wave_take(&b.c->nhull, hull);
-    (void)hsum;
+    const int slot = block_take(&b.c->nkeep, keep ? 1 : 0);
+    if (hull) atomicAdd(&b.c->nhull, hull);
     if (keep) { keys[slot] = key; vals[slot] = t; }
   }
 }
@@ -802,7 +1139,8 @@ __global__ void k_emit(Bld b, int nk, const int *vals, const int *newid, int4 *o
   const int stride = gridDim.x * blockDim.x;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nk; k += stride) {
     const int t = vals[k];
-    const int4 v = b.tv[t], n = b.tn[t], sg = b.ts[t];
+    const int4 vr = b.tv[t], n = b.tn[t], sg = b.ts[t];
+    const int4 v = make_int4(b.id[vr.x], b.id[vr.y], b.id[vr.z], 0);
     const int r = (v.y < v.x && v.y < v.z) ? 1 : ((v.z < v.x && v.z < v.y) ? 2 : 0);
     int vv[3], nn[3], ss[3];
     for (int i = 0; i < 3; i++) {
@@ -850,32 +1188,52 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const uint64_t *keys
   hist[threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of hist[0..m) in place by one workgroup of kSortScanThreads:
-// each thread sums a contiguous chunk, the chunk sums are scanned in LDS, then
-// each thread rewrites its chunk.
+// Exclusive scan of hist[0..m) in place by one workgroup: kScanPer entries per
+// thread and step, read and written as vectors (m is a multiple of 256).
 constexpr int kSortScanThreads = 1024;
 __global__ __launch_bounds__(kSortScanThreads) void k_sort_scan(int *hist, int m) {
-  __shared__ int part[kSortScanThreads];
-  const int chunk = (m + kSortScanThreads - 1) / kSortScanThreads;
-  const int lo = threadIdx.x * chunk, hi = min(m, lo + chunk);
-  int s = 0;
-  for (int i = lo; i < hi; i++) s += hist[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < kSortScanThreads; i++) {
-      const int x = part[i];
-      part[i] = run;
-      run += x;
+  __shared__ int part[kSortScanThreads / 64];
+  __shared__ int s_carry;
+  const int lane = __lane_id(), wid = threadIdx.x >> 6;
+  int carry = 0;
+  for (int base = 0; base < m; base += kSortScanThreads * 16) {
+    const int i0 = base + (int)threadIdx.x * 16;
+    int4 v[4];
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      v[k] = i0 + 4 * k < m ? *reinterpret_cast<const int4 *>(hist + i0 + 4 * k) : make_int4(0, 0, 0, 0);
+      sum += v[k].x + v[k].y + v[k].z + v[k].w;
     }
-  }
-  __syncthreads();
-  int run = part[threadIdx.x];
-  for (int i = lo; i < hi; i++) {
-    const int x = hist[i];
-    hist[i] = run;
-    run += x;
+    int x = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(x, d);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) part[wid] = x;
+    __syncthreads();
+    if (threadIdx.x < kSortScanThreads / 64) {
+      int y = part[threadIdx.x];
+      for (int d = 1; d < kSortScanThreads / 64; d <<= 1) {
+        const int z = __shfl_up(y, d);
+        if ((int)threadIdx.x >= d) y += z;
+      }
+      part[threadIdx.x] = y;
+      if (threadIdx.x == kSortScanThreads / 64 - 1) s_carry = y;
+    }
+    __syncthreads();
+    int run = carry + x - sum + (wid ? part[wid - 1] : 0);
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      int4 o;
+      o.x = run; run += v[k].x;
+      o.y = run; run += v[k].y;
+      o.z = run; run += v[k].z;
+      o.w = run; run += v[k].w;
+      if (i0 + 4 * k < m) *reinterpret_cast<int4 *>(hist + i0 + 4 * k) = o;
+    }
+    carry += s_carry;
+    __syncthreads();
   }
 }
 
@@ -921,15 +1279,15 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const uint64_t *k
   }
 }
 
-// Sorts n pairs by key bits [0, 32 + vbits) and [32, 32 + vbits) (a key is
-// (a << 32) | b with a, b < 2^vbits); the result ends in (k1, v1).  hist
-// holds 256 * ceil(n / kSortTile) ints.
+// Sorts n pairs by the low vbits of each 32-bit half of the key (halves: 1:
+// the low half only, else a key is (a << 32) | b with a, b < 2^vbits); the
+// result ends in (k1, v1).  hist holds 256 * ceil(n / kSortTile) ints.
 hipError_t radix_sort_pairs(hipStream_t stream, uint64_t *k0, int *v0, uint64_t *k1, int *v1, int n, int vbits,
-                            int *hist) {
+                            int *hist, int halves = 2) {
   if (n <= 0) return hipSuccess;
   const int ntiles = (n + kSortTile - 1) / kSortTile;
   int shifts[16], ns = 0;
-  for (int half = 0; half < 2; half++)
+  for (int half = 0; half < halves; half++)
     for (int b = 0; b < vbits; b += 8) shifts[ns++] = 32 * half + b;
   uint64_t *kin = k0, *kout = k1;
   int *vin = v0, *vout = v1;
@@ -981,31 +1339,27 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
                   int4 *otn, int4 *ots, int32_t cap_out, int32_t *n_tri, DevCdtStats *stats, std::string &err,
                   DevCdtWork *ws) {
   if (nv < 3) { err = "bad arguments"; return GDP_E_ARG; }
-  // enclosing triangle, as the host builder places it
-  std::vector<double2> hxy(nv);
-  if (hipMemcpyAsync(hxy.data(), d_xy, sizeof(double2) * nv, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess) { err = "copy failed"; return GDP_E_DEVICE; }
-  double mx = 1.0;
-  for (int i = 0; i < nv; i++) mx = std::max(mx, std::max(std::fabs(hxy[i].x), std::fabs(hxy[i].y)));
-  const double Lb = std::exp2(std::ceil(std::log2(mx)) + 1.0);
-  const double2 enc[3] = {make_double2(-4 * Lb, -4 * Lb), make_double2(8 * Lb, -4 * Lb), make_double2(-4 * Lb, 8 * Lb)};
   const int capT = 2 * nv + 8;
-  const int pool_cap = std::max(16 * capT + 4096, 8 * (kBigCap + 8));
+  const int pool_cap = 16 * capT + 4096;
   void *mem = nullptr;
-  // layout
+  // layout; some arrays lie where another stage's will be: the points' walks
+  // under the segments' starts, the split stamps under the new ids, the ranks
+  // under the used marks, the renumbered segments in the sort keys (when they
+  // fit: a planar set has fewer than 3 nv segments)
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
   const size_t o_tv = take(sizeof(int4) * capT), o_tn = take(sizeof(int4) * capT), o_ts = take(sizeof(int4) * capT);
-  const size_t o_pick = take(8 * (size_t)capT), o_mark = take(8 * (size_t)capT), o_ring = take(8 * (size_t)capT);
-  const size_t o_hint = take(4 * (size_t)nv), o_state = take(4 * (size_t)std::max(nv, ns));
-  const int big_all = std::max(kBigSlots * kBigCap, capT);
-  const size_t o_vt = take(4 * (size_t)(nv + 3)), o_big = take(4 * (size_t)big_all);
+  const size_t o_pick = take(8 * (size_t)capT), o_mark = take(8 * (size_t)capT);
+  const size_t o_state = take(4 * (size_t)std::max(nv, ns));
+  const size_t o_vt = take(4 * (size_t)(nv + 3)), o_wstamp = take(4 * (size_t)capT);
   const size_t o_pool = take(4 * (size_t)pool_cap);
+  const size_t o_P = take(sizeof(double2) * (size_t)(nv + 3)), o_id = take(4 * (size_t)(nv + 3));
   const size_t o_p0 = take(4 * (size_t)std::max(nv, ns)), o_p1 = take(4 * (size_t)std::max(nv, ns));
-  const size_t o_ctr = take(sizeof(Ctr)), o_ntri = take(4), o_used = take(4 * (size_t)nv);
+  const size_t o_ctr = take(sizeof(Ctr)), o_box = take(4 * 8), o_used = take(4 * (size_t)nv);
   const size_t o_keys = take(8 * (size_t)capT), o_keys2 = take(8 * (size_t)capT);
   const size_t o_vals = take(4 * (size_t)capT), o_vals2 = take(4 * (size_t)capT), o_newid = take(4 * (size_t)capT);
   const size_t o_sort = take(4 * 256 * (size_t)((capT + kSortTile - 1) / kSortTile));
+  const size_t o_seg = ns <= 2 * (int64_t)capT ? o_keys : take(sizeof(int2) * (size_t)ns);
   Ctr *hctr = nullptr;
   if (ws) {
     // every earlier build on the workspace has finished (each one ends with
@@ -1033,76 +1387,137 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
     }
     return rc;
   };
+  double2 *P = (double2 *)(base + o_P);
+  int *id = (int *)(base + o_id), *rank = (int *)(base + o_used);
   Bld b;
-  b.P = d_xy;
+  b.P = P;
+  b.id = id;
   b.nv = nv;
   b.tv = (int4 *)(base + o_tv); b.tn = (int4 *)(base + o_tn); b.ts = (int4 *)(base + o_ts);
   b.capT = capT;
-  b.ntri = (int *)(base + o_ntri);
-  b.pick = (uint64_t *)(base + o_pick); b.mark = (uint64_t *)(base + o_mark); b.ring = (uint64_t *)(base + o_ring);
-  b.hint = (int *)(base + o_hint); b.state = (int *)(base + o_state);
-  b.vt = (int *)(base + o_vt); b.big = (int *)(base + o_big);
-  b.big_all = big_all;
+  b.pick = (uint64_t *)(base + o_pick); b.mark = (uint64_t *)(base + o_mark);
+  b.loc = b.state = (int *)(base + o_state);
+  b.vt = (int *)(base + o_vt);
   b.pool = (int *)(base + o_pool); b.pool_cap = pool_cap;
   b.c = (Ctr *)(base + o_ctr);
+  // the lists of the flip passes lie in the pool of the segment recovery and
+  // in the sort buffers of the last stage, which come after them
+  b.sstamp = (int *)(base + o_newid); b.wstamp = (int *)(base + o_wstamp);
+  b.fc0 = (int4 *)(base + o_pool);
+  b.fc1 = b.fc0 + 2 * (size_t)capT;
+  b.grp = b.fc0;
+  b.fprio = (uint64_t *)(base + o_keys);
+  b.list[0] = (int *)(base + o_vals);
+  b.list[1] = (int *)(base + o_vals2);
+  unsigned long long *box = (unsigned long long *)(base + o_box);
   int *pl[2] = {(int *)(base + o_p0), (int *)(base + o_p1)};
-  if (hipMemcpyAsync(d_xy + nv, enc, sizeof(enc), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipMemsetAsync(b.pick, 0, 8 * (size_t)capT, stream) != hipSuccess ||
+  auto dev_err = [&](const char *what) { err = what; return done(GDP_E_DEVICE); };
+  if (hipMemsetAsync(b.pick, 0, 8 * (size_t)capT, stream) != hipSuccess ||
       hipMemsetAsync(b.mark, 0, 8 * (size_t)capT, stream) != hipSuccess ||
-      hipMemsetAsync(b.ring, 0, 8 * (size_t)capT, stream) != hipSuccess ||
+      hipMemsetAsync(b.sstamp, 0, 4 * (size_t)capT, stream) != hipSuccess ||
+      hipMemsetAsync(b.wstamp, 0, 4 * (size_t)capT, stream) != hipSuccess ||
+      hipMemsetAsync(box, 0, 4 * 8, stream) != hipSuccess ||
       hipMemsetAsync(b.c, 0, sizeof(Ctr), stream) != hipSuccess)
-    { err = "device call failed"; return done(GDP_E_DEVICE); }
-  k_init<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(b, pl[0]);
+    return dev_err("device call failed");
   auto round_trip = [&]() -> bool {
     if (hipMemcpyAsync(hctr, b.c, sizeof(Ctr), hipMemcpyDeviceToHost, stream) != hipSuccess) return false;
     return hipStreamSynchronize(stream) == hipSuccess;
   };
-  uint32_t round = 0;
-  // np: points still to insert; nl: entries of the pending list (inserted
-  // points stay in it as -1 until more than an eighth of it is stale)
-  int np = nv, nl = nv, cur = 0, solo = 0, dt_rounds = 0, seg_rounds = 0;
-  int64_t t_reloc = 1;  // triangles at the last refresh of every start triangle
+  // the points along a Morton curve of their box, and the enclosing triangle
+  // (placed as the host builder places it)
+  k_box<<<std::min(grid_for(nv, kBlk), 256), kBlk, 0, stream>>>(d_xy, nv, box);
+  unsigned long long hbox[4];
+  if (hipMemcpyAsync(hbox, box, sizeof hbox, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+      hipStreamSynchronize(stream) != hipSuccess)
+    return dev_err("copy failed");
+  const double x1 = ord_to(hbox[0]), y1 = ord_to(hbox[1]), x0 = -ord_to(hbox[2]), y0 = -ord_to(hbox[3]);
+  const double mx = std::max({1.0, std::fabs(x0), std::fabs(x1), std::fabs(y0), std::fabs(y1)});
+  const double Lb = std::exp2(std::ceil(std::log2(mx)) + 1.0);
+  const double side = std::max({x1 - x0, y1 - y0, 0x1p-100});
+  uint64_t *keys = (uint64_t *)(base + o_keys), *keys2 = (uint64_t *)(base + o_keys2);
+  int *vals = (int *)(base + o_vals), *vals2 = (int *)(base + o_vals2), *newid = (int *)(base + o_newid);
+  k_morton<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(d_xy, nv, x0, y0, 65536.0 / side, 65536.0 / side, keys, vals);
+  if (radix_sort_pairs(stream, keys, vals, keys2, vals2, nv, 32, (int *)(base + o_sort), 1) != hipSuccess)
+    return dev_err("sort failed");
+  k_reorder<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(b, d_xy, P, vals2, id, rank, Lb);
+  // the sample in one workgroup, then every other point round by round
+  const int step = (nv + kSeedMax - 1) / kSeedMax, n_seed = (nv + step - 1) / step;
+  k_dt_seed<<<1, kSeedBlk, 0, stream>>>(b, n_seed, step, pl[0], pl[1]);
+  if (n_seed < nv) {
+    k_vt<<<grid_for(2 * n_seed + 1, kBlk), kBlk, 0, stream>>>(b, 2 * n_seed + 1);
+    k_dt_start<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(b, n_seed, step, pl[0]);
+  }
+  if (!round_trip()) return dev_err("device call failed");
+  int dt_rounds = hctr->nwin, seg_rounds = 0;
+  auto points_failed = [&]() {
+    err = std::string("points (round " + std::to_string(dt_rounds) + "): ") + cdt_err_string(hctr->err);
+    return done(hctr->err >= kEInternal ? GDP_E_DEVICE : GDP_E_INPUT);
+  };
+  if (hctr->err) return points_failed();
+  int np = nv - n_seed, cur = 0, stamp = hctr->first_stamp;
+  uint64_t pass = (uint64_t)hctr->first_pass;
+  uint32_t round = (uint32_t)dt_rounds;
   while (np > 0) {
     round++;
     dt_rounds++;
-    const int compact = (nl - np) * 8 >= nl;
-    const int64_t ntri = 1 + 2 * (int64_t)(nv - np);
-    const double frac = solo ? 1.0 : 4.0 * (double)ntri / (double)np;
-    const uint32_t thresh = frac >= 1.0 ? 0xffffffffu : (uint32_t)(frac * 4294967296.0);
-    int relocate = 0;
-    if (thresh != 0xffffffffu && ntri >= 2 * t_reloc) { relocate = 1; t_reloc = ntri; }
-    if (hipMemsetAsync(b.c, 0, 4 * sizeof(int), stream) != hipSuccess ||
-        hipMemsetAsync(&b.c->first, 0x7f, sizeof(int), stream) != hipSuccess) { err = "device call failed"; return done(GDP_E_DEVICE); }
-    k_locate<<<grid_for(nl, kBlk), kBlk, 0, stream>>>(b, pl[cur], nl, round, solo, thresh, relocate);
-    k_mark<<<grid_for(nl, kCavBlk), kCavBlk, 0, stream>>>(b, pl[cur], nl, round, solo, thresh);
-    k_insert<<<grid_for(nl, kCavBlk), kCavBlk, 0, stream>>>(b, pl[cur], nl, round, pl[cur ^ 1], compact, solo);
-    if (!round_trip()) { err = "device call failed"; return done(GDP_E_DEVICE); }
-    if (hctr->err) { err = std::string("points (round " + std::to_string(dt_rounds) + "): ") + cdt_err_string(hctr->err); return done(hctr->err == kECavity ? GDP_E_CAVITY : (hctr->err >= kEInternal ? GDP_E_DEVICE : GDP_E_INPUT)); }
-    if (compact && hctr->npend != np - hctr->nwin) { err = "device CDT builder: lost points"; return done(GDP_E_DEVICE); }
-    if (solo && hctr->nwin == 0) { err = "device CDT builder: no insertion progress"; return done(GDP_E_DEVICE); }
-    solo = hctr->nwin == 0;
-    np -= hctr->nwin;
-    if (compact) {
-      nl = np;
-      cur ^= 1;
+    if (hipMemsetAsync(&b.c->npend, 0, 2 * sizeof(int), stream) != hipSuccess ||  // npend, nwin
+        hipMemsetAsync(&b.c->nlist[0], 0, 4 * sizeof(int), stream) != hipSuccess)
+      return dev_err("device call failed");
+    stamp++;
+    k_dt_locate<<<grid_for(np, kBlk), kBlk, 0, stream>>>(b, pl[cur], np, round);
+    k_dt_split<<<grid_for(np, kBlk), kBlk, 0, stream>>>(b, pl[cur], np, round, stamp, pl[cur ^ 1]);
+    // at most one point per triangle, three new triangles each (four for the
+    // rare one on an edge)
+    int64_t est = 4 * std::min<int64_t>(np, hctr->ntri);
+    k_dt_fix<<<grid_for((int)std::min<int64_t>(est, 1 << 30), kBlk), kBlk, 0, stream>>>(b, round);
+    for (int batch = 0;; batch++) {
+      if (pass > kPassMax) return dev_err("device CDT builder: flip passes did not converge");
+      for (int q = 0; q < kPassBatch; q++) {
+        pass++;
+        const unsigned g = grid_for((int)std::min<int64_t>(est, 1 << 30), kBlk);
+        k_dt_check<<<g, kBlk, 0, stream>>>(b, q & 1, stamp, pass);
+        stamp++;
+        k_dt_apply<<<g, kBlk, 0, stream>>>(b, q & 1, stamp, pass);
+      }
+      k_dt_tail<<<1, kSeedBlk, 0, stream>>>(b, 0, stamp, pass);
+      if (!round_trip()) return dev_err("device call failed");
+      if (hctr->err) return points_failed();
+      // (the tail sets nwin to the stamp of what it leaves, if it ran)
+      if (hctr->nlist[0] == 0) {
+        stamp += kTailGap;
+        pass += kTailGap;
+        break;
+      }
+      if (hctr->nwin > stamp) {
+        stamp = hctr->nwin;
+        pass += kTailGap;
+      }
+      est = hctr->nlist[0];
+      if (stamp > (1 << 30)) return dev_err("device CDT builder: flip passes did not converge");
     }
+    if (hctr->npend >= np) { err = "device CDT builder: no insertion progress"; return done(GDP_E_DEVICE); }
+    np = hctr->npend;
+    cur ^= 1;
   }
-  int nt = 0;
-  if (hipMemcpyAsync(&nt, b.ntri, 4, hipMemcpyDeviceToHost, stream) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess)
-    { err = "device call failed"; return done(GDP_E_DEVICE); }
+  const int nt = hctr->ntri;
   if (nt != 2 * nv + 1) { err = "device CDT builder: triangle count"; return done(GDP_E_DEVICE); }
-  // segments
+  // segments, between the points' places along the curve
+  int2 *sseg = (int2 *)(base + o_seg);
   k_vt<<<grid_for(nt, kBlk), kBlk, 0, stream>>>(b, nt);
+  if (hipMemsetAsync(b.ts, 0xff, sizeof(int4) * (size_t)nt, stream) != hipSuccess ||
+      hipMemsetAsync(b.mark, 0, 8 * (size_t)nt, stream) != hipSuccess)
+    return dev_err("device call failed");
+  if (ns > 0) k_seg_rank<<<grid_for(ns, kBlk), kBlk, 0, stream>>>(d_seg, ns, rank, sseg);
   int *sstart = b.state;
-  nl = ns;
+  int nl = ns;
   cur = 0;
   if (ns > 0) k_iota<<<grid_for(ns, kBlk), kBlk, 0, stream>>>(ns, pl[0]);
   while (nl > 0) {
     round++;
     seg_rounds++;
-    if (hipMemsetAsync(b.c, 0, 4 * sizeof(int), stream) != hipSuccess) { err = "device call failed"; return done(GDP_E_DEVICE); }
-    k_seg_mark<<<grid_for(nl, kBlk), kBlk, 0, stream>>>(b, d_seg, pl[cur], nl, round, sstart);
-    k_seg_insert<<<grid_for(nl, kBlk), kBlk, 0, stream>>>(b, d_seg, pl[cur], nl, round, sstart, pl[cur ^ 1]);
+    if (hipMemsetAsync(b.c, 0, 3 * sizeof(int), stream) != hipSuccess) { err = "device call failed"; return done(GDP_E_DEVICE); }
+    k_seg_mark<<<grid_for(nl, kBlk), kBlk, 0, stream>>>(b, sseg, pl[cur], nl, round, sstart);
+    k_seg_insert<<<grid_for((int)std::min<int64_t>((int64_t)nl * kSegGrp, 1 << 30), kBlk), kBlk, 0, stream>>>(b, sseg, pl[cur], nl, round, sstart, pl[cur ^ 1]);
     if (!round_trip()) { err = "device call failed"; return done(GDP_E_DEVICE); }
     if (hctr->err) { err = std::string("segments (round " + std::to_string(seg_rounds) + "): ") + cdt_err_string(hctr->err); return done(hctr->err >= kEInternal ? GDP_E_DEVICE : GDP_E_INPUT); }
     if (hctr->npend > 0 && hctr->nwin == 0 && hctr->npend == nl) { err = "device CDT builder: no segment progress"; return done(GDP_E_DEVICE); }
@@ -1111,8 +1526,6 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   }
   // outside removal and canonical order
   int *used = (int *)(base + o_used);
-  uint64_t *keys = (uint64_t *)(base + o_keys), *keys2 = (uint64_t *)(base + o_keys2);
-  int *vals = (int *)(base + o_vals), *vals2 = (int *)(base + o_vals2), *newid = (int *)(base + o_newid);
   if (hipMemsetAsync(used, 0, 4 * (size_t)nv, stream) != hipSuccess || hipMemsetAsync(b.c, 0, sizeof(Ctr), stream) != hipSuccess)
     { err = "device call failed"; return done(GDP_E_DEVICE); }
   k_keep<<<grid_for(nt, kBlk), kBlk, 0, stream>>>(b, nt, used, keys, vals);
