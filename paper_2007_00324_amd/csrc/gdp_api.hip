@@ -2713,6 +2713,18 @@ gdp_status ff_next_pass(gdp_mesh *M, uint64_t &out) {
   return GDP_OK;
 }
 
+// Room for the stamps and passes of a flip tail after the newest ones.
+gdp_status ff_tail_room(gdp_mesh *M) {
+  gdp_ctx *ctx = M->ctx;
+  FfBufs &F = *M->ff;
+  if (F.pass + kFfTailPasses >= (1ull << 23)) {
+    HIPCHECK(hipMemsetAsync(F.claim, 0, sizeof(uint64_t) * F.capT, ctx->stream));
+    HIPCHECK(hipMemsetAsync(F.vmark, 0, sizeof(uint64_t) * F.capV, ctx->stream));
+    F.pass = 0;
+  }
+  return GDP_OK;
+}
+
 FfView ff_view(gdp_mesh *M, const gdp_params *P, int32_t nmk) {
   FfBufs &F = *M->ff;
   const DevMesh &m = M->m;
@@ -2763,14 +2775,15 @@ gdp_status ff_read(gdp_mesh *M, FfCount &c) {
 
 // Flip passes until no edge is left to check.  The first input list is
 // F.list[cur] (length n_list[cur]), written with stamp in_stamp; est sizes
-// the grids.  A pass is two launches; the host reads the counters after
-// batches of 4, 8, then 16 passes.
-gdp_status ff_lawson(gdp_mesh *M, FfView &V, int &cur, int &in_stamp, int tst, int64_t est) {
+// the grids.  A pass is two launches; after batches of 4, 8, then 16 passes a
+// short worklist is finished in one workgroup and the host reads the counters
+// (left in c).
+gdp_status ff_lawson(gdp_mesh *M, FfView &V, int &cur, int &in_stamp, int tst, int64_t est, FfCount &c) {
   gdp_ctx *ctx = M->ctx;
   hipStream_t s = ctx->stream;
   FfBufs &F = *M->ff;
   gdp_status st;
-  int batch = 4;
+  int batch = est <= kFfTailMax ? 0 : 4;
   hipLaunchKernelGGL(kf_ctl, dim3(1), dim3(64), 0, s, F.d_c, 0, cur ^ 1);  // candidate counts start at 0
   for (int64_t done = 0; done < (1 << 15);) {
     for (int q = 0; q < batch; q++, done++) {
@@ -2788,11 +2801,22 @@ gdp_status ff_lawson(gdp_mesh *M, FfView &V, int &cur, int &in_stamp, int tst, i
       in_stamp = wst;
       cur ^= 1;
     }
-    FfCount c;
+    // (in_stamp is the newest stamp but for a round's touched stamp: the tail's
+    // follow the newest)
+    if ((st = ff_tail_room(M))) return st;
+    const int w0 = F.stamp;
+    const uint64_t p0 = F.pass;
+    hipLaunchKernelGGL(kf_flip_tail, dim3(1), dim3(kFfTailBlk), 0, s, V, F.list[cur], F.list[cur ^ 1], cur, in_stamp,
+                       w0, p0, tst);
     if ((st = ff_read(M, c))) return st;
+    F.stamp += c.tail_passes;
+    F.pass += (uint64_t)c.tail_passes;
+    done += c.tail_passes;
+    if (c.tail_passes > 0) in_stamp = F.stamp;
+    cur ^= c.tail_passes & 1;
     if (c.n_list[cur] == 0) return GDP_OK;
     est = c.n_list[cur];
-    batch = std::min(batch * 2, 16);
+    batch = est <= kFfTailMax ? 0 : std::min(std::max(batch * 2, 4), 16);
   }
   return fail(ctx, GDP_E_CAVITY, "flip passes did not converge");
 }
@@ -2824,7 +2848,8 @@ gdp_status ff_canonical(gdp_mesh *M, const gdp_params *P) {
   ff_target(M, V, 0);
   hipLaunchKernelGGL(kf_all_slots, dim3(ff_grid(nT)), dim3(256), 0, s, V, nT, wst);
   int cur = 0, in_stamp = wst;
-  if ((st = ff_lawson(M, V, cur, in_stamp, tst, nT))) return st;
+  FfCount c;
+  if ((st = ff_lawson(M, V, cur, in_stamp, tst, nT, c))) return st;
   return ff_reset(M);
 }
 
@@ -2854,31 +2879,37 @@ gdp_status ff_line8(gdp_mesh *M, const gdp_params *P, int32_t np, int32_t nmid, 
   hipLaunchKernelGGL(kf_split, dim3(ff_grid(np)), dim3(256), 0, s, V, split_stamp, wst, tst);
   hipLaunchKernelGGL(kf_split_fix, dim3(ff_grid(np)), dim3(256), 0, s, V, split_stamp);
   int cur = 0, in_stamp = wst;
-  if ((st = ff_lawson(M, V, cur, in_stamp, tst, 3 * (int64_t)np))) return st;
   FfCount c;
+  if ((st = ff_lawson(M, V, cur, in_stamp, tst, 3 * (int64_t)np, c))) return st;
   for (int it = 0;; it++) {
     if (it > (1 << 16)) return fail(ctx, GDP_E_CAVITY, "redundant points keep appearing");
-    if ((st = ff_read(M, c))) return st;
     hipLaunchKernelGGL(kf_ctl, dim3(1), dim3(64), 0, s, F.d_c, 2, 0);
     hipLaunchKernelGGL(kf_vtri, dim3(ff_grid(c.n_touched)), dim3(256), 0, s, V);
     hipLaunchKernelGGL(kf_detect, dim3(ff_grid(np)), dim3(256), 0, s, V);
     if ((st = ff_read(M, c))) return st;
     if (c.n_red == 0) break;
-    // removal passes; their triangles form the next flip worklist
+    // removal passes; their triangles form the next flip worklist.  The points
+    // left are in F.hole and F.mover by turns (the compaction's lists), and
+    // the host reads how many after batches of 4 passes.
     if ((st = ff_next_stamp(M, wst))) return st;
     ff_target(M, V, cur);
     hipLaunchKernelGGL(kf_ctl, dim3(1), dim3(64), 0, s, F.d_c, 0, cur);
-    for (int pass_i = 0;; pass_i++) {
+    int32_t *left[2] = {F.hole, F.mover}, *n_left[2] = {&F.d_c->n_red, &F.d_c->n_hole};
+    for (int pass_i = 0, left_n = c.n_red;;) {
       if (pass_i > (1 << 16)) return fail(ctx, GDP_E_CAVITY, "removal passes did not finish");
-      uint64_t pass;
-      if ((st = ff_next_pass(M, pass))) return st;
-      const uint64_t pbase = pass << 32;
-      hipLaunchKernelGGL(kf_ctl, dim3(1), dim3(64), 0, s, F.d_c, 1, 0);
-      hipLaunchKernelGGL(kf_rm_mark, dim3(ff_grid(np)), dim3(256), 0, s, V, pbase);
-      hipLaunchKernelGGL(kf_rm_decide, dim3(ff_grid(np)), dim3(256), 0, s, V, pbase);
-      hipLaunchKernelGGL(kf_rm_apply, dim3(ff_grid(np)), dim3(256), 0, s, V, wst, tst);
+      const unsigned g = ff_grid((int64_t)left_n * 16);
+      for (int q = 0; q < 4; q++, pass_i++) {
+        uint64_t pass;
+        if ((st = ff_next_pass(M, pass))) return st;
+        const int in = pass_i & 1, out = in ^ 1;
+        hipLaunchKernelGGL(kf_rm_mark, dim3(g), dim3(256), 0, s, V, (const int32_t *)left[in], (const int32_t *)n_left[in],
+                           n_left[out], pass << 32);
+        hipLaunchKernelGGL(kf_rm_apply, dim3(g), dim3(256), 0, s, V, (const int32_t *)left[in], (const int32_t *)n_left[in],
+                           left[out], n_left[out], pass << 32, wst, tst);
+      }
       if ((st = ff_read(M, c))) return st;
-      if (c.n_left == 0) break;
+      left_n = (pass_i & 1) ? c.n_hole : c.n_red;
+      if (left_n == 0) break;
       if (c.pool_short) {
         // a removal found no room in the pool: grow it (nothing is in flight)
         const int64_t nc = F.pool_cap * 2;
@@ -2889,7 +2920,7 @@ gdp_status ff_line8(gdp_mesh *M, const gdp_params *P, int32_t np, int32_t nmid, 
       }
     }
     in_stamp = wst;
-    if ((st = ff_lawson(M, V, cur, in_stamp, tst, c.n_list[cur]))) return st;
+    if ((st = ff_lawson(M, V, cur, in_stamp, tst, c.n_list[cur], c))) return st;
   }
   // final ids, renumbering, pending flags
   // ranks of the kept points: a tiled exclusive scan of alive (newid holds

@@ -48,6 +48,8 @@ struct FfCount {
   int32_t flags;          // subsegments newly flagged by encroaching circumcenters
   int32_t nwin, nwin_mid; // points of S kept, of which midpoints (after the last pass)
   int64_t flips, removals, n_dep, n_enc, iters, passes, rm_passes;
+  int32_t star_used;      // entries of the kept stars of a removal pass
+  int32_t tail_passes;    // passes the last flip tail took
 };
 
 // Everything the steps read and write.
@@ -98,6 +100,11 @@ constexpr int kFfStSkip = 64;
 // Tile of the scan that ranks the kept points (the refinement's scan tile).
 constexpr int kFfScanTile = 2048;
 constexpr int kFfWalkCap = 1 << 20;
+// Flip passes over at most kFfTailMax triangles run in one workgroup, at most
+// kFfTailPasses of them in a launch.
+constexpr int kFfTailBlk = 1024;
+constexpr int kFfTailMax = 2048;
+constexpr int kFfTailPasses = 4096;
 
 // Atomic operations of the kernels.  Additions to a shared counter are
 // combined per wave first (one atomic for the active lanes of the wave, each
@@ -127,13 +134,19 @@ struct FfDevOps {
     if (rank == 0) base = atomicAdd(p, __popcll(mask));
     return __builtin_amdgcn_readfirstlane(base) + rank;
   }
-  __device__ static void add64(int64_t *p, int64_t v) {
-    const uint64_t mask = __ballot(1);
-    const int lane = __lane_id();
-    long long total = 0;
-    for (uint64_t m = mask; m; m &= m - 1) total += __shfl((long long)v, __ffsll((unsigned long long)m) - 1);
-    if (lane == __ffsll((unsigned long long)mask) - 1 && total)
-      atomicAdd((unsigned long long *)p, (unsigned long long)total);
+  // add(p, v) for v in 0..3
+  __device__ static int add3(int32_t *p, int v) {
+    const uint64_t lanes = __ballot(1), one = __ballot(v & 1), two = __ballot(v & 2);
+    const uint64_t below = (1ull << __lane_id()) - 1;
+    const int total = __popcll(one) + 2 * __popcll(two);
+    int base = 0;
+    if ((lanes & below) == 0 && total) base = atomicAdd(p, total);
+    return __builtin_amdgcn_readfirstlane(base) + __popcll(one & below) + 2 * __popcll(two & below);
+  }
+  __device__ static void inc64(int64_t *p) {
+    const uint64_t lanes = __ballot(1);
+    if ((lanes & ((1ull << __lane_id()) - 1)) == 0)
+      atomicAdd((unsigned long long *)p, (unsigned long long)__popcll(lanes));
   }
   __device__ static int exch(int32_t *p, int v) { return atomicExch(p, v); }
   __device__ static int or32(int32_t *p, int v) { return atomicOr(p, v); }
@@ -147,7 +160,8 @@ struct FfDevOps {
 struct FfHostOps {
   static int add(int32_t *p, int v) { const int o = *p; *p += v; return o; }
   static int append(int32_t *p) { return (*p)++; }
-  static void add64(int64_t *p, int64_t v) { *p += v; }
+  static int add3(int32_t *p, int v) { return add(p, v); }
+  static void inc64(int64_t *p) { *p += 1; }
   static int exch(int32_t *p, int v) { const int o = *p; *p = v; return o; }
   static int or32(int32_t *p, int v) { const int o = *p; *p |= v; return o; }
   static void max64(uint64_t *p, uint64_t v) { if (v > *p) *p = v; }
@@ -189,10 +203,25 @@ GDP_HD void ff_push(int32_t *list, int32_t *cnt, int32_t *stamps, int stamp, int
 }
 
 // Both lists a written slot goes to: the flip worklist and the touched list.
+// (A slot that a plain load finds touched is: the stamp changes once a round.)
 template <class O>
 GDP_HD void ff_wrote(const FfView &V, int slot, int wstamp, int tstamp) {
+  const bool fresh = V.tstamp[slot] != tstamp;
   ff_push<O>(V.list_out, V.n_out, V.wstamp, wstamp, slot);
-  ff_push<O>(V.touched, &V.c->n_touched, V.tstamp, tstamp, slot);
+  if (fresh) ff_push<O>(V.touched, &V.c->n_touched, V.tstamp, tstamp, slot);
+}
+// ... and two slots with one allocation per list and the exchanges in flight
+// together: a flip's time is that of the atomics it waits for.
+template <class O>
+GDP_HD void ff_wrote2(const FfView &V, int s0, int s1, int wstamp, int tstamp) {
+  const int u0 = V.tstamp[s0], u1 = V.tstamp[s1];
+  const int e0 = O::exch(&V.wstamp[s0], wstamp), e1 = O::exch(&V.wstamp[s1], wstamp);
+  const bool p0 = e0 != wstamp, p1 = e1 != wstamp;
+  int at = O::add3(V.n_out, (p0 ? 1 : 0) + (p1 ? 1 : 0));
+  if (p0) V.list_out[at++] = s0;
+  if (p1) V.list_out[at] = s1;
+  if (u0 != tstamp) ff_push<O>(V.touched, &V.c->n_touched, V.tstamp, tstamp, s0);
+  if (u1 != tstamp) ff_push<O>(V.touched, &V.c->n_touched, V.tstamp, tstamp, s1);
 }
 
 // Every point of S starts in the mesh and not redundant.
@@ -332,36 +361,62 @@ GDP_HD void ff_split_fix_one(const FfView &V, int r, int split_stamp) {
 template <class O>
 GDP_HD void ff_flip_check_one(const FfView &V, int i, int in_stamp, uint64_t pass) {
   const int t = V.list_in[i];
-  const int4 a = V.tv[t];
-  if (a.x < 0) return;  // freed by a removal
-  const int4 na = V.tn[t];
+  const int4 a = V.tv[t], na = V.tn[t];
+  int flip = 0;  // bits: the edges to flip
+  int j[3] = {0, 0, 0};
+  if (a.x >= 0) {  // (a slot freed by a removal holds -1)
+    // the three neighbours and their far vertices, loaded together
+    int4 b[3];
+    int st[3], d[3];
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int o = ffc(na, e);
+      b[e] = V.tv[o < 0 ? t : o];
+      st[e] = V.wstamp[o < 0 ? t : o];
+    }
+    const double2 P[3] = {V.vxy[a.x], V.vxy[a.y], V.vxy[a.z]};
+    double2 D[3];
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int u = ffc(a, e), v = ffc(a, e == 2 ? 0 : e + 1);
+      j[e] = ff_eidx(b[e], v, u);
+      d[e] = j[e] < 0 ? u : ffc(b[e], j[e] == 0 ? 2 : j[e] - 1);
+      D[e] = V.vxy[d[e]];
+    }
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int o = ffc(na, e);
+      if (((a.w >> e) & 1) || o < 0) continue;
+      if (o < t && st[e] == in_stamp) continue;  // the lower slot on the list checks the edge
+      if (j[e] < 0) { O::err(&V.c->err, 4); continue; }
+      const double2 U = P[e], W = P[e == 2 ? 0 : e + 1], C = P[e == 0 ? 2 : e - 1];
+      int in = incircle_filter(U.x, U.y, W.x, W.y, C.x, C.y, D[e].x, D[e].y);
+      if (in == kUndecided)
+        in = incircle_sos(U.x, U.y, W.x, W.y, C.x, C.y, D[e].x, D[e].y, ffc(a, e), ffc(a, e == 2 ? 0 : e + 1),
+                          ffc(a, e == 0 ? 2 : e - 1), d[e]);
+      if (in > 0) flip |= 1 << e;
+    }
+  }
+  int idx = O::add3(V.n_cand, (flip & 1) + ((flip >> 1) & 1) + (flip >> 2));
+#pragma unroll
   for (int e = 0; e < 3; e++) {
-    if ((a.w >> e) & 1) continue;
+    if (!((flip >> e) & 1)) continue;
+    const int at = idx++;
+    if (at >= V.cand_cap) continue;  // no room and no claims: ff_flip_requeue_one
     const int o = ffc(na, e);
-    if (o < 0) continue;
-    if (o < t && V.wstamp[o] == in_stamp) continue;  // the lower slot on the list checks the edge
-    const int u = ffc(a, e), v = ffc(a, (e + 1) % 3), w = ffc(a, (e + 2) % 3);
-    const int4 b = V.tv[o];
-    const int j = ff_eidx(b, v, u);
-    if (j < 0) { O::err(&V.c->err, 4); continue; }
-    const int d = ffc(b, (j + 2) % 3);
-    const double2 U = V.vxy[u], W = V.vxy[v], C = V.vxy[w], D = V.vxy[d];
-    if (incircle_sos(U.x, U.y, W.x, W.y, C.x, C.y, D.x, D.y, u, v, w, d) <= 0) continue;
     const int4 nb = V.tn[o];
-    const int n_vw = ffc(na, (e + 1) % 3), n_wu = ffc(na, (e + 2) % 3);
-    const int n_ud = ffc(nb, (j + 1) % 3), n_dv = ffc(nb, (j + 2) % 3);
-    const uint64_t prio = (pass << 40) | (uint64_t)(t < o ? 4 * (int64_t)t + e : 4 * (int64_t)o + j);
-    const int idx = O::append(V.n_cand);
-    if (idx >= V.cand_cap) continue;  // no room and no claims: ff_flip_requeue_one
+    const int n_vw = ffc(na, e == 2 ? 0 : e + 1), n_wu = ffc(na, e == 0 ? 2 : e - 1);
+    const int n_ud = ffc(nb, j[e] == 2 ? 0 : j[e] + 1), n_dv = ffc(nb, j[e] == 0 ? 2 : j[e] - 1);
+    const uint64_t prio = (pass << 40) | (uint64_t)(t < o ? 4 * (int64_t)t + e : 4 * (int64_t)o + j[e]);
     O::max64(&V.claim[t], prio);
     O::max64(&V.claim[o], prio);
     if (n_vw >= 0) O::max64(&V.claim[n_vw], prio);
     if (n_wu >= 0) O::max64(&V.claim[n_wu], prio);
     if (n_ud >= 0) O::max64(&V.claim[n_ud], prio);
     if (n_dv >= 0) O::max64(&V.claim[n_dv], prio);
-    V.fc0[idx] = make_int4(t, e, o, j);
-    V.fc1[idx] = make_int4(n_vw, n_wu, n_ud, n_dv);
-    V.fprio[idx] = prio;
+    V.fc0[at] = make_int4(t, e, o, j[e]);
+    V.fc1[at] = make_int4(n_vw, n_wu, n_ud, n_dv);
+    V.fprio[at] = prio;
   }
 }
 
@@ -391,12 +446,9 @@ GDP_HD void ff_flip_apply_one(const FfView &V, int i, int wst, int tst) {
   const int4 f = V.fc0[i], g = V.fc1[i];
   const uint64_t prio = V.fprio[i];
   const int t = f.x, e = f.y, o = f.z, j = f.w;
-  bool win = V.claim[t] == prio && V.claim[o] == prio;
-  for (int q = 0; q < 4 && win; q++) {
-    const int s = ffc(g, q < 3 ? q : 0);
-    const int x = q == 3 ? g.w : s;
-    if (x >= 0 && V.claim[x] != prio) win = false;
-  }
+  const uint64_t m0 = V.claim[t], m1 = V.claim[o], m2 = V.claim[g.x < 0 ? t : g.x], m3 = V.claim[g.y < 0 ? t : g.y],
+                 m4 = V.claim[g.z < 0 ? t : g.z], m5 = V.claim[g.w < 0 ? t : g.w];
+  const bool win = m0 == prio && m1 == prio && m2 == prio && m3 == prio && m4 == prio && m5 == prio;
   if (!win) {
     ff_push<O>(V.list_out, V.n_out, V.wstamp, wst, t);  // the edge is checked again
     return;
@@ -420,9 +472,8 @@ GDP_HD void ff_flip_apply_one(const FfView &V, int i, int wst, int tst) {
     if (q < 0) O::err(&V.c->err, 6);
     else ff_set(V, V.tn, n_vw, q, o);
   }
-  O::add64(&V.c->flips, 1);
-  ff_wrote<O>(V, t, wst, tst);
-  ff_wrote<O>(V, o, wst, tst);
+  O::inc64(&V.c->flips);
+  ff_wrote2<O>(V, t, o, wst, tst);
 }
 
 // ---------------------------------------------------------------------------
@@ -472,6 +523,32 @@ GDP_HD int ff_star(const FfView &V, int p, int t0, bool &open, F &&f) {
   return n;
 }
 
+// The same triangles in any order: one turn from t0, and the rest from the
+// other side where the star is open.
+template <class F>
+GDP_HD int ff_star_any(const FfView &V, int p, int t0, F &&f) {
+  int n = 0, t = t0, i0 = -1;
+  for (;;) {
+    const int4 tri = V.tv[t], nb = V.tn[t];
+    const int i = ff_vidx(tri, p);
+    if (i < 0 || n > kFfWalkCap) return 0;
+    if (n == 0) i0 = ffc(nb, i);  // across (p, next vertex): clockwise
+    f(t, tri, i);
+    n++;
+    t = ffc(nb, i == 0 ? 2 : i - 1);  // across (previous vertex, p): counter-clockwise
+    if (t == t0) return n;
+    if (t < 0) break;
+  }
+  for (t = i0; t >= 0; n++) {
+    const int4 tri = V.tv[t], nb = V.tn[t];
+    const int i = ff_vidx(tri, p);
+    if (i < 0 || n > kFfWalkCap) return 0;
+    f(t, tri, i);
+    t = ffc(nb, i);
+  }
+  return n;
+}
+
 template <class O>
 GDP_HD void ff_detect_one(const FfView &V, int r) {
   if (!V.alive[r]) return;
@@ -479,9 +556,7 @@ GDP_HD void ff_detect_one(const FfView &V, int r) {
   const bool is_cc = V.pinfo[r].x == 0;
   const double2 P = V.vxy[p];
   bool dep = false, enc = false;
-  bool open;
-  const int n = ff_star(V, p, V.vtri[r], open, [&](int t, int i) {
-    const int4 tri = V.tv[t];
+  const int n = ff_star_any(V, p, V.vtri[r], [&](int t, const int4 &tri, int i) {
     const int u = ffc(tri, (i + 1) % 3), w = ffc(tri, (i + 2) % 3);
     if ((u >= V.nV && u < p) || (w >= V.nV && w < p)) dep = true;
     if (is_cc && ((tri.w >> ((i + 1) % 3)) & 1)) {
@@ -496,13 +571,16 @@ GDP_HD void ff_detect_one(const FfView &V, int r) {
   if (n == 0) { O::err(&V.c->err, 7); return; }
   if (enc || dep) {
     V.red[r] = enc ? 2 : 1;
-    O::append(&V.c->n_red);
-    if (enc) O::add64(&V.c->n_enc, 1);
-    else O::add64(&V.c->n_dep, 1);
+    V.hole[O::append(&V.c->n_red)] = r;  // (a list of the compaction, free until then)
+    if (enc) O::inc64(&V.c->n_enc);
+    else O::inc64(&V.c->n_dep);
   }
 }
 
-// Removal passes: a redundant point stamps itself and its neighbours with
+// Removal passes (here one point after the other, as a sequential run takes
+// them; the kernels run the same pass with a group of lanes per point and
+// ff_rm_apply_one only for the stars too large for a group): a redundant
+// point stamps itself and its neighbours with
 // (pass, rank); it is removed in the pass only if every stamp is its own, so
 // no two removals of a pass are within two edges of each other and their
 // stars, and the triangles around them, are disjoint.
@@ -734,7 +812,7 @@ GDP_HD void ff_rm_apply_one(const FfView &V, int r, int wst, int tst) {
   }
   V.alive[r] = 0;
   V.red[r] = 0;
-  O::add64(&V.c->removals, 1);
+  O::inc64(&V.c->removals);
 }
 
 // ---------------------------------------------------------------------------

@@ -195,11 +195,13 @@ __global__ void kf_split_fix(FfView V, int split_stamp);
 __global__ void kf_ctl(FfCount *c, int op, int arg);
 __global__ void kf_flip_check(FfView V, int in_stamp, uint64_t pass);
 __global__ void kf_flip_apply(FfView V, int wst, int tst);
+__global__ void kf_flip_tail(FfView V, int32_t *list0, int32_t *list1, int cur0, int in_stamp, int stamp, uint64_t pass,
+                             int tst);
 __global__ void kf_vtri(FfView V);
 __global__ void kf_detect(FfView V);
-__global__ void kf_rm_mark(FfView V, uint64_t pbase);
-__global__ void kf_rm_decide(FfView V, uint64_t pbase);
-__global__ void kf_rm_apply(FfView V, int wst, int tst);
+__global__ void kf_rm_mark(FfView V, const int32_t *list, const int32_t *n_list, int32_t *n_next, uint64_t pbase);
+__global__ void kf_rm_apply(FfView V, const int32_t *list, const int32_t *n_list, int32_t *next, int32_t *n_next,
+                            uint64_t pbase, int wst, int tst);
 __global__ void kf_nwin_mid(FfView V);  // after the scan of alive into newid
 __global__ void kf_final_point(FfView V);
 __global__ void kf_final_tri(FfView V);
