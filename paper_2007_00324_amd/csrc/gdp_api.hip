@@ -104,6 +104,10 @@ struct gdp_mesh {
   gdp_ctx *ctx = nullptr;
   gdp_arena *arena = nullptr;  // non-null: the device arrays below live in a batch arena
   DevMesh m;
+  void *slab = nullptr;  // device allocation that the arrays below start in (see slab_new)
+  size_t slab_bytes = 0;
+  void *pin = nullptr;   // pinned block of the host mirrors
+  size_t pin_bytes = 0;
   // Two rounds (parity p, then the other) captured as one HIP graph, for
   // groups of small rounds; rebuilt when a buffer, a parameter or the grid
   // estimate changes.
@@ -215,6 +219,17 @@ gdp_status fail(gdp_ctx *ctx, gdp_status s, const std::string &msg) {
       return fail(ctx, GDP_E_DEVICE, std::string(#call ": ") + hipGetErrorString(e_));   \
   } while (0)
 
+// Every coordinate finite and zero or of a magnitude in [2^-100, 2^20] (no
+// early exit: the loop is vectorised).
+bool coords_ok(const double *xy, int64_t n) {
+  int bad = 0;
+  for (int64_t i = 0; i < n; i++) {
+    const double a = std::fabs(xy[i]);
+    bad |= (int)!(a <= 0x1p20) | ((int)(a != 0.0) & (int)(a < 0x1p-100));
+  }
+  return !bad;
+}
+
 template <class T>
 hipError_t dalloc(T **p, size_t n) {
   return hipMalloc((void **)p, sizeof(T) * std::max<size_t>(n, 1));
@@ -222,8 +237,20 @@ hipError_t dalloc(T **p, size_t n) {
 
 // Grows a device array from old_n to new_n elements, keeping the first keep_n
 // elements and filling the new tail with `fill` bytes.
+// A mesh's arrays are pieces of one allocation (its slab) until they grow out
+// of it, and its pinned mirrors pieces of one block.
+inline bool within(const void *p, const void *base, size_t n) {
+  return base && (const char *)p >= (const char *)base && (const char *)p < (const char *)base + n;
+}
+void dfree(const gdp_mesh *M, void *p) {
+  if (p && !within(p, M->slab, M->slab_bytes)) (void)hipFree(p);
+}
+void hfree(const gdp_mesh *M, void *p) {
+  if (p && !within(p, M->pin, M->pin_bytes)) (void)hipHostFree(p);
+}
+
 template <class T>
-hipError_t dgrow(T **p, size_t old_n, size_t new_n, size_t keep_n, int fill, hipStream_t s) {
+hipError_t dgrow(const gdp_mesh *M, T **p, size_t old_n, size_t new_n, size_t keep_n, int fill, hipStream_t s) {
   T *q = nullptr;
   hipError_t e = hipMalloc((void **)&q, sizeof(T) * std::max<size_t>(new_n, 1));
   if (e != hipSuccess) return e;
@@ -238,7 +265,7 @@ hipError_t dgrow(T **p, size_t old_n, size_t new_n, size_t keep_n, int fill, hip
   }
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
-  if (*p) (void)hipFree(*p);
+  dfree(M, *p);
   *p = q;
   (void)old_n;
   return hipSuccess;
@@ -262,28 +289,28 @@ gdp_status grow_tri(gdp_mesh *M, int32_t need) {
   int64_t nc64 = std::max<int64_t>(need, (int64_t)oc + oc / 2 + 1024);
   if (nc64 > (1 << 29)) return fail(ctx, GDP_E_NOMEM, "triangle capacity limit exceeded");
   int32_t nc = (int32_t)nc64;
-  HIPCHECK(dgrow(&M->m.tv, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->m.tn, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->m.ts, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->mark, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.elem, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.key, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.p, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.loc, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.state, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.off, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->cc.len, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->w0_t, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->win_t, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->rank_t, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->repl, 4 * (size_t)oc, 4 * (size_t)nc, 0, 0xff, s));
-  HIPCHECK(dgrow(&M->prev_cc_elem, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->prev_cc_key, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->prev_cc_p, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->tstamp, oc, nc, oc, 0xff, s));
-  HIPCHECK(dgrow(&M->cidx_t, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->hvis, oc, nc, 0, 0, s));
-  HIPCHECK(dgrow(&M->hlist, oc, nc, 0, 0, s));
+  HIPCHECK(dgrow(M, &M->m.tv, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.tn, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.ts, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->mark, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.elem, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.key, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.p, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.loc, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.state, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.off, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->cc.len, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->w0_t, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->win_t, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->rank_t, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->repl, 4 * (size_t)oc, 4 * (size_t)nc, 0, 0xff, s));
+  HIPCHECK(dgrow(M, &M->prev_cc_elem, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->prev_cc_key, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->prev_cc_p, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->tstamp, oc, nc, oc, 0xff, s));
+  HIPCHECK(dgrow(M, &M->cidx_t, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->hvis, oc, nc, 0, 0, s));
+  HIPCHECK(dgrow(M, &M->hlist, oc, nc, 0, 0, s));
   M->m.capT = nc;
   return GDP_OK;
 }
@@ -300,26 +327,26 @@ gdp_status grow_seg(gdp_mesh *M, int32_t need) {
   int64_t nc64 = std::max<int64_t>(need, (int64_t)oc + oc / 2 + 1024);
   if (nc64 > (1 << 28)) return fail(ctx, GDP_E_NOMEM, "subsegment capacity limit exceeded");
   int32_t nc = (int32_t)nc64;
-  HIPCHECK(dgrow(&M->m.sv, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->m.spar, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->m.spend, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->sadj, 2 * (size_t)oc, 2 * (size_t)nc, 2 * (size_t)oc, 0xff, s));
-  HIPCHECK(dgrow(&M->mflag, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.sv, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.spar, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.spend, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->sadj, 2 * (size_t)oc, 2 * (size_t)nc, 2 * (size_t)oc, 0xff, s));
+  HIPCHECK(dgrow(M, &M->mflag, oc, nc, oc, 0, s));
   size_t om = 2 * (size_t)oc, nm = 2 * (size_t)nc;  // a flagged subsegment can appear twice
-  HIPCHECK(dgrow(&M->mid.elem, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.key, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.p, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.loc, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.state, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.off, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->mid.len, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->prev_mid_elem, om, nm, om, 0, s));
-  HIPCHECK(dgrow(&M->cidx_s, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->w0_s, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->win_s, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->rank_s, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->win_h, words(oc), words(nc), words(oc), 0, s));
-  HIPCHECK(dgrow(&M->rank_h, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->mid.elem, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.key, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.p, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.loc, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.state, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.off, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->mid.len, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->prev_mid_elem, om, nm, om, 0, s));
+  HIPCHECK(dgrow(M, &M->cidx_s, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->w0_s, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->win_s, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->rank_s, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->win_h, words(oc), words(nc), words(oc), 0, s));
+  HIPCHECK(dgrow(M, &M->rank_h, words(oc), words(nc), words(oc), 0, s));
   M->m.capS = nc;
   return GDP_OK;
 }
@@ -336,8 +363,8 @@ gdp_status grow_vtx(gdp_mesh *M, int32_t need) {
   int64_t nc64 = std::max<int64_t>(need, (int64_t)oc + oc / 2 + 1024);
   if (nc64 > (1 << 29)) return fail(ctx, GDP_E_NOMEM, "vertex capacity limit exceeded");
   int32_t nc = (int32_t)nc64;
-  HIPCHECK(dgrow(&M->m.vxy, oc, nc, oc, 0, s));
-  HIPCHECK(dgrow(&M->m.vkind, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.vxy, oc, nc, oc, 0, s));
+  HIPCHECK(dgrow(M, &M->m.vkind, oc, nc, oc, 0, s));
   M->m.capV = nc;
   return GDP_OK;
 }
@@ -355,17 +382,17 @@ gdp_status grow_cand(gdp_mesh *M) {
   int64_t nc = std::max<int64_t>(need, (int64_t)M->wT + M->wT / 2);
   // may run while a round is abandoned: keep what is already written
   size_t keep = (size_t)M->wT;
-  HIPCHECK(dgrow(&M->w0_list, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->win_rank, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->win_fresh, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->fan_off, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->fan_len, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->big, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(&M->keys, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->w0_list, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->win_rank, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->win_fresh, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->fan_off, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->fan_len, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->big, keep, nc, keep, 0, s));
+  HIPCHECK(dgrow(M, &M->keys, keep, nc, keep, 0, s));
   int64_t nt = nc / kScanTileSize + 2;
-  HIPCHECK(dgrow(&M->tiles_t, 0, nt, 0, 0, s));
-  HIPCHECK(dgrow(&M->tiles_s, 0, nt, 0, 0, s));
-  HIPCHECK(dgrow(&M->tiles_h, 0, nt, 0, 0, s));
+  HIPCHECK(dgrow(M, &M->tiles_t, 0, nt, 0, 0, s));
+  HIPCHECK(dgrow(M, &M->tiles_s, 0, nt, 0, 0, s));
+  HIPCHECK(dgrow(M, &M->tiles_h, 0, nt, 0, 0, s));
   M->tiles_cap = (int32_t)nt;
   M->wT = (int32_t)nc;
   return GDP_OK;
@@ -474,22 +501,21 @@ gdp_status scan_winners(gdp_mesh *M, const Work &w, int64_t n_bound) {
   return GDP_OK;
 }
 
+gdp_status alloc_host_mirrors(gdp_mesh *M);
+
 // Small device buffers and their pinned host mirrors.
 gdp_status alloc_control(gdp_mesh *M) {
   gdp_ctx *ctx = M->ctx;
   auto ok = [](hipError_t e) { return e == hipSuccess; };
-  if (!ok(dalloc(&M->d_cnt, 1)) || !ok(hipHostMalloc((void **)&M->h_cnt, sizeof(DevCounters))) ||
-      !ok(dalloc(&M->d_stat, kStatStripes)) ||
-      !ok(dalloc(&M->d_st, 1)) || !ok(hipHostMalloc((void **)&M->h_st, sizeof(DevState))) ||
-      !ok(dalloc(&M->d_hist, kHistCap)) || !ok(hipHostMalloc((void **)&M->h_hist, sizeof(DevCounters) * kHistCap)) ||
-      !ok(dalloc(&M->rhist, 256)) || !ok(dalloc(&M->sel, 4)))
+  if (!ok(dalloc(&M->d_cnt, 1)) || !ok(dalloc(&M->d_stat, kStatStripes)) || !ok(dalloc(&M->d_st, 1)) ||
+      !ok(dalloc(&M->d_hist, kHistCap)) || !ok(dalloc(&M->rhist, 256)) || !ok(dalloc(&M->sel, 4)))
     return fail(ctx, GDP_E_NOMEM, "allocation failed");
   HIPCHECK(hipMemsetAsync(M->d_cnt, 0, sizeof(DevCounters), ctx->stream));
   HIPCHECK(hipMemsetAsync(M->d_stat, 0, sizeof(StatLine) * kStatStripes, ctx->stream));
   HIPCHECK(hipMemsetAsync(M->d_st, 0, sizeof(DevState), ctx->stream));
   HIPCHECK(hipMemsetAsync(M->rhist, 0, 256 * sizeof(int32_t), ctx->stream));
   HIPCHECK(hipMemsetAsync(M->sel, 0, 4 * sizeof(uint64_t), ctx->stream));
-  return GDP_OK;
+  return alloc_host_mirrors(M);
 }
 
 void free_extras(gdp_mesh *M);
@@ -509,9 +535,9 @@ void free_mesh_arrays(gdp_mesh *M) {
                   M->win_fresh, M->fan_off, M->fan_len, M->repl, M->pool, M->fan, M->big, M->keys, M->rhist, M->sel,
                   M->d_st, M->d_hist, M->tiles_t, M->tiles_s, M->tiles_h, M->prev_cc_elem, M->prev_cc_key, M->prev_cc_p, M->prev_mid_elem, M->tstamp,
                   M->cidx_t, M->cidx_s, M->hvis, M->hlist};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
+  for (void *p : ptrs) dfree(M, p);
   free_extras(M);
+  if (M->slab) (void)hipFree(M->slab);
 }
 
 // Allocations a mesh owns even inside a batch arena: pinned host mirrors,
@@ -529,20 +555,159 @@ void free_extras(gdp_mesh *M) {
     delete F;
     M->ff = nullptr;
   }
-  if (M->h_cnt) (void)hipHostFree(M->h_cnt);
-  if (M->h_st) (void)hipHostFree(M->h_st);
-  if (M->h_hist) (void)hipHostFree(M->h_hist);
+  hfree(M, M->h_cnt);
+  hfree(M, M->h_st);
+  hfree(M, M->h_hist);
   for (auto &g : M->graph)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (M->d_eng) (void)hipFree(M->d_eng);
-  if (M->d_head) (void)hipFree(M->d_head);
-  if (M->h_eng) (void)hipHostFree(M->h_eng);
+  dfree(M, M->d_eng);
+  dfree(M, M->d_head);
+  hfree(M, M->h_eng);
+  if (M->pin) (void)hipHostFree(M->pin);
   if (M->cap_stream) (void)hipStreamDestroy(M->cap_stream);
 }
 
+struct Caps {
+  int64_t V, T, S, W, tiles, pool, fan;
+};
+
+Caps caps_of(const gdp_mesh *M) {
+  return {M->m.capV, M->m.capT, M->m.capS, M->wT, M->tiles_cap, M->pool_cap, M->fan_cap};
+}
+
+// Every device array of a mesh: f(pointer, element bytes, length, fill byte).
+// The lengths match the grow_* functions for the same capacities.
+template <class F>
+void for_each_array(gdp_mesh *M, const Caps &c, F f) {
+  const int64_t wT = c.T / 32 + 1, wS = c.S / 32 + 1;
+  f((void **)&M->m.vxy, sizeof(double2), c.V, 0);
+  f((void **)&M->m.vkind, 4, c.V, 0);
+  f((void **)&M->m.tv, sizeof(int4), c.T, 0);
+  f((void **)&M->m.tn, sizeof(int4), c.T, 0);
+  f((void **)&M->m.ts, sizeof(int4), c.T, 0);
+  f((void **)&M->m.sv, sizeof(int2), c.S, 0);
+  f((void **)&M->m.spar, 4, c.S, 0);
+  f((void **)&M->m.spend, 4, c.S, 0);
+  f((void **)&M->mark, 8, c.T, 0);
+  f((void **)&M->sadj, 4, 2 * c.S, 0xff);
+  f((void **)&M->mflag, 4, c.S, 0);
+  CandSet *sets[2] = {&M->cc, &M->mid};
+  for (int k = 0; k < 2; k++) {
+    const int64_t n = k == 0 ? c.T : 2 * c.S;
+    CandSet &cs = *sets[k];
+    f((void **)&cs.elem, 4, n, 0);
+    f((void **)&cs.key, 8, n, 0);
+    f((void **)&cs.p, sizeof(double2), n, 0);
+    f((void **)&cs.loc, 4, n, 0);
+    f((void **)&cs.state, 4, n, 0);
+    f((void **)&cs.off, 4, n, 0);
+    f((void **)&cs.len, 4, n, 0);
+  }
+  f((void **)&M->prev_cc_elem, 4, c.T, 0);
+  f((void **)&M->prev_cc_key, 8, c.T, 0);
+  f((void **)&M->prev_cc_p, sizeof(double2), c.T, 0);
+  f((void **)&M->prev_mid_elem, 4, 2 * c.S, 0);
+  f((void **)&M->w0_t, 4, wT, 0);
+  f((void **)&M->win_t, 4, wT, 0);
+  f((void **)&M->rank_t, 4, wT, 0);
+  f((void **)&M->w0_s, 4, wS, 0);
+  f((void **)&M->win_s, 4, wS, 0);
+  f((void **)&M->rank_s, 4, wS, 0);
+  f((void **)&M->win_h, 4, wS, 0);
+  f((void **)&M->rank_h, 4, wS, 0);
+  f((void **)&M->repl, 4, 4 * c.T, 0xff);
+  f((void **)&M->tstamp, 4, c.T, 0xff);
+  f((void **)&M->cidx_t, 4, c.T, 0);
+  f((void **)&M->hvis, 4, c.T, 0);
+  f((void **)&M->hlist, 4, c.T, 0);
+  f((void **)&M->cidx_s, 4, c.S, 0);
+  f((void **)&M->w0_list, 4, c.W, 0);
+  f((void **)&M->win_rank, 4, c.W, 0);
+  f((void **)&M->win_fresh, 4, c.W, 0);
+  f((void **)&M->fan_off, 4, c.W, 0);
+  f((void **)&M->fan_len, 4, c.W, 0);
+  f((void **)&M->big, 4, c.W, 0);
+  f((void **)&M->keys, 8, c.W, 0);
+  f((void **)&M->tiles_t, 4, c.tiles, 0);
+  f((void **)&M->tiles_s, 4, c.tiles, 0);
+  f((void **)&M->tiles_h, 4, c.tiles, 0);
+  f((void **)&M->pool, 4, c.pool, 0);
+  f((void **)&M->fan, sizeof(FanRec), c.fan, 0);
+  f((void **)&M->d_stat, sizeof(StatLine), kStatStripes, 0);
+  f((void **)&M->d_cnt, sizeof(DevCounters), 1, 0);
+  f((void **)&M->d_st, sizeof(DevState), 1, 0);
+  f((void **)&M->d_hist, sizeof(DevCounters), kHistCap, 0);
+  f((void **)&M->rhist, 4, 256, 0);
+  f((void **)&M->sel, 8, 4, 0);
+}
+
+inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// The arrays of for_each_array that hold the mesh itself come first.
+constexpr int kMeshArrays = 8;
+// Up to this size a new mesh's arrays are one allocation.  Sixty of them cost
+// 2.3 ms for 1,000,000 points (37 us each) and 10 ms when the mesh is freed
+// (164 us each), 60,013 points 1.6 + 3.7 ms.  An array that grows moves to an
+// allocation of its own and its piece stays unused until the mesh is freed,
+// so above this each array has its own from the start, as their cost is then
+// small against the work.
+constexpr size_t kSlabMax = (size_t)8 << 30;
+
+// Lays the arrays of M out in one allocation for the capacities c; false (and
+// M as it was) if they are too large or there is no room.
+bool slab_new(gdp_mesh *M, const Caps &c) {
+  size_t total = 0;
+  for_each_array(M, c, [&](void **, size_t es, int64_t n, int) { total += align256(es * (size_t)std::max<int64_t>(n, 1)); });
+  if (total > kSlabMax) return false;
+  void *p = nullptr;
+  if (hipMalloc(&p, total) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  M->slab = p;
+  M->slab_bytes = total;
+  size_t run = 0;
+  for_each_array(M, c, [&](void **pp, size_t es, int64_t n, int) {
+    *pp = (char *)p + run;
+    run += align256(es * (size_t)std::max<int64_t>(n, 1));
+  });
+  M->m.capV = (int32_t)c.V; M->m.capT = (int32_t)c.T; M->m.capS = (int32_t)c.S;
+  M->wT = (int32_t)c.W; M->tiles_cap = (int32_t)c.tiles;
+  M->pool_cap = (int32_t)c.pool; M->fan_cap = (int32_t)c.fan;
+  return true;
+}
+
+// Sets the slab's arrays first .. last - 1 to their fill bytes, neighbours of
+// one value together (the cavity pool and the fan records need none).
+gdp_status slab_fill(gdp_mesh *M, int first, int last) {
+  gdp_ctx *ctx = M->ctx;
+  char *at = nullptr;
+  size_t len = 0;
+  int val = 0, i = 0;
+  hipError_t e = hipSuccess;
+  auto flush = [&]() {
+    if (len && e == hipSuccess) e = hipMemsetAsync(at, val, len, ctx->stream);
+    len = 0;
+  };
+  for_each_array(M, caps_of(M), [&](void **pp, size_t es, int64_t n, int fill) {
+    const bool in = i >= first && i < last && pp != (void **)&M->pool && pp != (void **)&M->fan;
+    i++;
+    if (!in || fill != val) flush();
+    if (!in) return;
+    if (!len) at = (char *)*pp;
+    val = fill;
+    len += align256(es * (size_t)std::max<int64_t>(n, 1));
+  });
+  flush();
+  HIPCHECK(e);
+  return GDP_OK;
+}
+
 // Allocates a device mesh with room for the given counts (arrays not filled).
+// (fill_work false: a slab's workspace is left as it is, to be used and then
+// filled by the caller.)
 gdp_status mesh_new(gdp_ctx *ctx, int32_t nV, int32_t nIV, int32_t nT, int32_t nS, int32_t nIS, int32_t rounds,
-                    gdp_mesh **out) {
+                    gdp_mesh **out, bool fill_work = true) {
   gdp_mesh *M = new gdp_mesh();
   M->ctx = ctx;
   auto bail = [&](gdp_status st) {
@@ -561,6 +726,13 @@ gdp_status mesh_new(gdp_ctx *ctx, int32_t nV, int32_t nIV, int32_t nT, int32_t n
   if (cT > (1 << 29) || cS > (1 << 28)) return bail(fail(ctx, GDP_E_NOMEM, "mesh too large"));
   M->m.capV = 0; M->m.capT = 0; M->m.capS = 0;
   gdp_status st;
+  const int64_t cW = cT + 2 * cS + 2;
+  if (slab_new(M, {cV, cT, cS, cW, cW / kScanTileSize + 2, std::max<int64_t>(1 << 16, 2 * cT + 65536),
+                   std::max<int64_t>(1 << 16, 2 * cT)})) {
+    if ((st = alloc_host_mirrors(M)) || (st = slab_fill(M, 0, fill_work ? 1 << 30 : kMeshArrays))) return bail(st);
+    *out = M;
+    return GDP_OK;
+  }
   if ((st = grow_vtx(M, (int32_t)cV)) != GDP_OK) return bail(st);
   if ((st = grow_tri(M, (int32_t)cT)) != GDP_OK) return bail(st);
   if ((st = grow_seg(M, (int32_t)cS)) != GDP_OK) return bail(st);
@@ -642,14 +814,14 @@ gdp_status grow_after_abort(gdp_mesh *M, const DevCounters &c, int keep_fan) {
     int64_t nc = std::max<int64_t>((int64_t)c.pool_used * 2, (int64_t)M->pool_cap * 2);
     if (nc > (1LL << 30)) return fail(ctx, GDP_E_NOMEM, "cavity pool limit exceeded");
     if (M->arena && (st = detach(M))) return st;
-    HIPCHECK(dgrow(&M->pool, M->pool_cap, nc, 0, 0, ctx->stream));
+    HIPCHECK(dgrow(M, &M->pool, M->pool_cap, nc, 0, 0, ctx->stream));
     M->pool_cap = (int32_t)nc;
   }
   int64_t fan_need = (int64_t)std::max(c.pool_used, M->pool_cap) + 2 * (int64_t)nwin + 1024;
   if (fan_need > M->fan_cap) {
     if (fan_need > (1LL << 30)) return fail(ctx, GDP_E_NOMEM, "fan buffer limit exceeded");
     if (M->arena && (st = detach(M))) return st;
-    HIPCHECK(dgrow(&M->fan, M->fan_cap, fan_need, keep_fan, 0, ctx->stream));
+    HIPCHECK(dgrow(M, &M->fan, M->fan_cap, fan_need, keep_fan, 0, ctx->stream));
     M->fan_cap = (int32_t)fan_need;
   }
   return GDP_OK;
@@ -870,7 +1042,7 @@ gdp_status reserve_group(gdp_mesh *M, int64_t last_cand, int R) {
     int64_t nc = std::max<int64_t>(pool_need, (int64_t)M->pool_cap * 3 / 2);
     if (nc > (1LL << 30)) return fail(ctx, GDP_E_NOMEM, "cavity pool limit exceeded");
     if (M->arena && (st = detach(M))) return st;
-    HIPCHECK(dgrow(&M->pool, M->pool_cap, nc, 0, 0, ctx->stream));
+    HIPCHECK(dgrow(M, &M->pool, M->pool_cap, nc, 0, 0, ctx->stream));
     M->pool_cap = (int32_t)nc;
   }
   return GDP_OK;
@@ -943,11 +1115,9 @@ gdp_status launch_pairs(gdp_mesh *M, double B2, const gdp_params *P, int p, int 
 gdp_status launch_engine(gdp_mesh *M, double B2, const gdp_params *P, int rounds) {
   gdp_ctx *ctx = M->ctx;
   hipStream_t s = ctx->stream;
-  if (!M->d_eng) {
-    HIPCHECK(dalloc(&M->d_eng, 1));
-    HIPCHECK(dalloc(&M->d_head, 1));
-    HIPCHECK(hipHostMalloc((void **)&M->h_eng, sizeof(EngDesc)));
-  }
+  if (!M->d_eng) HIPCHECK(dalloc(&M->d_eng, 1));
+  if (!M->d_head) HIPCHECK(dalloc(&M->d_head, 1));
+  if (!M->h_eng) HIPCHECK(hipHostMalloc((void **)&M->h_eng, sizeof(EngDesc)));
   // the previous launch has finished (the host synchronised since), so the
   // pinned descriptor can be rewritten
   EngDesc &d = *M->h_eng;
@@ -974,86 +1144,25 @@ gdp_status launch_engine(gdp_mesh *M, double B2, const gdp_params *P, int rounds
 
 
 // ---- batched form: many meshes in one arena, one persistent launch ---------
-struct Caps {
-  int64_t V, T, S, W, tiles, pool, fan;
-};
-
-Caps caps_of(const gdp_mesh *M) {
-  return {M->m.capV, M->m.capT, M->m.capS, M->wT, M->tiles_cap, M->pool_cap, M->fan_cap};
-}
-
-// Every device array of a mesh: f(pointer, element bytes, length, fill byte).
-// The lengths match the grow_* functions for the same capacities.
-template <class F>
-void for_each_array(gdp_mesh *M, const Caps &c, F f) {
-  const int64_t wT = c.T / 32 + 1, wS = c.S / 32 + 1;
-  f((void **)&M->m.vxy, sizeof(double2), c.V, 0);
-  f((void **)&M->m.vkind, 4, c.V, 0);
-  f((void **)&M->m.tv, sizeof(int4), c.T, 0);
-  f((void **)&M->m.tn, sizeof(int4), c.T, 0);
-  f((void **)&M->m.ts, sizeof(int4), c.T, 0);
-  f((void **)&M->m.sv, sizeof(int2), c.S, 0);
-  f((void **)&M->m.spar, 4, c.S, 0);
-  f((void **)&M->m.spend, 4, c.S, 0);
-  f((void **)&M->mark, 8, c.T, 0);
-  f((void **)&M->sadj, 4, 2 * c.S, 0xff);
-  f((void **)&M->mflag, 4, c.S, 0);
-  CandSet *sets[2] = {&M->cc, &M->mid};
-  for (int k = 0; k < 2; k++) {
-    const int64_t n = k == 0 ? c.T : 2 * c.S;
-    CandSet &cs = *sets[k];
-    f((void **)&cs.elem, 4, n, 0);
-    f((void **)&cs.key, 8, n, 0);
-    f((void **)&cs.p, sizeof(double2), n, 0);
-    f((void **)&cs.loc, 4, n, 0);
-    f((void **)&cs.state, 4, n, 0);
-    f((void **)&cs.off, 4, n, 0);
-    f((void **)&cs.len, 4, n, 0);
-  }
-  f((void **)&M->prev_cc_elem, 4, c.T, 0);
-  f((void **)&M->prev_cc_key, 8, c.T, 0);
-  f((void **)&M->prev_cc_p, sizeof(double2), c.T, 0);
-  f((void **)&M->prev_mid_elem, 4, 2 * c.S, 0);
-  f((void **)&M->w0_t, 4, wT, 0);
-  f((void **)&M->win_t, 4, wT, 0);
-  f((void **)&M->rank_t, 4, wT, 0);
-  f((void **)&M->w0_s, 4, wS, 0);
-  f((void **)&M->win_s, 4, wS, 0);
-  f((void **)&M->rank_s, 4, wS, 0);
-  f((void **)&M->win_h, 4, wS, 0);
-  f((void **)&M->rank_h, 4, wS, 0);
-  f((void **)&M->repl, 4, 4 * c.T, 0xff);
-  f((void **)&M->tstamp, 4, c.T, 0xff);
-  f((void **)&M->cidx_t, 4, c.T, 0);
-  f((void **)&M->hvis, 4, c.T, 0);
-  f((void **)&M->hlist, 4, c.T, 0);
-  f((void **)&M->cidx_s, 4, c.S, 0);
-  f((void **)&M->w0_list, 4, c.W, 0);
-  f((void **)&M->win_rank, 4, c.W, 0);
-  f((void **)&M->win_fresh, 4, c.W, 0);
-  f((void **)&M->fan_off, 4, c.W, 0);
-  f((void **)&M->fan_len, 4, c.W, 0);
-  f((void **)&M->big, 4, c.W, 0);
-  f((void **)&M->keys, 8, c.W, 0);
-  f((void **)&M->tiles_t, 4, c.tiles, 0);
-  f((void **)&M->tiles_s, 4, c.tiles, 0);
-  f((void **)&M->tiles_h, 4, c.tiles, 0);
-  f((void **)&M->pool, 4, c.pool, 0);
-  f((void **)&M->fan, sizeof(FanRec), c.fan, 0);
-  f((void **)&M->d_stat, sizeof(StatLine), kStatStripes, 0);
-  f((void **)&M->d_cnt, sizeof(DevCounters), 1, 0);
-  f((void **)&M->d_st, sizeof(DevState), 1, 0);
-  f((void **)&M->d_hist, sizeof(DevCounters), kHistCap, 0);
-  f((void **)&M->rhist, 4, 256, 0);
-  f((void **)&M->sel, 8, 4, 0);
-}
-
-inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 // Pinned host mirrors of a mesh's control block (a batch member gets them
 // when it is first refined on its own).
 gdp_status alloc_host_mirrors(gdp_mesh *M) {
   gdp_ctx *ctx = M->ctx;
+  if (!M->h_cnt && !M->h_st && !M->h_hist && !M->pin) {
+    const size_t o_cnt = align256(sizeof(DevCounters) * kHistCap), o_st = o_cnt + align256(sizeof(DevCounters)),
+                 o_eng = o_st + align256(sizeof(DevState));
+    M->pin_bytes = o_eng + sizeof(EngDesc);
+    if (hipHostMalloc(&M->pin, M->pin_bytes) != hipSuccess) {
+      M->pin = nullptr;
+      return fail(ctx, GDP_E_NOMEM, "pinned allocation failed");
+    }
+    char *b = (char *)M->pin;
+    M->h_hist = (DevCounters *)b;
+    M->h_cnt = (DevCounters *)(b + o_cnt);
+    M->h_st = (DevState *)(b + o_st);
+    if (!M->h_eng) M->h_eng = (EngDesc *)(b + o_eng);
+    return GDP_OK;
+  }
   if (!M->h_cnt && hipHostMalloc((void **)&M->h_cnt, sizeof(DevCounters)) != hipSuccess)
     return fail(ctx, GDP_E_NOMEM, "pinned allocation failed");
   if (!M->h_st && hipHostMalloc((void **)&M->h_st, sizeof(DevState)) != hipSuccess)
@@ -1071,11 +1180,28 @@ gdp_status detach(gdp_mesh *M) {
   hipStream_t s = ctx->stream;
   std::vector<void **> slot;
   std::vector<size_t> bytes;
-  for_each_array(M, caps_of(M), [&](void **pp, size_t es, int64_t n, int) {
+  const Caps c = caps_of(M);
+  for_each_array(M, c, [&](void **pp, size_t es, int64_t n, int) {
     slot.push_back(pp);
     bytes.push_back(es * (size_t)std::max<int64_t>(n, 1));
   });
-  std::vector<void *> fresh(slot.size(), nullptr);
+  std::vector<void *> old, fresh(slot.size(), nullptr);
+  for (void **pp : slot) old.push_back(*pp);
+  if (slab_new(M, c)) {
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < slot.size() && e == hipSuccess; i++)
+      e = hipMemcpyAsync(*slot[i], old[i], bytes[i], hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+      for (size_t i = 0; i < slot.size(); i++) *slot[i] = old[i];
+      (void)hipFree(M->slab);
+      M->slab = nullptr;
+    }
+    HIPCHECK(e);
+    arena_release(M->arena);
+    M->arena = nullptr;
+    return alloc_host_mirrors(M);
+  }
   for (size_t i = 0; i < slot.size(); i++) {
     if (hipMalloc(&fresh[i], bytes[i]) != hipSuccess) {
       for (void *q : fresh)
@@ -1381,12 +1507,9 @@ gdp_status check_pslg_for_device(const gdp_pslg *pslg, std::string &e) {
   const int32_t nv = pslg->n_vertices, ns = pslg->n_segments;
   if (nv < 3 || !pslg->xy || ns < 0 || (ns > 0 && !pslg->seg)) { e = "bad arguments"; return GDP_E_ARG; }
   if (nv > (1 << 28) - 8) { e = "mesh too large"; return GDP_E_NOMEM; }
-  for (int64_t i = 0; i < 2 * (int64_t)nv; i++) {
-    const double a = std::fabs(pslg->xy[i]);
-    if (!std::isfinite(pslg->xy[i]) || a > 0x1p20 || (a != 0.0 && a < 0x1p-100)) {
-      e = "coordinate not finite, or nonzero with magnitude outside [2^-100, 2^20]";
-      return GDP_E_INPUT;
-    }
+  if (!coords_ok(pslg->xy, 2 * (int64_t)nv)) {
+    e = "coordinate not finite, or nonzero with magnitude outside [2^-100, 2^20]";
+    return GDP_E_INPUT;
   }
   for (int32_t k = 0; k < ns; k++) {
     const int32_t a = pslg->seg[2 * k], b = pslg->seg[2 * k + 1];
@@ -2628,60 +2751,60 @@ gdp_status ff_reserve(gdp_mesh *M, int32_t np) {
   if (needK > F.capK) {
     // the claims' output (skey0, sref0) may already hold S: keep it
     const size_t n = (size_t)needK, o = (size_t)F.capK;
-    HIPCHECK(dgrow(&F.skey0, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.skey1, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.sref0, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.sref1, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.shist, 0, 256 * ((n + kSortPairsTile - 1) / kSortPairsTile), 0, 0, s));
+    HIPCHECK(dgrow(M, &F.skey0, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.skey1, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.sref0, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.sref1, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.shist, 0, 256 * ((n + kSortPairsTile - 1) / kSortPairsTile), 0, 0, s));
     F.capK = (int32_t)needK;
   }
   if (np + 1 > F.capP) {
     const size_t n = (size_t)std::max<int64_t>({(int64_t)np + 1, (int64_t)F.capP * 3 / 2, 1024});
-    HIPCHECK(dgrow(&F.pt, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.pinfo, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.pslots, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.pab, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.alive, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.red, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.vtri, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.newid, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.ntiles, 0, n / kFfScanTile + 2, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.pt, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.pinfo, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.pslots, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.pab, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.alive, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.red, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.vtri, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.newid, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.ntiles, 0, n / kFfScanTile + 2, 0, 0, s));
     F.capP = (int32_t)n;
   }
   if (m.capT > F.capT) {
     const size_t n = (size_t)m.capT, o = (size_t)F.capT;
     // stamps and claims keep their values (they are compared with newer ones)
-    HIPCHECK(dgrow(&F.sstamp, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.wstamp, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.tstamp, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.claim, o, n, o, 0, s));
-    HIPCHECK(dgrow(&F.grp, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.moved, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.fc0, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.fc1, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.fprio, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.list[0], 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.list[1], 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.touched, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.dead, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.hole, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.mover, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.sstamp, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.wstamp, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.tstamp, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.claim, o, n, o, 0, s));
+    HIPCHECK(dgrow(M, &F.grp, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.moved, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.fc0, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.fc1, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.fprio, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.list[0], 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.list[1], 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.touched, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.dead, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.hole, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.mover, 0, n, 0, 0, s));
     F.capT = (int32_t)n;
   }
   const int64_t need_pool = std::max<int64_t>(1 << 20, 4 * (int64_t)m.capT);
   if (need_pool > F.pool_cap) {
-    HIPCHECK(dgrow(&F.pool, 0, (size_t)need_pool, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.pool, 0, (size_t)need_pool, 0, 0, s));
     F.pool_cap = need_pool;
   }
   if (m.capV > F.capV) {
-    HIPCHECK(dgrow(&F.vmark, (size_t)F.capV, (size_t)m.capV, (size_t)F.capV, 0, s));
+    HIPCHECK(dgrow(M, &F.vmark, (size_t)F.capV, (size_t)m.capV, (size_t)F.capV, 0, s));
     F.capV = m.capV;
   }
   if ((int64_t)m.capS + F.capP > F.capS) {
     // cleared by every round's last kernels: no contents to keep
     const size_t n = (size_t)m.capS + (size_t)F.capP;
-    HIPCHECK(dgrow(&F.sflag, 0, n, 0, 0, s));
-    HIPCHECK(dgrow(&F.mid_rank, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.sflag, 0, n, 0, 0, s));
+    HIPCHECK(dgrow(M, &F.mid_rank, 0, n, 0, 0, s));
     F.capS = (int32_t)n;
   }
   return GDP_OK;
@@ -2913,7 +3036,7 @@ gdp_status ff_line8(gdp_mesh *M, const gdp_params *P, int32_t np, int32_t nmid, 
       if (c.pool_short) {
         // a removal found no room in the pool: grow it (nothing is in flight)
         const int64_t nc = F.pool_cap * 2;
-        HIPCHECK(dgrow(&F.pool, 0, (size_t)nc, 0, 0, s));
+        HIPCHECK(dgrow(M, &F.pool, 0, (size_t)nc, 0, 0, s));
         F.pool_cap = nc;
         V.pool = F.pool;
         V.pool_cap = nc;
@@ -3256,11 +3379,8 @@ gdp_status gdp_mesh_create_device(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh *
   if (nv > (1 << 28) - 8) return fail(ctx, GDP_E_NOMEM, "mesh too large");
   // the checks of the host builder that need no sort; duplicate points and
   // repeated segments are found by the kernels
-  for (int64_t i = 0; i < 2 * (int64_t)nv; i++) {
-    const double a = std::fabs(xy[i]);
-    if (!std::isfinite(xy[i]) || a > 0x1p20 || (a != 0.0 && a < 0x1p-100))
-      return fail(ctx, GDP_E_INPUT, "coordinate not finite, or nonzero with magnitude outside [2^-100, 2^20]");
-  }
+  if (!coords_ok(xy, 2 * (int64_t)nv))
+    return fail(ctx, GDP_E_INPUT, "coordinate not finite, or nonzero with magnitude outside [2^-100, 2^20]");
   for (int32_t k = 0; k < ns; k++) {
     const int32_t a = seg[2 * k], b = seg[2 * k + 1];
     if (a < 0 || b < 0 || a >= nv || b >= nv || a == b)
@@ -3268,7 +3388,7 @@ gdp_status gdp_mesh_create_device(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh *
   }
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, GDP_E_DEVICE, "hipSetDevice failed");
   gdp_mesh *M = nullptr;
-  gdp_status st = mesh_new(ctx, nv, nv, 0, ns, ns, 0, &M);
+  gdp_status st = mesh_new(ctx, nv, nv, 0, ns, ns, 0, &M, false);
   if (st != GDP_OK) return st;
   hipStream_t s = ctx->stream;
   std::vector<int32_t> spar(ns);
@@ -3284,7 +3404,16 @@ gdp_status gdp_mesh_create_device(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh *
   std::string e;
   int32_t nt = 0;
   DevCdtStats cs;
-  const int rc = dev_cdt_build(s, nv, M->m.vxy, ns, M->m.sv, M->m.tv, M->m.tn, M->m.ts, M->m.capT, &nt, &cs, e);
+  // the mesh's workspace is the builder's scratch until it is filled
+  DevCdtWork ws;
+  if (M->slab) {
+    ws.lent = true;
+    ws.mem = M->mark;
+    ws.bytes = (size_t)((char *)M->d_stat - (char *)M->mark);
+    ws.hctr = M->h_hist;
+  }
+  const int rc = dev_cdt_build(s, nv, M->m.vxy, ns, M->m.sv, M->m.tv, M->m.tn, M->m.ts, M->m.capT, &nt, &cs, e,
+                               M->slab ? &ws : nullptr);
   if (rc != GDP_OK) {
     mesh_delete(M);
     return fail(ctx, (gdp_status)rc, e);
@@ -3292,6 +3421,10 @@ gdp_status gdp_mesh_create_device(gdp_ctx *ctx, const gdp_pslg *pslg, gdp_mesh *
   M->m.nT = nt;
   M->cdt_rounds[0] = cs.dt_rounds;
   M->cdt_rounds[1] = cs.seg_rounds;
+  if (M->slab && (st = slab_fill(M, kMeshArrays, 1 << 30))) {
+    mesh_delete(M);
+    return st;
+  }
   *out = M;
   return GDP_OK;
 }
@@ -3311,11 +3444,7 @@ gdp_status gdp_mesh_upload(gdp_ctx *ctx, int32_t n_v, int32_t n_input_v, const d
   }
   for (int64_t i = 0; i < 2 * (int64_t)n_s; i++)
     if (sub_v[i] < 0 || sub_v[i] >= n_v) return fail(ctx, GDP_E_ARG, "subsegment vertex out of range");
-  for (int64_t i = 0; i < 2 * (int64_t)n_v; i++) {
-    double a = fabs(xy[i]);
-    if (!std::isfinite(xy[i]) || a > 0x1p20 || (a != 0.0 && a < 0x1p-100))
-      return fail(ctx, GDP_E_ARG, "coordinate out of range");
-  }
+  if (!coords_ok(xy, 2 * (int64_t)n_v)) return fail(ctx, GDP_E_ARG, "coordinate out of range");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, GDP_E_DEVICE, "hipSetDevice failed");
   return upload(ctx, n_v, n_input_v, xy, vkind, n_t, tri, nbr, sub_on_edge, n_s, n_input_s, sub_v, sub_parent,
                 sub_pending, rounds, out);
@@ -3685,6 +3814,15 @@ gdp_status gdp_mesh_clone(gdp_ctx *ctx, const gdp_mesh *src, gdp_mesh **out) {
   M->ctx = ctx;
   gdp_status st;
   auto chk = [&](hipError_t e) { return e == hipSuccess; };
+  if (slab_new(M, caps_of(src))) {
+    if ((st = alloc_host_mirrors(M)) || (st = slab_fill(M, 0, 1 << 30)) || (st = gdp_mesh_assign(ctx, M, src))) {
+      free_mesh_arrays(M);
+      delete M;
+      return st;
+    }
+    *out = M;
+    return GDP_OK;
+  }
   if ((st = grow_vtx(M, src->m.capV)) || (st = grow_tri(M, src->m.capT)) || (st = grow_seg(M, src->m.capS)) ||
       (st = grow_cand(M))) {
     free_mesh_arrays(M);

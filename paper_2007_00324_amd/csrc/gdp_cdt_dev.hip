@@ -1360,8 +1360,18 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   const size_t o_vals = take(4 * (size_t)capT), o_vals2 = take(4 * (size_t)capT), o_newid = take(4 * (size_t)capT);
   const size_t o_sort = take(4 * 256 * (size_t)((capT + kSortTile - 1) / kSortTile));
   const size_t o_seg = ns <= 2 * (int64_t)capT ? o_keys : take(sizeof(int2) * (size_t)ns);
+  static_assert(sizeof(Ctr) <= sizeof(DevCounters), "lent pinned memory holds the counters of a round");
   Ctr *hctr = nullptr;
-  if (ws) {
+  if (ws && ws->lent) {
+    if (ws->bytes < off) {
+      ws = nullptr;
+    } else {
+      mem = ws->mem;
+      hctr = (Ctr *)ws->hctr;
+    }
+  }
+  if (mem) {
+  } else if (ws) {
     // every earlier build on the workspace has finished (each one ends with
     // a stream synchronisation), so its scratch can be replaced
     if (ws->bytes < off) {

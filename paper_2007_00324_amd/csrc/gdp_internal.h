@@ -40,8 +40,10 @@ hipError_t sort_pairs_u64(hipStream_t stream, uint64_t *k0, int *v0, uint64_t *k
 // A reusable workspace for repeated builds (a long-lived caller such as the
 // server's Line-1 thread): device scratch that grows to the largest build
 // seen, and one pinned counter block.  Without one, a build allocates and
-// frees its own.
+// frees its own; so it does where lent memory (a caller's, never grown or
+// freed here) is too small.
 struct DevCdtWork {
+  bool lent = false;
   void *mem = nullptr;
   size_t bytes = 0;
   void *hctr = nullptr;
