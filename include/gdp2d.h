@@ -147,8 +147,11 @@ typedef struct {
                                many vertices get their initial CDT (Line 1) from
                                the device builder of gdp_mesh_create_device (the
                                same CDT), on library threads with streams of their
-                               own, while host threads build the others; 0 = every
-                               input on the host */
+                               own, while host threads build the others; 0 = chosen
+                               by the sizes: host threads for a batch of few
+                               vertices, the device for one of many, most of it by
+                               one workgroup for each mesh (the same CDT either
+                               way) */
 } gdp_params;
 
 /* Per-kernel totals of the last profiled gdp_mesh_refine. */

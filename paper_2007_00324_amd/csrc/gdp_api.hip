@@ -1500,6 +1500,18 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
 constexpr int64_t kBatchSplitFew = 4000, kBatchSplitMany = 8000;
 constexpr int kBatchGangRounds = 4;  // shared rounds between two host reads: no job waits to join a batch
 constexpr size_t kBatchGangMax = 256;  // batched meshes in one group of shared rounds, at most
+// Line 1 of a batch that leaves the choice open.  Sixteen host threads build
+// small meshes faster than a workgroup each does (0.45 us a vertex and thread
+// against 0.7 and 2 ms), many workgroups do more at once: 16 x 20,000 vertices
+// 62.9 ms on the host, 62.0 by workgroups, 128 x 2,000 458 and 456, 1,000 x 500
+// 243 and 231, 128 of 100 to 50,000 (1.03 million in all) 108 and 68 ms, while
+// 16 x 5,000 take 26 and 34.  So a batch of at least kBatchLine1DevTotal
+// vertices is built on the device: by a workgroup each up to kBatchLine1WgMax
+// vertices, above by the builder for one mesh (128 meshes again: 30,000: 69.4,
+// 40,000: 68.4, 70,000: 71.6 ms; the larger ones on the host instead: 75).
+constexpr int64_t kBatchLine1DevTotal = 400000;
+constexpr int32_t kBatchLine1WgMax = 40000;
+constexpr size_t kBatchLine1Scratch = (size_t)4 << 30;  // of workgroup builds that run at once
 constexpr int32_t kBatchLine1DevThreads = 8;  // device Line-1 builders of a batch, each on its own stream
 
 // The checks of the device builder's caller (gdp_mesh_create_device).
@@ -1569,7 +1581,9 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   }
   // Line 1.  Inputs with at least batch_line1_device_min_v vertices are
   // triangulated by the device builder (threads with a stream each, writing
-  // into the arena), the others on host threads, both at once.  The arena is
+  // into the arena), the others on host threads, both at once; without that
+  // parameter a batch of many vertices is built on the device, most of it by
+  // a workgroup for each mesh.  The arena is
   // sized before Line 1 from the input counts (a CDT of V vertices has at
   // most 2V triangles and keeps the input segments), with the device-built
   // meshes last in every array region so that the host-built ones are
@@ -1577,21 +1591,27 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   const int64_t dev_min = P->batch_line1_device_min_v;
   std::vector<int> rc(count, GDP_OK);
   std::vector<std::string> errs(count);
-  std::vector<int32_t> ok, ok_dev;
+  std::vector<int32_t> ok, ok_wg, ok_dev;
+  int64_t total_v = 0;
+  for (int32_t i = 0; i < count; i++) total_v += std::max(pslgs[i].n_vertices, 0);
   for (int32_t i = 0; i < count; i++) {
     const gdp_pslg &q = pslgs[i];
     if (q.n_vertices < 3 || !q.xy || q.n_segments < 0 || (q.n_segments > 0 && !q.seg)) {
       rc[i] = GDP_E_ARG;
       errs[i] = "bad arguments";
-    } else if (dev_min > 0 && q.n_vertices >= dev_min) {
+    } else if (dev_min > 0 ? q.n_vertices >= dev_min : total_v >= kBatchLine1DevTotal) {
       rc[i] = check_pslg_for_device(&q, errs[i]);
-      if (rc[i] == GDP_OK) ok_dev.push_back(i);
+      if (rc[i] == GDP_OK) (dev_min > 0 || q.n_vertices > kBatchLine1WgMax ? ok_dev : ok_wg).push_back(i);
     } else {
       ok.push_back(i);
     }
     if (rc[i] != GDP_OK && status) status[i] = (gdp_status)rc[i];
   }
   const int32_t n_host = (int32_t)ok.size();
+  int32_t n_wg = (int32_t)ok_wg.size();
+  // (workgroups start in order: the largest first)
+  std::stable_sort(ok_wg.begin(), ok_wg.end(), [&](int32_t a, int32_t b) { return pslgs[a].n_vertices > pslgs[b].n_vertices; });
+  ok.insert(ok.end(), ok_wg.begin(), ok_wg.end());
   ok.insert(ok.end(), ok_dev.begin(), ok_dev.end());
   if (elapsed_ms) *elapsed_ms = 0.0;
   if (ok.empty()) return GDP_OK;
@@ -1708,9 +1728,79 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
     ds.full = 1;
     memcpy(b + pk[k][C_ST], &ds, sizeof ds);
   };
+  // the workgroup builds: inputs packed by host threads, one copy, and builds
+  // (the last group of them runs on while the host goes on).  Without room for
+  // their scratch they go to the device builder's threads.
+  std::vector<DevCdtJob> wg_jobs(n_wg);
+  std::vector<DevCdtResult> wg_out(n_wg);
+  size_t wg_done = 0;  // results read
+  DevCdtResult *wg_res = nullptr;
+  char *wg_mem = nullptr;
+  std::unique_ptr<char[]> wg_pk;
+  if (n_wg > 0) {
+    std::vector<size_t> at(n_wg);
+    size_t in = 0;
+    for (int32_t q = 0; q < n_wg; q++) {
+      const gdp_pslg &g = pslgs[ok[n_host + q]];
+      const gdp_mesh *M = mesh[n_host + q];
+      at[q] = in;
+      in += align256(sizeof(double2) * (size_t)g.n_vertices) + align256(sizeof(int2) * (size_t)g.n_segments);
+      wg_jobs[q] = DevCdtJob{nullptr, nullptr, g.n_vertices, g.n_segments, M->m.vxy, M->m.sv, M->m.spar,
+                             M->m.tv, M->m.tn, M->m.ts, M->m.capT, M->d_st};
+    }
+    // groups of at most kBatchLine1Scratch bytes (or one mesh)
+    std::vector<size_t> group{0};
+    size_t scratch = 0;
+    for (size_t q = 0; q < wg_jobs.size();) {
+      size_t need = 0, e = q;
+      for (; e < wg_jobs.size(); e++) {
+        const size_t n1 = dev_cdt_batch_bytes(wg_jobs.data() + e, 1);
+        if (e > q && need + n1 > kBatchLine1Scratch) break;
+        need += n1;
+      }
+      scratch = std::max(scratch, align256(need));
+      group.push_back(q = e);
+    }
+    wg_pk.reset(new (std::nothrow) char[in]);
+    bool up = wg_pk && hipMalloc((void **)&wg_mem, scratch + in) == hipSuccess;
+    if (up) {
+      std::atomic<int32_t> next(0);
+      auto pack_in = [&]() {
+        for (int32_t q; (q = next.fetch_add(1)) < n_wg;) {
+          const gdp_pslg &g = pslgs[ok[n_host + q]];
+          memcpy(wg_pk.get() + at[q], g.xy, sizeof(double2) * (size_t)g.n_vertices);
+          if (g.n_segments)
+            memcpy(wg_pk.get() + at[q] + align256(sizeof(double2) * (size_t)g.n_vertices), g.seg,
+                   sizeof(int2) * (size_t)g.n_segments);
+        }
+      };
+      std::vector<std::thread> pool;
+      for (size_t t = 0; t < std::min<size_t>(7, in >> 20); t++) pool.emplace_back(pack_in);
+      pack_in();
+      for (auto &th : pool) th.join();
+      for (int32_t q = 0; q < n_wg; q++) {
+        const char *b = wg_mem + scratch + at[q];
+        wg_jobs[q].xy = (const double2 *)b;
+        wg_jobs[q].seg = (const int2 *)(b + align256(sizeof(double2) * (size_t)wg_jobs[q].nv));
+      }
+      up = hipMemcpyAsync(wg_mem + scratch, wg_pk.get(), in, hipMemcpyHostToDevice, s) == hipSuccess;
+      for (size_t g = 0; up && g + 1 < group.size(); g++) {
+        up = dev_cdt_batch(s, wg_jobs.data() + group[g], group[g + 1] - group[g], wg_mem, &wg_res) == GDP_OK;
+        if (!up || g + 2 == group.size()) break;
+        up = hipMemcpyAsync(&wg_out[wg_done], wg_res, sizeof(DevCdtResult) * (group[g + 1] - wg_done),
+                            hipMemcpyDeviceToHost, s) == hipSuccess &&
+             hipStreamSynchronize(s) == hipSuccess;
+        wg_done = group[g + 1];
+      }
+    }
+    if (!up) {
+      (void)hipGetLastError();
+      n_wg = 0;
+    }
+  }
   {
     std::atomic<int32_t> next_h(0), next_d(0);
-    const int32_t n_dev = n - n_host;
+    const int32_t n_dev = n - n_host - n_wg;
     unsigned nth = std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16));
     nth = std::min<unsigned>(nth, (unsigned)std::max(n_host, 1));
     const unsigned ndt = (unsigned)std::min<int32_t>(n_dev, kBatchLine1DevThreads);
@@ -1739,7 +1829,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
         DevCdtWork ws;
         if (hipStreamCreateWithFlags(&ds, hipStreamNonBlocking) != hipSuccess) ds = nullptr;
         for (int32_t q; (q = next_d.fetch_add(1)) < n_dev;) {
-          const int32_t k = n_host + q, i = ok[k];
+          const int32_t k = n_host + n_wg + q, i = ok[k];
           if (!ds) {
             rc[i] = GDP_E_DEVICE;
             errs[i] = "stream creation failed";
@@ -1754,6 +1844,23 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
         dev_cdt_work_free(ws);
       });
     for (auto &th : pool) th.join();
+  }
+  if (n_wg > 0) {
+    const bool got = hipMemcpyAsync(&wg_out[wg_done], wg_res, sizeof(DevCdtResult) * (n_wg - wg_done),
+                                    hipMemcpyDeviceToHost, s) == hipSuccess &&
+                     hipStreamSynchronize(s) == hipSuccess;
+    for (int32_t q = 0; q < n_wg; q++) {
+      const int32_t k = n_host + q, i = ok[k];
+      rc[i] = got ? dev_cdt_result(wg_out[q], errs[i]) : GDP_E_DEVICE;
+      if (rc[i] != GDP_OK) continue;
+      nT0[k] = wg_out[q].nt;
+      mesh[k]->cdt_rounds[0] = wg_out[q].dt_rounds;
+      mesh[k]->cdt_rounds[1] = wg_out[q].seg_rounds;
+    }
+  }
+  if (wg_mem) {
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(wg_mem);
   }
   // meshes whose Line 1 failed leave the batch (their arena room stays unused)
   std::vector<bool> live(n, true);

@@ -237,23 +237,34 @@ __global__ __launch_bounds__(kBlk) void k_box(const double2 *xy, int nv, unsigne
 }
 
 // 16-bit cells of the box per axis, interleaved.
-__global__ __launch_bounds__(kBlk) void k_morton(const double2 *xy, int nv, double x0, double y0, double sx, double sy,
+__device__ __forceinline__ uint32_t morton_of(double2 p, double x0, double y0, double sc) {
+  uint32_t c[2] = {(uint32_t)min(max((p.x - x0) * sc, 0.0), 65535.0), (uint32_t)min(max((p.y - y0) * sc, 0.0), 65535.0)};
+  for (int k = 0; k < 2; k++) {
+    uint32_t x = c[k];
+    x = (x | (x << 8)) & 0x00ff00ffu;
+    x = (x | (x << 4)) & 0x0f0f0f0fu;
+    x = (x | (x << 2)) & 0x33333333u;
+    x = (x | (x << 1)) & 0x55555555u;
+    c[k] = x;
+  }
+  return c[0] | (c[1] << 1);
+}
+__global__ __launch_bounds__(kBlk) void k_morton(const double2 *xy, int nv, double x0, double y0, double sc,
                                                  uint64_t *keys, int *vals) {
   const int stride = gridDim.x * blockDim.x;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
-    const double2 p = xy[i];
-    uint32_t c[2] = {(uint32_t)min(max((p.x - x0) * sx, 0.0), 65535.0), (uint32_t)min(max((p.y - y0) * sy, 0.0), 65535.0)};
-    for (int k = 0; k < 2; k++) {
-      uint32_t x = c[k];
-      x = (x | (x << 8)) & 0x00ff00ffu;
-      x = (x | (x << 4)) & 0x0f0f0f0fu;
-      x = (x | (x << 2)) & 0x33333333u;
-      x = (x | (x << 1)) & 0x55555555u;
-      c[k] = x;
-    }
-    keys[i] = c[0] | (c[1] << 1);
+    keys[i] = morton_of(xy[i], x0, y0, sc);
     vals[i] = i;
   }
+}
+
+__device__ __forceinline__ void first_triangle(const Bld &b, double2 *P, int *id, double L) {
+  P[b.nv] = make_double2(-4 * L, -4 * L);
+  P[b.nv + 1] = make_double2(8 * L, -4 * L);
+  P[b.nv + 2] = make_double2(-4 * L, 8 * L);
+  for (int k = 0; k < 3; k++) id[b.nv + k] = b.nv + k;
+  b.tv[0] = make_int4(b.nv, b.nv + 1, b.nv + 2, 0);
+  b.tn[0] = make_int4(-1, -1, -1, 0);
 }
 
 // The points along the curve, their ids, the inverse permutation and the
@@ -268,12 +279,7 @@ __global__ __launch_bounds__(kBlk) void k_reorder(Bld b, const double2 *xy, doub
     rank[v] = i;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    P[b.nv] = make_double2(-4 * L, -4 * L);
-    P[b.nv + 1] = make_double2(8 * L, -4 * L);
-    P[b.nv + 2] = make_double2(-4 * L, 8 * L);
-    for (int k = 0; k < 3; k++) id[b.nv + k] = b.nv + k;
-    b.tv[0] = make_int4(b.nv, b.nv + 1, b.nv + 2, 0);
-    b.tn[0] = make_int4(-1, -1, -1, 0);
+    first_triangle(b, P, id, L);
     b.c->ntri = 1;
   }
 }
@@ -672,26 +678,21 @@ __global__ __launch_bounds__(kSeedBlk) void k_dt_tail(Bld b, int cur, int stamp,
   }
 }
 
-// The sample: every step-th point along the curve, inserted round by round
-// in one workgroup, where a round costs barriers instead of launches (4,096
-// points 3.0 ms; with samples of 512, 1,024 or 2,048 and more rounds on the grid
-// a build of 60,013 points took 15.3, 14.7, 14.6 ms against 15.1 and one of a
-// million 38.6, 39.4, 38.7 against 37.6).  pend: two lists of ns entries.  Leaves the rounds in
-// nwin and the remaining points (0) in npend.
-__global__ __launch_bounds__(kSeedBlk) void k_dt_seed(Bld b, int ns, int step, int *pend0, int *pend1) {
-  __shared__ SeedShared sh;
-  __shared__ int s_ntri, s_left, s_err;
-  int *pend[2] = {pend0, pend1};
-  for (int i = threadIdx.x; i < ns; i += blockDim.x) {
-    pend0[i] = i * step;
-    b.loc[i * step] = 3;
-  }
-  if (threadIdx.x == 0) s_ntri = 1;
-  int np = ns, pc = 0, cur = 0, stamp = 0;
+// Inserts the np points of pend[0] (b.loc: a triangle to start from, times 4, +
+// 3) round by round in one workgroup, where a round costs barriers instead of
+// launches.  Returns the points left (0).
+struct InsertState {
+  int stamp = 0;
   uint32_t round = 0;
   uint64_t pass = 0;
+};
+__device__ __forceinline__ int wg_insert(const Bld &b, SeedShared &sh, int *s_ntri, int *pend0, int *pend1, int np,
+                                         InsertState &st) {
+  __shared__ int s_left, s_err;
+  int *pend[2] = {pend0, pend1};
+  int pc = 0, cur = 0;
   while (np > 0) {
-    round++;
+    st.round++;
     if (threadIdx.x == 0) {
       s_left = 0;
       sh.n[0] = 0;
@@ -702,26 +703,26 @@ __global__ __launch_bounds__(kSeedBlk) void k_dt_seed(Bld b, int ns, int step, i
     if (s_err) break;
     for (int base = 0; base < np; base += blockDim.x) {
       const int i = base + threadIdx.x;
-      dt_locate(b, i < np ? pend[pc][i] : 0, i < np, round);
+      dt_locate(b, i < np ? pend[pc][i] : 0, i < np, st.round);
     }
     __syncthreads();
-    stamp++;
+    st.stamp++;
     for (int base = 0; base < np; base += blockDim.x) {
       const int i = base + threadIdx.x;
       const int p = i < np ? pend[pc][i] : 0;
-      const bool done = dt_split<false>(b, p, i < np, round, stamp, &s_ntri, &sh.n[0]);
+      const bool done = dt_split<false>(b, p, i < np, st.round, st.stamp, s_ntri, &sh.n[0]);
       const int po = wave_take(&s_left, i < np && !done ? 1 : 0);
       if (i < np && !done) pend[pc ^ 1][po] = p;
     }
     __syncthreads();
     const int nl = sh.n[0];
-    for (int i = threadIdx.x; i < nl; i += blockDim.x) dt_fix(b, b.list[0][i], round);
+    for (int i = threadIdx.x; i < nl; i += blockDim.x) dt_fix(b, b.list[0][i], st.round);
     __syncthreads();
     cur = 0;
-    dt_flips(b, sh, cur, stamp, pass);
+    dt_flips(b, sh, cur, st.stamp, st.pass);
     __syncthreads();
     // every round inserts at least the point of the largest key
-    if (s_left >= np || pass > kPassMax) {
+    if (s_left >= np || st.pass > kPassMax) {
       if (threadIdx.x == 0) set_err(b.c, kEInternal + 6);
       np = s_left;
       break;
@@ -730,37 +731,57 @@ __global__ __launch_bounds__(kSeedBlk) void k_dt_seed(Bld b, int ns, int step, i
     pc ^= 1;
     __syncthreads();
   }
+  return np;
+}
+
+// The sample: every step-th point along the curve, in one workgroup (4,096
+// points 3.0 ms; with samples of 512, 1,024 or 2,048 and more rounds on the grid
+// a build of 60,013 points took 15.3, 14.7, 14.6 ms against 15.1 and one of a
+// million 38.6, 39.4, 38.7 against 37.6).  pend: two lists of ns entries.
+// Leaves the rounds in nwin and the remaining points (0) in npend.
+__global__ __launch_bounds__(kSeedBlk) void k_dt_seed(Bld b, int ns, int step, int *pend0, int *pend1) {
+  __shared__ SeedShared sh;
+  __shared__ int s_ntri;
+  for (int i = threadIdx.x; i < ns; i += blockDim.x) {
+    pend0[i] = i * step;
+    b.loc[i * step] = 3;
+  }
+  if (threadIdx.x == 0) s_ntri = 1;
+  InsertState st;
+  const int np = wg_insert(b, sh, &s_ntri, pend0, pend1, ns, st);
   if (threadIdx.x == 0) {
     b.c->ntri = s_ntri;
     b.c->npend = np;
-    b.c->nwin = (int)round;
-    b.c->first_stamp = stamp;
-    b.c->first_pass = (int)pass;
+    b.c->nwin = (int)st.round;
+    b.c->first_stamp = st.stamp;
+    b.c->first_pass = (int)st.pass;
   }
 }
 
 // Every other point starts at a triangle of the sample point before it.
+__device__ __forceinline__ void start_one(const Bld &b, int ns, int step, int *pend, int i) {
+  const int s = min(i / step, ns - 1), k = i - s * step;
+  if (k == 0) return;
+  b.loc[i] = 4 * b.vt[s * step] + 3;
+  pend[i - s - 1] = i;
+}
 __global__ __launch_bounds__(kBlk) void k_dt_start(Bld b, int ns, int step, int *pend) {
   const int stride = gridDim.x * blockDim.x;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < b.nv; i += stride) {
-    const int s = min(i / step, ns - 1), k = i - s * step;
-    if (k == 0) continue;
-    b.loc[i] = 4 * b.vt[s * step] + 3;
-    pend[i - s - 1] = i;
-  }
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < b.nv; i += stride) start_one(b, ns, step, pend, i);
 }
 
 // ---------------------------------------------------------------------------
 // Stage 2: segment recovery
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void vt_one(const Bld &b, int t) {
+  const int4 v = b.tv[t];
+  b.vt[v.x] = t;
+  b.vt[v.y] = t;
+  b.vt[v.z] = t;
+}
 __global__ void k_vt(Bld b, int nt) {
   const int stride = gridDim.x * blockDim.x;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += stride) {
-    const int4 v = b.tv[t];
-    b.vt[v.x] = t;
-    b.vt[v.y] = t;
-    b.vt[v.z] = t;
-  }
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += stride) vt_one(b, t);
 }
 
 // Around vertex a: the edge a-b (returns 1 with t, i of edge a->b or b->a),
@@ -810,7 +831,7 @@ __device__ int seg_walk(const Bld &b, int a, int bb, int t0, uint64_t key, int m
   auto stamp = [&](int t) -> bool {
     if (t < 0) return true;
     if (mode == 0) { atomicMax((unsigned long long *)&b.mark[t], (unsigned long long)key); return true; }
-    return b.mark[t] == key;
+    return __hip_atomic_load(&b.mark[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key;
   };
   if (!stamp(t0)) return -2;
   int4 v = b.tv[t0];
@@ -887,35 +908,37 @@ __global__ void k_seg_rank(const int2 *seg, int ns, const int *rank, int2 *out) 
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ns; i += stride) out[i] = make_int2(rank[seg[i].x], rank[seg[i].y]);
 }
 
+// A segment whose edge is there constrains it; another stamps what it crosses.
+__device__ __forceinline__ void seg_mark_one(const Bld &b, const int2 *seg, int s, uint32_t round, int *sstart) {
+  const int2 ab = seg[s];
+  int t = -1, e = -1;
+  const int r = around(b, ab.x, ab.y, t, e);
+  if (r < 0) { set_err(b.c, -r); sstart[s] = -1; return; }
+  if (r == 1) {
+    // the edge is there: constrain both sides
+    const int o = comp(b.tn[t], e);
+    const int prev = atomicCAS(comp_ptr(b.ts, t, e), -1, s);
+    if (prev != -1 && prev != s) set_err(b.c, kERepeat);
+    if (o >= 0) {
+      const int4 vt = b.tv[t];
+      const int oe = eidx(b.tv[o], comp(vt, (e + 1) % 3), comp(vt, e));
+      if (oe < 0) { set_err(b.c, kEInternal + 9); sstart[s] = -1; return; }
+      const int p2 = atomicCAS(comp_ptr(b.ts, o, oe), -1, s);
+      if (p2 != -1 && p2 != s) set_err(b.c, kERepeat);
+    }
+    sstart[s] = -1;
+    return;
+  }
+  const uint64_t key = ((uint64_t)round << 32) | mix32((uint32_t)s);
+  int m, n;
+  const int kc = seg_walk(b, ab.x, ab.y, t, key, 0, WalkOut{}, m, n);
+  if (kc < -2) { set_err(b.c, -kc - 16); sstart[s] = -1; return; }
+  sstart[s] = t;
+}
 __global__ void k_seg_mark(Bld b, const int2 *seg, const int *list, int nl, uint32_t round, int *sstart) {
   const int stride = gridDim.x * blockDim.x;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += stride) {
-    const int s = list[i];
-    const int2 ab = seg[s];
-    int t = -1, e = -1;
-    const int r = around(b, ab.x, ab.y, t, e);
-    if (r < 0) { set_err(b.c, -r); sstart[s] = -1; continue; }
-    if (r == 1) {
-      // the edge is there: constrain both sides
-      const int o = comp(b.tn[t], e);
-      const int prev = atomicCAS(comp_ptr(b.ts, t, e), -1, s);
-      if (prev != -1 && prev != s) set_err(b.c, kERepeat);
-      if (o >= 0) {
-        const int4 vt = b.tv[t];
-        const int oe = eidx(b.tv[o], comp(vt, (e + 1) % 3), comp(vt, e));
-        if (oe < 0) { set_err(b.c, kEInternal + 9); sstart[s] = -1; continue; }
-        const int p2 = atomicCAS(comp_ptr(b.ts, o, oe), -1, s);
-        if (p2 != -1 && p2 != s) set_err(b.c, kERepeat);
-      }
-      sstart[s] = -1;
-      continue;
-    }
-    const uint64_t key = ((uint64_t)round << 32) | mix32((uint32_t)s);
-    int m, n;
-    const int kc = seg_walk(b, ab.x, ab.y, t, key, 0, WalkOut{}, m, n);
-    if (kc < -2) { set_err(b.c, -kc - 16); sstart[s] = -1; continue; }
-    sstart[s] = t;
-  }
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += stride)
+    seg_mark_one(b, seg, list[i], round, sstart);
 }
 
 constexpr int kSegGrp = 8;
@@ -981,99 +1004,106 @@ __device__ int tri_poly(const Bld &b, int p, int q, const int *c, int m, const i
   return root;
 }
 
-// The segments that keep every stamp of their walk are inserted, kSegGrp lanes
-// to a segment.  Bound by the dependent loads of the longest segment (about
-// one microsecond for each triangle it crosses and walk).  One thread per
-// segment, which compared every chain edge with every crossed triangle for the
-// slits and scanned for each apex alone, took 1.83 ms a round of a million
-// points against 0.51 here.
+// Entry i of the list (act: i < nl) by its group of kSegGrp lanes, if it keeps
+// every stamp of its walk; else it goes to the next list.  All lanes of the
+// wave take part.
+__device__ __forceinline__ void seg_insert_group(const Bld &b, const int2 *seg, const int *list, int i, bool act,
+                                                 uint32_t round, const int *sstart, int *list_out, int *pool,
+                                                 int *npend, int *nwin) {
+  const int gl = __lane_id() & (kSegGrp - 1), g0 = __lane_id() - gl;
+  int s = -1, kc = -2, m = 0, n = 0, t0 = -1;
+  int2 ab = make_int2(0, 0);
+  uint64_t key = 0;
+  if (act) {
+    s = list[i];
+    t0 = sstart[s];
+    if (t0 < 0) act = false;  // constrained in place (or failed)
+  }
+  if (act) {
+    ab = seg[s];
+    key = ((uint64_t)round << 32) | mix32((uint32_t)s);
+    kc = seg_walk(b, ab.x, ab.y, t0, key, 1, WalkOut{}, m, n);
+    if (kc < -2) { set_err(b.c, -kc - 16); act = false; }
+  }
+  const bool win = act && kc > 0;
+  const int need = win ? kc + 3 * (m + 1) + 3 * (n + 1) + 4 * (kc + 2) + (m + n + 2) : 0;
+  const int po = __shfl(wave_take(pool, gl == 0 ? need : 0), g0);
+  const int lo = wave_take(npend, gl == 0 && act && !win ? 1 : 0);
+  if (gl == 0 && act && !win) list_out[lo] = s;
+  if (!win) return;
+  if (po + need > b.pool_cap) { set_err(b.c, kEInternal + 11); return; }
+  int *q = b.pool + po;
+  WalkOut w;
+  w.crossed = q; q += kc;
+  w.lc = q; q += m + 1;
+  w.lo = q; q += m + 1;
+  w.lcn = q; q += m + 1;
+  w.rc = q; q += n + 1;
+  w.ro = q; q += n + 1;
+  w.rcn = q; q += n + 1;
+  int *stk = q; q += 4 * (kc + 2);
+  int *rev = q;  // right chain reversed
+  int m2, n2;
+  if (seg_walk(b, ab.x, ab.y, t0, key, 2, w, m2, n2) != kc || m2 != m || n2 != n) { set_err(b.c, kEInternal + 12); return; }
+  // Where the crossed region wraps around a vertex, an edge of a chain has
+  // crossed triangles on both sides (a slit): it stays an edge of the new
+  // triangulation, linked between the two new triangles that carry it.
+  for (int x = gl; x < kc; x += kSegGrp) b.pick[w.crossed[x]] = key;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  bool slit = false;
+  for (int k = gl; k <= m + n + 1; k += kSegGrp) {
+    int *op = k <= m ? &w.lo[k] : &w.ro[k - m - 1];
+    if (*op >= 0 && b.pick[*op] == key) {
+      *op = -2;
+      slit = true;
+    }
+  }
+  slit = ((__ballot(slit) >> g0) & ((1u << kSegGrp) - 1)) != 0;
+  // right side: base b->a, chain R_n..R_1, out[i] = edge R_{n-i} -> R_{n+1-i}
+  for (int k = gl; k < n; k += kSegGrp) rev[k] = w.rc[n - 1 - k];
+  for (int k = gl; k <= n / 2; k += kSegGrp) {
+    const int x = n - k;
+    int t1 = w.ro[k]; w.ro[k] = w.ro[x]; w.ro[x] = t1;
+    int t2 = w.rcn[k]; w.rcn[k] = w.rcn[x]; w.rcn[x] = t2;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (gl == 0) atomicAdd(nwin, 1);
+  int next = 0;
+  const int rl = tri_poly(b, ab.x, ab.y, w.lc, m, w.lo, w.lcn, w.crossed, next, stk);
+  const int rr = tri_poly(b, ab.y, ab.x, rev, n, w.ro, w.rcn, w.crossed, next, stk);
+  if (next != kc) { set_err(b.c, kEInternal + 13); return; }
+  *comp_ptr(b.tn, rl, 0) = rr;
+  *comp_ptr(b.tn, rr, 0) = rl;
+  *comp_ptr(b.ts, rl, 0) = s;
+  *comp_ptr(b.ts, rr, 0) = s;
+  for (int x = 0; x < kc && slit; x++) {
+    const int t = w.crossed[x];
+    const int4 tv = b.tv[t];
+    for (int e = 0; e < 3; e++) {
+      if (*comp_ptr(b.tn, t, e) != -2) continue;
+      const int u = comp(tv, e), v = comp(tv, (e + 1) % 3);
+      int found = -1;
+      for (int y = 0; y < kc && found < 0; y++) {
+        const int ye = eidx(b.tv[w.crossed[y]], v, u);
+        if (ye >= 0) { found = y; *comp_ptr(b.tn, w.crossed[y], ye) = t; }
+      }
+      if (found < 0) { set_err(b.c, kEInternal + 15); continue; }
+      *comp_ptr(b.tn, t, e) = w.crossed[found];
+    }
+  }
+}
+
+// The segments of a round, kSegGrp lanes to each.  Bound by the dependent loads
+// of the longest segment (about one microsecond for each triangle it crosses
+// and walk).  One thread per segment, which compared every chain edge with
+// every crossed triangle for the slits and scanned for each apex alone, took
+// 1.83 ms a round of a million points against 0.51 here.
 __global__ __launch_bounds__(kBlk) void k_seg_insert(Bld b, const int2 *seg, const int *list, int nl, uint32_t round,
                                                      const int *sstart, int *list_out) {
   const int per = kBlk / kSegGrp, stride = gridDim.x * per;
-  const int gl = __lane_id() & (kSegGrp - 1), g0 = __lane_id() - gl;
   for (int base = blockIdx.x * per; base < nl; base += stride) {
     const int i = base + (int)threadIdx.x / kSegGrp;
-    bool act = i < nl;
-    int s = -1, kc = -2, m = 0, n = 0, t0 = -1;
-    int2 ab = make_int2(0, 0);
-    uint64_t key = 0;
-    if (act) {
-      s = list[i];
-      t0 = sstart[s];
-      if (t0 < 0) act = false;  // constrained in place (or failed)
-    }
-    if (act) {
-      ab = seg[s];
-      key = ((uint64_t)round << 32) | mix32((uint32_t)s);
-      kc = seg_walk(b, ab.x, ab.y, t0, key, 1, WalkOut{}, m, n);
-      if (kc < -2) { set_err(b.c, -kc - 16); act = false; }
-    }
-    const bool win = act && kc > 0;
-    const int need = win ? kc + 3 * (m + 1) + 3 * (n + 1) + 4 * (kc + 2) + (m + n + 2) : 0;
-    const int po = __shfl(wave_take(&b.c->pool, gl == 0 ? need : 0), g0);
-    const int lo = wave_take(&b.c->npend, gl == 0 && act && !win ? 1 : 0);
-    if (gl == 0 && act && !win) list_out[lo] = s;
-    if (!win) continue;
-    if (po + need > b.pool_cap) { set_err(b.c, kEInternal + 11); continue; }
-    int *q = b.pool + po;
-    WalkOut w;
-    w.crossed = q; q += kc;
-    w.lc = q; q += m + 1;
-    w.lo = q; q += m + 1;
-    w.lcn = q; q += m + 1;
-    w.rc = q; q += n + 1;
-    w.ro = q; q += n + 1;
-    w.rcn = q; q += n + 1;
-    int *stk = q; q += 4 * (kc + 2);
-    int *rev = q;  // right chain reversed
-    int m2, n2;
-    if (seg_walk(b, ab.x, ab.y, t0, key, 2, w, m2, n2) != kc || m2 != m || n2 != n) { set_err(b.c, kEInternal + 12); continue; }
-    // Where the crossed region wraps around a vertex, an edge of a chain has
-    // crossed triangles on both sides (a slit): it stays an edge of the new
-    // triangulation, linked between the two new triangles that carry it.
-    for (int x = gl; x < kc; x += kSegGrp) b.pick[w.crossed[x]] = key;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    bool slit = false;
-    for (int k = gl; k <= m + n + 1; k += kSegGrp) {
-      int *op = k <= m ? &w.lo[k] : &w.ro[k - m - 1];
-      if (*op >= 0 && b.pick[*op] == key) {
-        *op = -2;
-        slit = true;
-      }
-    }
-    slit = ((__ballot(slit) >> g0) & ((1u << kSegGrp) - 1)) != 0;
-    // right side: base b->a, chain R_n..R_1, out[i] = edge R_{n-i} -> R_{n+1-i}
-    for (int k = gl; k < n; k += kSegGrp) rev[k] = w.rc[n - 1 - k];
-    for (int k = gl; k <= n / 2; k += kSegGrp) {
-      const int x = n - k;
-      int t1 = w.ro[k]; w.ro[k] = w.ro[x]; w.ro[x] = t1;
-      int t2 = w.rcn[k]; w.rcn[k] = w.rcn[x]; w.rcn[x] = t2;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (gl == 0) atomicAdd(&b.c->nwin, 1);
-    int next = 0;
-    const int rl = tri_poly(b, ab.x, ab.y, w.lc, m, w.lo, w.lcn, w.crossed, next, stk);
-    const int rr = tri_poly(b, ab.y, ab.x, rev, n, w.ro, w.rcn, w.crossed, next, stk);
-    if (next != kc) { set_err(b.c, kEInternal + 13); continue; }
-    *comp_ptr(b.tn, rl, 0) = rr;
-    *comp_ptr(b.tn, rr, 0) = rl;
-    *comp_ptr(b.ts, rl, 0) = s;
-    *comp_ptr(b.ts, rr, 0) = s;
-    for (int x = 0; x < kc && slit; x++) {
-      const int t = w.crossed[x];
-      const int4 tv = b.tv[t];
-      for (int e = 0; e < 3; e++) {
-        if (*comp_ptr(b.tn, t, e) != -2) continue;
-        const int u = comp(tv, e), v = comp(tv, (e + 1) % 3);
-        int found = -1;
-        for (int y = 0; y < kc && found < 0; y++) {
-          const int ye = eidx(b.tv[w.crossed[y]], v, u);
-          if (ye >= 0) { found = y; *comp_ptr(b.tn, w.crossed[y], ye) = t; }
-        }
-        if (found < 0) { set_err(b.c, kEInternal + 15); continue; }
-        *comp_ptr(b.tn, t, e) = w.crossed[found];
-      }
-    }
+    seg_insert_group(b, seg, list, i, i < nl, round, sstart, list_out, &b.c->pool, &b.c->npend, &b.c->nwin);
   }
 }
 
@@ -1086,38 +1116,41 @@ __device__ __forceinline__ bool is_out(const Bld &b, int t) {
   return v.x >= b.nv || v.y >= b.nv || v.z >= b.nv;
 }
 
+// Whether triangle t stays; its sort key and hull edges.
+__device__ __forceinline__ bool keep_one(const Bld &b, int t, int *used, uint64_t &key, int &hull) {
+  if (is_out(b, t)) return false;
+  const int4 v = b.tv[t], n = b.tn[t], sg = b.ts[t];
+  used[v.x] = 1; used[v.y] = 1; used[v.z] = 1;
+  for (int e = 0; e < 3; e++) {
+    if (!is_out(b, comp(n, e))) continue;
+    hull++;
+    if (comp(sg, e) < 0) { set_err(b.c, kEHull); continue; }
+    // the boundary must turn left at its end vertex
+    const int u = comp(v, e), x = comp(v, (e + 1) % 3);
+    int cur = t, ce = (e + 1) % 3;
+    for (int guard = 0; guard < kWalkCap; guard++) {
+      const int o = comp(b.tn[cur], ce);
+      if (is_out(b, o)) break;
+      cur = o;
+      ce = vidx(b.tv[o], x);
+      if (ce < 0) { set_err(b.c, kEInternal + 14); ce = 0; break; }
+    }
+    const int y = comp(b.tv[cur], (ce + 1) % 3);
+    if (orient_ids(b.P, u, x, y) < 0) set_err(b.c, kEDisk);
+  }
+  const int4 w = make_int4(b.id[v.x], b.id[v.y], b.id[v.z], 0);
+  const int r = (w.y < w.x && w.y < w.z) ? 1 : ((w.z < w.x && w.z < w.y) ? 2 : 0);
+  key = ((uint64_t)(uint32_t)comp(w, r) << 32) | (uint32_t)comp(w, (r + 1) % 3);
+  return true;
+}
+
 __global__ __launch_bounds__(kBlk) void k_keep(Bld b, int nt, int *used, uint64_t *keys, int *vals) {
   const int stride = gridDim.x * blockDim.x;
   for (int base = blockIdx.x * blockDim.x; base < nt; base += stride) {
     const int t = base + threadIdx.x;
-    bool keep = false;
     int hull = 0;
     uint64_t key = 0;
-    if (t < nt && !is_out(b, t)) {
-      keep = true;
-      const int4 v = b.tv[t], n = b.tn[t], sg = b.ts[t];
-      used[v.x] = 1; used[v.y] = 1; used[v.z] = 1;
-      for (int e = 0; e < 3; e++) {
-        if (!is_out(b, comp(n, e))) continue;
-        hull++;
-        if (comp(sg, e) < 0) { set_err(b.c, kEHull); continue; }
-        // the boundary must turn left at its end vertex
-        const int u = comp(v, e), x = comp(v, (e + 1) % 3);
-        int cur = t, ce = (e + 1) % 3;
-        for (int guard = 0; guard < kWalkCap; guard++) {
-          const int o = comp(b.tn[cur], ce);
-          if (is_out(b, o)) break;
-          cur = o;
-          ce = vidx(b.tv[o], x);
-          if (ce < 0) { set_err(b.c, kEInternal + 14); ce = 0; break; }
-        }
-        const int y = comp(b.tv[cur], (ce + 1) % 3);
-        if (orient_ids(b.P, u, x, y) < 0) set_err(b.c, kEDisk);
-      }
-      const int4 w = make_int4(b.id[v.x], b.id[v.y], b.id[v.z], 0);
-      const int r = (w.y < w.x && w.y < w.z) ? 1 : ((w.z < w.x && w.z < w.y) ? 2 : 0);
-      key = ((uint64_t)(uint32_t)comp(w, r) << 32) | (uint32_t)comp(w, (r + 1) % 3);
-    }
+    const bool keep = t < nt && keep_one(b, t, used, key, hull);
     const int slot = block_take(&b.c->nkeep, keep ? 1 : 0);
     if (hull) atomicAdd(&b.c->nhull, hull);
     if (keep) { keys[slot] = key; vals[slot] = t; }
@@ -1135,26 +1168,28 @@ __global__ void k_newid(int nk, const int *vals, int *newid) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nk; k += stride) newid[vals[k]] = k;
 }
 
+__device__ __forceinline__ void emit_one(const Bld &b, int k, const int *vals, const int *newid, int4 *otv, int4 *otn,
+                                         int4 *ots) {
+  const int t = vals[k];
+  const int4 vr = b.tv[t], n = b.tn[t], sg = b.ts[t];
+  const int4 v = make_int4(b.id[vr.x], b.id[vr.y], b.id[vr.z], 0);
+  const int r = (v.y < v.x && v.y < v.z) ? 1 : ((v.z < v.x && v.z < v.y) ? 2 : 0);
+  int vv[3], nn[3], ss[3];
+  for (int i = 0; i < 3; i++) {
+    const int src = (r + i) % 3;
+    vv[i] = comp(v, src);
+    const int o = comp(n, src);
+    nn[i] = is_out(b, o) ? -1 : newid[o];
+    ss[i] = comp(sg, src);
+  }
+  const int mask = (ss[0] >= 0 ? 1 : 0) | (ss[1] >= 0 ? 2 : 0) | (ss[2] >= 0 ? 4 : 0);
+  otv[k] = make_int4(vv[0], vv[1], vv[2], mask);
+  otn[k] = make_int4(nn[0], nn[1], nn[2], 0);
+  ots[k] = make_int4(ss[0], ss[1], ss[2], 0);
+}
 __global__ void k_emit(Bld b, int nk, const int *vals, const int *newid, int4 *otv, int4 *otn, int4 *ots) {
   const int stride = gridDim.x * blockDim.x;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nk; k += stride) {
-    const int t = vals[k];
-    const int4 vr = b.tv[t], n = b.tn[t], sg = b.ts[t];
-    const int4 v = make_int4(b.id[vr.x], b.id[vr.y], b.id[vr.z], 0);
-    const int r = (v.y < v.x && v.y < v.z) ? 1 : ((v.z < v.x && v.z < v.y) ? 2 : 0);
-    int vv[3], nn[3], ss[3];
-    for (int i = 0; i < 3; i++) {
-      const int src = (r + i) % 3;
-      vv[i] = comp(v, src);
-      const int o = comp(n, src);
-      nn[i] = is_out(b, o) ? -1 : newid[o];
-      ss[i] = comp(sg, src);
-    }
-    const int mask = (ss[0] >= 0 ? 1 : 0) | (ss[1] >= 0 ? 2 : 0) | (ss[2] >= 0 ? 4 : 0);
-    otv[k] = make_int4(vv[0], vv[1], vv[2], mask);
-    otn[k] = make_int4(nn[0], nn[1], nn[2], 0);
-    ots[k] = make_int4(ss[0], ss[1], ss[2], 0);
-  }
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nk; k += stride) emit_one(b, k, vals, newid, otv, otn, ots);
 }
 
 // ---------------------------------------------------------------------------
@@ -1314,7 +1349,399 @@ __global__ void k_iota(int n, int *a) {
 
 int grid_for(int n, int blk) { return std::max(1, std::min((n + blk - 1) / blk, 4096)); }
 
+// The scratch of a build and its view; some arrays lie where another stage's
+// will be: the lists of the flip passes in the pool of the segment recovery
+// and in the sort buffers of the last stage, the points' walks under the
+// segments' starts, the split stamps under the new ids, the ranks under the
+// used marks, the renumbered segments in the sort keys (when they fit: a
+// planar set has fewer than 3 nv segments).  Returns the bytes (base may be
+// null).
+struct Scratch {
+  Bld b;
+  double2 *P;
+  int *id, *rank, *pl[2], *used, *vals, *vals2, *newid, *hist;
+  uint64_t *keys, *keys2;
+  unsigned long long *box;
+  int2 *sseg;
+};
+size_t cdt_scratch(int nv, int ns, char *base, Scratch &S) {
+  const int capT = 2 * nv + 8;
+  const int pool_cap = 16 * capT + 4096;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return base + o; };
+  Bld &b = S.b;
+  b.nv = nv;
+  b.capT = capT;
+  b.pool_cap = pool_cap;
+  b.tv = (int4 *)take(sizeof(int4) * capT);
+  b.tn = (int4 *)take(sizeof(int4) * capT);
+  b.ts = (int4 *)take(sizeof(int4) * capT);
+  b.pick = (uint64_t *)take(8 * (size_t)capT);
+  b.mark = (uint64_t *)take(8 * (size_t)capT);
+  b.loc = b.state = (int *)take(4 * (size_t)std::max(nv, ns));
+  b.vt = (int *)take(4 * (size_t)(nv + 3));
+  b.wstamp = (int *)take(4 * (size_t)capT);
+  b.pool = (int *)take(4 * (size_t)pool_cap);
+  S.P = (double2 *)take(sizeof(double2) * (size_t)(nv + 3));
+  S.id = (int *)take(4 * (size_t)(nv + 3));
+  S.pl[0] = (int *)take(4 * (size_t)std::max(nv, ns));
+  S.pl[1] = (int *)take(4 * (size_t)std::max(nv, ns));
+  b.c = (Ctr *)take(sizeof(Ctr));
+  S.box = (unsigned long long *)take(4 * 8);
+  S.used = S.rank = (int *)take(4 * (size_t)nv);
+  S.keys = (uint64_t *)take(8 * (size_t)capT);
+  S.keys2 = (uint64_t *)take(8 * (size_t)capT);
+  S.vals = (int *)take(4 * (size_t)capT);
+  S.vals2 = (int *)take(4 * (size_t)capT);
+  S.newid = (int *)take(4 * (size_t)capT);
+  S.hist = (int *)take(4 * 256 * (size_t)((capT + kSortTile - 1) / kSortTile));
+  S.sseg = ns <= 2 * (int64_t)capT ? (int2 *)S.keys : (int2 *)take(sizeof(int2) * (size_t)ns);
+  b.P = S.P;
+  b.id = S.id;
+  b.sstamp = S.newid;
+  b.fc0 = (int4 *)b.pool;
+  b.fc1 = b.fc0 + 2 * (size_t)capT;
+  b.grp = b.fc0;
+  b.fprio = S.keys;
+  b.list[0] = S.vals;
+  b.list[1] = S.vals2;
+  return off;
+}
+
+// ---------------------------------------------------------------------------
+// Many small builds at once: one workgroup to a mesh, all stages in it.
+// ---------------------------------------------------------------------------
+struct MeshJob {
+  Scratch S;
+  DevCdtJob j;
+};
+
+// Radix sort by the 8-bit digits at the given shifts, as k_sort_*: the digit
+// counts of all pairs, then the pairs in their order, a workgroup's worth at a
+// time.  Returns whether the result is in (k1, v1) (else (k0, v0)).
+struct SortShared {
+  int run[256], wcnt[kSeedBlk / 64][256];
+};
+__device__ bool wg_sort(SortShared &S, uint64_t *k0, int *v0, uint64_t *k1, int *v1, int n, int vbits, int halves) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  bool odd = false;
+  for (int half = 0; half < halves; half++)
+    for (int bit0 = 0; bit0 < vbits; bit0 += 8, odd = !odd) {
+      const uint64_t *kin = odd ? k1 : k0;
+      const int *vin = odd ? v1 : v0;
+      uint64_t *kout = odd ? k0 : k1;
+      int *vout = odd ? v0 : v1;
+      const int shift = 32 * half + bit0;
+      if (tid < 256) S.run[tid] = 0;
+      for (int i = tid; i < 256 * (kSeedBlk / 64); i += kSeedBlk) (&S.wcnt[0][0])[i] = 0;
+      __syncthreads();
+      for (int i = tid; i < n; i += kSeedBlk) atomicAdd(&S.run[(kin[i] >> shift) & 0xff], 1);
+      __syncthreads();
+      if (wave == 0) {  // exclusive scan, four digits to a lane
+        int c[4], sum = 0;
+        for (int q = 0; q < 4; q++) {
+          c[q] = S.run[4 * lane + q];
+          sum += c[q];
+        }
+        int x = sum;
+        for (int d = 1; d < 64; d <<= 1) {
+          const int y = __shfl_up(x, d);
+          if (lane >= d) x += y;
+        }
+        x -= sum;
+        for (int q = 0; q < 4; q++) {
+          S.run[4 * lane + q] = x;
+          x += c[q];
+        }
+      }
+      __syncthreads();
+      for (int base = 0; base < n; base += kSeedBlk) {
+        const int i = base + tid;
+        const bool act = i < n;
+        const uint64_t k = act ? kin[i] : 0ull;
+        const int v = act ? vin[i] : 0;
+        const int d = (int)((k >> shift) & 0xff);
+        uint64_t peers = __ballot(act);
+        for (int bit = 0; bit < 8; bit++) {
+          const uint64_t m = __ballot((d >> bit) & 1);
+          peers &= ((d >> bit) & 1) ? m : ~m;
+        }
+        const int rank = __popcll(peers & below);
+        if (act && rank == 0) S.wcnt[wave][d] = __popcll(peers);
+        __syncthreads();
+        if (act) {
+          int pos = S.run[d] + rank;
+          for (int w = 0; w < wave; w++) pos += S.wcnt[w][d];
+          kout[pos] = k;
+          vout[pos] = v;
+        }
+        __syncthreads();
+        if (tid < 256) {
+          int add = 0;
+          for (int w = 0; w < kSeedBlk / 64; w++) {
+            add += S.wcnt[w][tid];
+            S.wcnt[w][tid] = 0;
+          }
+          S.run[tid] += add;
+        }
+        __syncthreads();
+      }
+    }
+  return odd;
+}
+
+// Barrier after which plain loads see what atomics of other waves wrote.
+__device__ __forceinline__ void wg_sync() {
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// Whether a stage of the workgroup's mesh found an error (uniform).
+__device__ __forceinline__ bool wg_failed(const Ctr *c) {
+  __shared__ int s_err;
+  __syncthreads();
+  if (threadIdx.x == 0) s_err = __hip_atomic_load(&c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int e = s_err;
+  __syncthreads();
+  return e != 0;
+}
+
+// The stages are a launch each, a workgroup to a mesh, the scratch zero at
+// first; an error (c->err) skips the later ones.  Bound by the largest mesh:
+// 40,000 vertices take 25 ms of insertion (latency while the lists are short,
+// then the one workgroup's issue rate) and 5 ms of the rest, 128 meshes of 100
+// to 40,000 side by side no more.  All stages in one kernel kept so many
+// pointers that the insertion spilled: 36 ms for 50,004 points, of which the
+// sample took 8 instead of 3.  With 512 or 256 threads a batch of 128 takes 74
+// or 92 ms instead of 68.
+__global__ __launch_bounds__(kSeedBlk) void k_mesh_sort(const MeshJob *jobs) {
+  __shared__ SortShared so;
+  __shared__ unsigned long long s_box[4];
+  const MeshJob &J = jobs[blockIdx.x];
+  const Bld b = J.S.b;
+  const int nv = b.nv, tid = threadIdx.x;
+  const double2 *xy = J.j.xy;
+  if (tid < 4) s_box[tid] = 0;
+  __syncthreads();
+  {
+    unsigned long long m[4] = {0, 0, 0, 0};
+    for (int i = tid; i < nv; i += kSeedBlk) {
+      const double2 p = xy[i];
+      m[0] = max(m[0], ord_of(p.x));
+      m[1] = max(m[1], ord_of(p.y));
+      m[2] = max(m[2], ord_of(-p.x));
+      m[3] = max(m[3], ord_of(-p.y));
+    }
+    for (int k = 0; k < 4; k++) {
+      for (int d = 32; d >= 1; d >>= 1) {
+        const unsigned long long o = (unsigned long long)__shfl_xor((long long)m[k], d);
+        m[k] = max(m[k], o);
+      }
+      if (__lane_id() == 0) atomicMax(&s_box[k], m[k]);
+    }
+  }
+  __syncthreads();
+  double ext[4];
+  for (int k = 0; k < 4; k++) {
+    const unsigned long long o = s_box[k], u = (o >> 63) ? (o & ~(1ull << 63)) : ~o;
+    ext[k] = __longlong_as_double((long long)u);
+  }
+  const double x0 = -ext[2], y0 = -ext[3], side = max(max(ext[0] - x0, ext[1] - y0), 0x1p-100);
+  const double mx = max(max(max(1.0, fabs(x0)), fabs(ext[0])), max(fabs(y0), fabs(ext[1])));
+  int ex;
+  (void)frexp(mx, &ex);
+  const double L = ldexp(1.0, ex + 1);
+  for (int i = tid; i < nv; i += kSeedBlk) {
+    J.S.keys[i] = morton_of(xy[i], x0, y0, 65536.0 / side);
+    J.S.vals[i] = i;
+  }
+  __syncthreads();
+  (void)wg_sort(so, J.S.keys, J.S.vals, J.S.keys2, J.S.vals2, nv, 32, 1);  // (an even number of digits)
+  for (int i = tid; i < nv; i += kSeedBlk) {
+    const int v = J.S.vals[i];
+    J.S.P[i] = xy[v];
+    J.S.id[i] = v;
+    J.S.rank[v] = i;
+  }
+  if (tid == 0) first_triangle(b, J.S.P, J.S.id, L);
+}
+
+// Insertion: bound by latency while lists are short, then by the one
+// workgroup's issue rate.
+__global__ __launch_bounds__(kSeedBlk) void k_mesh_insert(const MeshJob *jobs) {
+  __shared__ SeedShared sh;
+  __shared__ int s_ntri;
+  const Bld b = jobs[blockIdx.x].S.b;
+  int *pl0 = jobs[blockIdx.x].S.pl[0], *pl1 = jobs[blockIdx.x].S.pl[1];
+  const int nv = b.nv, tid = threadIdx.x;
+  const int step = (nv + kSeedMax - 1) / kSeedMax, n_seed = (nv + step - 1) / step;
+  if (tid == 0) s_ntri = 1;
+  for (int i = tid; i < n_seed; i += kSeedBlk) {
+    pl0[i] = i * step;
+    b.loc[i * step] = 3;
+  }
+  __syncthreads();
+  InsertState st;
+  // the sample, then the other points
+  for (int part = 0; part < (n_seed < nv ? 2 : 1); part++) {
+    if (part == 1) {
+      __syncthreads();
+      for (int t = tid; t < s_ntri; t += kSeedBlk) vt_one(b, t);
+      __syncthreads();
+      for (int i = tid; i < nv; i += kSeedBlk) start_one(b, n_seed, step, pl0, i);
+      __syncthreads();
+    }
+    (void)wg_insert(b, sh, &s_ntri, pl0, pl1, part == 0 ? n_seed : nv - n_seed, st);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    if (s_ntri != 2 * nv + 1) set_err(b.c, kEInternal + 16);
+    b.c->ntri = s_ntri;
+    b.c->nwin = (int)st.round;
+  }
+}
+
+__global__ __launch_bounds__(kSeedBlk) void k_mesh_segs(const MeshJob *jobs, DevCdtResult *res) {
+  __shared__ int s_pool, s_npend, s_nwin;
+  const MeshJob &J = jobs[blockIdx.x];
+  const Bld b = J.S.b;
+  const int ns = J.j.ns, tid = threadIdx.x, nt = b.c->ntri, dt_rounds = b.c->nwin;
+  if (wg_failed(b.c)) {
+    if (tid == 0) res[blockIdx.x] = DevCdtResult{b.c->err, 0, 0, dt_rounds, 0};
+    return;
+  }
+  int seg_rounds = 0;
+  for (int t = tid; t < nt; t += kSeedBlk) {
+    vt_one(b, t);
+    b.ts[t] = make_int4(-1, -1, -1, -1);
+    b.mark[t] = 0;
+  }
+  for (int i = tid; i < ns; i += kSeedBlk) {
+    const int2 sg = J.j.seg[i];
+    J.S.sseg[i] = make_int2(J.S.rank[sg.x], J.S.rank[sg.y]);
+    J.S.pl[0][i] = i;
+  }
+  wg_sync();
+  uint32_t round = (uint32_t)dt_rounds;
+  for (int nl = ns, cur = 0; nl > 0; cur ^= 1) {
+    round++;
+    seg_rounds++;
+    if (tid == 0) s_pool = s_npend = s_nwin = 0;
+    for (int i = tid; i < nl; i += kSeedBlk) seg_mark_one(b, J.S.sseg, J.S.pl[cur][i], round, b.state);
+    wg_sync();
+    constexpr int per = kSeedBlk / kSegGrp;
+    for (int base = 0; base < nl; base += per) {
+      const int i = base + tid / kSegGrp;
+      seg_insert_group(b, J.S.sseg, J.S.pl[cur], i, i < nl, round, b.state, J.S.pl[cur ^ 1], &s_pool, &s_npend, &s_nwin);
+    }
+    wg_sync();
+    const int left = s_npend;
+    if (tid == 0 && left > 0 && s_nwin == 0 && left == nl) set_err(b.c, kEInternal + 17);
+    if (wg_failed(b.c)) break;
+    nl = left;
+  }
+  if (tid == 0)
+    res[blockIdx.x] =
+        DevCdtResult{__hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 1, 0, dt_rounds, seg_rounds};
+}
+
+// Outside removal and canonical order.
+__global__ __launch_bounds__(kSeedBlk) void k_mesh_final(const MeshJob *jobs, DevCdtResult *res) {
+  __shared__ SortShared so;
+  __shared__ int s_npend, s_nwin;
+  const MeshJob &J = jobs[blockIdx.x];
+  const Bld b = J.S.b;
+  const int nv = b.nv, ns = J.j.ns, tid = threadIdx.x, nt = b.c->ntri;
+  if (wg_failed(b.c)) return;
+  for (int i = tid; i < nv; i += kSeedBlk) J.S.used[i] = 0;
+  if (tid == 0) s_npend = s_nwin = 0;  // kept triangles, hull edges
+  wg_sync();
+  for (int base = 0; base < nt; base += kSeedBlk) {
+    const int t = base + tid;
+    int hull = 0;
+    uint64_t key = 0;
+    const bool keep = t < nt && keep_one(b, t, J.S.used, key, hull);
+    const int slot = wave_take(&s_npend, keep ? 1 : 0);
+    if (hull) atomicAdd(&s_nwin, hull);
+    if (keep) { J.S.keys[slot] = key; J.S.vals[slot] = t; }
+  }
+  __syncthreads();
+  for (int i = tid; i < nv; i += kSeedBlk)
+    if (!J.S.used[i]) set_err(b.c, kEUnused);
+  const int nk = s_npend;
+  if (!wg_failed(b.c) && tid == 0) {
+    if ((int64_t)nk != 2 * (int64_t)nv - s_nwin - 2) set_err(b.c, kEDisk);
+    else if (nk > J.j.cap_out) set_err(b.c, kEInternal + 18);
+  }
+  if (wg_failed(b.c)) {
+    if (tid == 0) {
+      res[blockIdx.x].stage = 2;
+      res[blockIdx.x].err = __hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return;
+  }
+  int vbits = 1;
+  while (vbits < 31 && (1 << vbits) < nv + 3) vbits++;
+  const int *vals = wg_sort(so, J.S.keys, J.S.vals, J.S.keys2, J.S.vals2, nk, vbits, 2) ? J.S.vals2 : J.S.vals;
+  for (int k = tid; k < nk; k += kSeedBlk) J.S.newid[vals[k]] = k;
+  __syncthreads();
+  for (int k = tid; k < nk; k += kSeedBlk) emit_one(b, k, vals, J.S.newid, J.j.tv, J.j.tn, J.j.ts);
+  for (int i = tid; i < nv; i += kSeedBlk) J.j.vxy[i] = J.j.xy[i];
+  for (int i = tid; i < ns; i += kSeedBlk) {
+    J.j.sv[i] = J.j.seg[i];
+    J.j.spar[i] = i;
+  }
+  if (tid == 0) {
+    DevState *d = J.j.st;
+    d->nV = nv;
+    d->nT = nk;
+    d->nS = ns;
+    d->wT = nk / 32 + 1;
+    d->wS = ns / 32 + 1;
+    d->full = 1;
+    res[blockIdx.x].nt = nk;
+  }
+}
+
 }  // namespace
+
+size_t dev_cdt_batch_bytes(const DevCdtJob *jobs, size_t n) {
+  auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  size_t bytes = 0;
+  Scratch S;
+  for (size_t i = 0; i < n; i++) bytes += up(cdt_scratch(jobs[i].nv, jobs[i].ns, nullptr, S));
+  return bytes + up(sizeof(MeshJob) * n) + up(sizeof(DevCdtResult) * n);
+}
+
+// Queues the builds of jobs (scratch: dev_cdt_batch_bytes bytes of device
+// memory); *res is their results in it, valid once the stream has finished.
+int dev_cdt_batch(hipStream_t stream, const DevCdtJob *jobs, size_t n, void *scratch, DevCdtResult **res) {
+  std::vector<MeshJob> d(n);
+  char *at = (char *)scratch;
+  for (size_t i = 0; i < n; i++) {
+    d[i].j = jobs[i];
+    at += (cdt_scratch(jobs[i].nv, jobs[i].ns, at, d[i].S) + 255) & ~(size_t)255;
+  }
+  MeshJob *dj = (MeshJob *)at;
+  *res = (DevCdtResult *)(at + ((sizeof(MeshJob) * n + 255) & ~(size_t)255));
+  if (hipMemsetAsync(scratch, 0, (size_t)(at - (char *)scratch), stream) != hipSuccess ||
+      hipMemcpyAsync(dj, d.data(), sizeof(MeshJob) * n, hipMemcpyHostToDevice, stream) != hipSuccess ||
+      hipStreamSynchronize(stream) != hipSuccess)  // d is a local
+    return GDP_E_DEVICE;
+  k_mesh_sort<<<(unsigned)n, kSeedBlk, 0, stream>>>(dj);
+  k_mesh_insert<<<(unsigned)n, kSeedBlk, 0, stream>>>(dj);
+  k_mesh_segs<<<(unsigned)n, kSeedBlk, 0, stream>>>(dj, *res);
+  k_mesh_final<<<(unsigned)n, kSeedBlk, 0, stream>>>(dj, *res);
+  return hipGetLastError() == hipSuccess ? GDP_OK : GDP_E_DEVICE;
+}
+
+int dev_cdt_result(const DevCdtResult &r, std::string &err) {
+  if (!r.err) return GDP_OK;
+  err = std::string(r.stage == 0 ? "points: " : (r.stage == 1 ? "segments: " : "final: ")) + cdt_err_string(r.err);
+  return r.err >= kEInternal ? GDP_E_DEVICE : GDP_E_INPUT;
+}
 
 // Sorts n (64-bit key, int) pairs by the whole key (8 digit passes); the
 // result ends in (k1, v1).  hist holds 256 * ceil(n / 2048) ints.
@@ -1339,27 +1766,9 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
                   int4 *otn, int4 *ots, int32_t cap_out, int32_t *n_tri, DevCdtStats *stats, std::string &err,
                   DevCdtWork *ws) {
   if (nv < 3) { err = "bad arguments"; return GDP_E_ARG; }
-  const int capT = 2 * nv + 8;
-  const int pool_cap = 16 * capT + 4096;
   void *mem = nullptr;
-  // layout; some arrays lie where another stage's will be: the points' walks
-  // under the segments' starts, the split stamps under the new ids, the ranks
-  // under the used marks, the renumbered segments in the sort keys (when they
-  // fit: a planar set has fewer than 3 nv segments)
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-  const size_t o_tv = take(sizeof(int4) * capT), o_tn = take(sizeof(int4) * capT), o_ts = take(sizeof(int4) * capT);
-  const size_t o_pick = take(8 * (size_t)capT), o_mark = take(8 * (size_t)capT);
-  const size_t o_state = take(4 * (size_t)std::max(nv, ns));
-  const size_t o_vt = take(4 * (size_t)(nv + 3)), o_wstamp = take(4 * (size_t)capT);
-  const size_t o_pool = take(4 * (size_t)pool_cap);
-  const size_t o_P = take(sizeof(double2) * (size_t)(nv + 3)), o_id = take(4 * (size_t)(nv + 3));
-  const size_t o_p0 = take(4 * (size_t)std::max(nv, ns)), o_p1 = take(4 * (size_t)std::max(nv, ns));
-  const size_t o_ctr = take(sizeof(Ctr)), o_box = take(4 * 8), o_used = take(4 * (size_t)nv);
-  const size_t o_keys = take(8 * (size_t)capT), o_keys2 = take(8 * (size_t)capT);
-  const size_t o_vals = take(4 * (size_t)capT), o_vals2 = take(4 * (size_t)capT), o_newid = take(4 * (size_t)capT);
-  const size_t o_sort = take(4 * 256 * (size_t)((capT + kSortTile - 1) / kSortTile));
-  const size_t o_seg = ns <= 2 * (int64_t)capT ? o_keys : take(sizeof(int2) * (size_t)ns);
+  Scratch S;
+  const size_t off = cdt_scratch(nv, ns, nullptr, S);
   static_assert(sizeof(Ctr) <= sizeof(DevCounters), "lent pinned memory holds the counters of a round");
   Ctr *hctr = nullptr;
   if (ws && ws->lent) {
@@ -1397,30 +1806,13 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
     }
     return rc;
   };
-  double2 *P = (double2 *)(base + o_P);
-  int *id = (int *)(base + o_id), *rank = (int *)(base + o_used);
-  Bld b;
-  b.P = P;
-  b.id = id;
-  b.nv = nv;
-  b.tv = (int4 *)(base + o_tv); b.tn = (int4 *)(base + o_tn); b.ts = (int4 *)(base + o_ts);
-  b.capT = capT;
-  b.pick = (uint64_t *)(base + o_pick); b.mark = (uint64_t *)(base + o_mark);
-  b.loc = b.state = (int *)(base + o_state);
-  b.vt = (int *)(base + o_vt);
-  b.pool = (int *)(base + o_pool); b.pool_cap = pool_cap;
-  b.c = (Ctr *)(base + o_ctr);
-  // the lists of the flip passes lie in the pool of the segment recovery and
-  // in the sort buffers of the last stage, which come after them
-  b.sstamp = (int *)(base + o_newid); b.wstamp = (int *)(base + o_wstamp);
-  b.fc0 = (int4 *)(base + o_pool);
-  b.fc1 = b.fc0 + 2 * (size_t)capT;
-  b.grp = b.fc0;
-  b.fprio = (uint64_t *)(base + o_keys);
-  b.list[0] = (int *)(base + o_vals);
-  b.list[1] = (int *)(base + o_vals2);
-  unsigned long long *box = (unsigned long long *)(base + o_box);
-  int *pl[2] = {(int *)(base + o_p0), (int *)(base + o_p1)};
+  (void)cdt_scratch(nv, ns, base, S);
+  const Bld b = S.b;
+  const int capT = b.capT;
+  double2 *P = S.P;
+  int *id = S.id, *rank = S.rank;
+  unsigned long long *box = S.box;
+  int *pl[2] = {S.pl[0], S.pl[1]};
   auto dev_err = [&](const char *what) { err = what; return done(GDP_E_DEVICE); };
   if (hipMemsetAsync(b.pick, 0, 8 * (size_t)capT, stream) != hipSuccess ||
       hipMemsetAsync(b.mark, 0, 8 * (size_t)capT, stream) != hipSuccess ||
@@ -1444,10 +1836,10 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   const double mx = std::max({1.0, std::fabs(x0), std::fabs(x1), std::fabs(y0), std::fabs(y1)});
   const double Lb = std::exp2(std::ceil(std::log2(mx)) + 1.0);
   const double side = std::max({x1 - x0, y1 - y0, 0x1p-100});
-  uint64_t *keys = (uint64_t *)(base + o_keys), *keys2 = (uint64_t *)(base + o_keys2);
-  int *vals = (int *)(base + o_vals), *vals2 = (int *)(base + o_vals2), *newid = (int *)(base + o_newid);
-  k_morton<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(d_xy, nv, x0, y0, 65536.0 / side, 65536.0 / side, keys, vals);
-  if (radix_sort_pairs(stream, keys, vals, keys2, vals2, nv, 32, (int *)(base + o_sort), 1) != hipSuccess)
+  uint64_t *keys = S.keys, *keys2 = S.keys2;
+  int *vals = S.vals, *vals2 = S.vals2, *newid = S.newid;
+  k_morton<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(d_xy, nv, x0, y0, 65536.0 / side, keys, vals);
+  if (radix_sort_pairs(stream, keys, vals, keys2, vals2, nv, 32, S.hist, 1) != hipSuccess)
     return dev_err("sort failed");
   k_reorder<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(b, d_xy, P, vals2, id, rank, Lb);
   // the sample in one workgroup, then every other point round by round
@@ -1480,7 +1872,7 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
     // rare one on an edge)
     int64_t est = 4 * std::min<int64_t>(np, hctr->ntri);
     k_dt_fix<<<grid_for((int)std::min<int64_t>(est, 1 << 30), kBlk), kBlk, 0, stream>>>(b, round);
-    for (int batch = 0;; batch++) {
+    for (;;) {
       if (pass > kPassMax) return dev_err("device CDT builder: flip passes did not converge");
       for (int q = 0; q < kPassBatch; q++) {
         pass++;
@@ -1512,7 +1904,7 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   const int nt = hctr->ntri;
   if (nt != 2 * nv + 1) { err = "device CDT builder: triangle count"; return done(GDP_E_DEVICE); }
   // segments, between the points' places along the curve
-  int2 *sseg = (int2 *)(base + o_seg);
+  int2 *sseg = S.sseg;
   k_vt<<<grid_for(nt, kBlk), kBlk, 0, stream>>>(b, nt);
   if (hipMemsetAsync(b.ts, 0xff, sizeof(int4) * (size_t)nt, stream) != hipSuccess ||
       hipMemsetAsync(b.mark, 0, 8 * (size_t)nt, stream) != hipSuccess)
@@ -1535,7 +1927,7 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
     cur ^= 1;
   }
   // outside removal and canonical order
-  int *used = (int *)(base + o_used);
+  int *used = S.used;
   if (hipMemsetAsync(used, 0, 4 * (size_t)nv, stream) != hipSuccess || hipMemsetAsync(b.c, 0, sizeof(Ctr), stream) != hipSuccess)
     { err = "device call failed"; return done(GDP_E_DEVICE); }
   k_keep<<<grid_for(nt, kBlk), kBlk, 0, stream>>>(b, nt, used, keys, vals);
@@ -1547,7 +1939,7 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   if (nk > cap_out) { err = "output capacity"; return done(GDP_E_NOMEM); }
   int vbits = 1;
   while (vbits < 31 && (1 << vbits) < nv + 3) vbits++;
-  if (radix_sort_pairs(stream, keys, vals, keys2, vals2, nk, vbits, (int *)(base + o_sort)) != hipSuccess)
+  if (radix_sort_pairs(stream, keys, vals, keys2, vals2, nk, vbits, S.hist) != hipSuccess)
     { err = "sort failed"; return done(GDP_E_DEVICE); }
   k_newid<<<grid_for(nk, kBlk), kBlk, 0, stream>>>(nk, vals2, newid);
   k_emit<<<grid_for(nk, kBlk), kBlk, 0, stream>>>(b, nk, vals2, newid, otv, otn, ots);

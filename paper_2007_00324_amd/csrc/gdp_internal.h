@@ -48,6 +48,26 @@ struct DevCdtWork {
   size_t bytes = 0;
   void *hctr = nullptr;
 };
+// One of many builds that run side by side, a workgroup each: input and
+// outputs (the arrays of a mesh, zero so far) in device memory.
+struct DevState;
+struct DevCdtJob {
+  const double2 *xy;
+  const int2 *seg;
+  int32_t nv, ns;
+  double2 *vxy;
+  int2 *sv;
+  int32_t *spar;
+  int4 *tv, *tn, *ts;
+  int32_t cap_out;
+  DevState *st;
+};
+struct DevCdtResult {
+  int32_t err, stage, nt, dt_rounds, seg_rounds;
+};
+size_t dev_cdt_batch_bytes(const DevCdtJob *jobs, size_t n);  // (of a part: at least its share)
+int dev_cdt_batch(hipStream_t stream, const DevCdtJob *jobs, size_t n, void *scratch, DevCdtResult **res);
+int dev_cdt_result(const DevCdtResult &r, std::string &err);  // GDP_OK, or the status and text of its error
 void dev_cdt_work_free(DevCdtWork &ws);
 int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, const int2 *d_seg, int4 *otv,
                   int4 *otn, int4 *ots, int32_t cap_out, int32_t *n_tri, DevCdtStats *stats, std::string &err,
