@@ -3767,7 +3767,7 @@ gdp_status gdp_mesh_quality_noalloc(gdp_ctx *ctx, const gdp_mesh *mesh, double r
   auto *n_part = (unsigned long long *)base;
   auto *a_part = (double *)((char *)base + sizeof(unsigned long long) * kQualBlocks);
   hipLaunchKernelGGL(k_quality, dim3(g), dim3(256), 0, s, mesh->m, ratio_bound_sq, max_edge_len_sq, n_part, a_part);
-  hipLaunchKernelGGL(k_quality_sum, dim3(1), dim3(64), 0, s, (int)g, n_part, a_part, d_n_bad, d_bad_area);
+  hipLaunchKernelGGL(k_quality_sum, dim3(1), dim3(256), 0, s, (int)g, n_part, a_part, d_n_bad, d_bad_area);
   if (hipGetLastError() != hipSuccess) return fail(ctx, GDP_E_DEVICE, "quality kernels failed to launch");
   return GDP_OK;
 }
@@ -3784,22 +3784,24 @@ gdp_status gdp_mesh_quality(gdp_ctx *ctx, const gdp_mesh *mesh, double ratio_bou
   const size_t bytes = (size_t)(kQualBlocks + 1) * (sizeof(unsigned long long) + sizeof(double));
   char *buf = nullptr;
   if (hipMalloc(&buf, bytes) != hipSuccess) return fail(ctx, GDP_E_NOMEM, "allocation failed");
+  // (the totals lie side by side: one copy)
   auto *n_part = (unsigned long long *)buf;
-  auto *a_part = (double *)(buf + sizeof(unsigned long long) * (kQualBlocks + 1));
+  auto *a_part = (double *)(n_part + kQualBlocks);
+  auto *total = (unsigned long long *)(a_part + kQualBlocks);
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kQualBlocks, ((int64_t)mesh->m.nT + 255) / 256));
   hipLaunchKernelGGL(k_quality, dim3(g), dim3(256), 0, s, mesh->m, ratio_bound_sq, max_edge_len_sq, n_part, a_part);
-  hipLaunchKernelGGL(k_quality_sum, dim3(1), dim3(64), 0, s, (int)g, n_part, a_part, n_part + kQualBlocks,
-                     a_part + kQualBlocks);
-  unsigned long long hn = 0;
-  double ha = 0.0;
+  hipLaunchKernelGGL(k_quality_sum, dim3(1), dim3(256), 0, s, (int)g, n_part, a_part, total, (double *)(total + 1));
+  struct {
+    unsigned long long n = 0;
+    double a = 0.0;
+  } h;
   bool ok = hipGetLastError() == hipSuccess &&
-            hipMemcpyAsync(&hn, n_part + kQualBlocks, sizeof hn, hipMemcpyDeviceToHost, s) == hipSuccess &&
-            hipMemcpyAsync(&ha, a_part + kQualBlocks, sizeof ha, hipMemcpyDeviceToHost, s) == hipSuccess &&
+            hipMemcpyAsync(&h, total, sizeof h, hipMemcpyDeviceToHost, s) == hipSuccess &&
             hipStreamSynchronize(s) == hipSuccess;
   (void)hipFree(buf);
   if (!ok) return fail(ctx, GDP_E_DEVICE, "quality kernels failed");
-  *n_bad = (int64_t)hn;
-  *bad_area = ha;
+  *n_bad = (int64_t)h.n;
+  *bad_area = h.a;
   return GDP_OK;
 }
 

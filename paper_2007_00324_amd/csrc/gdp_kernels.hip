@@ -2462,17 +2462,41 @@ __global__ void k_scatter_copy(const int32_t *src, const CopyEnt *ents, int n) {
   }
 }
 
-__global__ void k_quality_sum(int n_part, const unsigned long long *n_in, const double *a_in,
-                              unsigned long long *n_out, double *a_out) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// One workgroup.  The areas are added one after the other in the order of the
+// workgroups, which is what bounds it: the partials come to LDS side by side,
+// and one thread adds them eight loads ahead (512 partials: 9 us; loaded by the
+// adding thread one by one, 55 us).
+__global__ __launch_bounds__(256) void k_quality_sum(int n_part, const unsigned long long *n_in, const double *a_in,
+                                                     unsigned long long *n_out, double *a_out) {
+  __shared__ __attribute__((aligned(16))) double s_a[kQualBlocks];
+  __shared__ unsigned long long s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   unsigned long long n = 0;
   double a = 0.0;
-  for (int i = 0; i < n_part; i++) {
+  const int m = min(n_part, kQualBlocks);
+  for (int i = threadIdx.x; i < m; i += 256) {
     n += n_in[i];
-    a += a_in[i];
+    s_a[i] = a_in[i];
   }
-  *n_out = n;
-  *a_out = a;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int i = 0;
+    for (; i + 8 <= m; i += 8) {
+      double x[8];
+#pragma unroll
+      for (int k = 0; k < 8; k++) x[k] = s_a[i + k];
+#pragma unroll
+      for (int k = 0; k < 8; k++) a += x[k];
+    }
+    for (; i < m; i++) a += s_a[i];
+  }
+  atomicAdd(&s_n, n);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    *n_out = s_n;
+    *a_out = a;
+  }
 }
 
 // ---------------------------------------------------------------------------
