@@ -429,11 +429,11 @@ def batched_leg(ctx, ps, plain_every: int, line1_dev_min: int = 0) -> dict:
     bad = sum(1 for s_ in st if s_ != 0)
     steiner = sum(m.info()["n_vertices"] - p.n_vertices for m, p in zip(meshes, ps) if m is not None)
     del meshes
-    log(f"batched (tuned: engine up to {prm.batch_engine_max_v or 'all'} input vertices, shared rounds above): "
+    log(f"batched (tuned: engine up to {prm.batch_engine_max_v or 500} input vertices, shared rounds above): "
         f"{count:,} jobs, device {dev_ms:.1f} ms, call {wall:.2f} s (host CDT, upload, download), {bad} not OK")
     m2, st2, default_ms = gdp2d.gdp_refine_batch(ctx, inputs, bsq, default_prm)
     del m2
-    log(f"batched (default: every mesh in the engine): device {default_ms:.1f} ms")
+    log(f"batched (the library's default): device {default_ms:.1f} ms")
     line1_dev = None
     if line1_dev_min > 0:
         prm_dev = tune_batch.tuned_params(table)

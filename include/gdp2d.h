@@ -121,7 +121,7 @@ typedef struct {
                                run in shared rounds (each phase one launch for all
                                of them, over the whole chip), the others one
                                workgroup each in the single-workgroup engine;
-                               0 = chosen by the number of meshes */
+                               0 = 500 */
   /* perf only */
   int32_t cavity_thread_cap;  /* per-thread cavity slots of the grid path (0 = 39;
                                12, 24 or 39): larger cavities go to the cooperative

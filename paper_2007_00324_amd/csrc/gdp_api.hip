@@ -135,7 +135,6 @@ struct gdp_mesh {
   int32_t pool_cap = 0;
   FanRec *fan = nullptr;
   int32_t fan_cap = 0;
-  int32_t *big = nullptr;
   int32_t *hvis = nullptr, *hlist = nullptr;  // [capT] cavities beyond the LDS list (device-memory path)
   bool huge_mode = false;  // launch the device-memory cavity path (set once a round needed it)
   bool engine_off = false; // a single-workgroup engine round met a cavity beyond its LDS list
@@ -387,7 +386,6 @@ gdp_status grow_cand(gdp_mesh *M) {
   HIPCHECK(dgrow(M, &M->win_fresh, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(M, &M->fan_off, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(M, &M->fan_len, keep, nc, keep, 0, s));
-  HIPCHECK(dgrow(M, &M->big, keep, nc, keep, 0, s));
   HIPCHECK(dgrow(M, &M->keys, keep, nc, keep, 0, s));
   int64_t nt = nc / kScanTileSize + 2;
   HIPCHECK(dgrow(M, &M->tiles_t, 0, nt, 0, 0, s));
@@ -448,7 +446,8 @@ Work make_work(gdp_mesh *M, const gdp_params *P, int parity) {
   w.repl = M->repl;
   w.pool = M->pool; w.pool_cap = M->pool_cap;
   w.fan = M->fan; w.fan_cap = M->fan_cap;
-  w.big = M->big; w.big_cap = M->wT;
+  // (the queue of large cavities is done with before the fan lengths are written)
+  w.big = M->fan_len; w.big_cap = M->wT;
   w.hvis = M->hvis; w.hlist = M->hlist; w.hcap = M->m.capT;
   w.huge_ok = M->huge_mode ? 1 : 0;
   w.tstamp = M->tstamp;
@@ -532,7 +531,7 @@ void free_mesh_arrays(gdp_mesh *M) {
                   M->cc.elem, M->cc.key, M->cc.p, M->cc.loc, M->cc.state, M->cc.off, M->cc.len,
                   M->mid.elem, M->mid.key, M->mid.p, M->mid.loc, M->mid.state, M->mid.off, M->mid.len,
                   M->w0_t, M->w0_s, M->win_t, M->win_s, M->win_h, M->rank_t, M->rank_s, M->rank_h, M->w0_list, M->win_rank,
-                  M->win_fresh, M->fan_off, M->fan_len, M->repl, M->pool, M->fan, M->big, M->keys, M->rhist, M->sel,
+                  M->win_fresh, M->fan_off, M->fan_len, M->repl, M->pool, M->fan, M->keys, M->rhist, M->sel,
                   M->d_st, M->d_hist, M->tiles_t, M->tiles_s, M->tiles_h, M->prev_cc_elem, M->prev_cc_key, M->prev_cc_p, M->prev_mid_elem, M->tstamp,
                   M->cidx_t, M->cidx_s, M->hvis, M->hlist};
   for (void *p : ptrs) dfree(M, p);
@@ -626,7 +625,6 @@ void for_each_array(gdp_mesh *M, const Caps &c, F f) {
   f((void **)&M->win_fresh, 4, c.W, 0);
   f((void **)&M->fan_off, 4, c.W, 0);
   f((void **)&M->fan_len, 4, c.W, 0);
-  f((void **)&M->big, 4, c.W, 0);
   f((void **)&M->keys, 8, c.W, 0);
   f((void **)&M->tiles_t, 4, c.tiles, 0);
   f((void **)&M->tiles_s, 4, c.tiles, 0);
@@ -1349,9 +1347,9 @@ void gang_round(hipStream_t s, const GangBufs &B, unsigned n, const GangGrids &g
   const GangDesc *D = B.d_desc;
   const int32_t *me = B.d_map + g.off[kGangElem], *mg = B.d_map + g.off[kGangGroup], *mf = B.d_map + g.off[kGangFinish];
   const dim3 ge(g.n[kGangElem]), gg(g.n[kGangGroup]);
-  // cooperative cavities: one workgroup fills a compute unit's LDS, so they
-  // share the chip's 256 between the meshes
-  const unsigned nbig = std::max(1u, 256u / n);
+  // (cooperative cavities: as many workgroups as fit on the chip, two to a
+  // compute unit's LDS)
+  const unsigned nbig = 512;
   hipLaunchKernelGGL(kg_collect, ge, dim3(bs), 0, s, D, me);
   hipLaunchKernelGGL(kg_pending, ge, dim3(bs), 0, s, D, me);
   hipLaunchKernelGGL(kg_gate, dim3(1, n), dim3(256), 0, s, D);
@@ -1367,10 +1365,10 @@ void gang_round(hipStream_t s, const GangBufs &B, unsigned n, const GangGrids &g
   if (any_pre)
     for (int mode = 0; mode < 6; mode++) hipLaunchKernelGGL(kg_prefilter, ge, dim3(128), 0, s, D, me, mode);
   hipLaunchKernelGGL(kg_cavity<1>, gg, dim3(kCavBlockSize), 0, s, D, mg);
-  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig, n), dim3(kBigBlockSize), 0, s, D, 0);
+  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig), dim3(kBigBlockSize), 0, s, D, (int)n, 0);
   if (any_huge) hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 0);
   hipLaunchKernelGGL(kg_cavity<0>, gg, dim3(kCavBlockSize), 0, s, D, mg);
-  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig, n), dim3(kBigBlockSize), 0, s, D, 1);
+  hipLaunchKernelGGL(kg_cavity_big, dim3(nbig), dim3(kBigBlockSize), 0, s, D, (int)n, 1);
   if (any_huge) hipLaunchKernelGGL(kg_cavity_huge, dim3(1, n), dim3(kHugeBlock), 0, s, D, 1);
   hipLaunchKernelGGL(kg_own, ge, dim3(bs), 0, s, D, me);
   hipLaunchKernelGGL(kg_dep, gg, dim3(bs), 0, s, D, mg);
@@ -1490,14 +1488,15 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
 
 // Input vertices above which a batched mesh runs in shared rounds when the
 // caller leaves the choice to the library: the engine takes as long as its
-// largest mesh on one compute unit (4,000 points 11 ms, 50,000 points 96 ms),
-// the shared rounds about 0.2 ms a round for all their meshes.  128 meshes of
-// 100 to 50,000 points take 110 ms of device time in the engine alone, 51 in
-// shared rounds alone, 44 / 46 / 42 / 49 split at 1,000 / 2,000 / 4,000 /
-// 8,000.  With more meshes than compute units the engine is busy with several
-// each, and larger ones stay in it: 768 such meshes take 128 ms in the engine
-// alone, 132 split at 4,000, 100 at 8,000.
-constexpr int64_t kBatchSplitFew = 4000, kBatchSplitMany = 8000;
+// slowest mesh on one compute unit (4,000 points 11 ms, 50,000 points 96 ms, a
+// mesh with thousands of large cavities, which it grows one after the other,
+// a second), the shared rounds about 0.2 ms a round for all their meshes.
+// Device ms with the line at 250 / 500 / 1,000 / 2,000 / 4,000 vertices and
+// with every mesh in the engine: 128 meshes of 100 to 50,000 uniform points
+// 19.4 / 19.9 / 21.6 / 21.7 / 27.7 / 102; 256 of the mixed workload 58 / 58 /
+// 214 / 209 / 208 / 2,174; 1,024 of it 106 / 107 / 102 / 98 / 91 / 133 and,
+// with another seed, 217 / 215 / 214 / 210 / 382 / 723.
+constexpr int64_t kBatchSplit = 500;
 constexpr int kBatchGangRounds = 4;  // shared rounds between two host reads: no job waits to join a batch
 constexpr size_t kBatchGangMax = 256;  // batched meshes in one group of shared rounds, at most
 // Line 1 of a batch that leaves the choice open.  Sixteen host threads build
@@ -1916,7 +1915,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   // (every phase one launch for all of them, the whole chip per round), the
   // others one workgroup each in the engine launch.  Either way each mesh is
   // the plain loop's.
-  const int64_t split = P->batch_engine_max_v > 0 ? P->batch_engine_max_v : (n <= 256 ? kBatchSplitFew : kBatchSplitMany);
+  const int64_t split = P->batch_engine_max_v > 0 ? P->batch_engine_max_v : kBatchSplit;
   std::vector<int32_t> order, gang_k;
   for (int32_t k = 0; k < n; k++)
     if (live[k]) (pslgs[ok[k]].n_vertices > split ? gang_k : order).push_back(k);
@@ -2653,7 +2652,8 @@ void job_caps(gdp_server *S, Job *J, int64_t nV, int64_t nT, int64_t nS) {
   c.S = 16 * nS + 64;
   c.W = c.T + 2 * c.S + 2;
   c.tiles = c.W / kScanTileSize + 2;
-  c.pool = 2 * c.T + 4096;
+  // (the hull midpoints' bitmap and its ranks come out of the pool's room)
+  c.pool = 2 * c.T + 4096 - 2 * (int64_t)(align256(4 * (size_t)(c.S / 32 + 1)) / 4);
   c.fan = 2 * c.T + 4096;
   J->caps = c;
   gdp_mesh tmp;

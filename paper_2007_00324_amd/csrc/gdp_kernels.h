@@ -162,7 +162,7 @@ __global__ void kg_locate(const GangDesc *G, const int32_t *map);
 __global__ void kg_prefilter(const GangDesc *G, const int32_t *map, int mode);
 template <int IS_CC>
 __global__ void kg_cavity(const GangDesc *G, const int32_t *map);
-__global__ void kg_cavity_big(const GangDesc *G, int phase);
+__global__ void kg_cavity_big(const GangDesc *G, int n, int phase);
 __global__ void kg_cavity_huge(const GangDesc *G, int phase);
 __global__ void kg_own(const GangDesc *G, const int32_t *map);
 __global__ void kg_dep(const GangDesc *G, const int32_t *map);

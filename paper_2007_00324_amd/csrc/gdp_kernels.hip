@@ -3027,16 +3027,39 @@ __global__ __launch_bounds__(kCavBlock, 5) void kg_cavity(const GangDesc *G, con
 template __global__ void kg_cavity<0>(const GangDesc *G, const int32_t *map);
 template __global__ void kg_cavity<1>(const GangDesc *G, const int32_t *map);
 
-__global__ __launch_bounds__(kBigBlock) void kg_cavity_big(const GangDesc *G, int phase) {
+// The large cavities of all n meshes, shared out one by one over the
+// workgroups: a mesh's queue length is known on the device only, and the
+// meshes differ (most have none, one can have thousands).  Every workgroup
+// sums the queues of kBigBlock meshes at a time and finds its entries by the
+// sums.  A fixed 256 / n workgroups for each mesh instead left a round of 64
+// or 256 meshes waiting for one of them.
+__global__ __launch_bounds__(kBigBlock) void kg_cavity_big(const GangDesc *G, int n, int phase) {
   __shared__ BigShared sh;
-  GANG_MESH
-  if (w.st->halt) return;
-  int nbig = min(w.cnt->nbig, w.big_cap);
-  for (int b = blockIdx.x; b < nbig; b += gridDim.x) {
-    int ref = w.big[b];
-    int is_cc = (ref & 0x80000000) ? 0 : 1;
-    if (is_cc != (phase == 0 ? 1 : 0)) continue;
-    big_one(m, w, sh, b);
+  __shared__ int s_first[kBigBlock], s_total;
+  for (int base = 0; base < n; base += kBigBlock) {
+    const int q = base + (int)threadIdx.x;
+    int len = 0;
+    if (q < n) {
+      const Work &w = G[q].e.w[0];  // (the counters are the same for both parities)
+      if (!w.st->halt) len = min(w.cnt->nbig, w.big_cap);
+    }
+    const int first = block_excl_scan(len, &s_total);
+    s_first[threadIdx.x] = first;
+    __syncthreads();
+    const int total = s_total;
+    for (int i = blockIdx.x; i < total; i += gridDim.x) {
+      int lo = 0, hi = kBigBlock - 1;  // the last mesh whose entries start at or before i
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_first[mid] <= i) lo = mid;
+        else hi = mid - 1;
+      }
+      const int e = i - s_first[lo];
+      GANG_MESH_OF(__builtin_amdgcn_readfirstlane(base + lo))
+      const int is_cc = (w.big[e] & 0x80000000) ? 0 : 1;
+      if (is_cc == (phase == 0 ? 1 : 0)) big_one(m, w, sh, e);
+      __syncthreads();
+    }
     __syncthreads();
   }
 }

@@ -27,15 +27,17 @@ import time
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tuning", "batch.json")
 # size classes of the batched workload (input vertices, log-uniform 100..50,000)
-CLASS_EDGES = [100, 1_000, 3_000, 10_000, 25_000, 50_001]
-SPLITS = [0, 25_000, 10_000, 3_000, 1_000]      # 0: every mesh in the engine
+CLASS_EDGES = [100, 250, 1_000, 3_000, 10_000, 25_000, 50_001]
+ENGINE_ALL = 1 << 30
+# 0: the library's own choice
+SPLITS = [0, ENGINE_ALL, 25_000, 10_000, 3_000, 1_000, 250]
 ROUNDS = [2, 4]
 
 
 def classes_for(split: int) -> list[dict]:
     out = []
     for lo, hi in zip(CLASS_EDGES[:-1], CLASS_EDGES[1:]):
-        path = "engine" if split == 0 or hi - 1 <= split else "shared rounds"
+        path = "library's choice" if split == 0 else ("engine" if hi - 1 <= split else "shared rounds")
         out.append({"input_vertices": [lo, hi - 1], "path": path})
     return out
 
@@ -79,26 +81,28 @@ def main() -> int:
     args = ap.parse_args()
     import workloads
     t = time.perf_counter()
-    ps = workloads.batch_config3(args.sample, seed=args.seed, workers=args.workers)
-    print(f"[tune] sample of {len(ps)} PSLGs in {time.perf_counter() - t:.1f} s", file=sys.stderr, flush=True)
+    # two samples: a mesh with thousands of large cavities in one of them may
+    # decide its time
+    samples = [workloads.batch_config3(args.sample, seed=sd, workers=args.workers) for sd in (args.seed, args.seed + 46)]
+    ps = [p for sample in samples for p in sample]
+    print(f"[tune] samples of {len(ps)} PSLGs in {time.perf_counter() - t:.1f} s", file=sys.stderr, flush=True)
     import torch
     from paper_2007_00324_amd import gdp2d
     assert torch.cuda.is_available(), "the tuner measures on a HIP device"
     ctx = gdp2d.Context(0)
-    inputs = [(p.xy, p.seg) for p in ps]
-    bsq = [p.ratio_bound_sq for p in ps]
-    gdp2d.gdp_refine_batch(ctx, inputs[:16], bsq[:16], gdp2d.make_params())  # warm-up
+    calls = [([(p.xy, p.seg) for p in sample], [p.ratio_bound_sq for p in sample]) for sample in samples]
+    gdp2d.gdp_refine_batch(ctx, calls[0][0][:16], calls[0][1][:16], gdp2d.make_params())  # warm-up
     rows = []
     for split in SPLITS:
-        for rounds in (ROUNDS if split else [0]):
-            ms = measure(ctx, inputs, bsq, split, rounds)
+        for rounds in (ROUNDS if 0 < split < ENGINE_ALL else [0]):
+            ms = sum(measure(ctx, inputs, bsq, split, rounds) for inputs, bsq in calls)
             rows.append({"batch_engine_max_v": split, "rounds_per_group": rounds, "device_ms": ms,
                          "jobs_per_s": len(ps) / (ms / 1000.0)})
             print(f"[tune] split {split:>6} rounds {rounds}: {ms:8.1f} ms, {rows[-1]['jobs_per_s']:8.0f} jobs/s",
                   file=sys.stderr, flush=True)
     best = min(rows, key=lambda r: r["device_ms"])
-    table = {"sample": f"{len(ps)} PSLGs of the batched workload's distribution, seed {args.seed}",
-             "batch_engine_max_v": best["batch_engine_max_v"], "rounds_per_group": best["rounds_per_group"] or 2,
+    table = {"sample": f"2 x {args.sample} PSLGs of the batched workload's distribution, seeds {args.seed} and {args.seed + 46}",
+             "batch_engine_max_v": best["batch_engine_max_v"], "rounds_per_group": best["rounds_per_group"],
              "classes": classes_for(best["batch_engine_max_v"]), "measured": rows}
     with open(args.out, "w") as fh:
         json.dump(table, fh, indent=1)
