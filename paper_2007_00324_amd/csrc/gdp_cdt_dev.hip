@@ -766,6 +766,7 @@ __device__ __forceinline__ void start_one(const Bld &b, int ns, int step, int *p
   pend[i - s - 1] = i;
 }
 __global__ __launch_bounds__(kBlk) void k_dt_start(Bld b, int ns, int step, int *pend) {
+  if (b.c->err) return;  // (see k_vt_seed)
   const int stride = gridDim.x * blockDim.x;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < b.nv; i += stride) start_one(b, ns, step, pend, i);
 }
@@ -781,6 +782,15 @@ __device__ __forceinline__ void vt_one(const Bld &b, int t) {
 }
 __global__ void k_vt(Bld b, int nt) {
   const int stride = gridDim.x * blockDim.x;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += stride) vt_one(b, t);
+}
+// The sample's triangles, queued before the host has read how many there are:
+// a sample that an error cut short (points that coincide) leaves fewer than
+// its points call for, and the slots beyond them hold whatever the scratch
+// memory held.
+__global__ void k_vt_seed(Bld b) {
+  if (b.c->err) return;
+  const int nt = b.c->ntri, stride = gridDim.x * blockDim.x;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += stride) vt_one(b, t);
 }
 
@@ -1846,7 +1856,7 @@ int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, con
   const int step = (nv + kSeedMax - 1) / kSeedMax, n_seed = (nv + step - 1) / step;
   k_dt_seed<<<1, kSeedBlk, 0, stream>>>(b, n_seed, step, pl[0], pl[1]);
   if (n_seed < nv) {
-    k_vt<<<grid_for(2 * n_seed + 1, kBlk), kBlk, 0, stream>>>(b, 2 * n_seed + 1);
+    k_vt_seed<<<grid_for(2 * n_seed + 1, kBlk), kBlk, 0, stream>>>(b);
     k_dt_start<<<grid_for(nv, kBlk), kBlk, 0, stream>>>(b, n_seed, step, pl[0]);
   }
   if (!round_trip()) return dev_err("device call failed");
