@@ -843,12 +843,14 @@ __device__ __forceinline__ int grow_group(const DevMesh &m, const Work &w, int32
     const int oc = max(o, 0);
     const double2 U = m.vxy[u], V = m.vxy[v];
     const int4 to = m.tv[oc], no = m.tn[oc];
-    // listed: an internal edge (reached the other way)
+    // listed: an internal edge (reached the other way; an edge without a
+    // triangle across is none, whatever the list's padding holds)
     bool in = false;
     for (int q = 0; q < len; q += 4) {
       const int4 x = *reinterpret_cast<const int4 *>(list + q);
       in |= (x.x == o) | (x.y == o) | (x.z == o) | (x.w == o);
     }
+    in &= o >= 0;
     // far vertex, and its index in the record (the edge is v -> u there)
     const bool f0 = (to.x != u) & (to.x != v), f1 = (to.y != u) & (to.y != v);
     const int fi = f0 ? 0 : (f1 ? 1 : 2);
