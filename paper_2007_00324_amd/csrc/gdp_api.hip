@@ -3910,6 +3910,7 @@ gdp_status gdp_mesh_assign(gdp_ctx *ctx, gdp_mesh *dst, const gdp_mesh *src) {
   HIPCHECK(hipMemsetAsync(dst->win_t, 0, sizeof(uint32_t) * words(b.capT), s));
   HIPCHECK(hipMemsetAsync(dst->w0_s, 0, sizeof(uint32_t) * words(b.capS), s));
   HIPCHECK(hipMemsetAsync(dst->win_s, 0, sizeof(uint32_t) * words(b.capS), s));
+  HIPCHECK(hipMemsetAsync(dst->win_h, 0, sizeof(uint32_t) * words(b.capS), s));
   b.nV = a.nV; b.nT = a.nT; b.nS = a.nS;
   b.n_input_v = a.n_input_v; b.n_input_s = a.n_input_s; b.rounds = a.rounds;
   HIPCHECK(hipStreamSynchronize(s));
