@@ -1729,7 +1729,8 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   };
   // the workgroup builds: inputs packed by host threads, one copy, and builds
   // (the last group of them runs on while the host goes on).  Without room for
-  // their scratch they go to the device builder's threads.
+  // their scratch, or after a failed call, they go to the device builder's
+  // threads.
   std::vector<DevCdtJob> wg_jobs(n_wg);
   std::vector<DevCdtResult> wg_out(n_wg);
   size_t wg_done = 0;  // results read
@@ -1793,6 +1794,8 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
       }
     }
     if (!up) {
+      // (groups that were launched still write the meshes the builders get)
+      (void)hipStreamSynchronize(s);
       (void)hipGetLastError();
       n_wg = 0;
     }

@@ -1,5 +1,6 @@
 """The library's host code where the device's answers have to be scripted (a
-HIP runtime in host memory, tests/hipstub): what a call clears."""
+HIP runtime in host memory, tests/hipstub): what a call clears,
+and what it waits for after a failure."""
 from tests import hipstub
 
 
@@ -11,3 +12,10 @@ def test_assign_clears_every_bitmap():
     cap = [n // 8 for v, n in fills if v == 0xff]  # the side slots, two per subsegment
     assert len(cap) == 1
     assert fills.count((0, 4 * (cap[0] // 32 + 1))) == 3, fills
+
+
+def test_batch_waits_before_the_builders_take_over():
+    """Workgroup builds of a batch whose launch fails part way may be running:
+    the builder threads, which write the same meshes on streams of their own,
+    begin when nothing is left on the caller's stream."""
+    assert hipstub.run("launch") == [["pending", "0"]]
