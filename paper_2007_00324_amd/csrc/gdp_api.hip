@@ -1864,11 +1864,16 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
     (void)hipStreamSynchronize(s);
     (void)hipFree(wg_mem);
   }
-  // meshes whose Line 1 failed leave the batch (their arena room stays unused)
+  // meshes whose Line 1 failed leave the batch (their arena room stays unused);
+  // one that the library's own choice sent to the device, and that failed
+  // there for another reason than its input, is refined on its own at the end,
+  // from a CDT built on the host
+  std::vector<int32_t> alone;
   std::vector<bool> live(n, true);
   for (int32_t k = 0; k < n; k++) {
     const int32_t i = ok[k];
     if (rc[i] == GDP_OK) continue;
+    if (k >= n_host && dev_min <= 0 && rc[i] != GDP_E_INPUT) alone.push_back(i);
     live[k] = false;
     if (status) status[i] = (gdp_status)rc[i];
     arena->refs--;
@@ -2067,6 +2072,10 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
       gdp_mesh_free(M);
       mesh[k] = nullptr;
     }
+  }
+  for (int32_t i : alone) {
+    const gdp_status r = gdp_refine(ctx, &pslgs[i], bsq[i], P, &outs[i]);
+    if (status) status[i] = r;
   }
   return GDP_OK;
 }

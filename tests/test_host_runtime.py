@@ -1,6 +1,6 @@
 """The library's host code where the device's answers have to be scripted (a
 HIP runtime in host memory, tests/hipstub): what a call clears,
-and what it waits for after a failure."""
+what it waits for after a failure, and what it does without device memory."""
 from tests import hipstub
 
 
@@ -19,3 +19,13 @@ def test_batch_waits_before_the_builders_take_over():
     the builder threads, which write the same meshes on streams of their own,
     begin when nothing is left on the caller's stream."""
     assert hipstub.run("launch") == [["pending", "0"]]
+
+
+def test_batch_without_room_for_device_builds():
+    """The library's choice to build a batch's CDTs on the device costs no
+    member: without device memory for those builds (workgroups and builder
+    threads) each is refined from the host's CDT, as a smaller batch's are."""
+    out = hipstub.run("scratch")
+    assert out[0] == ["batch", "0"] and len(out) == 8
+    for word, status, got, want in out[1:]:
+        assert word == "member" and status == "0" and got == want, out
