@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void seg_insert_group(const Bld &b, const int2 *seg, 
   const int lo = wave_take(npend, gl == 0 && act && !win ? 1 : 0);
   if (gl == 0 && act && !win) list_out[lo] = s;
   if (!win) return;
-  if (po + need > b.pool_cap) { set_err(b.c, kEInternal + 11); return; }
+  if (po < 0 || (int64_t)po + need > b.pool_cap) { set_err(b.c, kEInternal + 11); return; }
   int *q = b.pool + po;
   WalkOut w;
   w.crossed = q; q += kc;
@@ -1376,13 +1376,15 @@ struct Scratch {
 };
 size_t cdt_scratch(int nv, int ns, char *base, Scratch &S) {
   const int capT = 2 * nv + 8;
-  const int pool_cap = 16 * capT + 4096;
+  // (ints; from 67 million vertices on more than an int counts, of which the
+  // segment recovery uses what it can count)
+  const int64_t pool_ints = 16 * (int64_t)capT + 4096;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return base + o; };
   Bld &b = S.b;
   b.nv = nv;
   b.capT = capT;
-  b.pool_cap = pool_cap;
+  b.pool_cap = (int)std::min<int64_t>(pool_ints, 0x7fffffff);
   b.tv = (int4 *)take(sizeof(int4) * capT);
   b.tn = (int4 *)take(sizeof(int4) * capT);
   b.ts = (int4 *)take(sizeof(int4) * capT);
@@ -1391,7 +1393,7 @@ size_t cdt_scratch(int nv, int ns, char *base, Scratch &S) {
   b.loc = b.state = (int *)take(4 * (size_t)std::max(nv, ns));
   b.vt = (int *)take(4 * (size_t)(nv + 3));
   b.wstamp = (int *)take(4 * (size_t)capT);
-  b.pool = (int *)take(4 * (size_t)pool_cap);
+  b.pool = (int *)take(4 * (size_t)pool_ints);
   S.P = (double2 *)take(sizeof(double2) * (size_t)(nv + 3));
   S.id = (int *)take(4 * (size_t)(nv + 3));
   S.pl[0] = (int *)take(4 * (size_t)std::max(nv, ns));

@@ -157,6 +157,14 @@ int main(int argc, char **argv) {
     g_log_fills = true;
     return gdp_mesh_assign(ctx, ma, mb) == GDP_OK ? 0 : 1;
   }
+  if (what == "sizes") {
+    for (int nv : {1000, 1000000, 67000000, 67200000, 89000000}) {
+      gdp::DevCdtJob j{};
+      j.nv = nv;
+      printf("scratch %d %zu\n", nv, gdp::dev_cdt_batch_bytes(&j, 1));
+    }
+    return 0;
+  }
   if (what == "launch") {
     g_fail_launch = true;
     return batch(ctx);

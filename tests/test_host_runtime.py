@@ -1,6 +1,7 @@
 """The library's host code where the device's answers have to be scripted (a
 HIP runtime in host memory, tests/hipstub): what a call clears,
-what it waits for after a failure, and what it does without device memory."""
+what it waits for after a failure, what it does without device memory, and the
+sizes it asks for."""
 from tests import hipstub
 
 
@@ -29,3 +30,14 @@ def test_batch_without_room_for_device_builds():
     assert out[0] == ["batch", "0"] and len(out) == 8
     for word, status, got, want in out[1:]:
         assert word == "member" and status == "0" and got == want, out
+
+
+def test_builder_scratch_of_large_inputs():
+    """The device CDT builder's scratch holds its arrays at every size that a
+    mesh can have (89 million vertices): per triangle slot at least three
+    16-byte records, two 8-byte stamps and two lists of two flip candidates (16
+    bytes each, twice)."""
+    out = hipstub.run("sizes")
+    assert len(out) == 5
+    for word, nv, nbytes in out:
+        assert word == "scratch" and int(nbytes) >= 2 * int(nv) * (3 * 16 + 2 * 8 + 4 * 16), (nv, nbytes)
