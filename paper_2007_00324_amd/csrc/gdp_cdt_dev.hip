@@ -593,6 +593,10 @@ __global__ __launch_bounds__(kBlk) void k_dt_apply(Bld b, int cur, int wst, uint
 
 // Passes over a short worklist inside one workgroup (two barriers instead of
 // two launches each), until it is empty: list s_n[cur] entries in b.list[cur].
+// The waves of a workgroup run on one compute unit, so its barrier, a release
+// and an acquire at workgroup scope, is enough for a phase's plain loads to see
+// what the phases before stored or changed by atomics (here and in all the
+// one-workgroup kernels of this file).
 struct SeedShared {
   int n[2], ncand;
 };
@@ -696,8 +700,7 @@ __device__ __forceinline__ int wg_insert(const Bld &b, SeedShared &sh, int *s_nt
     if (threadIdx.x == 0) {
       s_left = 0;
       sh.n[0] = 0;
-      // (set by atomics of other waves: read past the first-level cache)
-      s_err = __hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_err = b.c->err;
     }
     __syncthreads();
     if (s_err) break;
@@ -1503,17 +1506,11 @@ __device__ bool wg_sort(SortShared &S, uint64_t *k0, int *v0, uint64_t *k1, int 
   return odd;
 }
 
-// Barrier after which plain loads see what atomics of other waves wrote.
-__device__ __forceinline__ void wg_sync() {
-  __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
-
 // Whether a stage of the workgroup's mesh found an error (uniform).
 __device__ __forceinline__ bool wg_failed(const Ctr *c) {
   __shared__ int s_err;
   __syncthreads();
-  if (threadIdx.x == 0) s_err = __hip_atomic_load(&c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) s_err = c->err;
   __syncthreads();
   const int e = s_err;
   __syncthreads();
@@ -1635,28 +1632,27 @@ __global__ __launch_bounds__(kSeedBlk) void k_mesh_segs(const MeshJob *jobs, Dev
     J.S.sseg[i] = make_int2(J.S.rank[sg.x], J.S.rank[sg.y]);
     J.S.pl[0][i] = i;
   }
-  wg_sync();
+  __syncthreads();
   uint32_t round = (uint32_t)dt_rounds;
   for (int nl = ns, cur = 0; nl > 0; cur ^= 1) {
     round++;
     seg_rounds++;
     if (tid == 0) s_pool = s_npend = s_nwin = 0;
     for (int i = tid; i < nl; i += kSeedBlk) seg_mark_one(b, J.S.sseg, J.S.pl[cur][i], round, b.state);
-    wg_sync();
+    __syncthreads();
     constexpr int per = kSeedBlk / kSegGrp;
     for (int base = 0; base < nl; base += per) {
       const int i = base + tid / kSegGrp;
       seg_insert_group(b, J.S.sseg, J.S.pl[cur], i, i < nl, round, b.state, J.S.pl[cur ^ 1], &s_pool, &s_npend, &s_nwin);
     }
-    wg_sync();
+    __syncthreads();
     const int left = s_npend;
     if (tid == 0 && left > 0 && s_nwin == 0 && left == nl) set_err(b.c, kEInternal + 17);
     if (wg_failed(b.c)) break;
     nl = left;
   }
   if (tid == 0)
-    res[blockIdx.x] =
-        DevCdtResult{__hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 1, 0, dt_rounds, seg_rounds};
+    res[blockIdx.x] = DevCdtResult{b.c->err, 1, 0, dt_rounds, seg_rounds};
 }
 
 // Outside removal and canonical order.
@@ -1669,7 +1665,7 @@ __global__ __launch_bounds__(kSeedBlk) void k_mesh_final(const MeshJob *jobs, De
   if (wg_failed(b.c)) return;
   for (int i = tid; i < nv; i += kSeedBlk) J.S.used[i] = 0;
   if (tid == 0) s_npend = s_nwin = 0;  // kept triangles, hull edges
-  wg_sync();
+  __syncthreads();
   for (int base = 0; base < nt; base += kSeedBlk) {
     const int t = base + tid;
     int hull = 0;
@@ -1690,7 +1686,7 @@ __global__ __launch_bounds__(kSeedBlk) void k_mesh_final(const MeshJob *jobs, De
   if (wg_failed(b.c)) {
     if (tid == 0) {
       res[blockIdx.x].stage = 2;
-      res[blockIdx.x].err = __hip_atomic_load(&b.c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      res[blockIdx.x].err = b.c->err;
     }
     return;
   }
