@@ -1493,12 +1493,18 @@ void gang_group(gdp_ctx *ctx, GangBufs &B, std::vector<GangItem> &active, int R,
 // a second), the shared rounds about 0.2 ms a round for all their meshes.
 // Device ms with the line at 250 / 500 / 1,000 / 2,000 / 4,000 vertices and
 // with every mesh in the engine: 128 meshes of 100 to 50,000 uniform points
-// 19.4 / 19.9 / 21.6 / 21.7 / 27.7 / 102; 256 of the mixed workload 58 / 58 /
-// 214 / 209 / 208 / 2,174; 1,024 of it 106 / 107 / 102 / 98 / 91 / 133 and,
-// with another seed, 217 / 215 / 214 / 210 / 382 / 723.
+// 27 / 28 / 28 / 30 / 149 / 138; 256 of the mixed workload 29 / 32 / 32 / 32 /
+// 34 / 92; 1,024 of it 83 / 88 / 85 / 83 / 82 / 133 and, with another seed,
+// 189 / 191 / 191 / 192 / 371 / 711.
 constexpr int64_t kBatchSplit = 500;
 constexpr int kBatchGangRounds = 4;  // shared rounds between two host reads: no job waits to join a batch
-constexpr size_t kBatchGangMax = 256;  // batched meshes in one group of shared rounds, at most
+// Batched meshes in one group of shared rounds, at most.  A round of small
+// meshes takes about as long for a thousand of them as for a few, so a smaller
+// group makes a batch of many wait: device ms with 256 / 512 / 1,024 / 4,096
+// and in the engine, 512 meshes of 700 uniform points 25.4 / 16.1 / 16.6 / 16.5
+// / 20.8, 1,024 of 1,500 62 / 45 / 34 / 34 / 43, 4,096 of 600 164 / 118 / 93 /
+// 82 / 99 (4,096 would take 15 MB of pinned memory for the states).
+constexpr size_t kBatchGangMax = 1024;
 // Line 1 of a batch that leaves the choice open.  Sixteen host threads build
 // small meshes faster than a workgroup each does (0.45 us a vertex and thread
 // against 0.7 and 2 ms), many workgroups do more at once: 16 x 20,000 vertices
