@@ -1538,6 +1538,18 @@ gdp_status check_pslg_for_device(const gdp_pslg *pslg, std::string &e) {
   return GDP_OK;
 }
 
+// Runs work on up to n threads of its own (each takes items until none is
+// left); where no thread can be had, the caller runs it.
+template <class F>
+void start_threads(std::vector<std::thread> &pool, unsigned n, F work) {
+  unsigned started = 0;
+  try {
+    for (; started < n; started++) pool.emplace_back(work);
+  } catch (const std::exception &) {
+  }
+  if (n > 0 && started == 0) work();
+}
+
 // Line 1 of one batched input by the device builder, into its arena slot M
 // (zeroed and filled beforehand): the input goes up, the canonical CDT is
 // written in place, then the mesh's device state.  nT receives the
@@ -1781,7 +1793,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
         }
       };
       std::vector<std::thread> pool;
-      for (size_t t = 0; t < std::min<size_t>(7, in >> 20); t++) pool.emplace_back(pack_in);
+      start_threads(pool, (unsigned)std::min<size_t>(7, in >> 20), pack_in);
       pack_in();
       for (auto &th : pool) th.join();
       for (int32_t q = 0; q < n_wg; q++) {
@@ -1813,44 +1825,45 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
     nth = std::min<unsigned>(nth, (unsigned)std::max(n_host, 1));
     const unsigned ndt = (unsigned)std::min<int32_t>(n_dev, kBatchLine1DevThreads);
     std::vector<std::thread> pool;
-    for (unsigned t = 0; t < nth && n_host > 0; t++)
-      pool.emplace_back([&]() {
-        for (int32_t k; (k = next_h.fetch_add(1)) < n_host;) {
-          const int32_t i = ok[k];
-          HostMesh h;
-          rc[i] = host_cdt_build(pslgs[i].n_vertices, pslgs[i].xy, pslgs[i].n_segments, pslgs[i].seg, h, errs[i]);
-          if (rc[i] == GDP_OK && (h.nV != pslgs[i].n_vertices || h.nS != pslgs[i].n_segments ||
-                                  (int64_t)h.nT > 2 * (int64_t)h.nV)) {
-            rc[i] = GDP_E_DEVICE;
-            errs[i] = "initial CDT outside the batch's room";
-          }
-          if (rc[i] == GDP_OK) {
-            nT0[k] = h.nT;
-            pack(k, h);
-          }
+    auto host_builds = [&]() {
+      for (int32_t k; (k = next_h.fetch_add(1)) < n_host;) {
+        const int32_t i = ok[k];
+        HostMesh h;
+        rc[i] = host_cdt_build(pslgs[i].n_vertices, pslgs[i].xy, pslgs[i].n_segments, pslgs[i].seg, h, errs[i]);
+        if (rc[i] == GDP_OK && (h.nV != pslgs[i].n_vertices || h.nS != pslgs[i].n_segments ||
+                                (int64_t)h.nT > 2 * (int64_t)h.nV)) {
+          rc[i] = GDP_E_DEVICE;
+          errs[i] = "initial CDT outside the batch's room";
         }
-      });
-    for (unsigned t = 0; t < ndt; t++)
-      pool.emplace_back([&]() {
-        (void)hipSetDevice(ctx->device);
-        hipStream_t ds = nullptr;
-        DevCdtWork ws;
-        if (hipStreamCreateWithFlags(&ds, hipStreamNonBlocking) != hipSuccess) ds = nullptr;
-        for (int32_t q; (q = next_d.fetch_add(1)) < n_dev;) {
-          const int32_t k = n_host + n_wg + q, i = ok[k];
-          if (!ds) {
-            rc[i] = GDP_E_DEVICE;
-            errs[i] = "stream creation failed";
-            continue;
-          }
-          rc[i] = batch_line1_device(ds, ws, pslgs[i], mesh[k], nT0[k], errs[i]);
+        if (rc[i] == GDP_OK) {
+          nT0[k] = h.nT;
+          pack(k, h);
         }
-        if (ds) {
-          (void)hipStreamSynchronize(ds);
-          (void)hipStreamDestroy(ds);
+      }
+    };
+    auto dev_builds = [&]() {
+      (void)hipSetDevice(ctx->device);
+      hipStream_t ds = nullptr;
+      DevCdtWork ws;
+      if (hipStreamCreateWithFlags(&ds, hipStreamNonBlocking) != hipSuccess) ds = nullptr;
+      for (int32_t q; (q = next_d.fetch_add(1)) < n_dev;) {
+        const int32_t k = n_host + n_wg + q, i = ok[k];
+        if (!ds) {
+          rc[i] = GDP_E_DEVICE;
+          errs[i] = "stream creation failed";
+          continue;
         }
-        dev_cdt_work_free(ws);
-      });
+        rc[i] = batch_line1_device(ds, ws, pslgs[i], mesh[k], nT0[k], errs[i]);
+      }
+      if (ds) {
+        (void)hipStreamSynchronize(ds);
+        (void)hipStreamDestroy(ds);
+      }
+      dev_cdt_work_free(ws);
+    };
+    // (the builders first: without threads the caller runs both, one after the other)
+    start_threads(pool, ndt, dev_builds);
+    if (n_host > 0) start_threads(pool, nth, host_builds);
     for (auto &th : pool) th.join();
   }
   if (n_wg > 0) {

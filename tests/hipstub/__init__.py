@@ -22,7 +22,7 @@ def run(scenario: str) -> list[list[str]]:
         tmp = f"{EXE}.{os.getpid()}"  # test workers may build at the same time
         subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
                         "-o", tmp, src, "-L", os.path.dirname(LIB), "-l:" + os.path.basename(LIB),
-                        "-Wl,-rpath," + os.path.dirname(LIB), "-rdynamic", "-lpthread"], check=True, capture_output=True)
+                        "-Wl,-rpath," + os.path.dirname(LIB), "-rdynamic", "-lpthread", "-ldl"], check=True, capture_output=True)
         os.replace(tmp, EXE)
     r = subprocess.run([EXE, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)

@@ -4,6 +4,9 @@
 // kernels do nothing, and a scenario (the argument) makes chosen calls fail
 // and prints what it saw for the test to judge.
 #include <hip/hip_runtime.h>
+#include <dlfcn.h>
+#include <errno.h>
+#include <pthread.h>
 #include <unistd.h>
 
 #include <cstdio>
@@ -26,11 +29,17 @@ const std::thread::id g_main = std::this_thread::get_id();
 const hipStream_t kUser = (hipStream_t)0x10;  // the stream of the caller's context
 bool g_log_fills = false;
 bool g_fail_launch = false;   // the next error query reports a failed launch
+bool g_fail_threads = false;  // no thread can be created
 bool g_fail_scratch = false;  // after the first allocation, every one until a batch's own buffers are made fails
 int g_allocs = 0;
 }  // namespace
 
 extern "C" {
+int pthread_create(pthread_t *t, const pthread_attr_t *a, void *(*f)(void *), void *arg) {
+  if (g_fail_threads) return EAGAIN;
+  static const auto real = (int (*)(pthread_t *, const pthread_attr_t *, void *(*)(void *), void *))dlsym(RTLD_NEXT, "pthread_create");
+  return real(t, a, f, arg);
+}
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *shared, hipStream_t *) {
   *shared = 0;
@@ -121,12 +130,12 @@ struct Input {
   }
 };
 
-// A batch that the library builds on the device: one input above the size of
-// a workgroup build, the others below.
-int batch(gdp_ctx *ctx) {
+// A batch that the library builds on the device (one input above the size of a
+// workgroup build, the others below), or a small one that it builds on the host.
+int batch(gdp_ctx *ctx, bool small = false) {
   std::vector<Input> in;
-  in.emplace_back(Input(300000));
-  for (int i = 0; i < 6; i++) in.emplace_back(Input(20000 + i));
+  in.emplace_back(Input(small ? 300 : 300000));
+  for (int i = 0; i < 6; i++) in.emplace_back(Input((small ? 20 : 20000) + i));
   std::vector<gdp_pslg> ps;
   for (Input &x : in) ps.push_back(x.p), ps.back().xy = x.xy.data(), ps.back().seg = x.seg.data();
   const int n = (int)ps.size();
@@ -135,7 +144,7 @@ int batch(gdp_ctx *ctx) {
   std::vector<gdp_status> st(n);
   const gdp_status rc = gdp_refine_batch(ctx, ps.data(), bsq.data(), nullptr, n, out.data(), st.data(), nullptr);
   printf("batch %d\n", (int)rc);
-  for (int i = 0; i < n && rc == GDP_OK; i++) {
+  for (int i = 0; i < n && rc == GDP_OK && !small; i++) {
     int32_t want = 0;
     gdp_mesh_info info{};
     if (gdp_cdt_host(&ps[i], &want, 0, nullptr, nullptr, nullptr, nullptr, 0) != GDP_OK) return 1;
@@ -169,7 +178,11 @@ int main(int argc, char **argv) {
     g_fail_launch = true;
     return batch(ctx);
   }
-  if (what == "scratch") {
+  if (what == "threads") {
+    g_fail_threads = true;
+    if (batch(ctx, true)) return 1;
+  }
+  if (what == "scratch" || what == "threads") {
     g_fail_scratch = true;
     return batch(ctx);
   }

@@ -1,7 +1,7 @@
 """The library's host code where the device's answers have to be scripted (a
 HIP runtime in host memory, tests/hipstub): what a call clears,
-what it waits for after a failure, what it does without device memory, and the
-sizes it asks for."""
+what it waits for after a failure, what it does without device memory or
+threads, and the sizes it asks for."""
 from tests import hipstub
 
 
@@ -29,6 +29,16 @@ def test_batch_without_room_for_device_builds():
     out = hipstub.run("scratch")
     assert out[0] == ["batch", "0"] and len(out) == 8
     for word, status, got, want in out[1:]:
+        assert word == "member" and status == "0" and got == want, out
+
+
+def test_batch_without_threads():
+    """Where no thread can be created the caller does their work: no exception
+    leaves the C call (a batch built on the host, then one meant for the
+    device)."""
+    out = hipstub.run("threads")
+    assert out[:2] == [["batch", "0"], ["batch", "0"]] and len(out) == 9
+    for word, status, got, want in out[2:]:
         assert word == "member" and status == "0" and got == want, out
 
 
