@@ -262,8 +262,8 @@ ABLATION_SETTINGS = [
     ("no_single_workgroup_rounds", dict(tail_engine_max=-1)),
 ]
 # Rule 3 (the cooperative path for large cavities) on the circles input, whose
-# circle interiors make cavities of hundreds of triangles: per-thread slices of
-# 12, 24 or 39 (the default) slots before a cavity goes cooperative.
+# circle interiors make cavities of hundreds of triangles: up to 12, 24 or 39
+# (the default) triangles by a group of lanes before a cavity goes cooperative.
 COOP_SETTINGS = [("coop_cap_39", dict(cavity_thread_cap=39)), ("coop_cap_24", dict(cavity_thread_cap=24)),
                  ("coop_cap_12", dict(cavity_thread_cap=12))]
 ABLATION_TRAFFIC_FILE = os.path.join(HERE, "profiles", "ablation_traffic.md")

@@ -123,9 +123,9 @@ typedef struct {
                                workgroup each in the single-workgroup engine;
                                0 = 500 */
   /* perf only */
-  int32_t cavity_thread_cap;  /* per-thread cavity slots of the grid path (0 = 39;
-                               12, 24 or 39): larger cavities go to the cooperative
-                               path (Rule 3) */
+  int32_t cavity_thread_cap;  /* triangles of the largest cavity that a group of
+                               lanes grows on the grid path (0 = 39; 12, 24 or 39):
+                               larger cavities go to the cooperative path (Rule 3) */
   /* semantic */
   int32_t insert_mode;      /* Line 8 insertion.  0: Bowyer-Watson cavities with
                                priority marks and the dependency test (Section 5.2);

@@ -1347,8 +1347,8 @@ void gang_round(hipStream_t s, const GangBufs &B, unsigned n, const GangGrids &g
   const GangDesc *D = B.d_desc;
   const int32_t *me = B.d_map + g.off[kGangElem], *mg = B.d_map + g.off[kGangGroup], *mf = B.d_map + g.off[kGangFinish];
   const dim3 ge(g.n[kGangElem]), gg(g.n[kGangGroup]);
-  // (cooperative cavities: as many workgroups as fit on the chip, two to a
-  // compute unit's LDS)
+  // (cooperative cavities: a workgroup takes 83 KB of a compute unit's 160 KB of
+  // LDS, so 256 run at a time, and as many again start as those end)
   const unsigned nbig = 512;
   hipLaunchKernelGGL(kg_collect, ge, dim3(bs), 0, s, D, me);
   hipLaunchKernelGGL(kg_pending, ge, dim3(bs), 0, s, D, me);

@@ -1521,10 +1521,11 @@ __device__ __forceinline__ bool wg_failed(const Ctr *c) {
 // first; an error (c->err) skips the later ones.  Bound by the largest mesh:
 // 40,000 vertices take 25 ms of insertion (latency while the lists are short,
 // then the one workgroup's issue rate) and 5 ms of the rest, 128 meshes of 100
-// to 40,000 side by side no more.  All stages in one kernel kept so many
-// pointers that the insertion spilled: 36 ms for 50,004 points, of which the
-// sample took 8 instead of 3.  With 512 or 256 threads a batch of 128 takes 74
-// or 92 ms instead of 68.
+// to 40,000 side by side no more.  All stages in one kernel kept more pointers
+// and spilled more: 36 ms for 50,004 points, of which the sample took 8 instead
+// of 3 (k_mesh_insert and k_mesh_segs spill 90 and 138 registers still, at the
+// 128 that a lane of 1,024 threads gets).  With 512 or 256 threads a batch of
+// 128 takes 74 or 92 ms instead of 68.
 __global__ __launch_bounds__(kSeedBlk) void k_mesh_sort(const MeshJob *jobs) {
   __shared__ SortShared so;
   __shared__ unsigned long long s_box[4];
@@ -1758,18 +1759,17 @@ hipError_t sort_pairs_u64(hipStream_t stream, uint64_t *k0, int *v0, uint64_t *k
   return radix_sort_pairs(stream, k0, v0, k1, v1, n, 32, hist);
 }
 
-// Builds the CDT of the PSLG whose vertices (nv, the first nv entries of
-// d_xy, which has room for nv + 3) and segments (d_seg) are on the device;
-// writes the canonical triangles to otv / otn / ots (capacity cap_out) and
-// their count to *n_tri.  Coordinates and segment endpoints are checked by
-// the caller.  Returns GDP_OK, GDP_E_INPUT (invalid PSLG, err set),
-// GDP_E_NOMEM or GDP_E_DEVICE.
 void dev_cdt_work_free(DevCdtWork &ws) {
   if (ws.mem) (void)hipFree(ws.mem);
   if (ws.hctr) (void)hipHostFree(ws.hctr);
   ws = DevCdtWork();
 }
 
+// Builds the CDT of the PSLG whose nv vertices (d_xy) and segments (d_seg) are
+// on the device; writes the canonical triangles to otv / otn / ots (capacity
+// cap_out) and their count to *n_tri.  Coordinates and segment endpoints are
+// checked by the caller.  Returns GDP_OK, GDP_E_INPUT (invalid PSLG, err set),
+// GDP_E_NOMEM or GDP_E_DEVICE.
 int dev_cdt_build(hipStream_t stream, int32_t nv, double2 *d_xy, int32_t ns, const int2 *d_seg, int4 *otv,
                   int4 *otn, int4 *ots, int32_t cap_out, int32_t *n_tri, DevCdtStats *stats, std::string &err,
                   DevCdtWork *ws) {

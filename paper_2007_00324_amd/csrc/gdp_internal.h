@@ -27,9 +27,8 @@ struct HostMesh {
 int host_cdt_build(int32_t nv, const double *xy, int32_t ns, const int32_t *seg, HostMesh &out,
                    std::string &err);
 
-// The same CDT built by kernels (gdp_cdt_dev.hip).  d_xy holds the nv input
-// points and room for three more; the canonical triangles go to otv / otn /
-// ots in the device mesh layout below.
+// The same CDT built by kernels (gdp_cdt_dev.hip) from the nv points of d_xy;
+// the canonical triangles go to otv / otn / ots in the device mesh layout below.
 struct DevCdtStats {
   int32_t dt_rounds = 0, seg_rounds = 0;
 };
@@ -117,7 +116,7 @@ struct DevCounters {
   int32_t nmk0;         // midpoint candidates after the collection (R4/R5 add more)
   int32_t nwin_hull;    // midpoint winners on the hull (one fresh slot instead of two)
   int32_t nhuge;        // cavities continued in device memory (beyond the LDS list)
-  int64_t cav_len[2];   // per-thread cavities [midpoints, circumcenters]: triangles grown
+  int64_t cav_len[2];   // cavities of lane groups [midpoints, circumcenters]: triangles grown
   int64_t cav_bnd[2];   // ... and their boundary edges
   int64_t n_in_tests;   // incircle evaluations of cavity growth and the dependency test
   int64_t n_or_tests;   // orient2d evaluations of the walk and the fan check

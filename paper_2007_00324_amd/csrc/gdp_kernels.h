@@ -89,7 +89,10 @@ __global__ void k_apply_cap(Work w);
 __global__ void k_locate(DevMesh m, Work w);
 __global__ void k_prefilter(DevMesh m, Work w, int mode, int n);
 constexpr int kApproxMaxN = 16;
-constexpr int kCavCapDefault = 39;  // largest cavity of the grid kernel's lane groups
+// Largest cavity of the grid kernel's lane groups: what a lane's list held when
+// each had a cavity of its own.  The groups' lists hold 56 (the engine uses 48);
+// larger values have not been measured here.
+constexpr int kCavCapDefault = 39;
 template <int IS_CC>
 __global__ void k_cavity(DevMesh m, Work w, int cap);
 __global__ void k_cavity_big(DevMesh m, Work w, int phase);

@@ -762,11 +762,12 @@ __global__ __launch_bounds__(kPreBlock) void k_prefilter(DevMesh m, Work w, int 
 // and one FP64 circle test, so a round lasts as long as its longest chain of
 // steps until the candidates fill the chip, and then as long as the lines it
 // gathers.  One lane per cavity (three circle tests per step, a step per
-// triangle, the wave waiting for its largest of 64 cavities) took 150 us a
-// round on the mesh of 50,000 points and 183 on that of 1,000,000; this takes
-// 49 and 116 (640,000 candidates: 318 -> 249).  Eight lanes: most steps of a
+// triangle, the wave waiting for its largest of 64 cavities) took 4.3 ms of a
+// refinement of the benchmark's mesh of 1,000,000 points (30 launches of 144
+// us); this takes 2.9 (38 launches of 77).  Eight lanes: most steps of a
 // cavity of 8 triangles (the average) keep under eight edges waiting; four
-// lanes and twice the cavities took 59 and 124.
+// lanes and twice the cavities took 59 and 124 us a launch on meshes of 50,000
+// and 1,000,000 points against 53 and 117.
 // ---------------------------------------------------------------------------
 constexpr int kGrp = 8;         // lanes per cavity
 constexpr int kRing = 64;       // queue entries (at most len + 4 wait at once)
@@ -815,7 +816,7 @@ template <bool FILTER>
 __device__ __forceinline__ int grow_group(const DevMesh &m, const Work &w, int32_t *S, int cap, int s0, int s1,
                                           double2 p, int skip_k, bool is_cc, CavCheck &ck) {
   int32_t *qo = S, *qu = S + kRing, *qv = S + 2 * kRing, *list = S + 3 * kRing;
-  const int gl = grp_lane(), g0 = grp_first();
+  const int gl = grp_lane();
   const unsigned below = (1u << gl) - 1u;
   int len = s1 >= 0 && s1 != s0 ? 2 : 1;
   int head = 0, tail = 3 * len;
