@@ -40,6 +40,7 @@ struct FfCount {
   int32_t n_cnd[2];       // flip candidates of a pass (by the parity of the pass)
   int32_t n_touched;      // slots written this round (each once)
   int32_t n_red;          // redundant points found by the last detection
+  int32_t n_left;         // redundant points a removal pass left for the next one
   int32_t n_dead;         // slots freed by removals
   int32_t pool_used, pool_short;
   int32_t n_hole, n_mover;
@@ -576,12 +577,27 @@ GDP_HD void ff_detect_one(const FfView &V, int r) {
   }
 }
 
-// Removal passes: a redundant point stamps itself and its neighbours with
+// Removal passes (here one point after the other, as a sequential run takes
+// them; the kernels run the same pass with a group of lanes per point and
+// ff_rm_apply_one only for the stars too large for a group): a redundant
+// point stamps itself and its neighbours with
 // (pass, rank); it is removed in the pass only if every stamp is its own, so
 // no two removals of a pass are within two edges of each other and their
-// stars, and the triangles around them, are disjoint.  The kernels give a
-// point a group of lanes (gdp_ff.hip) and leave the stars too large for a wave
-// to ff_rm_apply_one (red has bit 2 set: the point owns its stamps).
+// stars, and the triangles around them, are disjoint.
+template <class O>
+GDP_HD void ff_rm_mark_one(const FfView &V, int r, uint64_t pbase) {
+  if (!V.alive[r] || !V.red[r]) return;
+  const int p = V.nV + r;
+  const uint64_t prio = pbase | (uint64_t)(r + 1);
+  O::max64(&V.vmark[p], prio);
+  bool open;
+  const int n = ff_star(V, p, V.vtri[r], open, [&](int t, int i) {
+    const int4 tri = V.tv[t];
+    O::max64(&V.vmark[ffc(tri, (i + 1) % 3)], prio);
+    O::max64(&V.vmark[ffc(tri, (i + 2) % 3)], prio);
+  });
+  if (n == 0) O::err(&V.c->err, 8);
+}
 
 // Ear clipping of one polygon (m vertices, counter-clockwise) held in the
 // pool: pv vertex ids, info[q] the outer neighbour of edge (pv[q], pv[q+1])
@@ -645,6 +661,21 @@ GDP_HD int ff_clip(const FfView &V, double2 P, int m, int *pv, int *info, int *s
 }
 
 template <class O>
+GDP_HD void ff_rm_decide_one(const FfView &V, int r, uint64_t pbase) {
+  if (!V.alive[r] || !V.red[r]) return;
+  const int p = V.nV + r;
+  const uint64_t prio = pbase | (uint64_t)(r + 1);
+  bool own = V.vmark[p] == prio, open;
+  const int k = ff_star(V, p, V.vtri[r], open, [&](int t, int i) {
+    const int4 tri = V.tv[t];
+    if (V.vmark[ffc(tri, (i + 1) % 3)] != prio || V.vmark[ffc(tri, (i + 2) % 3)] != prio) own = false;
+  });
+  if (k == 0) { O::err(&V.c->err, 9); return; }
+  if (own) V.red[r] |= 4;
+  else O::append(&V.c->n_left);
+}
+
+template <class O>
 GDP_HD void ff_rm_apply_one(const FfView &V, int r, int wst, int tst) {
   if (!V.alive[r] || !(V.red[r] & 4)) return;
   const int p = V.nV + r;
@@ -658,6 +689,7 @@ GDP_HD void ff_rm_apply_one(const FfView &V, int r, int wst, int tst) {
   const int64_t base = O::add(&V.c->pool_used, (int)need);
   if (base + need > V.pool_cap) {
     O::or32(&V.c->pool_short, 1);
+    O::append(&V.c->n_left);
     V.red[r] &= 3;  // tried again in the next pass
     return;
   }

@@ -1,9 +1,7 @@
 """Sequential host run of the Flip-Flop steps (gdp_ff_core.h), driven from a
 point set S that the oracle's Flip-Flop round chose (test infrastructure).
 
-The library is built from ff_emu.cpp with hipcc as plain host code, and from
-ff_lanes.cpp, which runs the removal kernels' own text (gdp_ff.hip) lane by
-lane, as plain C++."""
+The library is built from ff_emu.cpp with hipcc as plain host code."""
 from __future__ import annotations
 
 import ctypes as C
@@ -20,17 +18,9 @@ _lib = None
 
 def build() -> str:
     tmp = f"{LIB}.{os.getpid()}.tmp"  # test workers may build at the same time
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    flags = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-I", CORE]
-    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc)))
-    subprocess.run([os.path.join(rocm, "llvm", "bin", "clang++"), "-x", "c++", *flags, "-D__HIP_PLATFORM_AMD__", "-w",
-                    "-I", os.path.join(rocm, "include"), "-c", "-o", f"{tmp}.o", os.path.join(HERE, "ff_lanes.cpp")],
-                   check=True, capture_output=True)
-    subprocess.run([hipcc, *flags, "-c", "-o", f"{tmp}.emu.o", os.path.join(HERE, "ff_emu.cpp")], check=True,
-                   capture_output=True)
-    subprocess.run([hipcc, "-shared", "-o", tmp, f"{tmp}.o", f"{tmp}.emu.o"], check=True, capture_output=True)
-    os.remove(f"{tmp}.o")
-    os.remove(f"{tmp}.emu.o")
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-ffp-contract=off", "-fno-fast-math", "-I", CORE, "-o", tmp, os.path.join(HERE, "ff_emu.cpp")]
+    subprocess.run(cmd, check=True, capture_output=True)
     os.replace(tmp, LIB)
     return LIB
 
@@ -38,9 +28,7 @@ def build() -> str:
 def load():
     global _lib
     if _lib is None:
-        srcs = [os.path.join(HERE, f) for f in ("ff_emu.cpp", "ff_lanes.cpp", "__init__.py")]
-        srcs += [os.path.join(CORE, f) for f in ("gdp_ff_core.h", "gdp_exact.h", "gdp_ff.hip", "gdp_kernels.h",
-                                                 "gdp_internal.h")]
+        srcs = [os.path.join(HERE, "ff_emu.cpp"), os.path.join(HERE, "__init__.py"), os.path.join(CORE, "gdp_ff_core.h"), os.path.join(CORE, "gdp_exact.h")]
         if not os.path.exists(LIB) or os.path.getmtime(LIB) < max(os.path.getmtime(s) for s in srcs):
             build()
         _lib = C.CDLL(LIB)
@@ -48,7 +36,7 @@ def load():
         D = C.POINTER(C.c_double)
         _lib.ffemu_round.argtypes = [C.c_int32] * 4 + [D, I, C.c_int32, I, I, I, C.c_int32, I, I, I, C.c_int32,
                                                        C.c_int32, C.c_int32, D, I, I, C.c_int32, I, I,
-                                                       C.POINTER(C.c_int64), C.c_int32, C.c_uint64, C.c_int32]
+                                                       C.POINTER(C.c_int64), C.c_int32, C.c_uint64]
         _lib.ffemu_round.restype = C.c_int32
     return _lib
 
@@ -76,10 +64,8 @@ def last_points(orc_lib):
                 flagged=ks[:nf])
 
 
-def round_from_points(arr: dict, n_input_v: int, S: dict, enc_mode: int = 0, cand_cap: int = 0, order_seed: int = 0,
-                      lanes: bool = False):
-    """Runs Line 8 on mesh arrays `arr` (oracle layout) for the points S
-    (lanes: the removals by the kernels' groups of lanes).
+def round_from_points(arr: dict, n_input_v: int, S: dict, enc_mode: int = 0, cand_cap: int = 0, order_seed: int = 0):
+    """Runs Line 8 on mesh arrays `arr` (oracle layout) for the points S.
     Returns (arrays in oracle layout, counters)."""
     lib = load()
     xy = np.ascontiguousarray(arr["xy"], dtype=np.float64)
@@ -128,7 +114,7 @@ def round_from_points(arr: dict, n_input_v: int, S: dict, enc_mode: int = 0, can
                          _ptr(SV, C.c_int32), _ptr(SP, C.c_int32), _ptr(SE, C.c_int32), capS,
                          np_, nmid, _ptr(pxy, C.c_double), _ptr(pinfo, C.c_int32), _ptr(pab, C.c_int32),
                          len(mid_elem), _ptr(mid_elem if len(mid_elem) else np.zeros(1, np.int32), C.c_int32),
-                         _ptr(mid_state, C.c_int32), _ptr(out, C.c_int64), cand_cap, order_seed, int(lanes))
+                         _ptr(mid_state, C.c_int32), _ptr(out, C.c_int64), cand_cap, order_seed)
     nV2, nT2, nS2 = int(out[0]), int(out[1]), int(out[2])
     res = dict(xy=X[:nV2].copy(), vkind=K[:nV2].copy(), tv=TV[:nT2, :3].copy(), tn=TN[:nT2, :3].copy(),
                ts=TS[:nT2, :3].copy(), sv=SV[:nS2].copy(), sparent=SP[:nS2].copy(), spend=SE[:nS2].astype(np.uint8))

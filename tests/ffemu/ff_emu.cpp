@@ -4,9 +4,7 @@
 // not contain it).
 //
 // Each "launch" runs the step for element 0, 1, ... in turn with plain
-// operations in place of atomics: a legal schedule of the kernels.  The removal
-// passes run either so, by the one-point steps, or as the kernels' text with
-// its groups of lanes (ff_lanes.cpp).
+// operations in place of atomics: a legal schedule of the kernels.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -66,44 +64,10 @@ struct Order {
 };
 }  // namespace
 
-namespace {
-// A removal pass one point after the other: stamps, then ownership (the
-// removal itself is ff_rm_apply_one).
-void rm_mark_one(const FfView &V, int r, uint64_t pbase) {
-  using O = FfHostOps;
-  if (!V.alive[r] || !V.red[r]) return;
-  const int p = V.nV + r;
-  const uint64_t prio = pbase | (uint64_t)(r + 1);
-  O::max64(&V.vmark[p], prio);
-  bool open;
-  const int n = ff_star(V, p, V.vtri[r], open, [&](int t, int i) {
-    const int4 tri = V.tv[t];
-    O::max64(&V.vmark[ffc(tri, (i + 1) % 3)], prio);
-    O::max64(&V.vmark[ffc(tri, (i + 2) % 3)], prio);
-  });
-  if (n == 0) O::err(&V.c->err, 8);
-}
-void rm_decide_one(const FfView &V, int r, uint64_t pbase) {
-  if (!V.alive[r] || !V.red[r]) return;
-  const int p = V.nV + r;
-  const uint64_t prio = pbase | (uint64_t)(r + 1);
-  bool own = V.vmark[p] == prio, open;
-  const int k = ff_star(V, p, V.vtri[r], open, [&](int t, int i) {
-    const int4 tri = V.tv[t];
-    if (V.vmark[ffc(tri, (i + 1) % 3)] != prio || V.vmark[ffc(tri, (i + 2) % 3)] != prio) own = false;
-  });
-  if (k == 0) FfHostOps::err(&V.c->err, 9);
-  else if (own) V.red[r] |= 4;
-}
-}  // namespace
-
-extern "C" int ffemu_removal_pass(const FfView *V, const int32_t *list, const int32_t *n_list, int32_t *next,
-                                  int32_t *n_next, uint64_t pbase, int wst, int tst, int grid);
-
 extern "C" int ffemu_round(int nV, int nT, int nS, int enc_mode, double *xy, int *vkind, int capV, int *tv, int *tn,
                            int *ts, int capT, int *sv, int *spar, int *spend, int capS, int np, int nmid,
                            const double *pxy, const int *pinfo, const int *pab, int nmk, const int *mid_elem,
-                           const int *mid_state, int64_t *out, int cand_cap, uint64_t order_seed, int lanes) {
+                           const int *mid_state, int64_t *out, int cand_cap, uint64_t order_seed) {
   Order ord{order_seed, {}};
   using O = FfHostOps;
   Bufs B;
@@ -208,38 +172,24 @@ extern "C" int ffemu_round(int nV, int nT, int nS, int enc_mode, double *xy, int
   for (int it = 0; it < 1000 && !C.err; it++) {
     C.iters++;
     for (int i : ord.of(C.n_touched)) ff_vtri_one<O>(V, i, np);
-    C.n_red = C.n_hole = C.star_used = 0;
+    C.n_red = 0;
     for (int r : ord.of(np)) ff_detect_one<O>(V, r);
     if (C.n_red == 0 || C.err) break;
     // removals write the next worklist
     wst = ++stamp;
     target(cur);
-    int32_t *left[2] = {B.hole.data(), B.mover.data()}, *n_left[2] = {&C.n_red, &C.n_hole};
-    for (int i = 0; lanes && !C.err; i++) {  // (the points left are in two lists by turns)
-      const int in = i & 1, n = *n_left[in];
-      if (n == 0) break;
-      pass++;
-      if (i > 100000 || ffemu_removal_pass(&V, left[in], n_left[in], left[in ^ 1], n_left[in ^ 1], pass << 32, wst, tst,
-                                           (n + 15) / 16)) {
-        C.err = 203;
-        break;
-      }
-      const int bad4 = validate(B, C.n_alloc);
-      if (bad4) { out[11] = 4000 + bad4; C.err = 204; }
-    }
-    for (int guard = 0; !lanes; guard++) {
+    for (int guard = 0;; guard++) {
       if (guard > 100000) { C.err = 99; break; }
       pass++;
       const uint64_t pbase = pass << 32;
+      C.n_left = 0;
       C.pool_used = 0;
-      for (int r : ord.of(np)) rm_mark_one(V, r, pbase);
-      for (int r : ord.of(np)) rm_decide_one(V, r, pbase);
+      for (int r : ord.of(np)) ff_rm_mark_one<O>(V, r, pbase);
+      for (int r : ord.of(np)) ff_rm_decide_one<O>(V, r, pbase);
       for (int r : ord.of(np)) ff_rm_apply_one<O>(V, r, wst, tst);
       const int bad3 = validate(B, C.n_alloc);
       if (bad3) { out[11] = 3000 + bad3; C.err = 202; break; }
-      bool more = false;
-      for (int r = 0; r < np; r++) more = more || (B.alive[r] && B.red[r]);
-      if (!more || C.err) break;
+      if (C.n_left == 0 || C.err) break;
     }
     in_stamp = wst;
     lawson();

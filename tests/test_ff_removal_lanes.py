@@ -1,15 +1,13 @@
 """The removal kernels of the Flip-Flop insertion (gdp_ff.hip), their own text
-run lane by lane on the host (tests/ffemu/ff_lanes.cpp), in rounds from the
+run lane by lane on the host (tests/fflanes), in rounds from the
 oracle's point sets: after every pass each triangle is counter-clockwise and
 the neighbours are mutual, and the round ends in the oracle's mesh.  The nested
 polygons have circumcenters with links beyond a group's 16 vertices and a
 wave's 64."""
-import ctypes as C
-
 import pytest
 
 import workloads
-from tests import ffemu
+from tests import ffemu, fflanes
 from tests.test_ff_steps_host import CASES, FF, _Arr
 from tests.test_oracle_ff import canon, same
 
@@ -40,8 +38,7 @@ def test_removal_kernels_match_oracle(orc, case, encroach_mode):
     p = make()
     m = orc.build_cdt(p.xy, p.seg)
     lib = orc.load()
-    links = (C.c_int64 * 3).in_dll(ffemu.load(), "ffemu_links")
-    before = list(links)
+    before = fflanes.links()
     removed = 0
     for r in range(rounds):
         nxt = m.clone()
@@ -51,8 +48,7 @@ def test_removal_kernels_match_oracle(orc, case, encroach_mode):
         if not nxt.stats:
             break
         S = ffemu.last_points(lib)
-        res, cnt = ffemu.round_from_points(m.arrays(), p.xy.shape[0], S, enc_mode=encroach_mode, order_seed=r,
-                                           lanes=True)
+        res, cnt = fflanes.round_from_points(m.arrays(), p.xy.shape[0], S, enc_mode=encroach_mode, order_seed=r)
         assert cnt["err"] == 0, (r, cnt)
         assert same(canon(nxt), canon(_Arr(res))), f"round {r}"
         removed += cnt["removals"]
@@ -61,4 +57,4 @@ def test_removal_kernels_match_oracle(orc, case, encroach_mode):
             break
     assert removed > 0
     if encroach_mode == 0:
-        assert all(links[c] > before[c] for c in classes), [links[c] - before[c] for c in range(3)]
+        assert all(fflanes.links()[c] > before[c] for c in classes), (before, fflanes.links())
