@@ -1639,6 +1639,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
   std::vector<Caps> caps(n);
   std::vector<int32_t> nT0(n, 0);  // triangles of each initial CDT
   gdp_arena *arena = new gdp_arena();
+  arena->refs = 1;  // the call's own: it may be left without a mesh
   for (int32_t k = 0; k < n; k++) {
     const int64_t nv = pslgs[ok[k]].n_vertices, ns = pslgs[ok[k]].n_segments;
     Caps c;
@@ -2092,6 +2093,7 @@ gdp_status refine_batch(gdp_ctx *ctx, const gdp_pslg *pslgs, const double *bsq, 
       mesh[k] = nullptr;
     }
   }
+  arena_release(arena);
   for (int32_t i : alone) {
     const gdp_status r = gdp_refine(ctx, &pslgs[i], bsq[i], P, &outs[i]);
     if (status) status[i] = r;

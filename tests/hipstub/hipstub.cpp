@@ -32,6 +32,7 @@ bool g_fail_launch = false;   // the next error query reports a failed launch
 bool g_fail_threads = false;  // no thread can be created
 bool g_fail_scratch = false;  // after the first allocation, every one until a batch's own buffers are made fails
 int g_allocs = 0;
+std::map<void *, size_t> g_live;  // allocations that have not been freed
 }  // namespace
 
 extern "C" {
@@ -71,11 +72,22 @@ hipError_t hipMalloc(void **p, size_t n) {
   std::lock_guard<std::mutex> g(g_mu);
   if (g_fail_scratch && (std::this_thread::get_id() != g_main || ++g_allocs == 2)) return hipErrorOutOfMemory;
   *p = calloc(n, 1);
+  g_live[*p] = n;
   return hipSuccess;
 }
-hipError_t hipFree(void *p) { free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(n, 1); return hipSuccess; }
-hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipFree(void *p) {
+  std::lock_guard<std::mutex> g(g_mu);
+  g_live.erase(p);
+  free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+  std::lock_guard<std::mutex> g(g_mu);
+  *p = calloc(n, 1);
+  g_live[*p] = n;
+  return hipSuccess;
+}
+hipError_t hipHostFree(void *p) { return hipFree(p); }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t) {
   memcpy(d, s, n);
   // a refinement has nothing left to do
@@ -151,6 +163,8 @@ int batch(gdp_ctx *ctx, bool small = false) {
     if (out[i]) gdp_mesh_info_get(out[i], &info);
     printf("member %d %d %d\n", (int)st[i], info.n_triangles, want);
   }
+  for (gdp_mesh *m : out) gdp_mesh_free(m);
+  printf("live %zu\n", g_live.size());
   return 0;
 }
 }  // namespace
